@@ -77,7 +77,7 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
     // 3.93 -> 3.65 ms; 4.3 GB fp32 table, 4 KB rows, 12.0 -> 10.2 ms).  Results are unchanged:
     // columns are independent.
     int64_t pass = F;
-    if (vec && a.table_bytes > GT_COLUMN_PASS_TABLE_BYTES && F * (int64_t)es >= 512 && g->n_edges >= GT_COLUMN_PASS_MIN_EDGES)
+    if (a.table_bytes > GT_COLUMN_PASS_TABLE_BYTES && F * (int64_t)es >= 512 && g->n_edges >= GT_COLUMN_PASS_MIN_EDGES)
         pass = 256 / (int64_t)es;
     // what one launch gathers from: the slice of a pass, not the whole table (picks the unroll)
     if (pass < F) a.table_bytes = n_in * pass * (int64_t)es;
@@ -90,8 +90,7 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
         a.bias = bias ? bias + c0 : nullptr;
         a.mask = mask ? static_cast<const char *>(mask) + c0 * es : nullptr;
         gt_status s;
-        if (in_dtype == GT_F32) s = vec ? dispatch<float, 4>(a, st) : dispatch<float, 1>(a, st);
-        else s = vec ? dispatch<bf16_t, 8>(a, st) : dispatch<bf16_t, 1>(a, st);
+        s = in_dtype == GT_F32 ? agg_dispatch<float>(a, vec, st) : agg_dispatch<bf16_t>(a, vec, st);
         if (s != GT_OK) return s;
     }
     return GT_OK;

@@ -70,9 +70,13 @@ template <> struct Raw<float, 1> { typedef float type; };
 template <> struct Raw<bf16_t, 8> { typedef uint4 type; };
 template <> struct Raw<bf16_t, 1> { typedef bf16_t type; };
 
+// Rows need only the alignment of their element type (gfx950 takes 16-byte global accesses at any such
+// address): the copies below compile to one 16-byte load or store whatever the row stride is.
 template <typename T, int V>
 __device__ inline typename Raw<T, V>::type load_raw(const T *p) {
-    return *reinterpret_cast<const typename Raw<T, V>::type *>(p);
+    typename Raw<T, V>::type r;
+    __builtin_memcpy(&r, p, sizeof(r));
+    return r;
 }
 
 // acc += c * raw  (fp32 accumulation)
@@ -117,27 +121,9 @@ __device__ inline void fma_vw(float (&acc)[V], float c, const RawT &x, const Raw
     }
 }
 
-// V consecutive elements starting at p (p is 16-byte aligned when V > 1) -> fp32
+// V consecutive elements starting at p -> fp32
 template <typename T, int V>
-__device__ inline void load_vec(const T *p, float (&out)[V]);
-
-template <>
-__device__ inline void load_vec<float, 4>(const float *p, float (&out)[4]) {
-    const float4 v = *reinterpret_cast<const float4 *>(p);
-    out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
-}
-template <>
-__device__ inline void load_vec<float, 1>(const float *p, float (&out)[1]) { out[0] = *p; }
-template <>
-__device__ inline void load_vec<bf16_t, 8>(const bf16_t *p, float (&out)[8]) {
-    const uint4 v = *reinterpret_cast<const uint4 *>(p);
-    out[0] = __uint_as_float(v.x << 16); out[1] = __uint_as_float(v.x & 0xffff0000u);
-    out[2] = __uint_as_float(v.y << 16); out[3] = __uint_as_float(v.y & 0xffff0000u);
-    out[4] = __uint_as_float(v.z << 16); out[5] = __uint_as_float(v.z & 0xffff0000u);
-    out[6] = __uint_as_float(v.w << 16); out[7] = __uint_as_float(v.w & 0xffff0000u);
-}
-template <>
-__device__ inline void load_vec<bf16_t, 1>(const bf16_t *p, float (&out)[1]) { out[0] = bf16_to_f32(*p); }
+__device__ inline void load_vec(const T *p, float (&out)[V]) { unpack_raw(load_raw<T, V>(p), out); }
 
 // store the first `n` (<= V) of V values; full vectors go out as 16-byte stores
 template <typename T, int V>
@@ -146,7 +132,8 @@ __device__ inline void store_vec(T *p, const float (&v)[V], int n);
 template <>
 __device__ inline void store_vec<float, 4>(float *p, const float (&v)[4], int n) {
     if (n >= 4) {
-        *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+        const float4 o = make_float4(v[0], v[1], v[2], v[3]);
+        __builtin_memcpy(p, &o, 16);
     } else {
         for (int i = 0; i < n; ++i) p[i] = v[i];
     }
@@ -161,7 +148,7 @@ __device__ inline void store_vec<bf16_t, 8>(bf16_t *p, const float (&v)[8], int 
         o.y = gt_pack_bf16(v[2], v[3]);
         o.z = gt_pack_bf16(v[4], v[5]);
         o.w = gt_pack_bf16(v[6], v[7]);
-        *reinterpret_cast<uint4 *>(p) = o;
+        __builtin_memcpy(p, &o, 16);
     } else {
         for (int i = 0; i < n; ++i) p[i] = (bf16_t)f32_to_bf16(v[i]);
     }
@@ -171,17 +158,23 @@ __device__ inline void store_vec<bf16_t, 1>(bf16_t *p, const float (&v)[1], int 
     if (n > 0) p[0] = (bf16_t)f32_to_bf16(v[0]);
 }
 
-// scale, bias, activation and store of one finished output row segment
+// SH: rows without 16-byte alignment.  The lane that holds a row's ragged end takes the row's last V columns instead of
+// starting at its own column: it repeats some of its neighbour's (and stores the same values there), and every
+// access is a whole vector inside the row.  Needs F >= V.
+template <bool SH, int V>
+__device__ inline int64_t agg_col(const AggArgs &a, int64_t own) { return SH && own > a.F - V ? a.F - V : own; }
+
 // the mask values of this lane's segments of output row `row` (16-byte loads where the segment is whole);
 // issued early by the callers so that the load is not a dependent round trip at the end of the item
-template <typename T, int V, int G, int NP>
+template <typename T, int V, int G, int NP, bool SH>
 __device__ inline void load_mask_row(const AggArgs &a, int row, int gl, int64_t col0, float (&m)[NP][V]) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const int64_t col = col0 + (int64_t)(p * G + gl) * V;
+        const int64_t own = col0 + (int64_t)(p * G + gl) * V;
 #pragma unroll
         for (int i = 0; i < V; ++i) m[p][i] = 1.0f;
-        if (col >= a.F) continue;
+        if (own >= a.F) continue;
+        const int64_t col = agg_col<SH, V>(a, own);
         const int n = (int)((a.F - col) < V ? (a.F - col) : V);
         const T *mp = static_cast<const T *>(a.mask) + (int64_t)row * a.ldmask + col;
         if (n >= V) {
@@ -197,7 +190,8 @@ __device__ inline void load_mask_row(const AggArgs &a, int row, int gl, int64_t 
     }
 }
 
-template <typename T, int V, int G, int NP>
+// scale, bias, activation and store of one finished output row segment
+template <typename T, int V, int G, int NP, bool SH>
 __device__ inline void finish_row(const AggArgs &a, int row, int gl, int64_t col0, float (&acc)[NP][V],
                                   const float (&msk)[NP][V]) {
     bool zero = false;
@@ -210,8 +204,9 @@ __device__ inline void finish_row(const AggArgs &a, int row, int gl, int64_t col
     T *y = static_cast<T *>(a.Y) + (int64_t)row * a.ldy;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const int64_t col = col0 + (int64_t)(p * G + gl) * V;
-        if (col >= a.F) continue;
+        const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+        if (own >= a.F) continue;
+        const int64_t col = agg_col<SH, V>(a, own);
         const int n = (int)((a.F - col) < V ? (a.F - col) : V);
         float o[V];
 #pragma unroll
@@ -263,7 +258,7 @@ static inline int agg_xcd_run(int64_t gx) {
 // blockIdx.y selects a column tile of G*V*NP columns.
 // MK: an output mask is present (its values are fetched when the item starts; a separate instance so
 // that the registers they occupy during the gather cost the unmasked kernel nothing)
-template <typename T, int V, int G, int NP, int U, int VWM = VWM_NONE, bool MK = false>
+template <typename T, int V, int G, int NP, int U, int VWM = VWM_NONE, bool MK = false, bool SH = false>
 __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63;
@@ -300,7 +295,7 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
 #pragma unroll
         for (int i = 0; i < V; ++i) msk[p][i] = 1.0f;
     if constexpr (MK) {
-        if (slot < 0) load_mask_row<T, V, G, NP>(a, row, gl, col0, msk);   // needed only when the row is finished here
+        if (slot < 0) load_mask_row<T, V, G, NP, SH>(a, row, gl, col0, msk);   // needed only when the row is finished here
     }
 
     typedef typename Raw<T, V>::type raw_t;
@@ -349,12 +344,12 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
                 const T *xr = X + (int64_t)src * a.ldx;
 #pragma unroll
                 for (int p = 0; p < NP; ++p) {
-                    const int64_t col = col0 + (int64_t)(p * G + gl) * V;
+                    const int64_t own = col0 + (int64_t)(p * G + gl) * V, col = agg_col<SH, V>(a, own);
                     v[u][p] = raw_t{};
-                    if (live && col < a.F) v[u][p] = load_raw<T, V>(xr + col);
+                    if (live && own < a.F) v[u][p] = load_raw<T, V>(xr + col);
                     if constexpr (VWM != VWM_NONE) {
                         w[u][p] = raw_t{};
-                        if (live && col < a.F) w[u][p] = load_raw<T, V>(VWp + (int64_t)we * a.ldvw + col);
+                        if (live && own < a.F) w[u][p] = load_raw<T, V>(VWp + (int64_t)we * a.ldvw + col);
                     }
                 }
             }
@@ -372,19 +367,26 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         float *P = a.partials + (int64_t)slot * a.ldp;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const int64_t col = col0 + (int64_t)(p * G + gl) * V;
-            if (col >= a.F) continue;
+            const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+            if (own >= a.F) continue;
+            const int64_t col = agg_col<SH, V>(a, own);   // (partial rows are padded to 8 floats: a whole vector always fits)
+            if constexpr (V == 1) {
+                P[col] = acc[p][0];
+            } else {
 #pragma unroll
-            for (int i = 0; i < V; ++i)
-                if (col + i < a.F) P[col + i] = acc[p][i];
+                for (int q = 0; q < V / 4; ++q) {
+                    const float4 x = make_float4(acc[p][4 * q], acc[p][4 * q + 1], acc[p][4 * q + 2], acc[p][4 * q + 3]);
+                    __builtin_memcpy(P + col + 4 * q, &x, 16);
+                }
+            }
         }
     } else {
-        finish_row<T, V, G, NP>(a, row, gl, col0, acc, msk);
+        finish_row<T, V, G, NP, SH>(a, row, gl, col0, acc, msk);
     }
 }
 
 // Second pass for split rows: add the row's partial rows in chunk order.
-template <typename T, int V, int G, int NP>
+template <typename T, int V, int G, int NP, bool SH>
 __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63;
@@ -405,7 +407,7 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
     for (int p = 0; p < NP; ++p)
 #pragma unroll
         for (int i = 0; i < V; ++i) msk[p][i] = 1.0f;
-    if (a.mask) load_mask_row<T, V, G, NP>(a, s.row, gl, col0, msk);
+    if (a.mask) load_mask_row<T, V, G, NP, SH>(a, s.row, gl, col0, msk);
     // UR partial rows are requested at a time (branch free: a request past the end re-reads the
     // last row and is discarded) and added in chunk order.  Partial rows are padded to a multiple
     // of 8 floats, so whole vectors can be read; padding lanes are never stored.  The kernel runs as
@@ -420,14 +422,14 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
             const float *P = a.partials + (int64_t)(s.first + kk) * a.ldp;
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                const int64_t col = col0 + (int64_t)(p * G + gl) * V;
-                const int64_t c = col < a.F ? col : 0;
+                const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+                const int64_t c = own < a.F ? agg_col<SH, V>(a, own) : 0;
                 if constexpr (V == 1) {
                     t[u][p][0] = P[c];
                 } else {
 #pragma unroll
                     for (int q = 0; q < V / 4; ++q) {
-                        const float4 x = *reinterpret_cast<const float4 *>(P + c + 4 * q);
+                        const float4 x = load_raw<float, 4>(P + c + 4 * q);
                         t[u][p][4 * q + 0] = x.x; t[u][p][4 * q + 1] = x.y;
                         t[u][p][4 * q + 2] = x.z; t[u][p][4 * q + 3] = x.w;
                     }
@@ -443,10 +445,10 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
                 for (int i = 0; i < V; ++i) acc[p][i] += live ? t[u][p][i] : 0.0f;
         }
     }
-    finish_row<T, V, G, NP>(a, s.row, gl, col0, acc, msk);
+    finish_row<T, V, G, NP, SH>(a, s.row, gl, col0, acc, msk);
 }
 
-template <typename T, int V, int G, int NP, int U, int VWM = VWM_NONE>
+template <typename T, int V, int G, int NP, int U, int VWM, bool SH>
 gt_status launch(const AggArgs &a, hipStream_t st) {
     constexpr int NG = 64 / G;
     const int64_t tile = (int64_t)G * V * NP;
@@ -458,17 +460,17 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
         const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
         gt_trace_variant(tr, V, G, NP, U, VWM == VWM_NONE && a.mask != nullptr);
         if constexpr (VWM == VWM_NONE) {
-            if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
-            else k_aggregate<T, V, G, NP, U, VWM, false><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
+            if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
+            else k_aggregate<T, V, G, NP, U, VWM, false, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
         } else {
-            k_aggregate<T, V, G, NP, U, VWM, false><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
+            k_aggregate<T, V, G, NP, U, VWM, false, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
         }
         gt_trace_close(tr, st);
         GT_LAUNCH_CHECK("k_aggregate");
     }
     if (a.n_splits > 0 && !a.no_reduce) {
         const int64_t gx = (a.n_splits + 4 * NG - 1) / (4 * NG);
-        k_reduce_partials<T, V, G, NP><<<dim3((unsigned)gx, gy), 256, 0, st>>>(a);
+        k_reduce_partials<T, V, G, NP, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(a);
         GT_LAUNCH_CHECK("k_reduce_partials");
     }
     return GT_OK;
@@ -477,25 +479,38 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
 // Row loads kept in flight per lane.  Measured on MI355X: two are enough (and best) once the
 // gathered table lives in HBM or rows are 512 bytes or more; narrow rows of a table that fits the
 // last-level cache gain from eight.
-template <typename T, int V, int G, int NP, int VWM = VWM_NONE>
+template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
     if constexpr (NP == 1 && G <= 16 && VWM == VWM_NONE) {
-        if (a.table_bytes <= ((int64_t)96 << 20)) return launch<T, V, G, NP, 8>(a, st);
+        if (a.table_bytes <= ((int64_t)96 << 20)) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
     }
-    return launch<T, V, G, NP, 2, VWM>(a, st);
+    return launch<T, V, G, NP, 2, VWM, SH>(a, st);
 }
 
-template <typename T, int V, int VWM = VWM_NONE>
+template <typename T, int V, int VWM = VWM_NONE, bool SH = false>
 gt_status dispatch(const AggArgs &a, hipStream_t st) {
     const int64_t nvec = (a.F + V - 1) / V;   // lanes needed to cover one row
-    if (nvec <= 4) return launch_u<T, V, 4, 1, VWM>(a, st);
-    if (nvec <= 8) return launch_u<T, V, 8, 1, VWM>(a, st);
-    if (nvec <= 16) return launch_u<T, V, 16, 1, VWM>(a, st);
-    if (nvec <= 32) return launch_u<T, V, 32, 1, VWM>(a, st);
-    if (nvec <= 64) return launch_u<T, V, 64, 1, VWM>(a, st);
-    if (nvec <= 128) return launch_u<T, V, 64, 2, VWM>(a, st);
-    if (nvec <= 192) return launch_u<T, V, 64, 3, VWM>(a, st);
-    return launch_u<T, V, 64, 4, VWM>(a, st);   // wider rows take several column tiles (grid.y)
+    if (nvec <= 4) return launch_u<T, V, 4, 1, VWM, SH>(a, st);
+    if constexpr (V == 1) return launch_u<T, V, 8, 1, VWM, SH>(a, st);   // rows shorter than a vector only (see agg_dispatch)
+    if (nvec <= 8) return launch_u<T, V, 8, 1, VWM, SH>(a, st);
+    if (nvec <= 16) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
+    if (nvec <= 32) return launch_u<T, V, 32, 1, VWM, SH>(a, st);
+    if (nvec <= 64) return launch_u<T, V, 64, 1, VWM, SH>(a, st);
+    if (nvec <= 128) return launch_u<T, V, 64, 2, VWM, SH>(a, st);
+    if (nvec <= 192) return launch_u<T, V, 64, 3, VWM, SH>(a, st);
+    return launch_u<T, V, 64, 4, VWM, SH>(a, st);   // wider rows take several column tiles (grid.y)
+}
+
+// Picks the access width.  `vec`: every row involved is 16-byte aligned and padded to 16 bytes.  Rows that are not take
+// whole vectors all the same, the last one shifted to the row's end (element-wise lanes moved 4 or 2 bytes each and
+// took twice as long: 16 M gathered rows of 47 bf16 columns without padding, two directions 2.29 -> 1.08 ms); only rows
+// shorter than one vector go element by element.
+template <typename T, int VWM = VWM_NONE>
+gt_status agg_dispatch(const AggArgs &a, bool vec, hipStream_t st) {
+    constexpr int V = 16 / (int)sizeof(T);
+    if (vec) return dispatch<T, V, VWM>(a, st);
+    if (a.F < V) return dispatch<T, 1, VWM>(a, st);
+    return dispatch<T, V, VWM, true>(a, st);
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }

@@ -33,8 +33,12 @@ struct EdgeArgs {
 
 enum { EO_MUL = 0, EO_BCAST = 1 };
 
+// SH: rows without 16-byte alignment, see agg_col
+template <bool SH, int V>
+__device__ inline int64_t edge_col(const EdgeArgs &a, int64_t own) { return SH && own > a.F - V ? a.F - V : own; }
+
 // W[e, :] = s_r * R[r, :] (.) X[nbr[e], :]   (EO_MUL)   or   s_r * R[r, :]   (EO_BCAST)
-template <typename T, int V, int G, int NP, int MODE>
+template <typename T, int V, int G, int NP, int MODE, bool SH>
 __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -53,9 +57,9 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
     const float s = a.rscale ? a.rscale[row] : 1.0f;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        const int64_t col = col0 + (int64_t)(p * G + gl) * V;
+        const int64_t own = col0 + (int64_t)(p * G + gl) * V;
         raw_t rv = raw_t{};
-        if (col < a.F && e0 < e1) rv = load_raw<T, V>(R + col);
+        if (own < a.F && e0 < e1) rv = load_raw<T, V>(R + edge_col<SH, V>(a, own));
         unpack_raw(rv, r[p]);
 #pragma unroll
         for (int i = 0; i < V; ++i) r[p][i] *= s;
@@ -75,9 +79,9 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
                     const T *xr = X + (int64_t)src * a.ldx;
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
-                        const int64_t col = col0 + (int64_t)(p * G + gl) * V;
+                        const int64_t own = col0 + (int64_t)(p * G + gl) * V;
                         v[u][p] = raw_t{};
-                        if (live && col < a.F) v[u][p] = load_raw<T, V>(xr + col);
+                        if (live && own < a.F) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, own));
                     }
                 }
             }
@@ -88,8 +92,9 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
                 T *wr = W + (int64_t)(base + jj) * a.ldw;
 #pragma unroll
                 for (int p = 0; p < NP; ++p) {
-                    const int64_t col = col0 + (int64_t)(p * G + gl) * V;
-                    if (col >= a.F) continue;
+                    const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+                    if (own >= a.F) continue;
+                    const int64_t col = edge_col<SH, V>(a, own);
                     const int n = (int)((a.F - col) < V ? (a.F - col) : V);
                     float o[V];
                     if constexpr (MODE == EO_MUL) {
@@ -109,7 +114,7 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
 }
 
 // w[e] = s_r * <R[r, :], X[nbr[e], :]>   (all columns inside one column tile)
-template <typename T, int V, int G, int NP>
+template <typename T, int V, int G, int NP, bool SH>
 __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -136,9 +141,9 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
             float r[NP][V];
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                const int64_t col = c0 + (int64_t)(p * G + gl) * V;
+                const int64_t own = c0 + (int64_t)(p * G + gl) * V;
                 raw_t rv = raw_t{};
-                if (col < a.F) rv = load_raw<T, V>(R + col);
+                if (own < a.F) rv = load_raw<T, V>(R + edge_col<SH, V>(a, own));
                 unpack_raw(rv, r[p]);
             }
             for (int j = 0; j < cnt; j += 2) {
@@ -150,9 +155,9 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
                     const T *xr = X + (int64_t)src * a.ldx;
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
-                        const int64_t col = c0 + (int64_t)(p * G + gl) * V;
+                        const int64_t own = c0 + (int64_t)(p * G + gl) * V;
                         v[u][p] = raw_t{};
-                        if (jj < cnt && col < a.F) v[u][p] = load_raw<T, V>(xr + col);
+                        if (jj < cnt && own < a.F) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, own));
                     }
                 }
 #pragma unroll
@@ -162,10 +167,11 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
                     for (int p = 0; p < NP; ++p) {
                         float x[V];
                         unpack_raw(v[u][p], x);
-                        const int64_t col = c0 + (int64_t)(p * G + gl) * V;
+                        const int64_t own = c0 + (int64_t)(p * G + gl) * V, col = edge_col<SH, V>(a, own);
 #pragma unroll
-                        for (int i = 0; i < V; ++i)   // padding elements of the last vector may hold anything
-                            part += (col + i < a.F) ? r[p][i] * x[i] : 0.0f;
+                        for (int i = 0; i < V; ++i)   // padding elements of the last vector may hold anything, and a
+                                                      // shifted vector starts with its neighbour's columns
+                            part += (col + i < a.F && col + i >= own) ? r[p][i] * x[i] : 0.0f;
                     }
                     // butterfly over the group's lanes: every lane ends with the full sum, fixed order
 #pragma unroll
@@ -178,7 +184,7 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
     }
 }
 
-template <typename T, int V, int G, int NP>
+template <typename T, int V, int G, int NP, bool SH>
 gt_status launch_edge(const EdgeArgs &a, int kind, hipStream_t st) {
     constexpr int NG = 64 / G;
     if (a.n_items <= 0) return GT_OK;
@@ -188,24 +194,25 @@ gt_status launch_edge(const EdgeArgs &a, int kind, hipStream_t st) {
     const dim3 grid((unsigned)gx, gy);
     EdgeArgs b = a;
     b.xcd_run = agg_xcd_run(gx);
-    if (kind == 0) k_edge_out<T, V, G, NP, EO_MUL><<<grid, 256, 0, st>>>(b);
-    else if (kind == 1) k_edge_out<T, V, G, NP, EO_BCAST><<<grid, 256, 0, st>>>(b);
-    else k_edge_dot<T, V, G, NP><<<grid, 256, 0, st>>>(b);
+    if (kind == 0) k_edge_out<T, V, G, NP, EO_MUL, SH><<<grid, 256, 0, st>>>(b);
+    else if (kind == 1) k_edge_out<T, V, G, NP, EO_BCAST, SH><<<grid, 256, 0, st>>>(b);
+    else k_edge_dot<T, V, G, NP, SH><<<grid, 256, 0, st>>>(b);
     GT_LAUNCH_CHECK("k_edge");
     return GT_OK;
 }
 
-template <typename T, int V>
+template <typename T, int V, bool SH = false>
 gt_status dispatch_edge(const EdgeArgs &a, int kind, hipStream_t st) {
     const int64_t nvec = (a.F + V - 1) / V;
-    if (nvec <= 4) return launch_edge<T, V, 4, 1>(a, kind, st);
-    if (nvec <= 8) return launch_edge<T, V, 8, 1>(a, kind, st);
-    if (nvec <= 16) return launch_edge<T, V, 16, 1>(a, kind, st);
-    if (nvec <= 32) return launch_edge<T, V, 32, 1>(a, kind, st);
-    if (nvec <= 64) return launch_edge<T, V, 64, 1>(a, kind, st);
-    if (nvec <= 128) return launch_edge<T, V, 64, 2>(a, kind, st);
-    if (nvec <= 192) return launch_edge<T, V, 64, 3>(a, kind, st);
-    return launch_edge<T, V, 64, 4>(a, kind, st);
+    if (nvec <= 4) return launch_edge<T, V, 4, 1, SH>(a, kind, st);
+    if constexpr (V == 1) return launch_edge<T, V, 8, 1, SH>(a, kind, st);   // rows shorter than a vector only
+    if (nvec <= 8) return launch_edge<T, V, 8, 1, SH>(a, kind, st);
+    if (nvec <= 16) return launch_edge<T, V, 16, 1, SH>(a, kind, st);
+    if (nvec <= 32) return launch_edge<T, V, 32, 1, SH>(a, kind, st);
+    if (nvec <= 64) return launch_edge<T, V, 64, 1, SH>(a, kind, st);
+    if (nvec <= 128) return launch_edge<T, V, 64, 2, SH>(a, kind, st);
+    if (nvec <= 192) return launch_edge<T, V, 64, 3, SH>(a, kind, st);
+    return launch_edge<T, V, 64, 4, SH>(a, kind, st);
 }
 
 bool vec_ok(gt_dtype t, const void *p, int64_t ld) {
@@ -220,8 +227,10 @@ gt_status run_edge(const gt_graph *g, int kind, gt_dtype t, int64_t F, const voi
     a.items = g->fwd.items; a.n_items = g->fwd.n_items; a.nbr = g->colidx;
     a.R = R; a.ldr = ldr; a.rscale = rscale; a.X = X; a.ldx = ldx; a.W = W; a.ldw = ldw; a.F = F;
     const bool vec = vec_ok(t, R, ldr) && vec_ok(t, X, ldx) && (kind == 2 || vec_ok(t, W, ldw));
-    if (t == GT_F32) return vec ? dispatch_edge<float, 4>(a, kind, st) : dispatch_edge<float, 1>(a, kind, st);
-    return vec ? dispatch_edge<bf16_t, 8>(a, kind, st) : dispatch_edge<bf16_t, 1>(a, kind, st);
+    const int ve = t == GT_F32 ? 4 : 8;
+    if (!vec && F < ve) return t == GT_F32 ? dispatch_edge<float, 1>(a, kind, st) : dispatch_edge<bf16_t, 1>(a, kind, st);
+    if (t == GT_F32) return vec ? dispatch_edge<float, 4>(a, kind, st) : dispatch_edge<float, 4, true>(a, kind, st);
+    return vec ? dispatch_edge<bf16_t, 8>(a, kind, st) : dispatch_edge<bf16_t, 8, true>(a, kind, st);
 }
 
 // gather: Y[r] = post( sum_e coef[ei] * coef2[e] * h(X[nbr e], VW[ei]) ), over the given or the
@@ -243,11 +252,10 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
     a.trace_kind = transposed ? GT_TRACE_AGG_BWD : GT_TRACE_AGG_FWD;
     a.n_rows = sc.n_rows; a.n_edges = g->n_edges;
     const bool vec = vec_ok(t, X, ldx) && vec_ok(t, Y, ldy) && vec_ok(t, VW, ldvw);
-#define GT_GATHER(T_, V_)                                                      \
-    (vwm == VWM_ADD ? dispatch<T_, V_, VWM_ADD>(a, st)                          \
-                    : vwm == VWM_MUL ? dispatch<T_, V_, VWM_MUL>(a, st) : dispatch<T_, V_, VWM_NONE>(a, st))
-    if (t == GT_F32) return vec ? GT_GATHER(float, 4) : GT_GATHER(float, 1);
-    return vec ? GT_GATHER(bf16_t, 8) : GT_GATHER(bf16_t, 1);
+#define GT_GATHER(T_)                                                          \
+    (vwm == VWM_ADD ? agg_dispatch<T_, VWM_ADD>(a, vec, st)                     \
+                    : vwm == VWM_MUL ? agg_dispatch<T_, VWM_MUL>(a, vec, st) : agg_dispatch<T_>(a, vec, st))
+    return t == GT_F32 ? GT_GATHER(float) : GT_GATHER(bf16_t);
 #undef GT_GATHER
 }
 
