@@ -299,45 +299,54 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     }
 
     typedef typename Raw<T, V>::type raw_t;
-    // The group fetches G neighbour ids and coefficients with one coalesced load and walks them;
-    // the next G are requested before the current ones are used, so the id fetch of the next
-    // batch overlaps the row gathers of this one.
-    int idx_next = 0, ei_next = 0;
-    float c_next = 0.0f;
-    auto fetch_entry = [&](int e) {
-        idx_next = a.nbr[e];
-        ei_next = a.eidx ? a.eidx[e] : e;
-        c_next = a.coef ? a.coef[ei_next] : 1.0f;
-        if (a.coef2) c_next *= a.coef2[e];
+    // The group fetches GB neighbour ids and coefficients with coalesced loads and walks them; the next GB are requested
+    // before the current ones are used, so the id fetch of the next batch overlaps the row gathers of this one.
+    // A narrow row has few lanes: with one id per lane (batches of 4 or 8) a long row is a chain of id and row
+    // round trips with no more than a batch of rows in flight, so narrow groups hold several ids per lane
+    // (2^21 vertices, 52 M edges, 47 bf16 columns, G = 8: 0.948 -> 0.881 ms).
+    constexpr int IPL = G >= 16 ? 1 : 16 / G, GB = G * IPL;
+    int idx_next[IPL], ei_next[IPL];
+    float c_next[IPL];
+    auto fetch = [&](int e_first) {
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) {
+            const int e = e_first + k * G + gl;
+            idx_next[k] = 0;
+            ei_next[k] = 0;
+            c_next[k] = 0.0f;
+            if (e < e1) {
+                idx_next[k] = a.nbr[e];
+                ei_next[k] = a.eidx ? a.eidx[e] : e;
+                c_next[k] = a.coef ? a.coef[ei_next[k]] : 1.0f;
+                if (a.coef2) c_next[k] *= a.coef2[e];
+            }
+        }
     };
-    if (e0 + gl < e1) fetch_entry(e0 + gl);
+    fetch(e0);
     const T *VWp = static_cast<const T *>(a.VW);
-    for (int base = e0; base < e1; base += G) {
-        const int idx = idx_next;
-        const int ei = ei_next;
-        const float c = c_next;
-        const int en = base + G + gl;
-        idx_next = 0;
-        ei_next = 0;
-        c_next = 0.0f;
-        if (en < e1) fetch_entry(en);
-        const int cnt = (e1 - base) < G ? (e1 - base) : G;
-        for (int j = 0; j < cnt; j += U) {
+    for (int base = e0; base < e1; base += GB) {
+        int idx[IPL], ei[IPL];
+        float c[IPL];
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) { idx[k] = idx_next[k]; ei[k] = ei_next[k]; c[k] = c_next[k]; }
+        fetch(base + GB);
+        const int cnt = (e1 - base) < GB ? (e1 - base) : GB;
+        auto step = [&](int j) {   // entries j .. j + U - 1 of the batch (j is a constant where IPL > 1)
             raw_t v[U][NP];
             raw_t w[VWM == VWM_NONE ? 1 : U][VWM == VWM_NONE ? 1 : NP];
             float cj[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int jj = j + u;
+                const int jj = j + u, k = IPL > 1 ? jj / G : 0;
                 int src, we = 0;
                 if constexpr (G == 64) {   // wave-uniform: scalar broadcast, scalar row base
-                    src = __builtin_amdgcn_readlane(idx, jj & 63);
-                    cj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), jj & 63));
-                    if constexpr (VWM != VWM_NONE) we = __builtin_amdgcn_readlane(ei, jj & 63);
+                    src = __builtin_amdgcn_readlane(idx[0], jj & 63);
+                    cj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c[0]), jj & 63));
+                    if constexpr (VWM != VWM_NONE) we = __builtin_amdgcn_readlane(ei[0], jj & 63);
                 } else {
-                    src = __shfl(idx, jj & (G - 1), G);
-                    cj[u] = __shfl(c, jj & (G - 1), G);
-                    if constexpr (VWM != VWM_NONE) we = __shfl(ei, jj & (G - 1), G);
+                    src = __shfl(idx[k], jj & (G - 1), G);
+                    cj[u] = __shfl(c[k], jj & (G - 1), G);
+                    if constexpr (VWM != VWM_NONE) we = __shfl(ei[k], jj & (G - 1), G);
                 }
                 const bool live = jj < cnt;
                 if (!live) cj[u] = 0.0f;
@@ -360,6 +369,13 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
                     if constexpr (VWM == VWM_NONE) fma_raw(acc[p], cj[u], v[u][p]);
                     else fma_vw<VWM, V>(acc[p], cj[u], v[u][p], w[u][p]);
                 }
+        };
+        if constexpr (IPL == 1) {
+            for (int j = 0; j < cnt; j += U) step(j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < GB; j += U)
+                if (j < cnt) step(j);
         }
     }
 
@@ -484,7 +500,10 @@ gt_status launch_u(const AggArgs &a, hipStream_t st) {
     if constexpr (NP == 1 && G <= 16 && VWM == VWM_NONE) {
         if (a.table_bytes <= ((int64_t)96 << 20)) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
     }
-    return launch<T, V, G, NP, 2, VWM, SH>(a, st);
+    // per-entry vector weights stream from memory, each row once, and the gathered table beside them is smaller than they
+    // are: eight in flight (4.2 M edges x 64 fp32: two 333 us, four 301, eight 296)
+    if constexpr (NP == 1 && VWM != VWM_NONE) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
+    else return launch<T, V, G, NP, 2, VWM, SH>(a, st);
 }
 
 template <typename T, int V, int VWM = VWM_NONE, bool SH = false>

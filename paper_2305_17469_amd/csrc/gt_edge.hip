@@ -64,53 +64,90 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
 #pragma unroll
         for (int i = 0; i < V; ++i) r[p][i] *= s;
     }
-    for (int base = e0; base < e1; base += G) {
-        int idx = 0;
-        if (MODE == EO_MUL && base + gl < e1) idx = a.nbr[base + gl];
-        const int cnt = (e1 - base) < G ? (e1 - base) : G;
-        for (int j = 0; j < cnt; j += 2) {
-            raw_t v[2][NP];
+    // U edges at a time; the rows of the next U are requested before the current ones are stored, so that a wait for
+    // rows never includes the stores just issued (loads and stores share one in-order counter).  Measured on MI355X,
+    // 4.2 M edges x 64 fp32 (1.07 GB written): 432 -> 330 us.
+    constexpr int U = NP == 1 ? (G >= 8 ? 8 : 4) : 2;
+    int idx = 0, idx_next = 0;
+    auto fetch = [&](int e) { return MODE == EO_MUL && e < e1 ? a.nbr[e] : 0; };
+    auto load = [&](raw_t (&v)[U][NP], int j, int left) {   // entries j .. j + U - 1 of the current ids
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int jj = j + u;
-                const bool live = jj < cnt;
-                if constexpr (MODE == EO_MUL) {
-                    const int src = __shfl(idx, jj & (G - 1), G);
-                    const T *xr = X + (int64_t)src * a.ldx;
+        for (int u = 0; u < U; ++u) {
+            const int src = __shfl(idx, (j + u) & (G - 1), G);
+            const T *xr = X + (int64_t)src * a.ldx;
 #pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        const int64_t own = col0 + (int64_t)(p * G + gl) * V;
-                        v[u][p] = raw_t{};
-                        if (live && own < a.F) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, own));
-                    }
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int jj = j + u;
-                if (jj >= cnt) continue;
-                T *wr = W + (int64_t)(base + jj) * a.ldw;
-#pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    const int64_t own = col0 + (int64_t)(p * G + gl) * V;
-                    if (own >= a.F) continue;
-                    const int64_t col = edge_col<SH, V>(a, own);
-                    const int n = (int)((a.F - col) < V ? (a.F - col) : V);
-                    float o[V];
-                    if constexpr (MODE == EO_MUL) {
-                        float x[V];
-                        unpack_raw(v[u][p], x);
-#pragma unroll
-                        for (int i = 0; i < V; ++i) o[i] = r[p][i] * x[i];
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < V; ++i) o[i] = r[p][i];
-                    }
-                    store_vec<T, V>(wr + col, o, n);
-                }
+            for (int p = 0; p < NP; ++p) {
+                const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+                if (u < left && own < a.F) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, own));
             }
         }
+    };
+    raw_t v[U][NP];
+    if constexpr (MODE == EO_MUL) {
+        idx = fetch(e0 + gl);
+        idx_next = fetch(e0 + G + gl);
+        load(v, 0, e1 - e0);
     }
+    for (int e = e0; e < e1; e += U) {
+        raw_t nx[U][NP];
+        if constexpr (MODE == EO_MUL) {
+            if (e + U < e1) {
+                const int jn = (e + U - e0) & (G - 1);
+                if (jn == 0) {
+                    idx = idx_next;
+                    idx_next = fetch(e + U + G + gl);
+                }
+                load(nx, jn, e1 - e - U);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (e + u >= e1) continue;
+            T *wr = W + (int64_t)(e + u) * a.ldw;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+                if (own >= a.F) continue;
+                const int64_t col = edge_col<SH, V>(a, own);
+                const int n = (int)((a.F - col) < V ? (a.F - col) : V);
+                float o[V];
+                if constexpr (MODE == EO_MUL) {
+                    float x[V];
+                    unpack_raw(v[u][p], x);
+#pragma unroll
+                    for (int i = 0; i < V; ++i) o[i] = r[p][i] * x[i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) o[i] = r[p][i];
+                }
+                store_vec<T, V>(wr + col, o, n);
+            }
+        }
+        if constexpr (MODE == EO_MUL) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) v[u][p] = nx[u][p];
+        }
+    }
+}
+
+// Sum over the G lanes of a group, in every lane, in a fixed order: exchanges inside 16 lanes ride on the addition itself
+// (data-parallel primitives: neighbour, pair, mirrored four, mirrored eight); only wider groups need a trip
+// through the LDS permute unit, of which the plain butterfly made log2 G per edge.
+template <int CTRL>
+__device__ inline float dpp_add(float x) {
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int G>
+__device__ inline float group_sum(float x) {
+    x = dpp_add<0xB1>(x);                    // quad_perm [1, 0, 3, 2]
+    x = dpp_add<0x4E>(x);                    // quad_perm [2, 3, 0, 1]
+    if constexpr (G >= 8) x = dpp_add<0x141>(x);    // mirror inside 8 lanes
+    if constexpr (G >= 16) x = dpp_add<0x140>(x);   // mirror inside 16 lanes
+    if constexpr (G >= 32) x += __shfl_xor(x, 16, G);
+    if constexpr (G >= 64) x += __shfl_xor(x, 32, G);
+    return x;
 }
 
 // w[e] = s_r * <R[r, :], X[nbr[e], :]>   (all columns inside one column tile)
@@ -130,9 +167,11 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
 
     const float s = a.rscale ? a.rscale[row] : 1.0f;
     constexpr int TILE = G * V * NP;
+    constexpr int U = NP == 1 ? (G >= 8 ? 8 : 4) : 2;   // row loads in flight per lane (8.4 M edges x 128 bf16, 67 MB table: 297 -> 217 us with eight)
+    int idx_next = e0 + gl < e1 ? a.nbr[e0 + gl] : 0;
     for (int base = e0; base < e1; base += G) {
-        int idx = 0;
-        if (base + gl < e1) idx = a.nbr[base + gl];
+        const int idx = idx_next;
+        idx_next = base + G + gl < e1 ? a.nbr[base + G + gl] : 0;   // requested before this batch's rows are used
         const int cnt = (e1 - base) < G ? (e1 - base) : G;
         float mine = 0.0f;   // lane gl keeps the result of edge base + gl
         // rows wider than one column tile are walked tile by tile; the row operand is re-read per
@@ -146,10 +185,10 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
                 if (own < a.F) rv = load_raw<T, V>(R + edge_col<SH, V>(a, own));
                 unpack_raw(rv, r[p]);
             }
-            for (int j = 0; j < cnt; j += 2) {
-                raw_t v[2][NP];
+            for (int j = 0; j < cnt; j += U) {
+                raw_t v[U][NP];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
+                for (int u = 0; u < U; ++u) {
                     const int jj = j + u;
                     const int src = __shfl(idx, jj & (G - 1), G);
                     const T *xr = X + (int64_t)src * a.ldx;
@@ -161,7 +200,7 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
+                for (int u = 0; u < U; ++u) {
                     float part = 0.0f;
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
@@ -173,9 +212,7 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
                                                       // shifted vector starts with its neighbour's columns
                             part += (col + i < a.F && col + i >= own) ? r[p][i] * x[i] : 0.0f;
                     }
-                    // butterfly over the group's lanes: every lane ends with the full sum, fixed order
-#pragma unroll
-                    for (int o = G / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, G);
+                    part = group_sum<G>(part);
                     if (gl == ((j + u) & (G - 1))) mine += part;
                 }
             }
@@ -248,7 +285,7 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.F = F;
     a.partials = static_cast<float *>(ws); a.ldp = (F + 7) / 8 * 8;
     a.splits = sc.splits; a.n_splits = sc.n_splits;
-    a.table_bytes = ((int64_t)1 << 40);   // keep the two-loads-in-flight variant
+    a.table_bytes = (transposed ? g->n_dst : g->n_src) * ldx * (int64_t)gt_dtype_size(t);
     a.trace_kind = transposed ? GT_TRACE_AGG_BWD : GT_TRACE_AGG_FWD;
     a.n_rows = sc.n_rows; a.n_edges = g->n_edges;
     const bool vec = vec_ok(t, X, ldx) && vec_ok(t, Y, ldy) && vec_ok(t, VW, ldvw);
