@@ -50,6 +50,10 @@ struct AggArgs {
     const gt_split *splits;
     int64_t n_splits;
     int64_t table_bytes;     // host-side: size of the gathered table (picks the unroll)
+    int64_t n_long;          // host-side: the first n_long items are long ones (gt_long_min)
+    int chunk;               // host-side: entries of a whole chunk item
+    int n_coop;              // set at launch: the first n_coop workgroups give their items a whole workgroup each
+    int coop_waves;          // (4) or a whole wavefront each (1)
     int xcd_run;             // item blocks per XCD run (0 or 1: plain order)
     int only_split;          // run only the chunk items of split rows (the whole-row items are someone else's)
     int no_reduce;           // host-side: do not launch the kernel that adds the partial rows
@@ -231,11 +235,11 @@ __device__ inline void finish_row(const AggArgs &a, int row, int gl, int64_t col
 // Item block of this workgroup under the XCD-run order (run <= 1: plain order).  The remapping is
 // a bijection on the blocks of every complete group of 8 * run blocks; the ragged end of the grid
 // keeps the plain order.
-__device__ inline int64_t agg_item_block(int run) {
-    int64_t bx = blockIdx.x;
+__device__ inline int64_t agg_item_block(int run, int first = 0) {   // first: blocks before the item blocks
+    int64_t bx = (int64_t)blockIdx.x - first;
     if (gridDim.y == 1 && run > 1) {
         const int64_t super = 8 * (int64_t)run;
-        const int64_t full = (int64_t)gridDim.x / super * super;
+        const int64_t full = ((int64_t)gridDim.x - first) / super * super;
         if (bx < full) {
             const int64_t w = bx % super;
             bx = bx - w + (w & 7) * run + (w >> 3);
@@ -254,6 +258,10 @@ static inline int agg_xcd_run(int64_t gx) {
     return run;
 }
 
+// Instances with cooperative workgroups for the long items (single column tile, eight row loads in flight)
+template <int U, int NP, int VWM>
+constexpr bool agg_coop() { return U == 8 && NP == 1 && VWM == 0; }
+
 // One group of G lanes per work item; 64/G items per wavefront; 4 wavefronts per workgroup.
 // blockIdx.y selects a column tile of G*V*NP columns.
 // MK: an output mask is present (its values are fetched when the item starts; a separate instance so
@@ -269,12 +277,27 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     // sorted so that neighbours in the list gather from the same slice of the table; runs of
     // xcd_run consecutive item blocks are therefore handed to ONE XCD (the runs themselves still
     // rotate over the XCDs, which keeps the longest-first order balanced).
-    const int64_t bx = agg_item_block(a.xcd_run);
-    const int64_t item_id = (bx * 4 + wave) * NG + grp;
-    if (item_id >= a.n_items) return;   // whole groups leave together; no barriers are used below
+    // Cooperative items: a long item walked by one group of lanes is a chain of len / U round trips, and narrow rows pack
+    // 64 / G such chains into one wavefront; a graph of a few million edges has nothing to hide them behind
+    // (100 K vertices, 3 M edges, 15 fp32 columns, both directions: 247 -> 101 us).  The first n_coop workgroups therefore
+    // give each of their items all groups of the workgroup, or of one wavefront where a workgroup's share would be less than
+    // four entries per group: every group sums a slice, and the slices are added in a fixed order.
+    constexpr bool COOP = agg_coop<U, NP, VWM>();
+    const bool coop = COOP && (int)blockIdx.x < a.n_coop;   // uniform over the workgroup
+    const bool one_wave = COOP && a.coop_waves == 1;
+    const int64_t item_id = coop ? (one_wave ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x)
+                                 : (COOP ? (int64_t)a.n_coop * (one_wave ? 4 : 1) : 0) + (agg_item_block(a.xcd_run, COOP ? a.n_coop : 0) * 4 + wave) * NG + grp;
+    if (item_id >= a.n_items) return;   // whole groups leave together; the only barrier below is the cooperative one
     const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
     int row = raw.x, e0 = raw.y, e1 = raw.z, slot = raw.w;
     if (a.only_split && slot < 0) return;   // uniform within the group
+    if (coop) {   // this group's slice
+        const int ng = one_wave ? NG : 4 * NG;
+        const int per = (e1 - e0 + ng - 1) / ng;
+        const int s0 = e0 + (one_wave ? grp : wave * NG + grp) * per;
+        e1 = s0 + per < e1 ? s0 + per : e1;
+        e0 = s0;   // (may lie past e1: an empty slice)
+    }
     if constexpr (G == 64) {   // one item per wavefront: keep its bounds in scalar registers
         row = __builtin_amdgcn_readfirstlane(row);
         e0 = __builtin_amdgcn_readfirstlane(e0);
@@ -379,6 +402,29 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         }
     }
 
+    if constexpr (COOP) {
+        __shared__ float red[4][G * V];
+        if (coop) {
+            // groups of a wavefront: exchanged pairwise; wavefronts: through LDS, in order
+#pragma unroll
+            for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+                for (int i = 0; i < V; ++i) acc[0][i] += __shfl_xor(acc[0][i], o, 64);
+            if (!one_wave) {   // uniform over the launch
+                if (grp == 0) {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) red[wave][i * G + gl] = acc[0][i];
+                }
+                __syncthreads();
+                if (wave != 0) return;
+            }
+            if (grp != 0) return;
+            if (!one_wave)
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+                acc[0][i] = ((red[0][i * G + gl] + red[1][i * G + gl]) + red[2][i * G + gl]) + red[3][i * G + gl];
+        }
+    }
     if (slot >= 0) {
         float *P = a.partials + (int64_t)slot * a.ldp;
 #pragma unroll
@@ -401,7 +447,9 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     }
 }
 
-// Second pass for split rows: add the row's partial rows in chunk order.
+// Second pass for split rows: add the row's partial rows.  One wavefront per row: its 64 / G groups take every (64 / G)-th
+// partial row each, in order, and their sums are added pairwise (a fixed order).  The kernel lasts as long as its
+// longest row, which one group alone walked 16 partial rows at a time (2^21 vertices, 170 partial rows on the longest: 22 -> 12 us).
 template <typename T, int V, int G, int NP, bool SH>
 __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
     constexpr int NG = 64 / G;
@@ -409,7 +457,7 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
     const int wave = threadIdx.x >> 6;
     const int gl = lane & (G - 1);
     const int grp = lane / G;
-    const int64_t sid = ((int64_t)blockIdx.x * 4 + wave) * NG + grp;
+    const int64_t sid = (int64_t)blockIdx.x * 4 + wave;
     if (sid >= a.n_splits) return;
     const gt_split s = a.splits[sid];
     const int64_t col0 = (int64_t)blockIdx.y * (G * V * NP);
@@ -424,17 +472,15 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
 #pragma unroll
         for (int i = 0; i < V; ++i) msk[p][i] = 1.0f;
     if (a.mask) load_mask_row<T, V, G, NP, SH>(a, s.row, gl, col0, msk);
-    // UR partial rows are requested at a time (branch free: a request past the end re-reads the
-    // last row and is discarded) and added in chunk order.  Partial rows are padded to a multiple
-    // of 8 floats, so whole vectors can be read; padding lanes are never stored.  The kernel runs as
-    // long as its longest row (a hub of 86 K entries has 170 partial rows), one memory round trip
-    // per UR rows: sixteen at a time where the registers allow it.
-    constexpr int UR = NP * V <= 8 ? 16 : (NP * V <= 16 ? 8 : 4);
-    for (int k = 0; k < s.count; k += UR) {
+    // UR partial rows per group are requested at a time (branch free: a request past the end re-reads the last row
+    // and is discarded).  Partial rows are padded to a multiple of 8 floats, so whole vectors can be read;
+    // padding lanes are never stored.
+    constexpr int UR = NP * V <= 4 ? 16 : (NP * V <= 16 ? 8 : 4);
+    for (int k = grp; k < s.count; k += UR * NG) {
         float t[UR][NP][V];
 #pragma unroll
         for (int u = 0; u < UR; ++u) {
-            const int kk = (k + u < s.count) ? k + u : s.count - 1;
+            const int kk = (k + u * NG < s.count) ? k + u * NG : s.count - 1;
             const float *P = a.partials + (int64_t)(s.first + kk) * a.ldp;
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
@@ -454,14 +500,20 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < UR; ++u) {
-            const bool live = k + u < s.count;
+            const bool live = k + u * NG < s.count;
 #pragma unroll
             for (int p = 0; p < NP; ++p)
 #pragma unroll
                 for (int i = 0; i < V; ++i) acc[p][i] += live ? t[u][p][i] : 0.0f;
         }
     }
-    finish_row<T, V, G, NP, SH>(a, s.row, gl, col0, acc, msk);
+#pragma unroll
+    for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[p][i] += __shfl_xor(acc[p][i], o, 64);
+    if (grp == 0) finish_row<T, V, G, NP, SH>(a, s.row, gl, col0, acc, msk);
 }
 
 template <typename T, int V, int G, int NP, int U, int VWM, bool SH>
@@ -470,9 +522,16 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
     const int64_t tile = (int64_t)G * V * NP;
     const unsigned gy = (unsigned)((a.F + tile - 1) / tile);
     if (a.n_items > 0) {
-        const int64_t gx = (a.n_items + 4 * NG - 1) / (4 * NG);
         AggArgs b = a;
-        b.xcd_run = agg_xcd_run(gx);
+        b.coop_waves = a.chunk >= 16 * NG ? 4 : 1;
+        const int64_t ipc = b.coop_waves == 1 ? 4 : 1;   // items per cooperative workgroup
+        // A launch that gathers more than 2 GB has enough items to hide a long one behind, and slicing only costs locality
+        // (1.9 GB, 41 fp32 columns: 215 us alone, 192 us cooperative; 2.1 GB, 128 bf16 columns: 244 and 256 us).
+        const bool coop = agg_coop<U, NP, VWM>() && (double)a.n_edges * (double)a.F * sizeof(T) <= 2.0e9;
+        b.n_coop = coop ? (int)((a.n_long + ipc - 1) / ipc) : 0;
+        const int64_t left = a.n_items > b.n_coop * ipc ? a.n_items - b.n_coop * ipc : 0;
+        const int64_t gi = (left + 4 * NG - 1) / (4 * NG), gx = b.n_coop + gi;
+        b.xcd_run = agg_xcd_run(gi);
         const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
         gt_trace_variant(tr, V, G, NP, U, VWM == VWM_NONE && a.mask != nullptr);
         if constexpr (VWM == VWM_NONE) {
@@ -485,7 +544,7 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
         GT_LAUNCH_CHECK("k_aggregate");
     }
     if (a.n_splits > 0 && !a.no_reduce) {
-        const int64_t gx = (a.n_splits + 4 * NG - 1) / (4 * NG);
+        const int64_t gx = (a.n_splits + 3) / 4;
         k_reduce_partials<T, V, G, NP, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(a);
         GT_LAUNCH_CHECK("k_reduce_partials");
     }
@@ -493,12 +552,12 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
 }
 
 // Row loads kept in flight per lane.  Measured on MI355X: two are enough (and best) once the
-// gathered table lives in HBM or rows are 512 bytes or more; narrow rows of a table that fits the
-// last-level cache gain from eight.
+// gathered table lives in HBM (2^18 vertices, 134 MB, 512-byte rows: 503 us, with four 527); rows of a table that
+// fits the last-level cache (rows above 256 bytes: the L2s) gain from eight.
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
-    if constexpr (NP == 1 && G <= 16 && VWM == VWM_NONE) {
-        if (a.table_bytes <= ((int64_t)96 << 20)) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
+    if constexpr (NP == 1 && VWM == VWM_NONE) {
+        if (a.table_bytes <= ((int64_t)(G <= 16 ? 96 : 32) << 20)) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
     }
     // per-entry vector weights stream from memory, each row once, and the gathered table beside them is smaller than they
     // are: eight in flight (4.2 M edges x 64 fp32: two 333 us, four 301, eight 296)

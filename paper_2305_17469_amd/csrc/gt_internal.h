@@ -34,6 +34,10 @@ static inline int gt_chunk_for(int64_t n_edges) {
     return c;
 }
 static inline int gt_split_min(int chunk) { return chunk + chunk / 2; }
+// Items of at least this many entries are "long": they come first in the work list, and kernels may give one a whole
+// workgroup.  A power of two no larger than the chunk: the list is sorted by half-octave length classes, so
+// the items from here on up are exactly its first n_long.
+static inline int gt_long_min(int chunk) { return chunk < 128 ? chunk : 128; }
 
 struct gt_item {   // 16 bytes, loaded as one int4
     int32_t row;   // output row
@@ -57,7 +61,7 @@ struct gt_sched {
     const float *coef_mean = nullptr; // [E] w_e / indeg(dst) (transposed direction only)
     const gt_item *items = nullptr;
     const gt_split *splits = nullptr;
-    int64_t n_rows = 0, n_items = 0, n_splits = 0, n_partials = 0;
+    int64_t n_rows = 0, n_items = 0, n_splits = 0, n_partials = 0, n_long = 0;
 };
 
 struct gt_graph {

@@ -109,13 +109,13 @@ __global__ void k_transposed_entries(const int32_t *rowptr, int64_t n_dst, const
     coef_mean_b[k] = w * rdeg[lo];
 }
 
-// per-row item / partial / split counts
-__global__ void k_item_counts(const int32_t *rowptr, int64_t n_rows, int chunk, int32_t *c_items, int32_t *c_parts,
-                              int32_t *c_splits) {
+// per-row item / partial / split / long-item counts
+__global__ void k_item_counts(const int32_t *rowptr, int64_t n_rows, int chunk, int long_min, int32_t *c_items, int32_t *c_parts,
+                              int32_t *c_splits, int32_t *c_long) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r > n_rows) return;
     if (r == n_rows) {   // the extra entry makes the exclusive scans end with the totals
-        c_items[r] = 0; c_parts[r] = 0; c_splits[r] = 0;
+        c_items[r] = 0; c_parts[r] = 0; c_splits[r] = 0; c_long[r] = 0;
         return;
     }
     const int32_t d = rowptr[r + 1] - rowptr[r];
@@ -124,11 +124,14 @@ __global__ void k_item_counts(const int32_t *rowptr, int64_t n_rows, int chunk, 
     c_items[r] = split ? chunks : 1;
     c_parts[r] = split ? chunks : 0;
     c_splits[r] = split ? 1 : 0;
+    // a split row's chunks are whole (long) except possibly the last
+    c_long[r] = split ? chunks - (d - (chunks - 1) * chunk < long_min ? 1 : 0) : (d >= long_min ? 1 : 0);
 }
 
-__global__ void k_collect_counts(const int32_t *ca, const int32_t *cb, const int32_t *cc, int64_t n_rows, int32_t *cnt3) {
+__global__ void k_collect_counts(const int32_t *ca, const int32_t *cb, const int32_t *cc, const int32_t *cd, int64_t n_rows,
+                                 int32_t *cnt4) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        cnt3[0] = ca[n_rows]; cnt3[1] = cb[n_rows]; cnt3[2] = cc[n_rows];
+        cnt4[0] = ca[n_rows]; cnt4[1] = cb[n_rows]; cnt4[2] = cc[n_rows]; cnt4[3] = cd[n_rows];
     }
 }
 
@@ -159,12 +162,13 @@ __device__ inline uint32_t item_key(int32_t len, const int32_t *nbr, int32_t e0,
 }
 
 __global__ void k_fill_items(const int32_t *rowptr, const int32_t *nbr, int64_t n_in, int64_t n_rows, int chunk,
-                             const int32_t *o_items, const int32_t *o_parts, const int32_t *o_splits, gt_item *items,
-                             uint32_t *keys, gt_split *splits) {
+                             const int32_t *o_items, const int32_t *o_parts, const int32_t *o_splits, const int32_t *o_long,
+                             int long_min, int64_t n_long, gt_item *items, uint32_t *keys, gt_split *splits) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n_rows) return;
     const int32_t b = rowptr[r], e = rowptr[r + 1], d = e - b;
-    int32_t it = o_items[r];
+    // long items first (their order among themselves and that of the others stays the row order)
+    int32_t it_long = o_long[r], it_short = (int32_t)n_long + o_items[r] - o_long[r];
     if (d > chunk + chunk / 2) {
         const int32_t chunks = (d + chunk - 1) / chunk;
         const int32_t p0 = o_parts[r];
@@ -177,14 +181,16 @@ __global__ void k_fill_items(const int32_t *rowptr, const int32_t *nbr, int64_t 
             x.e0 = b + c * chunk;
             x.e1 = min(e, x.e0 + chunk);
             x.slot = p0 + c;
-            items[it + c] = x;
-            keys[it + c] = item_key(x.e1 - x.e0, nbr, x.e0, n_in);
+            const int32_t at = x.e1 - x.e0 >= long_min ? it_long++ : it_short++;
+            items[at] = x;
+            keys[at] = item_key(x.e1 - x.e0, nbr, x.e0, n_in);
         }
     } else {
         gt_item x;
         x.row = (int32_t)r; x.e0 = b; x.e1 = e; x.slot = -1;
-        items[it] = x;
-        keys[it] = item_key(d, nbr, b, n_in);
+        const int32_t at = d >= long_min ? it_long : it_short;
+        items[at] = x;
+        keys[at] = item_key(d, nbr, b, n_in);
     }
 }
 
@@ -211,8 +217,8 @@ struct PlanLayout {
     size_t in_deg, out_deg, rowptr_t, colidx_t, perm, ew_t, dinv, rdeg;
     size_t items_f, splits_f, items_b, splits_b;
     size_t counts;                       // 8 int32 read back by the host
-    size_t ca, cb, cc;                   // per-row count arrays (max(n_dst, n_src) + 1 each), forward direction
-    size_t ca2, cb2, cc2;                // the same for the transposed direction
+    size_t ca, cb, cc, cd;               // per-row count arrays (max(n_dst, n_src) + 1 each), forward direction
+    size_t ca2, cb2, cc2, cd2;           // the same for the transposed direction
     size_t items_tmp, item_keys, item_keys2, item_idx, item_idx2;   // unsorted items, sort keys / indices
     size_t k0, v0, k1, v1;               // sort ping-pong (E each); k0, v0, v1 hold the coefficient arrays afterwards
     size_t hist, scan_tmp;
@@ -244,9 +250,11 @@ PlanLayout plan_layout(int64_t n_dst, int64_t n_src, int64_t E, bool has_ew) {
     L.ca = take((size_t)(nmax + 1) * 4);
     L.cb = take((size_t)(nmax + 1) * 4);
     L.cc = take((size_t)(nmax + 1) * 4);
+    L.cd = take((size_t)(nmax + 1) * 4);
     L.ca2 = take((size_t)(nmax + 1) * 4);
     L.cb2 = take((size_t)(nmax + 1) * 4);
     L.cc2 = take((size_t)(nmax + 1) * 4);
+    L.cd2 = take((size_t)(nmax + 1) * 4);
     L.items_tmp = take((size_t)imax * sizeof(gt_item));
     L.item_keys = take((size_t)imax * 4);
     L.item_keys2 = take((size_t)imax * 4);
@@ -268,20 +276,20 @@ PlanLayout plan_layout(int64_t n_dst, int64_t n_src, int64_t E, bool has_ew) {
 template <typename T>
 T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
 
-// counts of one direction into cnt[0..2] (items, partials, splits): scans of the per-row counts;
+// counts of one direction into cnt[0..3] (items, partials, splits, long items): scans of the per-row counts;
 // the exclusive scan over n_rows + 1 entries (last input 0) leaves the total in element n_rows.
 gt_status count_direction(const int32_t *rowptr, int64_t n_rows, int chunk, void *ws, const PlanLayout &L,
-                          bool transposed, int32_t *cnt3, hipStream_t st) {
+                          bool transposed, int32_t *cnt4, hipStream_t st) {
     int32_t *ca = at<int32_t>(ws, transposed ? L.ca2 : L.ca), *cb = at<int32_t>(ws, transposed ? L.cb2 : L.cb);
-    int32_t *cc = at<int32_t>(ws, transposed ? L.cc2 : L.cc);
+    int32_t *cc = at<int32_t>(ws, transposed ? L.cc2 : L.cc), *cd = at<int32_t>(ws, transposed ? L.cd2 : L.cd);
     int32_t *stmp = at<int32_t>(ws, L.scan_tmp);
-    k_item_counts<<<nblocks(n_rows + 1), PT, 0, st>>>(rowptr, n_rows, chunk, ca, cb, cc);
+    k_item_counts<<<nblocks(n_rows + 1), PT, 0, st>>>(rowptr, n_rows, chunk, gt_long_min(chunk), ca, cb, cc, cd);
     GT_LAUNCH_CHECK("k_item_counts");
     gt_status s;
-    const int32_t *in3[3] = {ca, cb, cc};
-    int32_t *out3[3] = {ca, cb, cc};
-    if ((s = scan_exclusive_batch(3, in3, out3, n_rows + 1, stmp, st)) != GT_OK) return s;
-    k_collect_counts<<<1, 64, 0, st>>>(ca, cb, cc, n_rows, cnt3);
+    const int32_t *in4[4] = {ca, cb, cc, cd};
+    int32_t *out4[4] = {ca, cb, cc, cd};
+    if ((s = scan_exclusive_batch(4, in4, out4, n_rows + 1, stmp, st)) != GT_OK) return s;
+    k_collect_counts<<<1, 64, 0, st>>>(ca, cb, cc, cd, n_rows, cnt4);
     GT_LAUNCH_CHECK("k_collect_counts");
     return GT_OK;
 }
@@ -289,19 +297,19 @@ gt_status count_direction(const int32_t *rowptr, int64_t n_rows, int chunk, void
 // items of one direction, sorted longest first (stable, so equal lengths keep row order).
 constexpr int64_t GT_SORT_ITEMS_MIN = 16384;
 gt_status build_direction(const int32_t *rowptr, const int32_t *nbr, int64_t n_in, int64_t n_rows, int chunk,
-                          int64_t n_items, void *ws, const PlanLayout &L, bool transposed, gt_item *items_out,
+                          int64_t n_items, int64_t n_long, void *ws, const PlanLayout &L, bool transposed, gt_item *items_out,
                           gt_split *splits_out, hipStream_t st) {
     if (n_rows <= 0 || n_items <= 0) return GT_OK;
     int32_t *ca = at<int32_t>(ws, transposed ? L.ca2 : L.ca), *cb = at<int32_t>(ws, transposed ? L.cb2 : L.cb);
-    int32_t *cc = at<int32_t>(ws, transposed ? L.cc2 : L.cc);
+    int32_t *cc = at<int32_t>(ws, transposed ? L.cc2 : L.cc), *cd = at<int32_t>(ws, transposed ? L.cd2 : L.cd);
     gt_item *tmp = at<gt_item>(ws, L.items_tmp);
     uint32_t *keys = at<uint32_t>(ws, L.item_keys), *keys2 = at<uint32_t>(ws, L.item_keys2);
     uint32_t *idx = at<uint32_t>(ws, L.item_idx), *idx2 = at<uint32_t>(ws, L.item_idx2);
     // A small graph is bound by launch latency, not by load balance or locality: its items stay in
-    // row order and the two sort passes and the gather are saved.
+    // row order (long ones first) and the two sort passes and the gather are saved.
     const bool sorted = n_items > GT_SORT_ITEMS_MIN;
-    k_fill_items<<<nblocks(n_rows), PT, 0, st>>>(rowptr, nbr, n_in, n_rows, chunk, ca, cb, cc, sorted ? tmp : items_out, keys,
-                                                 splits_out);
+    k_fill_items<<<nblocks(n_rows), PT, 0, st>>>(rowptr, nbr, n_in, n_rows, chunk, ca, cb, cc, cd, gt_long_min(chunk), n_long,
+                                                 sorted ? tmp : items_out, keys, splits_out);
     GT_LAUNCH_CHECK("k_fill_items");
     if (!sorted) return GT_OK;
     SortTmp t{at<int32_t>(ws, L.hist), at<int32_t>(ws, L.scan_tmp)};
@@ -422,18 +430,20 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
     g->fwd.rowptr = rowptr; g->fwd.nbr = colidx; g->fwd.wt = ew; g->fwd.n_rows = n_dst;
     g->fwd.coef_sym = g->coef_sym_f;
     g->fwd.n_items = h_counts[0]; g->fwd.n_partials = h_counts[1]; g->fwd.n_splits = h_counts[2];
+    g->fwd.n_long = h_counts[3];
     g->fwd.items = at<gt_item>(ws, L.items_f); g->fwd.splits = at<gt_split>(ws, L.splits_f);
     if (g->fwd.n_items > max_items(n_dst, E) || g->fwd.n_splits > max_splits(E))
         return fail(gt_fail(GT_ERR_INTERNAL, "gt_graph_create: forward work list exceeds its bound (is rowptr valid?)"));
     g->bwd.rowptr = g->rowptr_t; g->bwd.nbr = g->colidx_t; g->bwd.wt = g->ew_t; g->bwd.n_rows = n_src;
     g->bwd.coef_sym = g->coef_sym_b; g->bwd.coef_mean = g->coef_mean_b;
     g->bwd.n_items = h_counts[4]; g->bwd.n_partials = h_counts[5]; g->bwd.n_splits = h_counts[6];
+    g->bwd.n_long = h_counts[7];
     g->bwd.items = at<gt_item>(ws, L.items_b); g->bwd.splits = at<gt_split>(ws, L.splits_b);
     if (g->bwd.n_items > max_items(n_src, E) || g->bwd.n_splits > max_splits(E))
         return fail(gt_fail(GT_ERR_INTERNAL, "gt_graph_create: transposed work list exceeds its bound"));
-    if ((s = build_direction(rowptr, colidx, n_src, n_dst, g->chunk, g->fwd.n_items, ws, L, false,
+    if ((s = build_direction(rowptr, colidx, n_src, n_dst, g->chunk, g->fwd.n_items, g->fwd.n_long, ws, L, false,
                              at<gt_item>(ws, L.items_f), at<gt_split>(ws, L.splits_f), st)) != GT_OK) return fail(s);
-    if ((s = build_direction(g->rowptr_t, g->colidx_t, n_dst, n_src, g->chunk, g->bwd.n_items, ws, L, true,
+    if ((s = build_direction(g->rowptr_t, g->colidx_t, n_dst, n_src, g->chunk, g->bwd.n_items, g->bwd.n_long, ws, L, true,
                              at<gt_item>(ws, L.items_b), at<gt_split>(ws, L.splits_b), st)) != GT_OK) return fail(s);
     PLAN_HIP(hipStreamSynchronize(st));
 #undef PLAN_HIP

@@ -76,7 +76,7 @@ size_t scan_tmp_ints(int64_t n) {
     return t + 64;
 }
 
-// Up to three arrays of the same short length in one launch: one workgroup of 1,024 threads per
+// Up to four arrays of the same short length in one launch: one workgroup of 1,024 threads per
 // array walks it in steps of 8,192 elements and carries the running total.  A sampled batch's scans
 // (a few thousand rows) are bound by launch latency; this takes one launch where the tiled form
 // takes three per array.  Only up to two steps: beyond that the single workgroup's serial walk
@@ -84,7 +84,8 @@ size_t scan_tmp_ints(int64_t n) {
 // average on 20-64 K against about 10 us for the three tiled launches).
 constexpr int SCAN_SMALL_THREADS = 1024;
 constexpr int64_t SCAN_SMALL_MAX = 16384;
-struct ScanBatch { const int32_t *in[3]; int32_t *out[3]; };
+constexpr int SCAN_BATCH = 4;
+struct ScanBatch { const int32_t *in[SCAN_BATCH]; int32_t *out[SCAN_BATCH]; };
 
 __global__ void __launch_bounds__(SCAN_SMALL_THREADS) k_scan_small(const ScanBatch b, int64_t n) {
     __shared__ int32_t wave_sums[SCAN_SMALL_THREADS / 64];
@@ -129,12 +130,12 @@ __global__ void __launch_bounds__(SCAN_SMALL_THREADS) k_scan_small(const ScanBat
 
 gt_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *tmp, hipStream_t st);
 
-// out[k][i] = sum_{j<i} in[k][j] for `count` (1..3) arrays of n elements each (in == out allowed).
+// out[k][i] = sum_{j<i} in[k][j] for `count` (1..4) arrays of n elements each (in == out allowed).
 // tmp: scan_tmp_ints(n) int32.
 gt_status scan_exclusive_batch(int count, const int32_t *const *in, int32_t *const *out, int64_t n, int32_t *tmp,
                                hipStream_t st) {
     if (n <= 0 || count <= 0) return GT_OK;
-    if (count > 3) return gt_fail(GT_ERR_INTERNAL, "scan_exclusive_batch: more than three arrays");
+    if (count > SCAN_BATCH) return gt_fail(GT_ERR_INTERNAL, "scan_exclusive_batch: too many arrays");
     if (n <= SCAN_SMALL_MAX) {
         ScanBatch b{};
         for (int k = 0; k < count; ++k) { b.in[k] = in[k]; b.out[k] = out[k]; }

@@ -109,3 +109,32 @@ def test_unaligned_rows_keep_infinities_and_nan_apart(dtype):
     has[1, dst[ci == n - 1]] = True
     assert (np.isinf(Y[:, F - 1]) == has[0]).all() and (np.isnan(Y[:, 0]) == has[1]).all()
     assert np.isfinite(Y[:, 1:F - 1]).all()
+
+
+@pytest.mark.parametrize("hub", [63, 64, 96, 97, 128, 700, 5000])
+@pytest.mark.parametrize("F,dtype", [(3, "f32"), (16, "f32"), (41, "f32"), (100, "bf16"), (200, "f32")])
+def test_long_rows_summed_by_many_groups(F, dtype, hub):
+    """Long items are sliced over the groups of a wavefront or workgroup, and partial rows over the groups of a wavefront:
+    rows around the lengths where an item becomes long or split, on a list of few items (row order) and one of many
+    (sorted), against sums in 64 bits.  Bound: a term passes through at most hub fp32 additions, |error| <=
+    hub 2^-24 sum |x| (bf16: plus the rounding of the result)."""
+    from paper_2305_17469_amd import binding as B
+    for n in (6000, 40000):
+        rng = np.random.default_rng(hub + n)
+        dst = np.concatenate([np.repeat(np.arange(0, n, 37), 3), np.full(hub, 5), np.full(max(hub - 1, 1), 17)])
+        src = np.concatenate([rng.integers(0, n, dst.size - hub - max(hub - 1, 1)), rng.choice(n, hub, replace=False),
+                              rng.choice(n, max(hub - 1, 1), replace=False)])
+        rp, ci = graphs.csr_from_pairs(src, dst, n, n)
+        g = B.Graph(up_i32(rp), up_i32(ci), n)
+        announce("long rows", dtype, "F", F, "hub", hub, "n", n)
+        X = torch.randn((n, F), device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(hub))
+        if dtype == "bf16":
+            X = X.to(torch.bfloat16)
+        Y = B.gt_aggregate_fwd(g, "sum", X)
+        rows = torch.repeat_interleave(torch.arange(n, device="cuda:0"), up_i32(np.diff(rp)).long())
+        t = X.double()[up_i32(ci).long()]
+        ref = torch.zeros((n, F), dtype=torch.float64, device="cuda:0").index_add_(0, rows, t)
+        mag = torch.zeros((n, F), dtype=torch.float64, device="cuda:0").index_add_(0, rows, t.abs())
+        bound = hub * 2.0 ** -24 * mag + (2.0 ** -8 * ref.abs() if dtype == "bf16" else 0)
+        assert bool(((Y.double() - ref).abs() <= bound).all())
+        assert torch.equal(Y, B.gt_aggregate_fwd(g, "sum", X))
