@@ -149,7 +149,6 @@ __global__ void k_emit_local(const uint32_t *spos, int64_t n, int64_t n_dst, con
 
 struct ReindexLayout {
     size_t keysA, keysB, valsA, valsB, head, first, group, hist, scan_tmp, total;
-    int nblk;
 };
 
 ReindexLayout reindex_layout(int64_t n) {
@@ -163,9 +162,8 @@ ReindexLayout reindex_layout(int64_t n) {
     L.head = take((size_t)(n + 1) * 4);
     L.first = take((size_t)(n + 1) * 4);
     L.group = take((size_t)(n + 1) * 4);
-    L.nblk = rs_blocks(n > 0 ? n : 1);
-    L.hist = take((size_t)256 * L.nblk * 4);
-    size_t st = scan_tmp_ints((int64_t)256 * L.nblk), st2 = scan_tmp_ints(n + 1);
+    L.hist = take(rs_hist_ints(n) * 4);
+    size_t st = scan_tmp_ints((int64_t)rs_hist_ints(n)), st2 = 2 * scan_tmp_ints(n + 1);
     L.scan_tmp = take((st > st2 ? st : st2) * 4);
     L.total = off;
     return L;
@@ -295,7 +293,8 @@ extern "C" gt_status gt_reindex(const int32_t *dst, int64_t n_dst, const int32_t
     GT_LAUNCH_CHECK("k_mark_heads");
     const int32_t *in2[2] = {head, first};
     int32_t *out2[2] = {head, first};
-    gt_status s = scan_exclusive_batch(2, in2, out2, n + 1, tmp.scan_tmp, st);
+    const int64_t n2[2] = {n + 1, n + 1};
+    gt_status s = scan_exclusive_batch(2, in2, out2, n2, tmp.scan_tmp, st);
     if (s != GT_OK) return s;
     if (n > 0) {
         k_group_ids<<<nblocks(n), PT, 0, st>>>(kA, vA, n, head, first, group, src_global);

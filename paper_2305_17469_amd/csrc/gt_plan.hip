@@ -62,56 +62,134 @@ namespace {
 constexpr int PT = 256;
 inline unsigned nblocks(int64_t n, int per = PT) { return (unsigned)((n + per - 1) / per); }
 
-__global__ void k_row_degrees(const int32_t *rowptr, int64_t n_rows, int32_t *deg, float *rdeg, float *dinv) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rows) return;
-    const int32_t d = rowptr[r + 1] - rowptr[r];
-    deg[r] = d;
-    if (rdeg) rdeg[r] = d > 0 ? 1.0f / (float)d : 0.0f;
-    if (dinv) dinv[r] = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
-}
-
 // rowptr_t from the sorted source keys: rowptr_t[u] = first position whose key >= u.
 __global__ void k_boundaries(const uint32_t *skeys, int64_t E, int64_t n_src, int32_t *rowptr_t) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k > E) return;
     // position k closes the gap (key[k-1], key[k]]; k == E closes (key[E-1], n_src]
-    const int64_t lo = (k == 0) ? -1 : (int64_t)skeys[k - 1];
+    int64_t lo = (k == 0) ? -1 : (int64_t)skeys[k - 1];
     const int64_t hi = (k == E) ? n_src : (int64_t)skeys[k];
-    for (int64_t u = lo + 1; u <= hi; ++u) rowptr_t[u] = (int32_t)k;
+    // short gaps by their own thread, long ones (runs of vertices without out-edges) by all lanes that are here
+    const uint64_t here = __ballot(1), all = __ballot(hi - lo > 4);
+    const int lane = threadIdx.x & 63, lanes = __popcll(here), mine = __popcll(here & ((1ull << lane) - 1));
+    if (hi - lo <= 4)
+        for (int64_t u = lo + 1; u <= hi; ++u) rowptr_t[u] = (int32_t)k;
+    for (uint64_t m = all; m; m &= m - 1) {
+        const int l = __ffsll((unsigned long long)m) - 1;
+        const int64_t a = __shfl(lo, l), b = __shfl(hi, l), kk = __shfl(k, l);
+        for (int64_t u = a + 1 + mine; u <= b; u += lanes) rowptr_t[u] = (int32_t)kk;
+    }
 }
 
-// Per transposed entry k (position e = perm[k] in the given CSR): its destination, its weight, and
-// the per-entry coefficients of the normalised reduce modes, written in both entry orders:
-//   symmetric norm  w_e / sqrt(d(src) d(dst))   (coef_sym_f[e], coef_sym_b[k]; square graphs)
-//   mean, backward  w_e / indeg(dst)            (coef_mean_b[k])
-__global__ void k_transposed_entries(const int32_t *rowptr, int64_t n_dst, const int32_t *perm, int64_t E,
-                                     const int32_t *colidx, const float *ew, const float *dinv, const float *rdeg,
-                                     int32_t *colidx_t, float *ew_t, float *coef_sym_f, float *coef_sym_b,
+// Row of every entry of a CSR, written coalesced, and (square graphs) the symmetric-norm coefficient
+// w_e / sqrt(d(src) d(dst)) of every entry in the given order.  A workgroup takes ROWS_TILE consecutive entries: it finds the
+// row of its first entry by a 64-way search, marks in LDS where the rows of its range begin, and fills in between with a running
+// maximum.  (Looking up the row of each transposed entry by binary search over rowptr instead, 20 dependent loads
+// per entry, took 1.70 ms on 1 M vertices and 25 M entries; this takes 0.19 and the pass below 0.17.)
+constexpr int ROWS_PER = 8, ROWS_TILE = PT * ROWS_PER;
+__global__ void __launch_bounds__(PT) k_entry_rows(const int32_t *rowptr, int64_t n_rows, int64_t E, const int32_t *colidx,
+                                                   const float *ew, const float *dinv, int32_t *row_of, float *coef_sym) {
+    __shared__ int32_t mark[ROWS_TILE];
+    __shared__ int32_t wmax[PT / 64];
+    __shared__ int64_t bound_row[2];
+    const int64_t base = (int64_t)blockIdx.x * ROWS_TILE;
+    const int64_t end = base + ROWS_TILE < E ? base + ROWS_TILE : E;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = 0; i < ROWS_PER; ++i) mark[i * PT + threadIdx.x] = -1;
+    if (wave < 2) {   // the last row r with rowptr[r] <= at, for the first and the last entry of the tile
+        const int64_t at = wave == 0 ? base : end - 1;
+        int64_t lo = 0, hi = n_rows;
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + 63) / 64;
+            const int64_t r = lo + (lane + 1) * step;          // 64 ascending probes, the last at or past hi
+            const bool le = r < hi && (int64_t)rowptr[r] <= at;
+            const int k = __popcll(__ballot(le));              // probes 1..k are <= at
+            const int64_t nlo = lo + k * step, nhi = lo + (k + 1) * step;
+            lo = nlo;
+            hi = nhi < hi ? nhi : hi;
+        }
+        if (lane == 0) bound_row[wave] = lo;
+    }
+    __syncthreads();
+    const int64_t r0 = bound_row[0], r1 = bound_row[1];
+    if (threadIdx.x == 0) mark[0] = (int32_t)r0;
+    __syncthreads();
+    // rows that begin inside the tile; of several rows beginning at one entry (empty ones) the last owns it
+#pragma unroll 4
+    for (int64_t r = r0 + 1 + threadIdx.x; r <= r1; r += PT) {
+        const int64_t s = rowptr[r];
+        if (s >= base && s < end) atomicMax(&mark[s - base], (int32_t)r);
+    }
+    __syncthreads();
+    int32_t v[ROWS_PER], mx = -1;
+#pragma unroll
+    for (int i = 0; i < ROWS_PER; ++i) {
+        mx = max(mx, mark[threadIdx.x * ROWS_PER + i]);
+        v[i] = mx;
+    }
+    int32_t inc = mx;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t x = __shfl_up(inc, o, 64);
+        if (lane >= o) inc = max(inc, x);
+    }
+    if (lane == 63) wmax[wave] = inc;
+    int32_t pre = __shfl_up(inc, 1, 64);
+    if (lane == 0) pre = -1;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) pre = max(pre, wmax[w]);
+#pragma unroll
+    for (int i = 0; i < ROWS_PER; ++i) mark[threadIdx.x * ROWS_PER + i] = max(v[i], pre);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ROWS_PER; ++i) {
+        const int64_t e = base + i * PT + threadIdx.x;
+        if (e >= end) continue;
+        const int32_t r = mark[i * PT + threadIdx.x];
+        row_of[e] = r;
+        if (dinv) coef_sym[e] = ((ew ? ew[e] : 1.0f) * dinv[colidx[e]]) * dinv[r];
+    }
+}
+
+// Per transposed entry k (position e = perm[k] in the given CSR, source u = skeys[k]): its destination, its weight, and
+// the per-entry coefficients of the normalised reduce modes in this order:
+//   symmetric norm  w_e / sqrt(d(src) d(dst))   (coef_sym_b[k]; square graphs)
+//   mean, backward  w_e / indeg(dst)            (coef_mean_b[k]; may be the array of skeys)
+// row_of null: the destinations have travelled through the sort and are in colidx_t already (looking each one up by its
+// entry is a random 4-byte read from an array of E: 25 M entries 0.51 ms, carried along 0.28 ms more in the sort).
+__global__ void k_transposed_entries(const int32_t *perm, const uint32_t *skeys, const int32_t *row_of, int64_t E, const float *ew,
+                                     const int32_t *in_deg, int square, int32_t *colidx_t, float *ew_t, float *coef_sym_b,
                                      float *coef_mean_b) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= E) return;
-    const int32_t e = perm[k];
-    // destination of entry e: the last row v with rowptr[v] <= e
-    int64_t lo = 0, hi = n_dst;   // invariant: rowptr[lo] <= e < rowptr[hi]
-    while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (rowptr[mid] <= e) lo = mid; else hi = mid;
+    const uint32_t u = skeys[k];
+    int32_t v;
+    float w = 1.0f;
+    if (row_of) {
+        const int32_t e = perm[k];
+        v = row_of[e];
+        colidx_t[k] = v;
+    } else {
+        v = colidx_t[k];
     }
-    colidx_t[k] = (int32_t)lo;
-    const float w = ew ? ew[e] : 1.0f;
-    if (ew_t) ew_t[k] = w;
-    if (dinv) {
-        const float c = (w * dinv[colidx[e]]) * dinv[lo];
-        coef_sym_f[e] = c;
-        coef_sym_b[k] = c;
+    if (ew_t) {
+        w = ew[perm[k]];
+        ew_t[k] = w;
     }
-    coef_mean_b[k] = w * rdeg[lo];
+    // (the reciprocals from the degree, as k_row_counts forms them: one gather per vertex instead of two)
+    const int32_t d = in_deg[v];
+    if (square) {
+        const int32_t du = in_deg[u];
+        const float iu = du > 0 ? 1.0f / sqrtf((float)du) : 0.0f, iv = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
+        coef_sym_b[k] = (w * iu) * iv;
+    }
+    coef_mean_b[k] = w * (d > 0 ? 1.0f / (float)d : 0.0f);
 }
 
-// per-row item / partial / split / long-item counts
-__global__ void k_item_counts(const int32_t *rowptr, int64_t n_rows, int chunk, int long_min, int32_t *c_items, int32_t *c_parts,
-                              int32_t *c_splits, int32_t *c_long) {
+// per row: degree (with its reciprocal and reciprocal square root where wanted) and item / partial / split / long-item counts
+__global__ void k_row_counts(const int32_t *rowptr, int64_t n_rows, int chunk, int long_min, int32_t *deg, float *rdeg, float *dinv,
+                             int32_t *c_items, int32_t *c_parts, int32_t *c_splits, int32_t *c_long) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r > n_rows) return;
     if (r == n_rows) {   // the extra entry makes the exclusive scans end with the totals
@@ -119,6 +197,9 @@ __global__ void k_item_counts(const int32_t *rowptr, int64_t n_rows, int chunk, 
         return;
     }
     const int32_t d = rowptr[r + 1] - rowptr[r];
+    deg[r] = d;
+    if (rdeg) rdeg[r] = d > 0 ? 1.0f / (float)d : 0.0f;
+    if (dinv) dinv[r] = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
     const bool split = d > chunk + chunk / 2;
     const int32_t chunks = (d + chunk - 1) / chunk;
     c_items[r] = split ? chunks : 1;
@@ -128,11 +209,9 @@ __global__ void k_item_counts(const int32_t *rowptr, int64_t n_rows, int chunk, 
     c_long[r] = split ? chunks - (d - (chunks - 1) * chunk < long_min ? 1 : 0) : (d >= long_min ? 1 : 0);
 }
 
-__global__ void k_collect_counts(const int32_t *ca, const int32_t *cb, const int32_t *cc, const int32_t *cd, int64_t n_rows,
-                                 int32_t *cnt4) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        cnt4[0] = ca[n_rows]; cnt4[1] = cb[n_rows]; cnt4[2] = cc[n_rows]; cnt4[3] = cd[n_rows];
-    }
+struct CountArrays { const int32_t *c[8]; };   // forward: items, partials, splits, long items; transposed: the same
+__global__ void k_collect_counts(const CountArrays a, int64_t n_dst, int64_t n_src, int32_t *cnt8) {
+    if (threadIdx.x < 8) cnt8[threadIdx.x] = a.c[threadIdx.x][threadIdx.x < 4 ? n_dst : n_src];
 }
 
 __device__ inline uint32_t length_key(int32_t len) {
@@ -168,23 +247,32 @@ __global__ void k_fill_items(const int32_t *rowptr, const int32_t *nbr, int64_t 
     if (r >= n_rows) return;
     const int32_t b = rowptr[r], e = rowptr[r + 1], d = e - b;
     // long items first (their order among themselves and that of the others stays the row order)
-    int32_t it_long = o_long[r], it_short = (int32_t)n_long + o_items[r] - o_long[r];
-    if (d > chunk + chunk / 2) {
-        const int32_t chunks = (d + chunk - 1) / chunk;
-        const int32_t p0 = o_parts[r];
-        gt_split s;
-        s.row = (int32_t)r; s.first = p0; s.count = chunks; s.pad = 0;
-        splits[o_splits[r]] = s;
-        for (int32_t c = 0; c < chunks; ++c) {
+    const int32_t it_long = o_long[r], it_short = (int32_t)n_long + o_items[r] - o_long[r];
+    const bool split = d > chunk + chunk / 2;
+    const int32_t chunks = split ? (d + chunk - 1) / chunk : 0, p0 = split ? o_parts[r] : 0;
+    // the chunks of a split row are written by all lanes that are here (a hub row has hundreds, each with a dependent
+    // read of its median neighbour; one thread alone was the kernel's whole time)
+    const uint64_t here = __ballot(1);
+    const int lane = threadIdx.x & 63, lanes = __popcll(here), mine = __popcll(here & ((1ull << lane) - 1));
+    for (uint64_t m = __ballot(split); m; m &= m - 1) {
+        const int l = __ffsll((unsigned long long)m) - 1;
+        const int32_t row = __shfl((int32_t)r, l), rb = __shfl(b, l), re = __shfl(e, l), nc = __shfl(chunks, l), rp = __shfl(p0, l);
+        const int32_t al = __shfl(it_long, l), as = __shfl(it_short, l);
+        for (int32_t c = mine; c < nc; c += lanes) {
             gt_item x;
-            x.row = (int32_t)r;
-            x.e0 = b + c * chunk;
-            x.e1 = min(e, x.e0 + chunk);
-            x.slot = p0 + c;
-            const int32_t at = x.e1 - x.e0 >= long_min ? it_long++ : it_short++;
+            x.row = row;
+            x.e0 = rb + c * chunk;
+            x.e1 = min(re, x.e0 + chunk);
+            x.slot = rp + c;
+            const int32_t at = x.e1 - x.e0 >= long_min ? al + c : as;   // (only the last chunk may be short)
             items[at] = x;
             keys[at] = item_key(x.e1 - x.e0, nbr, x.e0, n_in);
         }
+    }
+    if (split) {
+        gt_split s;
+        s.row = (int32_t)r; s.first = p0; s.count = chunks; s.pad = 0;
+        splits[o_splits[r]] = s;
     } else {
         gt_item x;
         x.row = (int32_t)r; x.e0 = b; x.e1 = e; x.slot = -1;
@@ -220,7 +308,8 @@ struct PlanLayout {
     size_t ca, cb, cc, cd;               // per-row count arrays (max(n_dst, n_src) + 1 each), forward direction
     size_t ca2, cb2, cc2, cd2;           // the same for the transposed direction
     size_t items_tmp, item_keys, item_keys2, item_idx, item_idx2;   // unsorted items, sort keys / indices
-    size_t k0, v0, k1, v1;               // sort ping-pong (E each); k0, v0, v1 hold the coefficient arrays afterwards
+    size_t k0, v0, k1, v1, e0, e1;       // sort ping-pong (E each); one of k0 / k1, and v1, hold coefficients afterwards
+    size_t coef_f;                       // symmetric-norm coefficients of the given order
     size_t hist, scan_tmp;
     size_t total;
 };
@@ -264,35 +353,20 @@ PlanLayout plan_layout(int64_t n_dst, int64_t n_src, int64_t E, bool has_ew) {
     L.v0 = take((size_t)E * 4);
     L.k1 = take((size_t)E * 4);
     L.v1 = take((size_t)E * 4);
+    L.e0 = take((size_t)E * 4);
+    L.e1 = take((size_t)E * 4);
+    L.coef_f = take(n_dst == n_src ? (size_t)E * 4 : 0);
     const int64_t nsort = E > imax ? E : imax;
-    const int64_t hist_n = (int64_t)256 * (rs_blocks(nsort) + 1);
+    const int64_t hist_n = (int64_t)rs_hist_ints(nsort);
     L.hist = take((size_t)hist_n * 4);
-    const int64_t scan_n = hist_n > nmax + 1 ? hist_n : nmax + 1;
-    L.scan_tmp = take(scan_tmp_ints(scan_n) * 4);
+    const size_t scan_h = scan_tmp_ints(hist_n), scan_c = 8 * scan_tmp_ints(nmax + 1);
+    L.scan_tmp = take((scan_h > scan_c ? scan_h : scan_c) * 4);
     L.total = off;
     return L;
 }
 
 template <typename T>
 T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(ws) + off); }
-
-// counts of one direction into cnt[0..3] (items, partials, splits, long items): scans of the per-row counts;
-// the exclusive scan over n_rows + 1 entries (last input 0) leaves the total in element n_rows.
-gt_status count_direction(const int32_t *rowptr, int64_t n_rows, int chunk, void *ws, const PlanLayout &L,
-                          bool transposed, int32_t *cnt4, hipStream_t st) {
-    int32_t *ca = at<int32_t>(ws, transposed ? L.ca2 : L.ca), *cb = at<int32_t>(ws, transposed ? L.cb2 : L.cb);
-    int32_t *cc = at<int32_t>(ws, transposed ? L.cc2 : L.cc), *cd = at<int32_t>(ws, transposed ? L.cd2 : L.cd);
-    int32_t *stmp = at<int32_t>(ws, L.scan_tmp);
-    k_item_counts<<<nblocks(n_rows + 1), PT, 0, st>>>(rowptr, n_rows, chunk, gt_long_min(chunk), ca, cb, cc, cd);
-    GT_LAUNCH_CHECK("k_item_counts");
-    gt_status s;
-    const int32_t *in4[4] = {ca, cb, cc, cd};
-    int32_t *out4[4] = {ca, cb, cc, cd};
-    if ((s = scan_exclusive_batch(4, in4, out4, n_rows + 1, stmp, st)) != GT_OK) return s;
-    k_collect_counts<<<1, 64, 0, st>>>(ca, cb, cc, cd, n_rows, cnt4);
-    GT_LAUNCH_CHECK("k_collect_counts");
-    return GT_OK;
-}
 
 // items of one direction, sorted longest first (stable, so equal lengths keep row order).
 constexpr int64_t GT_SORT_ITEMS_MIN = 16384;
@@ -374,57 +448,72 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
 #define PLAN_HIP(call) do { hipError_t e__ = (call); if (e__ != hipSuccess) return fail(gt_hip_fail(e__, #call)); } while (0)
 #define PLAN_LAUNCH(what) do { hipError_t e__ = hipGetLastError(); if (e__ != hipSuccess) return fail(gt_hip_fail(e__, what)); } while (0)
 
-    // degrees of the given CSR
-    if (n_dst > 0) {
-        k_row_degrees<<<nblocks(n_dst), PT, 0, st>>>(rowptr, n_dst, g->in_deg, g->rdeg, g->dinv);
-        PLAN_LAUNCH("k_row_degrees");
-    }
-    // transposed structure: stable sort of (source, position) pairs by source
+    const int chunk = gt_chunk_for(E), long_min = gt_long_min(chunk);
+    g->chunk = chunk;
+    int32_t *ca = at<int32_t>(ws, L.ca), *cb = at<int32_t>(ws, L.cb), *cc = at<int32_t>(ws, L.cc), *cd = at<int32_t>(ws, L.cd);
+    int32_t *ca2 = at<int32_t>(ws, L.ca2), *cb2 = at<int32_t>(ws, L.cb2), *cc2 = at<int32_t>(ws, L.cc2), *cd2 = at<int32_t>(ws, L.cd2);
+    // degrees and work-list counts of the given CSR
+    k_row_counts<<<nblocks(n_dst + 1), PT, 0, st>>>(rowptr, n_dst, chunk, long_min, g->in_deg, g->rdeg, g->dinv, ca, cb, cc, cd);
+    PLAN_LAUNCH("k_row_counts");
+    // transposed structure: stable sort of (source, position) pairs by source.  A sort that runs pass by pass carries the
+    // entries' destinations along; the one-launch sort of a short list has its LDS full with the pairs.
     SortTmp t{at<int32_t>(ws, L.hist), at<int32_t>(ws, L.scan_tmp)};
     uint32_t *k0 = at<uint32_t>(ws, L.k0), *v0 = at<uint32_t>(ws, L.v0);
     uint32_t *k1 = at<uint32_t>(ws, L.k1), *v1 = at<uint32_t>(ws, L.v1);
+    uint32_t *e0 = at<uint32_t>(ws, L.e0), *e1 = at<uint32_t>(ws, L.e1);
+    int32_t *row_of = reinterpret_cast<int32_t *>(e1);   // read by the first pass, which writes e0 or the final place
+    const bool carry = E > RS_ONE_MAX;
     const uint32_t *sorted_keys = reinterpret_cast<const uint32_t *>(colidx);
     if (E > 0) {
+        g->coef_sym_f = g->dinv ? at<float>(ws, L.coef_f) : nullptr;
+        k_entry_rows<<<nblocks(E, ROWS_TILE), PT, 0, st>>>(rowptr, n_dst, E, colidx, ew, g->dinv, row_of, g->coef_sym_f);
+        PLAN_LAUNCH("k_entry_rows");
         int bits = 1;
         while (bits < 32 && ((int64_t)1 << bits) < n_src) ++bits;
         const int passes = (bits + 7) / 8;
         const uint32_t *kin = reinterpret_cast<const uint32_t *>(colidx);
-        const uint32_t *vin = nullptr;
+        const uint32_t *vin = nullptr, *ein = carry ? e1 : nullptr;
         SortPasses sp{};
         sp.passes = passes;
         for (int p = 0; p < passes; ++p) {
+            const bool last = p == passes - 1;
             uint32_t *ko = (p & 1) ? k1 : k0;
-            uint32_t *vo = (p == passes - 1) ? reinterpret_cast<uint32_t *>(g->perm) : ((p & 1) ? v1 : v0);
+            uint32_t *vo = last ? reinterpret_cast<uint32_t *>(g->perm) : ((p & 1) ? v1 : v0);
+            uint32_t *eo = last ? reinterpret_cast<uint32_t *>(g->colidx_t) : ((p & 1) ? e1 : e0);
             sp.kin[p] = kin; sp.vin[p] = vin; sp.kout[p] = ko; sp.vout[p] = vo;
+            sp.ein[p] = ein; sp.eout[p] = carry ? eo : nullptr;
             kin = ko; vin = vo;
+            if (carry) ein = eo;
         }
         if ((s = radix_sort(sp, E, t, st)) != GT_OK) return fail(s);
         sorted_keys = kin;
     }
-    if (n_src >= 0) {
-        k_boundaries<<<nblocks(E + 1), PT, 0, st>>>(sorted_keys, E, n_src, g->rowptr_t);
-        PLAN_LAUNCH("k_boundaries");
-    }
-    if (n_src > 0) {
-        k_row_degrees<<<nblocks(n_src), PT, 0, st>>>(g->rowptr_t, n_src, g->out_deg, nullptr, nullptr);
-        PLAN_LAUNCH("k_row_degrees(out)");
-    }
+    k_boundaries<<<nblocks(E + 1), PT, 0, st>>>(sorted_keys, E, n_src, g->rowptr_t);
+    PLAN_LAUNCH("k_boundaries");
+    k_row_counts<<<nblocks(n_src + 1), PT, 0, st>>>(g->rowptr_t, n_src, chunk, long_min, g->out_deg, nullptr, nullptr, ca2, cb2, cc2, cd2);
+    PLAN_LAUNCH("k_row_counts(out)");
     if (E > 0) {
-        // the sort's ping-pong buffers are dead from here on; three of them hold the coefficients
-        g->coef_sym_f = g->dinv ? reinterpret_cast<float *>(v0) : nullptr;
+        // the sort's ping-pong buffers are dead from here on, except the sorted keys (k0 or k1), which each entry's thread
+        // reads before it writes its mean coefficient in their place
         g->coef_sym_b = g->dinv ? reinterpret_cast<float *>(v1) : nullptr;
-        g->coef_mean_b = reinterpret_cast<float *>(k0);
-        k_transposed_entries<<<nblocks(E), PT, 0, st>>>(rowptr, n_dst, g->perm, E, colidx, ew, g->dinv, g->rdeg,
-                                                        g->colidx_t, g->ew_t, g->coef_sym_f, g->coef_sym_b,
-                                                        g->coef_mean_b);
+        g->coef_mean_b = reinterpret_cast<float *>(sorted_keys == k0 ? k0 : k1);
+        k_transposed_entries<<<nblocks(E), PT, 0, st>>>(g->perm, sorted_keys, carry ? nullptr : row_of, E, ew, g->in_deg, g->dinv ? 1 : 0,
+                                                        g->colidx_t, g->ew_t, g->coef_sym_b, g->coef_mean_b);
         PLAN_LAUNCH("k_transposed_entries");
     }
-    // work-list sizes of both directions, read back once
+    // work-list sizes of both directions: the exclusive scans over n_rows + 1 entries (last input 0) leave the totals in element
+    // n_rows; read back once
     int32_t *d_counts = at<int32_t>(ws, L.counts);
     int32_t h_counts[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    g->chunk = gt_chunk_for(E);
-    if ((s = count_direction(rowptr, n_dst, g->chunk, ws, L, false, d_counts, st)) != GT_OK) return fail(s);
-    if ((s = count_direction(g->rowptr_t, n_src, g->chunk, ws, L, true, d_counts + 4, st)) != GT_OK) return fail(s);
+    {
+        int32_t *const arr[8] = {ca, cb, cc, cd, ca2, cb2, cc2, cd2};
+        const int64_t len[8] = {n_dst + 1, n_dst + 1, n_dst + 1, n_dst + 1, n_src + 1, n_src + 1, n_src + 1, n_src + 1};
+        if ((s = scan_exclusive_batch(8, arr, arr, len, t.scan_tmp, st)) != GT_OK) return fail(s);
+        CountArrays counts;
+        for (int k = 0; k < 8; ++k) counts.c[k] = arr[k];
+        k_collect_counts<<<1, 64, 0, st>>>(counts, n_dst, n_src, d_counts);
+        PLAN_LAUNCH("k_collect_counts");
+    }
     PLAN_HIP(hipMemcpyAsync(h_counts, d_counts, 8 * 4, hipMemcpyDeviceToHost, st));
     PLAN_HIP(hipStreamSynchronize(st));
     g->fwd.rowptr = rowptr; g->fwd.nbr = colidx; g->fwd.wt = ew; g->fwd.n_rows = n_dst;

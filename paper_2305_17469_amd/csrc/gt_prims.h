@@ -7,29 +7,39 @@
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// exclusive scan of int32 (reduce-then-scan, recursive over block sums)
+// exclusive scan of int32, several arrays at a time
 // ---------------------------------------------------------------------------------------------
 
 constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_PER_THREAD = 8;
-constexpr int SCAN_TILE = SCAN_THREADS * SCAN_PER_THREAD;
+constexpr int SCAN_PER_THREAD = 16;
+constexpr int SCAN_TILE = SCAN_THREADS * SCAN_PER_THREAD;   // 4096
+constexpr int SCAN_BATCH = 8;
+constexpr int64_t SCAN_DIRECT_TILES = 1024;   // up to here every workgroup adds the tile sums before its own itself
 
+struct ScanBatch {
+    const int32_t *in[SCAN_BATCH];
+    int32_t *out[SCAN_BATCH];
+    int64_t n[SCAN_BATCH];
+    int32_t *sums[SCAN_BATCH];   // tile sums (or, scanned, tile offsets) of each array
+};
+
+// Exclusive prefix of v over a workgroup of 64 * W threads; *total = its sum.  Leaves with the staging free for reuse.
+template <int W>
 __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
-    // 256 threads; returns exclusive prefix of v over the block, *total = block sum
-    __shared__ int32_t wave_sums[SCAN_THREADS / 64];
+    __shared__ int32_t wave_sums[W];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t inc = v;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        int32_t o = __shfl_up(inc, d, 64);
+        const int32_t o = __shfl_up(inc, d, 64);
         if (lane >= d) inc += o;
     }
     if (lane == 63) wave_sums[wave] = inc;
     __syncthreads();
     int32_t base = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
-        int32_t s = wave_sums[w];
+    for (int w = 0; w < W; ++w) {
+        const int32_t s = wave_sums[w];
         if (w < wave) base += s;
         tot += s;
     }
@@ -38,192 +48,232 @@ __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
     return base + inc - v;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(const int32_t *in, int32_t *out, int64_t n,
-                                                             int32_t *tile_sums) {
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_PER_THREAD;
+// sums[tile] of array blockIdx.y
+__global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(const ScanBatch b) {
+    const int k = blockIdx.y;
+    const int64_t n = b.n[k], base = (int64_t)blockIdx.x * SCAN_TILE;
+    if (base >= n) return;
+    int32_t s = 0;
+#pragma unroll
+    for (int i = 0; i < SCAN_PER_THREAD; ++i) {
+        const int64_t p = base + i * SCAN_THREADS + threadIdx.x;
+        s += p < n ? b.in[k][p] : 0;
+    }
+    int32_t total;
+    block_exclusive_scan<SCAN_THREADS / 64>(s, &total);
+    if (threadIdx.x == 0) b.sums[k][blockIdx.x] = total;
+}
+
+// out of one tile of array blockIdx.y: the tile's offset is the sum of the tile sums before it (added up here, or
+// already scanned), the rest a scan inside the workgroup.  Two launches for all arrays, and every element is written
+// once (scanning tiles, then adding offsets in place, took three launches per array and wrote twice: the
+// eight count arrays of a plan over 1 M rows 190 -> 40 us).
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_apply(const ScanBatch b, int scanned) {
+    const int k = blockIdx.y;
+    const int64_t n = b.n[k], base = (int64_t)blockIdx.x * SCAN_TILE;
+    if (base >= n) return;
+    int32_t off = 0;
+    if (scanned) {
+        off = b.sums[k][blockIdx.x];
+    } else {
+        int32_t s = 0;
+        for (int t = threadIdx.x; t < (int)blockIdx.x; t += SCAN_THREADS) s += b.sums[k][t];
+        block_exclusive_scan<SCAN_THREADS / 64>(s, &off);
+    }
+    const int64_t p0 = base + (int64_t)threadIdx.x * SCAN_PER_THREAD;
     int32_t v[SCAN_PER_THREAD];
     int32_t s = 0;
 #pragma unroll
     for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-        v[i] = (base + i < n) ? in[base + i] : 0;
+        v[i] = p0 + i < n ? b.in[k][p0 + i] : 0;
         s += v[i];
     }
     int32_t total;
-    int32_t ex = block_exclusive_scan(s, &total);
+    int32_t ex = off + block_exclusive_scan<SCAN_THREADS / 64>(s, &total);
 #pragma unroll
     for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-        if (base + i < n) out[base + i] = ex;
+        if (p0 + i < n) b.out[k][p0 + i] = ex;
         ex += v[i];
     }
-    if (threadIdx.x == 0 && tile_sums) tile_sums[blockIdx.x] = total;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_add(int32_t *out, int64_t n, const int32_t *tile_offs) {
-    const int32_t add = tile_offs[blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_PER_THREAD;
-#pragma unroll
-    for (int i = 0; i < SCAN_PER_THREAD; ++i)
-        if (base + i < n) out[base + i] += add;
-}
-
+// int32 of scratch one array of n elements takes (a batch: the sum over its arrays)
 size_t scan_tmp_ints(int64_t n) {
-    size_t t = 0;
+    size_t t = 64;
     while (n > SCAN_TILE) {
-        int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-        t += gt_align_up((size_t)tiles * 4) / 4;
-        n = tiles;
+        n = (n + SCAN_TILE - 1) / SCAN_TILE;
+        t += gt_align_up((size_t)n * 4) / 4;
     }
-    return t + 64;
+    return t;
 }
 
-// Up to four arrays of the same short length in one launch: one workgroup of 1,024 threads per
-// array walks it in steps of 8,192 elements and carries the running total.  A sampled batch's scans
-// (a few thousand rows) are bound by launch latency; this takes one launch where the tiled form
-// takes three per array.  Only up to two steps: beyond that the single workgroup's serial walk
-// costs more than the launches it saves (measured on MI355X: 6.6 us at 13 K elements, 16.6 us
-// average on 20-64 K against about 10 us for the three tiled launches).
+// Short arrays in one launch: one workgroup of 1,024 threads per array walks it in steps of 16,384 elements and
+// carries the running total.  A sampled batch's scans (a few thousand rows) are bound by launch latency.
+// Only up to one step: beyond that the serial walk costs more than the launch it saves.
 constexpr int SCAN_SMALL_THREADS = 1024;
 constexpr int64_t SCAN_SMALL_MAX = 16384;
-constexpr int SCAN_BATCH = 4;
-struct ScanBatch { const int32_t *in[SCAN_BATCH]; int32_t *out[SCAN_BATCH]; };
 
-__global__ void __launch_bounds__(SCAN_SMALL_THREADS) k_scan_small(const ScanBatch b, int64_t n) {
-    __shared__ int32_t wave_sums[SCAN_SMALL_THREADS / 64];
-    const int32_t *in = b.in[blockIdx.x];
-    int32_t *out = b.out[blockIdx.x];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ void __launch_bounds__(SCAN_SMALL_THREADS) k_scan_small(const ScanBatch b) {
+    const int k = blockIdx.x;
+    const int64_t n = b.n[k];
     int32_t carry = 0;
     for (int64_t t0 = 0; t0 < n; t0 += (int64_t)SCAN_SMALL_THREADS * SCAN_PER_THREAD) {
-        const int64_t base = t0 + (int64_t)threadIdx.x * SCAN_PER_THREAD;
+        const int64_t p0 = t0 + (int64_t)threadIdx.x * SCAN_PER_THREAD;
         int32_t v[SCAN_PER_THREAD];
         int32_t s = 0;
 #pragma unroll
         for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-            v[i] = (base + i < n) ? in[base + i] : 0;
+            v[i] = p0 + i < n ? b.in[k][p0 + i] : 0;
             s += v[i];
         }
-        int32_t inc = s;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int32_t o = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += o;
-        }
-        if (lane == 63) wave_sums[wave] = inc;
-        __syncthreads();
-        int32_t before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < SCAN_SMALL_THREADS / 64; ++w) {
-            const int32_t ws = wave_sums[w];
-            if (w < wave) before += ws;
-            total += ws;
-        }
-        __syncthreads();   // wave_sums is rewritten in the next step
-        int32_t ex = carry + before + inc - s;
+        int32_t total;
+        int32_t ex = carry + block_exclusive_scan<SCAN_SMALL_THREADS / 64>(s, &total);
 #pragma unroll
         for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-            if (base + i < n) out[base + i] = ex;
+            if (p0 + i < n) b.out[k][p0 + i] = ex;
             ex += v[i];
         }
         carry += total;
     }
 }
 
-gt_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *tmp, hipStream_t st);
-
-// out[k][i] = sum_{j<i} in[k][j] for `count` (1..4) arrays of n elements each (in == out allowed).
-// tmp: scan_tmp_ints(n) int32.
-gt_status scan_exclusive_batch(int count, const int32_t *const *in, int32_t *const *out, int64_t n, int32_t *tmp,
+// out[k][i] = sum_{j<i} in[k][j] for `count` (1..8) arrays of n[k] elements (in == out allowed).
+// tmp: the sum of scan_tmp_ints(n[k]) int32.
+gt_status scan_exclusive_batch(int count, const int32_t *const *in, int32_t *const *out, const int64_t *n, int32_t *tmp,
                                hipStream_t st) {
-    if (n <= 0 || count <= 0) return GT_OK;
+    if (count <= 0) return GT_OK;
     if (count > SCAN_BATCH) return gt_fail(GT_ERR_INTERNAL, "scan_exclusive_batch: too many arrays");
-    if (n <= SCAN_SMALL_MAX) {
-        ScanBatch b{};
-        for (int k = 0; k < count; ++k) { b.in[k] = in[k]; b.out[k] = out[k]; }
-        k_scan_small<<<count, SCAN_SMALL_THREADS, 0, st>>>(b, n);
+    ScanBatch b{};
+    int64_t most = 0;
+    for (int k = 0; k < count; ++k) {
+        b.in[k] = in[k]; b.out[k] = out[k]; b.n[k] = n[k];
+        if (n[k] > most) most = n[k];
+    }
+    if (most <= 0) return GT_OK;
+    if (most <= SCAN_SMALL_MAX) {
+        k_scan_small<<<count, SCAN_SMALL_THREADS, 0, st>>>(b);
         GT_LAUNCH_CHECK("k_scan_small");
         return GT_OK;
     }
+    int64_t tiles[SCAN_BATCH] = {};
     for (int k = 0; k < count; ++k) {
-        const gt_status s = scan_exclusive(in[k], out[k], n, tmp, st);
+        tiles[k] = (n[k] + SCAN_TILE - 1) / SCAN_TILE;
+        b.sums[k] = tmp;
+        tmp += gt_align_up((size_t)tiles[k] * 4) / 4;
+    }
+    const int64_t mt = (most + SCAN_TILE - 1) / SCAN_TILE;
+    k_tile_sums<<<dim3((unsigned)mt, count), SCAN_THREADS, 0, st>>>(b);
+    GT_LAUNCH_CHECK("k_tile_sums");
+    const int scanned = mt > SCAN_DIRECT_TILES;
+    if (scanned) {
+        const gt_status s = scan_exclusive_batch(count, b.sums, b.sums, tiles, tmp, st);
         if (s != GT_OK) return s;
     }
+    k_scan_apply<<<dim3((unsigned)mt, count), SCAN_THREADS, 0, st>>>(b, scanned);
+    GT_LAUNCH_CHECK("k_scan_apply");
     return GT_OK;
 }
 
 // out[i] = sum_{j<i} in[j] for i < n (in == out allowed).  tmp: scan_tmp_ints(n) int32.
 gt_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *tmp, hipStream_t st) {
-    if (n <= 0) return GT_OK;
-    if (n <= SCAN_SMALL_MAX) return scan_exclusive_batch(1, &in, &out, n, tmp, st);
-    const int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-    if (tiles == 1) {
-        k_scan_tiles<<<1, SCAN_THREADS, 0, st>>>(in, out, n, nullptr);
-        GT_LAUNCH_CHECK("k_scan_tiles");
-        return GT_OK;
-    }
-    k_scan_tiles<<<(unsigned)tiles, SCAN_THREADS, 0, st>>>(in, out, n, tmp);
-    GT_LAUNCH_CHECK("k_scan_tiles");
-    int32_t *next = tmp + gt_align_up((size_t)tiles * 4) / 4;
-    gt_status s = scan_exclusive(tmp, tmp, tiles, next, st);
-    if (s != GT_OK) return s;
-    k_scan_add<<<(unsigned)tiles, SCAN_THREADS, 0, st>>>(out, n, tmp);
-    GT_LAUNCH_CHECK("k_scan_add");
-    return GT_OK;
+    return scan_exclusive_batch(1, &in, &out, &n, tmp, st);
 }
 
 // ---------------------------------------------------------------------------------------------
 // stable LSD radix sort of (key, value) pairs, 8 bits per pass
 // ---------------------------------------------------------------------------------------------
-constexpr int RS_THREADS = 256;
-constexpr int RS_WAVES = RS_THREADS / 64;
-constexpr int RS_CHUNKS = 16;                       // 64-item chunks per wave
-constexpr int RS_WAVE_ITEMS = RS_CHUNKS * 64;       // 1024
-constexpr int RS_TILE = RS_WAVES * RS_WAVE_ITEMS;   // 4096 items per block
+// A pass = per-tile digit counts, their offsets, and a scatter that ranks a tile's items (wavefront by wavefront, 64 items at a
+// time, in order, so equal digits keep their order), sorts the tile in LDS and writes it out from there: the runs of a
+// digit leave as consecutive stores (scattering from registers wrote 4-byte pieces: 25 M pairs 149 us per pass,
+// 58 us average over a plan with this).  Tiles: 8,192 pairs (8 wavefronts) on long inputs, where an XCD takes consecutive tiles so that
+// neighbouring runs of a digit meet in its L2; 4,096 and 1,024 pairs (4 wavefronts) on shorter ones, so that a few hundred thousand or
+// thousand pairs still spread over the compute units.  With at most RS_DIRECT tiles the scatter adds up the counts of the
+// tiles before its own itself: two launches per pass instead of four.
+template <int WAVES, int CH> constexpr int rs_tile() { return WAVES * CH * 64; }
+constexpr int RS_DIRECT = 128;
 
-__global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const uint32_t *keys, int64_t n, int shift,
-                                                        int32_t *hist, int nblk) {
+__device__ inline int64_t rs_tile_of_block(int nblk) {   // consecutive tiles on one XCD (workgroups go round-robin over 8)
+    const int per = (nblk + 7) / 8;
+    return (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+}
+static inline unsigned rs_grid(int nblk) { return (unsigned)((nblk + 7) / 8 * 8); }
+
+// counts of one tile: hist[tile][256] (direct) or hist[256][nblk] (to be scanned)
+template <int WAVES, int CH>
+__global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, int64_t n, int shift, int32_t *hist, int nblk,
+                                                        int direct) {
+    constexpr int NT = WAVES * 64, TILE = rs_tile<WAVES, CH>();
     __shared__ int32_t h[256];
-    h[threadIdx.x] = 0;
+    const int64_t tile = rs_tile_of_block(nblk);
+    if (tile >= nblk) return;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * RS_TILE + threadIdx.x;
-    uint32_t k[RS_TILE / RS_THREADS];
+    const int64_t base = tile * TILE + threadIdx.x;
+    uint32_t k[CH];
 #pragma unroll
-    for (int i = 0; i < RS_TILE / RS_THREADS; ++i) {
-        const int64_t p = base + (int64_t)i * RS_THREADS;
+    for (int i = 0; i < CH; ++i) {
+        const int64_t p = base + (int64_t)i * NT;
         k[i] = p < n ? keys[p] : 0u;
     }
 #pragma unroll
-    for (int i = 0; i < RS_TILE / RS_THREADS; ++i)
-        if (base + (int64_t)i * RS_THREADS < n) atomicAdd(&h[(k[i] >> shift) & 255u], 1);
+    for (int i = 0; i < CH; ++i)
+        if (base + (int64_t)i * NT < n) atomicAdd(&h[(k[i] >> shift) & 255u], 1);
     __syncthreads();
-    hist[(int64_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < 256) hist[direct ? tile * 256 + threadIdx.x : (int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
 }
 
-// Scatter phase of one pass for the tile of this workgroup.  `digit_off` is, for digit
-// d = threadIdx.x, the output position of the tile's first item with that digit.
-// vals_in == nullptr means value = position (iota).
-__device__ inline void rs_scatter_tile(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_out,
-                                       uint32_t *vals_out, int64_t n, int shift, int32_t digit_off) {
-    __shared__ int32_t cnt[RS_WAVES][256];
-    __shared__ int32_t wbase[RS_WAVES][256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < RS_WAVES * 256; i += RS_THREADS) (&cnt[0][0])[i] = 0;
-    __syncthreads();
-    const int64_t wstart = (int64_t)blockIdx.x * RS_TILE + (int64_t)wave * RS_WAVE_ITEMS;
-    uint32_t key[RS_CHUNKS];
-    int32_t rank[RS_CHUNKS];
+template <int WAVES, int CH, bool EXTRA>
+constexpr size_t rs_lds_bytes() { return (size_t)rs_tile<WAVES, CH>() * (EXTRA ? 12 : 8) + (size_t)WAVES * 256 * 4 + 256 * 4; }
+
+// vals_in == nullptr means value = position (iota).  EXTRA: a second value travels along.
+template <int WAVES, int CH, bool EXTRA>
+__global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_in, const uint32_t *vals_in, const uint32_t *ext_in,
+                                                           uint32_t *keys_out, uint32_t *vals_out, uint32_t *ext_out, int64_t n,
+                                                           int shift, const int32_t *hist, int nblk, int direct) {
+    constexpr int NT = WAVES * 64, TILE = rs_tile<WAVES, CH>();
+    extern __shared__ __align__(16) unsigned char rs_smem[];
+    uint32_t *lk = reinterpret_cast<uint32_t *>(rs_smem), *lv = lk + TILE;   // the tile, sorted
+    uint32_t *le = lv + TILE;                                                // (EXTRA only)
+    int32_t *cnt = reinterpret_cast<int32_t *>(EXTRA ? le + TILE : le);      // [WAVES][256] counts, then bases
+    int32_t *gdelta = cnt + WAVES * 256;                                     // output position minus tile position, per digit
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, d = threadIdx.x;
+    const int64_t tile = rs_tile_of_block(nblk);
+    if (tile >= nblk) return;   // whole workgroups leave
+    for (int i = threadIdx.x; i < WAVES * 256; i += NT) cnt[i] = 0;
+    const int64_t t0 = tile * TILE, wstart = t0 + (int64_t)wave * CH * 64;
+    uint32_t key[CH], val[CH], ext[EXTRA ? CH : 1];
+    int32_t rank[CH];
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     // all loads first, so that their latencies overlap instead of adding up chunk by chunk
 #pragma unroll
-    for (int c = 0; c < RS_CHUNKS; ++c) {
+    for (int c = 0; c < CH; ++c) {
         const int64_t p = wstart + (int64_t)c * 64 + lane;
         key[c] = p < n ? keys_in[p] : 0u;
+        val[c] = vals_in ? (p < n ? vals_in[p] : 0u) : (uint32_t)p;
+        if constexpr (EXTRA) ext[c] = p < n ? ext_in[p] : 0u;
     }
+    // digit d (threads 0..255): output position of the tile's first item with it
+    int32_t goff = 0, before = 0, all = 0;
+    if (d < 256) {
+        if (direct) {
+#pragma unroll 8
+            for (int t = 0; t < nblk; ++t) {
+                const int32_t x = hist[t * 256 + d];
+                before += t < (int)tile ? x : 0;
+                all += x;
+            }
+        } else {
+            goff = hist[(int64_t)d * nblk + tile];
+        }
+    }
+    int32_t unused;
+    if (direct) goff = block_exclusive_scan<WAVES>(all, &unused) + before;   // uniform branch; threads past 255 add 0
+    else __syncthreads();                                                    // the counters are zero from here on
 #pragma unroll
-    for (int c = 0; c < RS_CHUNKS; ++c) {
+    for (int c = 0; c < CH; ++c) {
         rank[c] = 0;
         if (wstart + (int64_t)c * 64 >= n) continue;   // wavefront-uniform: the chunk is empty
-        const int64_t p = wstart + (int64_t)c * 64 + lane;
-        const bool valid = p < n;
+        const bool valid = wstart + (int64_t)c * 64 + lane < n;
         const uint32_t digit = (key[c] >> shift) & 255u;
         uint64_t m = __ballot(valid);
 #pragma unroll
@@ -233,85 +283,59 @@ __device__ inline void rs_scatter_tile(const uint32_t *keys_in, const uint32_t *
             m &= bit ? bal : ~bal;
         }
         // m: valid lanes of this chunk with the same digit (meaningful on valid lanes)
-        const int before = __popcll(m & lt_mask);
+        const int ahead = __popcll(m & lt_mask);
         int32_t prev = 0;
-        if (valid) prev = cnt[wave][digit];
-        rank[c] = prev + before;
-        if (valid && before == 0) cnt[wave][digit] = prev + __popcll(m);
+        if (valid) prev = cnt[wave * 256 + digit];
+        rank[c] = prev + ahead;
+        if (valid && ahead == 0) cnt[wave * 256 + digit] = prev + __popcll(m);
     }
     __syncthreads();
-    {
-        const int d = threadIdx.x;   // 256 threads <-> 256 digits
-        int32_t run = digit_off;
+    int32_t tot = 0;
+    int32_t wb[WAVES];
+    if (d < 256) {
 #pragma unroll
-        for (int w = 0; w < RS_WAVES; ++w) {
-            wbase[w][d] = run;
-            run += cnt[w][d];
+        for (int w = 0; w < WAVES; ++w) {
+            wb[w] = tot;
+            tot += cnt[w * 256 + d];
         }
+    }
+    const int32_t start = block_exclusive_scan<WAVES>(tot, &unused);   // tile position of the digit's first item
+    if (d < 256) {
+        gdelta[d] = goff - start;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) cnt[w * 256 + d] = start + wb[w];
     }
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < RS_CHUNKS; ++c) {
-        const int64_t p = wstart + (int64_t)c * 64 + lane;
-        if (p < n) {
-            const uint32_t digit = (key[c] >> shift) & 255u;
-            const int64_t dst = (int64_t)wbase[wave][digit] + rank[c];
-            keys_out[dst] = key[c];
-            vals_out[dst] = vals_in ? vals_in[p] : (uint32_t)p;
+    for (int c = 0; c < CH; ++c) {
+        if (wstart + (int64_t)c * 64 + lane < n) {
+            const int pos = cnt[wave * 256 + ((key[c] >> shift) & 255u)] + rank[c];
+            lk[pos] = key[c];
+            lv[pos] = val[c];
+            if constexpr (EXTRA) le[pos] = ext[c];
         }
     }
-}
-
-__global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const uint32_t *keys_in, const uint32_t *vals_in,
-                                                           uint32_t *keys_out, uint32_t *vals_out, int64_t n,
-                                                           int shift, const int32_t *offs, int nblk) {
-    rs_scatter_tile(keys_in, vals_in, keys_out, vals_out, n, shift, offs[(int64_t)threadIdx.x * nblk + blockIdx.x]);
-}
-
-// A whole pass in one launch for inputs of at most RS_SMALL_TILES tiles: every workgroup counts
-// the digits of all tiles itself (the input is small enough to come from the L2), which gives it
-// the global digit bases and the counts of the tiles before its own without a histogram kernel,
-// a device-wide scan and their launch latencies.
-constexpr int RS_SMALL_TILES = 8;
-
-__global__ void __launch_bounds__(RS_THREADS) k_rs_pass_small(const uint32_t *keys_in, const uint32_t *vals_in,
-                                                              uint32_t *keys_out, uint32_t *vals_out, int64_t n,
-                                                              int shift, int nblk) {
-    __shared__ int32_t h[256];
-    const int d = threadIdx.x;
-    int32_t before = 0, total = 0;
-    for (int t = 0; t < nblk; ++t) {
-        h[d] = 0;
-        __syncthreads();
-        const int64_t base = (int64_t)t * RS_TILE + threadIdx.x;
-        uint32_t k[RS_TILE / RS_THREADS];
-#pragma unroll
-        for (int i = 0; i < RS_TILE / RS_THREADS; ++i) {
-            const int64_t p = base + (int64_t)i * RS_THREADS;
-            k[i] = p < n ? keys_in[p] : 0u;
-        }
-#pragma unroll
-        for (int i = 0; i < RS_TILE / RS_THREADS; ++i)
-            if (base + (int64_t)i * RS_THREADS < n) atomicAdd(&h[(k[i] >> shift) & 255u], 1);
-        __syncthreads();
-        const int32_t c = h[d];
-        if (t < (int)blockIdx.x) before += c;
-        total += c;
-        __syncthreads();
+    __syncthreads();
+    const int m = n - t0 < TILE ? (int)(n - t0) : TILE;
+    for (int i = threadIdx.x; i < m; i += NT) {
+        const uint32_t k = lk[i];
+        const int64_t dst = (int64_t)gdelta[(k >> shift) & 255u] + i;
+        keys_out[dst] = k;
+        vals_out[dst] = lv[i];
+        if constexpr (EXTRA) ext_out[dst] = le[i];
     }
-    int32_t all;
-    const int32_t digit_base = block_exclusive_scan(total, &all);
-    rs_scatter_tile(keys_in, vals_in, keys_out, vals_out, n, shift, digit_base + before);
 }
 
 // All passes of a sort of at most 16,384 pairs in one launch: a single workgroup of 16 wavefronts,
 // each owning 1,024 consecutive items, keeps keys and values in LDS (128 KB) between the passes:
-// a pass reads its items from LDS in order, ranks them exactly as rs_scatter_tile does (so the
+// a pass reads its items from LDS in order, ranks them exactly as k_rs_scatter does (so the
 // order is the same stable one) and writes them back to LDS at their sorted positions; the last
 // pass is followed by one coalesced copy to the caller's output.  A sampled batch sorts a few
 // thousand keys in 2-3 passes: one launch instead of one per pass, and no scattered 4-byte stores
 // to memory, which a single compute unit retires at about one cache line per clock (measured on
 // MI355X, 15 K pairs, 3 passes: 54 us as three launches, 47 us as one launch through memory).
+constexpr int RS_CHUNKS = 16;                       // 64-item chunks per wave
+constexpr int RS_WAVE_ITEMS = RS_CHUNKS * 64;       // 1024
 constexpr int RS_ONE_THREADS = 1024;
 constexpr int RS_ONE_WAVES = RS_ONE_THREADS / 64;
 constexpr int64_t RS_ONE_MAX = (int64_t)RS_ONE_WAVES * RS_WAVE_ITEMS;
@@ -323,6 +347,8 @@ struct SortPasses {
     const uint32_t *vin[RS_MAX_PASSES];   // null: value = position
     uint32_t *kout[RS_MAX_PASSES];
     uint32_t *vout[RS_MAX_PASSES];
+    const uint32_t *ein[RS_MAX_PASSES];   // second value, or null (multi-launch sorts only: n > RS_ONE_MAX)
+    uint32_t *eout[RS_MAX_PASSES];
     int passes;                           // pass p sorts by bits [8p, 8p + 8)
 };
 
@@ -433,28 +459,49 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
 }
 
 struct SortTmp {
-    int32_t *hist;      // 256 * nblk
-    int32_t *scan_tmp;  // scan_tmp_ints(256 * nblk)
+    int32_t *hist;      // rs_hist_ints(n)
+    int32_t *scan_tmp;  // scan_tmp_ints(rs_hist_ints(n))
 };
 
-int rs_blocks(int64_t n) { return (int)((n + RS_TILE - 1) / RS_TILE); }
+// tile of a pass over n pairs: the largest that still gives about a hundred tiles
+constexpr int64_t RS_T1 = rs_tile<4, 4>(), RS_T2 = rs_tile<4, 16>(), RS_T3 = rs_tile<8, 16>();   // 1,024 / 4,096 / 8,192
+int64_t rs_tile_for(int64_t n) { return n <= RS_T1 * RS_DIRECT ? RS_T1 : (n <= RS_T2 * RS_DIRECT ? RS_T2 : RS_T3); }
+// entries of `hist` for any input of at most n pairs
+size_t rs_hist_ints(int64_t n) { return (size_t)256 * (size_t)((n + RS_T2 - 1) / RS_T2 > RS_DIRECT ? (n + RS_T2 - 1) / RS_T2 : RS_DIRECT); }
 
-gt_status radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout, int64_t n,
-                     int shift, const SortTmp &t, hipStream_t st) {
-    if (n <= 0) return GT_OK;
-    const int nblk = rs_blocks(n);
-    if (nblk <= RS_SMALL_TILES) {
-        k_rs_pass_small<<<nblk, RS_THREADS, 0, st>>>(kin, vin, kout, vout, n, shift, nblk);
-        GT_LAUNCH_CHECK("k_rs_pass_small");
-        return GT_OK;
-    }
-    k_rs_hist<<<nblk, RS_THREADS, 0, st>>>(kin, n, shift, t.hist, nblk);
+template <int WAVES, int CH, bool EXTRA>
+gt_status radix_pass_t(const uint32_t *kin, const uint32_t *vin, const uint32_t *ein, uint32_t *kout, uint32_t *vout, uint32_t *eout,
+                       int64_t n, int shift, const SortTmp &t, hipStream_t st) {
+    constexpr int64_t TILE = rs_tile<WAVES, CH>();
+    constexpr size_t lds = rs_lds_bytes<WAVES, CH, EXTRA>();
+    const int nblk = (int)((n + TILE - 1) / TILE);
+    const int direct = nblk <= RS_DIRECT;
+    const unsigned grid = rs_grid(nblk);
+    k_rs_hist<WAVES, CH><<<grid, WAVES * 64, 0, st>>>(kin, n, shift, t.hist, nblk, direct);
     GT_LAUNCH_CHECK("k_rs_hist");
-    gt_status s = scan_exclusive(t.hist, t.hist, (int64_t)256 * nblk, t.scan_tmp, st);
-    if (s != GT_OK) return s;
-    k_rs_scatter<<<nblk, RS_THREADS, 0, st>>>(kin, vin, kout, vout, n, shift, t.hist, nblk);
+    if (!direct) {
+        const gt_status s = scan_exclusive(t.hist, t.hist, (int64_t)256 * nblk, t.scan_tmp, st);
+        if (s != GT_OK) return s;
+    }
+    if (lds > 64 * 1024)
+        GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rs_scatter<WAVES, CH, EXTRA>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    k_rs_scatter<WAVES, CH, EXTRA><<<grid, WAVES * 64, lds, st>>>(kin, vin, ein, kout, vout, eout, n, shift, t.hist, nblk, direct);
     GT_LAUNCH_CHECK("k_rs_scatter");
     return GT_OK;
+}
+
+gt_status radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout, int64_t n,
+                     int shift, const SortTmp &t, hipStream_t st, const uint32_t *ein = nullptr, uint32_t *eout = nullptr) {
+    if (n <= 0) return GT_OK;
+    const int64_t tile = rs_tile_for(n);
+    if (ein) {   // (8,192 triples leave a CU one workgroup: 228 us a pass over 25 M with 16 wavefronts, 202 with 4,096)
+        if (tile == RS_T1) return radix_pass_t<4, 4, true>(kin, vin, ein, kout, vout, eout, n, shift, t, st);
+        return radix_pass_t<8, 8, true>(kin, vin, ein, kout, vout, eout, n, shift, t, st);
+    }
+    if (tile == RS_T1) return radix_pass_t<4, 4, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, t, st);
+    if (tile == RS_T2) return radix_pass_t<4, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, t, st);
+    return radix_pass_t<8, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, t, st);
 }
 
 // Runs the passes of `a` in order: one launch when the input is short, one pass at a time otherwise.
@@ -462,6 +509,7 @@ gt_status radix_sort(const SortPasses &a, int64_t n, const SortTmp &t, hipStream
     if (n <= 0 || a.passes <= 0) return GT_OK;
     if (a.passes > RS_MAX_PASSES) return gt_fail(GT_ERR_INTERNAL, "radix_sort: too many passes");
     if (n <= RS_ONE_MAX) {
+        if (a.ein[0]) return gt_fail(GT_ERR_INTERNAL, "radix_sort: a second value on a one-launch sort");
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_rs_sort_one),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)RS_ONE_LDS);
         if (e != hipSuccess) return gt_hip_fail(e, "hipFuncSetAttribute(k_rs_sort_one)");
@@ -471,7 +519,7 @@ gt_status radix_sort(const SortPasses &a, int64_t n, const SortTmp &t, hipStream
         return GT_OK;
     }
     for (int p = 0; p < a.passes; ++p) {
-        const gt_status s = radix_pass(a.kin[p], a.vin[p], a.kout[p], a.vout[p], n, 8 * p, t, st);
+        const gt_status s = radix_pass(a.kin[p], a.vin[p], a.kout[p], a.vout[p], n, 8 * p, t, st, a.ein[p], a.eout[p]);
         if (s != GT_OK) return s;
     }
     return GT_OK;
