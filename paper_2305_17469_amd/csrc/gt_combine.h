@@ -40,12 +40,18 @@ struct GemmArgs {
     int c_bf16;
     int64_t M, N, K;
     int64_t k_per_split;           // multiple of KT
-    int vecA, vecB;                // 16-byte loads allowed
+    int vecA, vecB;                // rows 16-byte aligned and padded: a row's last 16-byte vector may be read whole anywhere
     int ntm, ntn;                  // output tiles along M and N (host side; see gemm_tile_of_block)
     int split_xcd;                 // splits % 8 == 0: the output tiles of one k-range run on one XCD
     int pad_c;                     // rows of C are padded and the padding may be written (zeros): a row's last
                                    // 16 bytes go out whole instead of in pieces (honoured by the staged epilogues)
 };
+
+// Whether the rows of a tile that ends before row `end` of a matrix of `rows` rows may be read in whole 16-byte vectors at any
+// alignment: a vector that runs past its row's end stays inside the matrix if eight more rows follow (even rows of one
+// element).  Only the tiles at the matrix's end are read element by element (rows of 602 bf16 without padding,
+// 2^19 x 602 -> 256: 759 -> 523 us).
+__device__ inline bool gemm_whole_vectors(int64_t end, int64_t rows) { return end + 8 <= rows; }
 
 // Workgroups are handed to the 8 XCDs round-robin by linear id, and each XCD has its own L2.  The
 // 1-D grid is therefore read as (xcd, sequence number within the xcd): an XCD walks one row tile
@@ -117,8 +123,8 @@ __device__ inline void gemm_epilogue(const GemmArgs &g, floatx16 (&acc)[TM][TN],
     if (partial) out_f += (int64_t)split * g.M * g.N;
     const bool as_bf16 = !partial && g.c_bf16;
     // whole vectors: inside N, or (padded rows whose padding may be written) the row's last one, zeros past N
-    const bool vec_ok = (ldc % 4 == 0) && (((uintptr_t)g.C & 15) == 0) &&
-                        (col + 4 <= g.N || (g.pad_c && !partial && col < g.N && col + 4 <= ldc));
+    // (at any element alignment)
+    const bool vec_ok = col + 4 <= g.N || (g.pad_c && !partial && col < g.N && col + 4 <= ldc);
     float bia[4] = {0.f, 0.f, 0.f, 0.f};
     if (!partial && g.bias) {
 #pragma unroll
@@ -164,8 +170,8 @@ __device__ inline void gemm_epilogue(const GemmArgs &g, floatx16 (&acc)[TM][TN],
             if (as_bf16) {
                 gemm_bf16_t *p = out_h + row * ldc + col;
                 if (vec_ok) {
-                    *reinterpret_cast<uint2 *>(p) = make_uint2(gt_pack_bf16(v[0], v[1]),
-                                                               gt_pack_bf16(v[2], v[3]));
+                    const uint2 o = make_uint2(gt_pack_bf16(v[0], v[1]), gt_pack_bf16(v[2], v[3]));
+                    __builtin_memcpy(p, &o, 8);
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -174,7 +180,8 @@ __device__ inline void gemm_epilogue(const GemmArgs &g, floatx16 (&acc)[TM][TN],
             } else {
                 float *p = out_f + row * ldc + col;
                 if (vec_ok) {
-                    *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+                    const float4 o = make_float4(v[0], v[1], v[2], v[3]);
+                    __builtin_memcpy(p, &o, 16);
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
@@ -190,5 +197,6 @@ gt_status gt_gemm_x3_launch(const GemmArgs &g, int transA, int transB, int split
 void gt_gemm_x3_tile(int64_t M, int64_t N, int64_t *bm, int64_t *bn);
 
 // Weight-stationary kernel for tall products with small K and N (gt_combine_ws.hip).
-bool gt_gemm_ws_applicable(gt_dtype dtype, int transA, int64_t M, int64_t N, int64_t K, int vecA);
+bool gt_gemm_ws_applicable(gt_dtype dtype, int transA, int64_t M, int64_t N, int64_t K);
+int64_t gt_gemm_ws_tail_rows(gt_dtype dtype, int64_t K, int64_t lda, int vecA);
 gt_status gt_gemm_ws_launch(const GemmArgs &g, gt_dtype dtype, int transB, hipStream_t st);

@@ -34,7 +34,8 @@ struct TileLoader {
 
     // Branch free: an out-of-range vector reads the (always valid) start of the matrix instead and
     // is masked to zero afterwards, so all loads of a tile are issued back to back and stay in
-    // flight together.  `vec` is uniform over the grid.
+    // flight together.  `vec` is uniform over the workgroup: whole vectors, at any element alignment; a row's last one may
+    // read past the row's end, which the matrix must allow (see gemm_whole_vectors).
     __device__ inline void load(const T *p, int64_t ld, int64_t r0, int64_t c0, int64_t rlim, int64_t clim, int vec) {
         if (vec) {
 #pragma unroll
@@ -43,7 +44,7 @@ struct TileLoader {
                 const int r = q / VPR, c = (q % VPR) * VE;
                 const int64_t gr = r0 + r, gc = c0 + c;
                 const bool ok = (TOTAL % 256 == 0 || q < TOTAL) && gr < rlim && gc < clim;
-                reg[it] = *reinterpret_cast<const uint4 *>(p + (ok ? gr * ld + gc : 0));
+                __builtin_memcpy(&reg[it], p + (ok ? gr * ld + gc : 0), 16);
                 nvalid[it] = ok ? (int)((clim - gc) < VE ? (clim - gc) : VE) : 0;
             }
         } else {
@@ -158,8 +159,10 @@ __global__ void __launch_bounds__(256) k_gemm(const GemmArgs g) {
     LoadA la[STAGES];
     LoadB lb[STAGES];
     auto fetch = [&](LoadA &sa, LoadB &sb, int64_t k0) {
-        if (TA) sa.load(A, g.lda, k0, m0, kend, g.M, VA); else sa.load(A, g.lda, m0, k0, g.M, kend, VA);
-        if (TB) sb.load(B, g.ldb, n0, k0, g.N, kend, VB); else sb.load(B, g.ldb, k0, n0, kend, g.N, VB);
+        if (TA) sa.load(A, g.lda, k0, m0, kend, g.M, VA || gemm_whole_vectors(k0 + KT, g.K));
+        else sa.load(A, g.lda, m0, k0, g.M, kend, VA || gemm_whole_vectors(m0 + BM, g.M));
+        if (TB) sb.load(B, g.ldb, n0, k0, g.N, kend, VB || gemm_whole_vectors(n0 + BN, g.N));
+        else sb.load(B, g.ldb, k0, n0, kend, g.N, VB || gemm_whole_vectors(k0 + KT, g.K));
     };
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
@@ -295,8 +298,8 @@ __global__ void __launch_bounds__(256) k_gemm(const GemmArgs g) {
 __device__ inline uint32_t tn_lo(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }   // lo16(a) | lo16(b) << 16
 __device__ inline uint32_t tn_hi(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }   // hi16(a) | hi16(b) << 16
 
-// BIG = false: 128 x 128 tile, 4 wavefronts of 64 x 64, k-tile 32.  BIG = true: ONE 256 x 256 tile per
-// workgroup, i.e. the whole output of a layer of up to 256 x 256 weights, one workgroup per k-range: every
+// BIG = false: 128 x 128 tile, 4 wavefronts of 64 x 64, k-tile 32.  BIG = true: a 256 x 256 tile per
+// workgroup; where that is the whole output (a layer of up to 256 x 256 weights), one workgroup per k-range: every
 // element of A and B is then read from memory exactly once (with 128 x 128 tiles each is read by two
 // workgroups, on different XCDs, and the product is bound by those reads).  That form runs 16 wavefronts
 // of 64 x 64 with a k-tile of 64: the bytes a CU has in flight are the loads its threads hold in
@@ -527,10 +530,13 @@ bool use_x3(gt_dtype dtype, int transA, int64_t M, int64_t N, int64_t K) {
 
 struct SplitPlan { int splits; int64_t k_per_split; };
 
-// bf16 weight gradients of up to 256 x 256 outputs over a long reduction: one 256 x 256 tile per workgroup
-// (k_gemm_tn_bf16<true>), one workgroup per CU
+// bf16 weight gradients over a long reduction: 256 x 256 tiles (k_gemm_tn_bf16<true>), one workgroup per CU.  One tile reads
+// both operands exactly once; with a few, the tiles of a k-range run back to back on one XCD and find the operand they
+// share in its L2 (602 x 256 over 2^19 rows: 445 us with 128 x 128 tiles, 332 us with these).  Beyond eight tiles the
+// k-ranges get too short to pay for their partial outputs.
+int64_t tn256_tiles(int64_t M, int64_t N) { return ((M + 255) / 256) * ((N + 255) / 256); }
 bool tn256_shape(int transA, int transB, int64_t M, int64_t N, int64_t K) {
-    return transA && !transB && M > 64 && M <= 256 && N > 64 && N <= 256 && K >= 8192 &&
+    return transA && !transB && M > 64 && N > 64 && tn256_tiles(M, N) <= 8 && K >= 8192 * tn256_tiles(M, N) &&
            (double)M * (double)N * (double)K >= 268435456.0;
 }
 
@@ -539,9 +545,10 @@ SplitPlan plan_split(int transA, int64_t M, int64_t N, int64_t K, bool x3, bool 
     if (x3) { gt_gemm_x3_tile(M, N, &t.bm, &t.bn); t.small = false; }
     if (tn256) {
         SplitPlan p{1, (K + KT - 1) / KT * KT};
-        int64_t want = 256, max_by_len = K / (4 * KT);
+        int64_t want = 256 / tn256_tiles(M, N), max_by_len = K / (4 * KT);
         if (want > max_by_len) want = max_by_len;
         if (want < 1) want = 1;
+        if (tn256_tiles(M, N) > 1 && want >= 16) want = want / 8 * 8;   // whole k-ranges per XCD (gemm_split_xcd)
         const int64_t kps = ((K + want - 1) / want + KT - 1) / KT * KT;
         p.splits = (int)((K + kps - 1) / kps);
         p.k_per_split = kps;
@@ -609,11 +616,12 @@ gt_status launch_gemm(GemmArgs g, int splits, hipStream_t st) {
 }
 
 gt_status launch_tn256(GemmArgs g, int splits, hipStream_t st) {
-    g.ntm = 1; g.ntn = 1;
+    g.ntm = (int)((g.M + 255) / 256); g.ntn = (int)((g.N + 255) / 256);
+    g.split_xcd = gemm_split_xcd(g.ntm, g.ntn, splits);
     constexpr size_t lds = tn_lds_bytes<true>();
     GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_tn_bf16<true>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    k_gemm_tn_bf16<true><<<dim3(1, 1, (unsigned)splits), 1024, lds, st>>>(g);
+    k_gemm_tn_bf16<true><<<dim3((unsigned)(g.ntm * g.ntn), 1, (unsigned)splits), 1024, lds, st>>>(g);
     GT_LAUNCH_CHECK("k_gemm_tn_bf16");
     return GT_OK;
 }
@@ -706,8 +714,21 @@ gt_status gt_gemm_run(const char *fn, gt_dtype dtype, int transA, int transB, in
     const int tr = gt_trace_open(GT_TRACE_COMBINE, N, M, M * N * K, st);
     // tall products with a small weight matrix are bound by streaming A and C once: the
     // weight-stationary kernel does exactly that
+    const int64_t tail = gt_gemm_ws_tail_rows(dtype, K, lda, g.vecA);   // rows at the end that go to the tiled kernel
     const bool ws_path = p.splits == 1 && c_dtype == dtype && !Cin && !rowscale &&
-                         gt_gemm_ws_applicable(dtype, transA, M, N, K, g.vecA);
+                         (!mask || (((uintptr_t)mask & 15) == 0 && ldmask % ve == 0)) &&
+                         gt_gemm_ws_applicable(dtype, transA, M - tail, N, K);
+    if (ws_path && tail > 0) {
+        GemmArgs h = g;
+        const int64_t r = M - tail;
+        h.M = tail;
+        h.A = static_cast<const char *>(A) + r * lda * es;
+        h.C = static_cast<char *>(C) + r * ldc * cs;
+        if (mask) h.mask = static_cast<const char *>(mask) + r * ldmask * cs;
+        const gt_status s0 = dtype == GT_F32 ? launch_gemm_t<float>(h, transA, transB, 1, st) : launch_gemm_t<bf16_t>(h, transA, transB, 1, st);
+        if (s0 != GT_OK) return s0;
+        g.M = r;
+    }
     gt_status s = ws_path ? gt_gemm_ws_launch(g, dtype, transB, st)
                   : tn256 ? launch_tn256(g, p.splits, st)
                   : x3 ? gt_gemm_x3_launch(g, transA, transB, p.splits, st)

@@ -34,6 +34,15 @@ template <typename T> struct WsGeom;
 template <> struct WsGeom<float>  { static constexpr int CK = 8,  HK = 4, SK = 32, PAD = 4; };
 template <> struct WsGeom<bf16_t> { static constexpr int CK = 16, HK = 8, SK = 64, PAD = 8; };
 
+// 16-byte accesses at any element address (rows of A, C and the mask need no alignment beyond their element's)
+__device__ inline uint4 ws_ld16(const void *p) {
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+template <typename V>
+__device__ inline void ws_st(void *p, const V &v) { __builtin_memcpy(p, &v, sizeof(V)); }
+
 // zero the elements of a 16-byte chunk from element nv on
 template <typename T>
 __device__ inline uint4 ws_mask(uint4 v, int nv) {
@@ -67,65 +76,45 @@ __device__ inline void ws_load_slice(uint4 (&r)[4], const T *A, int64_t lda, int
     for (int j = 0; j < 4; ++j) {
         int64_t row = rb * 32 + (lane >> 3) + 8 * j;
         if (row >= M) row = M - 1;
-        r[j] = *reinterpret_cast<const uint4 *>(A + row * lda + (k < K ? k : 0));
+        r[j] = ws_ld16(A + row * lda + (k < K ? k : 0));
     }
 }
 
 // The products are formed as (weights)^T x (rows)^T, so accumulator register r of lane (h, l32)
 // holds output row l32 of the block and column 8 (r / 4) + 4 h + r % 4 of the 32-column group:
-// four consecutive columns per register quadruple, stored straight from registers.  The bias is
+// four consecutive columns per register quadruple, stored straight from registers (streaming kernel).  The bias is
 // already in the accumulators (they start from it); only the activation is left to apply.
-// CB: C is bf16;  EX: bias and / or ReLU present.
-// FAST: every column group of the slice lies inside N and can be stored as one vector, so the
-// epilogue is straight-line code.
-template <bool CB, bool EX, bool FAST, int NB>
-__device__ inline void ws_epilogue(const GemmArgs &g, floatx16 (&acc)[NB], int64_t row, int64_t n0, int h, bool vec) {
+// EX: bias and / or ReLU present.
+template <bool EX>
+__device__ inline void ws_epilogue(const GemmArgs &g, floatx16 &acc, int64_t row, int h, bool vec) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
+    for (int q = 0; q < 4; ++q) {
+        const int64_t col = 8 * q + 4 * h;
+        if (col >= g.N) continue;
+        float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        if (EX) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int64_t col = n0 + b * 32 + 8 * q + 4 * h;
-            if (!FAST && col >= g.N) continue;
-            const bool whole = FAST || (vec && col + 4 <= g.N);
-            float v[4] = {acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
-            if (EX) {
+            for (int i = 0; i < 4; ++i) v[i] = (g.relu && !(v[i] > 0.0f)) ? 0.0f : v[i];
+            if (g.mask) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = (g.relu && !(v[i] > 0.0f)) ? 0.0f : v[i];
-                if (g.mask) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (!FAST && col + i >= g.N) continue;
-                        const float mk = CB ? gemm_bf16_to_f32(static_cast<const gemm_bf16_t *>(g.mask)[row * g.ldmask + col + i])
-                                            : static_cast<const float *>(g.mask)[row * g.ldmask + col + i];
-                        v[i] = mk > 0.0f ? v[i] : 0.0f;
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    if (col + i >= g.N) continue;
+                    v[i] = static_cast<const float *>(g.mask)[row * g.ldmask + col + i] > 0.0f ? v[i] : 0.0f;
                 }
             }
-            if (CB) {
-                gemm_bf16_t *p = static_cast<gemm_bf16_t *>(g.C) + row * g.ldc + col;
-                if (whole) {
-                    *reinterpret_cast<uint2 *>(p) = make_uint2(gt_pack_bf16(v[0], v[1]),
-                                                               gt_pack_bf16(v[2], v[3]));
-                } else {
+        }
+        float *p = static_cast<float *>(g.C) + row * g.ldc + col;
+        if (vec && col + 4 <= g.N) {
+            *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (col + i < g.N) p[i] = (gemm_bf16_t)gemm_f32_to_bf16(v[i]);
-                }
-            } else {
-                float *p = static_cast<float *>(g.C) + row * g.ldc + col;
-                if (whole) {
-                    *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (col + i < g.N) p[i] = v[i];
-                }
-            }
+            for (int i = 0; i < 4; ++i)
+                if (col + i < g.N) p[i] = v[i];
         }
     }
 }
 
-// fp32 output, whole column groups, rows of C 16-byte aligned: each 32-column group of the block
+// fp32 output: each 32-column group of the block
 // passes through the wavefront's private stage (free at this point: every fragment of the block has
 // been read) and is written row-major, eight lanes per row, so a store instruction covers whole
 // 128-byte lines of 8 rows instead of 32-byte pieces of 32 rows.  Rows past M hold the last row's
@@ -157,18 +146,17 @@ __device__ inline void ws_epilogue_rows_f32(const GemmArgs &g, floatx16 (&acc)[N
             if (row >= g.M) row = g.M - 1;
             const int64_t c0 = n0 + b * 32 + c4;
             if constexpr (MK) {   // the host passes a mask here only when its rows allow 16-byte loads
-                const float4 mk = *reinterpret_cast<const float4 *>(static_cast<const float *>(g.mask) + row * g.ldmask +
-                                                                    ((!RAGGED || c0 < g.N) ? c0 : 0));
-                v.x = mk.x > 0.0f ? v.x : 0.0f; v.y = mk.y > 0.0f ? v.y : 0.0f;
-                v.z = mk.z > 0.0f ? v.z : 0.0f; v.w = mk.w > 0.0f ? v.w : 0.0f;
+                const uint4 mk = ws_ld16(static_cast<const float *>(g.mask) + row * g.ldmask + ((!RAGGED || c0 < g.N) ? c0 : 0));
+                v.x = __uint_as_float(mk.x) > 0.0f ? v.x : 0.0f; v.y = __uint_as_float(mk.y) > 0.0f ? v.y : 0.0f;
+                v.z = __uint_as_float(mk.z) > 0.0f ? v.z : 0.0f; v.w = __uint_as_float(mk.w) > 0.0f ? v.w : 0.0f;
             }
             float *dst = static_cast<float *>(g.C) + row * g.ldc + c0;
             if constexpr (!RAGGED) {
-                *reinterpret_cast<float4 *>(dst) = v;
+                ws_st(dst, v);
             } else {
                 const int64_t left = g.N - c0;
                 if (left >= 4 || (g.pad_c && left > 0 && c0 + 4 <= g.ldc)) {   // (columns past N hold zeros)
-                    *reinterpret_cast<float4 *>(dst) = v;
+                    ws_st(dst, v);
                 } else if (left > 0) {
                     dst[0] = v.x;
                     if (left > 1) dst[1] = v.y;
@@ -180,7 +168,7 @@ __device__ inline void ws_epilogue_rows_f32(const GemmArgs &g, floatx16 (&acc)[N
     __asm__ volatile("" ::: "memory");
 }
 
-// The same for a bf16 C whose rows are 16-byte aligned: two 32-column groups at a time are rounded
+// The same for a bf16 C: two 32-column groups at a time are rounded
 // to bf16, staged as 32 rows x 64 columns (128 bytes + 16 of padding per row) and written eight lanes
 // per row, 16 bytes per lane: whole 128-byte lines again.
 // LATE: the mask vectors are requested when they are needed instead of before the round is staged (the
@@ -203,8 +191,7 @@ __device__ inline void ws_epilogue_rows_bf16(const GemmArgs &g, floatx16 (&acc)[
                 int64_t row = row0 + it * 8 + (lane >> 3);
                 if (row >= g.M) row = g.M - 1;
                 const int64_t cm = n0 + bp * 64 + (lane & 7) * 8;
-                mkv[it] = *reinterpret_cast<const uint4 *>(static_cast<const gemm_bf16_t *>(g.mask) + row * g.ldmask +
-                                                          ((!RAGGED || cm < g.N) ? cm : 0));
+                mkv[it] = ws_ld16(static_cast<const gemm_bf16_t *>(g.mask) + row * g.ldmask + ((!RAGGED || cm < g.N) ? cm : 0));
             }
         }
         __asm__ volatile("" ::: "memory");
@@ -232,25 +219,25 @@ __device__ inline void ws_epilogue_rows_bf16(const GemmArgs &g, floatx16 (&acc)[
             if (row >= g.M) row = g.M - 1;
             const int64_t c0 = n0 + bp * 64 + (lane & 7) * 8;
             if constexpr (MK) {
-                const uint4 mk = LATE ? *reinterpret_cast<const uint4 *>(static_cast<const gemm_bf16_t *>(g.mask) + row * g.ldmask +
-                                                                         ((!RAGGED || c0 < g.N) ? c0 : 0))
+                const uint4 mk = LATE ? ws_ld16(static_cast<const gemm_bf16_t *>(g.mask) + row * g.ldmask +
+                                                ((!RAGGED || c0 < g.N) ? c0 : 0))
                                       : mkv[it];
                 v.x = ws_mask_pair(v.x, mk.x); v.y = ws_mask_pair(v.y, mk.y);
                 v.z = ws_mask_pair(v.z, mk.z); v.w = ws_mask_pair(v.w, mk.w);
             }
             gemm_bf16_t *dst = static_cast<gemm_bf16_t *>(g.C) + row * g.ldc + c0;
             if constexpr (!RAGGED) {
-                *reinterpret_cast<uint4 *>(dst) = v;
+                ws_st(dst, v);
             } else {
                 const int64_t left = g.N - c0;
                 if (left >= 8 || (g.pad_c && left > 0 && c0 + 8 <= g.ldc)) {   // (columns past N hold zeros)
-                    *reinterpret_cast<uint4 *>(dst) = v;
+                    ws_st(dst, v);
                 } else if (left > 0) {
                     // 1..7 columns as an 8-, a 4- and a 2-byte piece
-                    if (left & 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(v.x, v.y);
+                    if (left & 4) ws_st(dst, make_uint2(v.x, v.y));
                     const uint32_t w2 = (left & 4) ? v.z : v.x, w3 = (left & 4) ? v.w : v.y;
                     gemm_bf16_t *d2 = dst + (left & 4);
-                    if (left & 2) *reinterpret_cast<uint32_t *>(d2) = w2;
+                    if (left & 2) ws_st(d2, w2);
                     if (left & 1) d2[left & 2] = (gemm_bf16_t)(((left & 2) ? w3 : w2) & 0xffffu);
                 }
             }
@@ -287,12 +274,13 @@ constexpr int ws_per_cu() { return ws_lds_bytes<T, NB, NS, 4>() <= 80 * 1024 ? 2
 // slices and chunks at or past K re-read the row's first chunk and are staged as zeros, masks are
 // always applied): with control flow in it the compiler waits for ALL outstanding memory
 // operations before it touches a prefetched slice.
-// FAST: N is a multiple of the slice width and C allows vector stores; then the epilogue is
-// straight-line code as well (rows past M store the last row's values onto the last row), and the
-// wait at the head of the row loop does not include the previous block's stores.
+// RG: N need not be a multiple of the slice width (guarded row ends).  Without it the epilogue is straight-line code
+// as well (rows past M store the last row's values onto the last row), and the wait at the head of the row loop
+// does not include the previous block's stores.  Either way the block leaves through the wavefront's stage, row-major: from
+// registers a row is written in 8-byte pieces (2^19 rows bf16, 256 -> 602: 1000 -> 445 us).
 // HALF (one-slice instances): K is at most half a slice, the MFMA steps of the empty half are left out
 // (2^20 x 16 -> 1024 fp32 spent 0.44 of its 1.0 ms multiplying zeros).
-template <typename T, int NB, int NS, bool EX, bool FAST, bool MK, bool HALF, bool RG>
+template <typename T, int NB, int NS, bool EX, bool MK, bool HALF, bool RG>
 __global__ void __launch_bounds__((ws_waves<T, NB, NS>() * 64), (ws_per_cu<T, NB, NS>())) k_gemm_ws(const GemmArgs g, const int transB) {
     constexpr int NW = ws_waves<T, NB, NS>(), NT = NW * 64;
     static_assert(!HALF || NS == 1, "HALF is a form of the one-slice instances");
@@ -365,24 +353,27 @@ __global__ void __launch_bounds__((ws_waves<T, NB, NS>() * 64), (ws_per_cu<T, NB
                 }
             }
         }
-    } else if (transB) {
-        for (int idx = threadIdx.x; idx < BN * KP; idx += NT) {
-            const int n = idx / KP, k = idx % KP;
-            const bool ok = n0 + n < g.N && k < g.K;
-            const T v = B[ok ? (n0 + n) * g.ldb + k : 0];
-            Ws[n * WSTR + k] = ok ? v : (T)0;
-        }
-    } else {
-        for (int idx = threadIdx.x; idx < BN * KP; idx += NT) {
-            const int k = idx / BN, n = idx % BN;
-            const bool ok = n0 + n < g.N && k < g.K;
-            const T v = B[ok ? (int64_t)k * g.ldb + n0 + n : 0];
-            Ws[n * WSTR + k] = ok ? v : (T)0;
+    } else {                         // element by element, eight loads in flight
+        for (int base = threadIdx.x; base < BN * KP; base += NT * 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int idx = base + u * NT;
+                const int n = transB ? idx / KP : idx % BN, k = transB ? idx % KP : idx / BN;
+                const bool ok = idx < BN * KP && n0 + n < g.N && k < g.K;
+                v[u] = B[ok ? (transB ? (n0 + n) * g.ldb + k : (int64_t)k * g.ldb + n0 + n) : 0];
+                if (!ok) v[u] = (T)0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int idx = base + u * NT;
+                const int n = transB ? idx / KP : idx % BN, k = transB ? idx % KP : idx / BN;
+                if (idx < BN * KP) Ws[n * WSTR + k] = v[u];
+            }
         }
     }
     __syncthreads();
 
-    const bool out_vec = (g.ldc % 4 == 0) && (((uintptr_t)g.C & 15) == 0);   // 4-column groups of C are aligned
     const int64_t nrb = (g.M + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * NW;
     int64_t rb = (int64_t)blockIdx.x * NW + wave;
@@ -463,10 +454,8 @@ __global__ void __launch_bounds__((ws_waves<T, NB, NS>() * 64), (ws_per_cu<T, NB
                 }
             }
         }
-        const int64_t row = rb * 32 + l32;
-        if constexpr (FAST && sizeof(T) == 4) ws_epilogue_rows_f32<EX, MK, RG, NB>(g, acc, rb * 32, n0, lane, reinterpret_cast<float *>(As));
-        else if constexpr (FAST) ws_epilogue_rows_bf16<EX, MK, (NW > 4), RG, NB>(g, acc, rb * 32, n0, lane, reinterpret_cast<uint32_t *>(As));
-        else if (row < g.M) ws_epilogue<sizeof(T) == 2, EX, false, NB>(g, acc, row, n0, h, out_vec);
+        if constexpr (sizeof(T) == 4) ws_epilogue_rows_f32<EX, MK, RG, NB>(g, acc, rb * 32, n0, lane, reinterpret_cast<float *>(As));
+        else ws_epilogue_rows_bf16<EX, MK, (NW > 4), RG, NB>(g, acc, rb * 32, n0, lane, reinterpret_cast<uint32_t *>(As));
     }
 }
 
@@ -495,7 +484,7 @@ constexpr size_t ws_x3_lds_bytes() {
 template <int NB, int NS>
 constexpr int ws_x3_per_cu() { return ws_x3_lds_bytes<NB, NS>() <= 80 * 1024 ? 2 : 1; }
 
-template <int NB, int NS, bool EX, bool FAST, bool MK, bool RG>
+template <int NB, int NS, bool EX, bool MK, bool RG>
 __global__ void __launch_bounds__(256, (ws_x3_per_cu<NB, NS>())) k_gemm_ws_x3(const GemmArgs g, const int transB) {
     constexpr int SK = 32;                      // k per slice (128 bytes of fp32)
     constexpr int KP = NS * SK;                 // K capacity of this instance
@@ -572,7 +561,6 @@ __global__ void __launch_bounds__(256, (ws_x3_per_cu<NB, NS>())) k_gemm_ws_x3(co
     }
     __syncthreads();
 
-    const bool out_vec = (g.ldc % 4 == 0) && (((uintptr_t)g.C & 15) == 0);
     const int64_t nrb = (g.M + 31) / 32;
     const int64_t stride = (int64_t)gridDim.x * 4;
     int64_t rb = (int64_t)blockIdx.x * 4 + wave;
@@ -643,9 +631,7 @@ __global__ void __launch_bounds__(256, (ws_x3_per_cu<NB, NS>())) k_gemm_ws_x3(co
                 }
             }
         }
-        const int64_t row = rb * 32 + l32;
-        if constexpr (FAST) ws_epilogue_rows_f32<EX, MK, RG, NB>(g, acc, rb * 32, n0, lane, As);
-        else if (row < g.M) ws_epilogue<false, EX, false, NB>(g, acc, row, n0, h, out_vec);
+        ws_epilogue_rows_f32<EX, MK, RG, NB>(g, acc, rb * 32, n0, lane, As);
     }
 }
 
@@ -718,7 +704,7 @@ __global__ void __launch_bounds__(WS_STREAM_WAVES * 64, 1) k_gemm_ws_stream_x3(c
         int k = s * SK;
         if (!KFULL && k + kb >= g.K) k = -kb;   // chunks at or past K re-read the row's first chunk
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = *reinterpret_cast<const uint4 *>(rp[i] + k);
+        for (int i = 0; i < 4; ++i) r[i] = ws_ld16(rp[i] + k);
     };
     const float *rp[4], *rpn[4];
     row_ptrs(rp, rb);
@@ -784,7 +770,7 @@ __global__ void __launch_bounds__(WS_STREAM_WAVES * 64, 1) k_gemm_ws_stream_x3(c
             }
         }
         const int64_t row = rb * 32 + l32;
-        if (row < g.M) ws_epilogue<false, EX, false, 1>(g, acc, row, 0, h, out_vec);
+        if (row < g.M) ws_epilogue<EX>(g, acc[0], row, h, out_vec);
 #pragma unroll
         for (int i = 0; i < 4; ++i) rp[i] = rpn[i];
     }
@@ -831,11 +817,11 @@ static gt_status ws_stream_launch(const GemmArgs &g, int transB, hipStream_t st)
     return ws_stream_launch_n<32>(g, transB, NR, st);
 }
 
-template <int NB, int NS, bool EX, bool FAST, bool MK = false, bool RG = false>
+template <int NB, int NS, bool EX, bool MK, bool RG>
 gt_status ws_x3_launch_ex(const GemmArgs &g, int transB, hipStream_t st) {
     constexpr size_t lds = ws_x3_lds_bytes<NB, NS>();
     if (lds > 64 * 1024) {
-        GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_ws_x3<NB, NS, EX, FAST, MK, RG>),
+        GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_ws_x3<NB, NS, EX, MK, RG>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     }
     const int64_t nrb = (g.M + 31) / 32;
@@ -843,35 +829,19 @@ gt_status ws_x3_launch_ex(const GemmArgs &g, int transB, hipStream_t st) {
     int64_t gx = (nrb + 3) / 4;
     if (gx > 256 * per_cu) gx = 256 * per_cu;
     dim3 grid((unsigned)gx, (unsigned)((g.N + NB * 32 - 1) / (NB * 32)), 1);
-    k_gemm_ws_x3<NB, NS, EX, FAST, MK, RG><<<grid, 256, lds, st>>>(g, transB);
+    k_gemm_ws_x3<NB, NS, EX, MK, RG><<<grid, 256, lds, st>>>(g, transB);
     GT_LAUNCH_CHECK("k_gemm_ws_x3");
     return GT_OK;
 }
 
-template <int NB, int NS>
+template <int NB, int NS, bool RG>
 gt_status ws_x3_launch(const GemmArgs &g, int transB, hipStream_t st) {
-    const bool extras = g.bias || g.relu || g.mask;
-    if constexpr (NB >= 4) {
-        const bool fast = g.N % (NB * 32) == 0 && g.ldc % 4 == 0 && (((uintptr_t)g.C & 15) == 0) &&
-                          (!g.mask || (g.ldmask % 8 == 0 && ((uintptr_t)g.mask & 15) == 0));
-        if (fast)
-            return g.mask ? ws_x3_launch_ex<NB, NS, true, true, true>(g, transB, st)
-                 : extras ? ws_x3_launch_ex<NB, NS, true, true>(g, transB, st)
-                          : ws_x3_launch_ex<NB, NS, false, true>(g, transB, st);
-    }
-    if constexpr (NB == 2) {   // at most 64 fp32 columns, any N: the staged, row-major epilogue with a ragged end
-        const bool rows = g.ldc % 4 == 0 && (((uintptr_t)g.C & 15) == 0) &&
-                          (!g.mask || (g.ldmask % 8 == 0 && ((uintptr_t)g.mask & 15) == 0));
-        if (rows)
-            return g.mask ? ws_x3_launch_ex<NB, NS, true, true, true, true>(g, transB, st)
-                 : extras ? ws_x3_launch_ex<NB, NS, true, true, false, true>(g, transB, st)
-                          : ws_x3_launch_ex<NB, NS, false, true, false, true>(g, transB, st);
-    }
-    return extras ? ws_x3_launch_ex<NB, NS, true, false>(g, transB, st)
-                  : ws_x3_launch_ex<NB, NS, false, false>(g, transB, st);
+    return g.mask ? ws_x3_launch_ex<NB, NS, true, true, RG>(g, transB, st)
+         : g.bias || g.relu ? ws_x3_launch_ex<NB, NS, true, false, RG>(g, transB, st)
+                            : ws_x3_launch_ex<NB, NS, false, false, RG>(g, transB, st);
 }
 
-template <typename T, int NB, int NS, bool EX, bool FAST, bool MK = false, bool HALF = false, bool RG = false>
+template <typename T, int NB, int NS, bool EX, bool MK, bool HALF, bool RG>
 gt_status ws_launch_ex(const GemmArgs &g, int transB, hipStream_t st) {
     constexpr int NW = ws_waves<T, NB, NS>();
     constexpr size_t lds = ws_lds_bytes<T, NB, NS, NW>();
@@ -879,7 +849,7 @@ gt_status ws_launch_ex(const GemmArgs &g, int transB, hipStream_t st) {
     // it (a host-side setting, no stream operation), so the first launch of an instance behaves
     // like any other, also under stream capture.
     if (lds > 64 * 1024) {
-        GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_ws<T, NB, NS, EX, FAST, MK, HALF, RG>),
+        GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_ws<T, NB, NS, EX, MK, HALF, RG>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     }
     const int64_t nrb = (g.M + 31) / 32;
@@ -887,56 +857,46 @@ gt_status ws_launch_ex(const GemmArgs &g, int transB, hipStream_t st) {
     int64_t gx = (nrb + NW - 1) / NW;
     if (gx > 256 * per_cu) gx = 256 * per_cu;
     dim3 grid((unsigned)gx, (unsigned)((g.N + NB * 32 - 1) / (NB * 32)), 1);
-    k_gemm_ws<T, NB, NS, EX, FAST, MK, HALF, RG><<<grid, NW * 64, lds, st>>>(g, transB);
+    k_gemm_ws<T, NB, NS, EX, MK, HALF, RG><<<grid, NW * 64, lds, st>>>(g, transB);
     GT_LAUNCH_CHECK("k_gemm_ws");
     return GT_OK;
 }
 
-template <typename T, int NB, int NS>
+template <typename T, int NB, int NS, bool HALF, bool RG>
 gt_status ws_launch(const GemmArgs &g, int transB, hipStream_t st) {
-    const bool extras = g.bias || g.relu || g.mask;
-    if constexpr (NB >= 4) {   // the branch-free form exists for the wide slices, where the stores dominate
-        // (a bf16 C is written 16 bytes, eight columns, per lane)
-        const bool fast = g.N % (NB * 32) == 0 && g.ldc % (sizeof(T) == 2 ? 8 : 4) == 0 && (((uintptr_t)g.C & 15) == 0) &&
-                          (!g.mask || (g.ldmask % 8 == 0 && ((uintptr_t)g.mask & 15) == 0));
-        if constexpr (NS == 1) {
-            if (fast && g.K <= WsGeom<T>::SK / 2)
-                return g.mask ? ws_launch_ex<T, NB, NS, true, true, true, true>(g, transB, st)
-                     : extras ? ws_launch_ex<T, NB, NS, true, true, false, true>(g, transB, st)
-                              : ws_launch_ex<T, NB, NS, false, true, false, true>(g, transB, st);
+    return g.mask ? ws_launch_ex<T, NB, NS, true, true, HALF, RG>(g, transB, st)
+         : g.bias || g.relu ? ws_launch_ex<T, NB, NS, true, false, HALF, RG>(g, transB, st)
+                            : ws_launch_ex<T, NB, NS, false, false, HALF, RG>(g, transB, st);
+}
+
+template <typename T, int NB, int NS>
+gt_status ws_pick_form(const GemmArgs &g, int transB, hipStream_t st) {
+    const bool whole = g.N % (NB * 32) == 0;
+    if constexpr (sizeof(T) == 4 && NB <= 4) {
+        // fp32 on the bf16 matrix cores for outputs of up to 128 columns (measured on MI355X, 2^18 rows:
+        // 128 -> 41 0.074 -> 0.052 ms, 41 -> 128 0.067 -> 0.053 ms); wider outputs are bound by their
+        // stores and ran slower this way (2^20 rows, 16 -> 1024: 1.15 -> 1.30 ms), they keep the fp32 MFMA
+        if constexpr (NB >= 4) {
+            if (whole) return ws_x3_launch<NB, NS, false>(g, transB, st);
         }
-        if (fast)
-            return g.mask ? ws_launch_ex<T, NB, NS, true, true, true>(g, transB, st)
-                 : extras ? ws_launch_ex<T, NB, NS, true, true>(g, transB, st)
-                          : ws_launch_ex<T, NB, NS, false, true>(g, transB, st);
+        return ws_x3_launch<NB, NS, true>(g, transB, st);
+    } else {
+        if constexpr (NB >= 4) {
+            if constexpr (NS == 1) {
+                if (whole && g.K <= WsGeom<T>::SK / 2) return ws_launch<T, NB, NS, true, false>(g, transB, st);
+            }
+            if (whole) return ws_launch<T, NB, NS, false, false>(g, transB, st);
+        }
+        return ws_launch<T, NB, NS, false, true>(g, transB, st);
     }
-    if constexpr (NB == 2 && sizeof(T) == 2) {   // at most 64 bf16 columns, any N: the staged, row-major epilogue with a ragged end
-        const bool rows = g.ldc % 8 == 0 && (((uintptr_t)g.C & 15) == 0) &&
-                          (!g.mask || (g.ldmask % 8 == 0 && ((uintptr_t)g.mask & 15) == 0));
-        if (rows)
-            return g.mask ? ws_launch_ex<T, NB, NS, true, true, true, false, true>(g, transB, st)
-                 : extras ? ws_launch_ex<T, NB, NS, true, true, false, false, true>(g, transB, st)
-                          : ws_launch_ex<T, NB, NS, false, true, false, false, true>(g, transB, st);
-    }
-    return extras ? ws_launch_ex<T, NB, NS, true, false>(g, transB, st)
-                  : ws_launch_ex<T, NB, NS, false, false>(g, transB, st);
 }
 
 template <typename T, int NB>
 gt_status ws_pick_ns(const GemmArgs &g, int transB, hipStream_t st) {
     const int64_t slices = (g.K + WsGeom<T>::SK - 1) / WsGeom<T>::SK;
-    if constexpr (sizeof(T) == 4 && NB <= 4) {
-        // fp32 on the bf16 matrix cores for outputs of up to 128 columns (measured on MI355X, 2^18 rows:
-        // 128 -> 41 0.074 -> 0.052 ms, 41 -> 128 0.067 -> 0.053 ms); wider outputs are bound by their
-        // stores and ran slower this way (2^20 rows, 16 -> 1024: 1.15 -> 1.30 ms), they keep the fp32 MFMA
-        if (slices <= 1) return ws_x3_launch<NB, 1>(g, transB, st);
-        if (slices <= 2) return ws_x3_launch<NB, 2>(g, transB, st);
-        return ws_x3_launch<NB, 4>(g, transB, st);
-    } else {
-        if (slices <= 1) return ws_launch<T, NB, 1>(g, transB, st);
-        if (slices <= 2) return ws_launch<T, NB, 2>(g, transB, st);
-        return ws_launch<T, NB, 4>(g, transB, st);
-    }
+    if (slices <= 1) return ws_pick_form<T, NB, 1>(g, transB, st);
+    if (slices <= 2) return ws_pick_form<T, NB, 2>(g, transB, st);
+    return ws_pick_form<T, NB, 4>(g, transB, st);
 }
 
 template <typename T>
@@ -948,11 +908,22 @@ gt_status ws_pick(const GemmArgs &g, int transB, hipStream_t st) {
 
 }  // namespace
 
-// (the caller also requires C to have A's element type and no row scale or addend)
-bool gt_gemm_ws_applicable(gt_dtype dtype, int transA, int64_t M, int64_t N, int64_t K, int vecA) {
+// (the caller also requires C to have A's element type, no row scale or addend, and a mask, if any, with padded, 16-byte
+// aligned rows)
+bool gt_gemm_ws_applicable(gt_dtype dtype, int transA, int64_t M, int64_t N, int64_t K) {
     const int64_t kcap = dtype == GT_BF16 ? 4 * WsGeom<bf16_t>::SK : 4 * WsGeom<float>::SK;   // 256 / 128
     int nr, nsp;
-    return !transA && vecA && K >= 1 && (K <= kcap || ws_stream_shape(dtype, N, K, &nr, &nsp)) && N >= 1 && M >= 8192;
+    // more than 128 fp32 columns run on the fp32 MFMA here, whose time passes that of the stores beyond 64 input columns:
+    // the tiled split-bf16 kernel is faster then (2^18 x 128 -> 602: 670 us here, 520 there; 16 -> 1024: 0.96 ms here, 1.3 there)
+    if (dtype == GT_F32 && N > 128 && K > 64) return false;
+    return !transA && K >= 1 && (K <= kcap || ws_stream_shape(dtype, N, K, &nr, &nsp)) && N >= 1 && M >= 8192;
+}
+
+// Rows at the end of A that these kernels must not be given: a row's last 16-byte chunk is read whole, which on unpadded rows
+// reads into the next row, and past the end of the matrix on the last one (or few, where rows are shorter than a chunk).
+int64_t gt_gemm_ws_tail_rows(gt_dtype dtype, int64_t K, int64_t lda, int vecA) {
+    const int64_t hk = dtype == GT_BF16 ? WsGeom<bf16_t>::HK : WsGeom<float>::HK;
+    return vecA || K % hk == 0 ? 0 : (hk - 1 + lda - 1) / lda;
 }
 
 gt_status gt_gemm_ws_launch(const GemmArgs &g, gt_dtype dtype, int transB, hipStream_t st) {

@@ -59,13 +59,13 @@ __device__ inline void store_run4(gemm_bf16_t *lds, int row, int k, float x0, fl
 // Four consecutive elements at p[off..off+3] (position c of a row that ends at clim).  Branch
 // free: an out-of-range request reads the (always valid) start of the matrix; `nv` receives the
 // number of elements that are real, and mask4 zeroes the rest when the data is consumed (masking at
-// load time would wait for the data and stall the prefetch).  `vec` is grid-uniform.
+// load time would wait for the data and stall the prefetch).  `vec` is uniform over the workgroup (see gemm_whole_vectors).
 __device__ inline float4 load4(const float *p, int64_t off, int64_t c, int64_t clim, bool row_ok, int vec, int &nv) {
     const bool ok = row_ok && c < clim;
     nv = ok ? (int)((clim - c) < 4 ? (clim - c) : 4) : 0;
     float4 v;
     if (vec) {
-        v = *reinterpret_cast<const float4 *>(p + (ok ? off : 0));
+        __builtin_memcpy(&v, p + (ok ? off : 0), 16);
     } else {
         v.x = p[nv > 0 ? off : 0];
         v.y = p[nv > 1 ? off + 1 : 0];
@@ -208,9 +208,11 @@ __global__ void __launch_bounds__(256) k_gemm_x3(const GemmArgs g) {
     for (int q = 0; q < NPB; ++q)
 #pragma unroll
         for (int e = 0; e < 4; ++e) cs[q][e] = 0.0f;
+    auto whole_a = [&](int64_t k0) { return VA || (TA ? gemm_whole_vectors(k0 + KT, g.K) : gemm_whole_vectors(m0 + BM, g.M)); };
+    auto whole_b = [&](int64_t k0) { return VB || (TB ? gemm_whole_vectors(n0 + BN, g.N) : gemm_whole_vectors(k0 + KT, g.K)); };
     if (kbeg < kend) {
-        la.load(A, g.lda, m0, kbeg, g.M, kend, VA);
-        lb.load(B, g.ldb, n0, kbeg, g.N, kend, VB);
+        la.load(A, g.lda, m0, kbeg, g.M, kend, whole_a(kbeg));
+        lb.load(B, g.ldb, n0, kbeg, g.N, kend, whole_b(kbeg));
     }
     // One register stage: the loads of k-tile t+1 are in flight while tile t is multiplied.  (Two
     // stages were measured slower on MI355X: the extra registers halve the occupancy.)
@@ -223,8 +225,8 @@ __global__ void __launch_bounds__(256) k_gemm_x3(const GemmArgs g) {
         }
         __syncthreads();
         if (k0 + KT < kend) {
-            la.load(A, g.lda, m0, k0 + KT, g.M, kend, VA);
-            lb.load(B, g.ldb, n0, k0 + KT, g.N, kend, VB);
+            la.load(A, g.lda, m0, k0 + KT, g.M, kend, whole_a(k0 + KT));
+            lb.load(B, g.ldb, n0, k0 + KT, g.N, kend, whole_b(k0 + KT));
         }
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
