@@ -12,12 +12,14 @@
 //
 // Structure (weights and staging as in the weight-stationary combination kernel): persistent
 // workgroups of NW wavefronts; the weight matrix is put into LDS once ([n][k], k contiguous,
-// zero padded).  Every wavefront then works alone on blocks of 32 work-list entries:
+// zero padded).  Every wavefront then works alone on blocks of 32 work-list entries, block b of B being
+// entries b, B + b, 2 B + b, ... of the longest-first list:
 //   gather   G = 8 * NS lanes per entry cover the KP = NS * 128 bytes of a row, 16 bytes per lane,
 //            64 / G entries at a time; an entry is a whole-row work item of the plan (its
-//            neighbours are gathered and summed in fp32 exactly as the aggregation kernel does) or,
+//            neighbours are gathered and summed in fp32 as the aggregation kernel does) or,
 //            after the item list, a split long row (its partial rows, written beforehand by the
-//            aggregation kernel over the chunk items, are added in chunk order);
+//            aggregation kernel over the chunk items, are added).  Rows of at least max(64, 4 G)
+//            entries and split rows are summed by all groups of the wavefront, one row at a time;
 //   stage    the finished row is scaled (mean), rounded to the working type and written to row
 //            r of the wavefront's LDS tile [32][KP];
 //   multiply the tile times the weights: v_mfma_f32_32x32x16_bf16 / v_mfma_f32_32x32x2f32 with the
@@ -25,6 +27,10 @@
 //            columns per register quadruple;
 //   store    bias is the accumulators' start value, ReLU is applied on the way out; rows go to the
 //            output rows the entries name (the work list is ordered by row length, not by row).
+// What bounds it is the latency of the gathers: a wavefront's block lasts as long as its longest row, and no other work
+// hides that.  Blocks of 32 consecutive entries, eight wavefronts and one group per row took (us) 3059 for a 2^20-vertex
+// power-law graph, bf16 256 -> 64, and 1331 + 184 (chunk items) for one of 2^20 vertices and 16 M edges, 128 -> 64; this form
+// 1364 and, both kernels, 710.
 #include "gt_aggregate_kernel.h"
 #include "gt_combine.h"
 
@@ -102,63 +108,92 @@ __global__ void __launch_bounds__(NW * 64) k_fused_agg_combine(const AggArgs a, 
     const int64_t col = (int64_t)gl * V;          // this lane's columns of a gathered row
     const bool col_live = col < K;
     const int64_t nblk = (f.n_entries + 31) / 32;
-    for (int64_t blk = (int64_t)blockIdx.x * NW + wave; blk < nblk; blk += (int64_t)gridDim.x * NW) {
+
+    // Entry t of block blk: the list is sorted longest first, so a block takes every nblk-th entry: one of the longest, one of the
+    // shortest (32 consecutive entries put a wavefront that owns the longest rows 20,000 neighbours behind the others).
+    // Lanes t and t + 32 hold entry t: x = output row, or -1 for none; y, z = its neighbours, or (split row) partial rows; w = 1: split.
+    auto fetch_entry = [&](int64_t blk) {
+        const int64_t e = (int64_t)(lane & 31) * nblk + blk;
+        int4 it = make_int4(-1, 0, 0, 0);
+        if (blk < nblk && e < a.n_items) {
+            const int4 x = reinterpret_cast<const int4 *>(a.items)[e];
+            if (x.w < 0) it = make_int4(x.x, x.y, x.z, 0);     // (chunk items of split rows were run beforehand)
+        } else if (blk < nblk && e < f.n_entries) {
+            const gt_split sp = a.splits[e - a.n_items];
+            it = make_int4(sp.row, sp.first, sp.first + sp.count, 1);
+        }
+        return it;
+    };
+    // sum of the neighbours e0 .. e1 - 1 into acc; the group's first G ids and coefficients are already in idx_next, c_next, and
+    // each next G are requested before the current ones are used
+    auto gather = [&](float (&acc)[V], int e0, int e1, int idx_next, float c_next) {
+        for (int base = e0; base < e1; base += G) {
+            const int idx = idx_next;
+            const float c = c_next;
+            const int en = base + G + gl;
+            idx_next = 0;
+            c_next = 0.0f;
+            if (en < e1) {
+                idx_next = a.nbr[en];
+                c_next = a.coef ? a.coef[en] : 1.0f;
+            }
+            const int cnt = (e1 - base) < G ? (e1 - base) : G;
+            for (int j = 0; j < cnt; j += U) {
+                raw_t v[U];
+                float cj[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int jj = j + u;
+                    const int src = __shfl(idx, jj & (G - 1), G);
+                    cj[u] = __shfl(c, jj & (G - 1), G);
+                    const bool live = jj < cnt;
+                    if (!live) cj[u] = 0.0f;
+                    v[u] = raw_t{};
+                    if (live && col_live) v[u] = load_raw<T, V>(X + (int64_t)src * a.ldx + col);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) fma_raw(acc, cj[u], v[u]);
+            }
+        }
+    };
+    // a finished row: divided by its entry count (mean), rounded, to row t of the tile.  Columns at or past K must be exact zeros in
+    // the tile (a 16-byte load may have brought in row padding of X or of a partial row, whatever that holds).
+    auto put_row = [&](float (&acc)[V], int t, int div) {
+        if (a.post_mode == 2) {
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[i] = div > 0 ? acc[i] / (float)div : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+            if (col + i >= K) acc[i] = 0.0f;
+        *reinterpret_cast<uint4 *>(As + t * STR + col) = pack_row(acc);
+    };
+    constexpr int LONG = 4 * G < 64 ? 64 : 4 * G;   // rows from here on are summed by all groups of the wavefront together
+
+    int64_t blk = (int64_t)blockIdx.x * NW + wave;
+    int4 next = fetch_entry(blk);
+    for (; blk < nblk; blk += (int64_t)gridDim.x * NW) {
         __asm__ volatile("" ::: "memory");   // this block's tile writes stay below the previous block's tile reads
-        // ---- gather: 32 entries, NG at a time, into the LDS tile
-        for (int r = 0; r < 32 / NG; ++r) {
-            const int trow = r * NG + grp;
-            const int64_t e = blk * 32 + trow;
+        const int4 ent = next;
+        next = fetch_entry(blk + (int64_t)gridDim.x * NW);
+        const int len = ent.z - ent.y;
+        if (lane < 32) rowid[lane] = ent.x;
+        // ---- long rows and split rows, one at a time: every group sums a slice (or every NG-th partial row), the groups are
+        // added pairwise
+        const uint64_t big = __ballot(lane < 32 && (ent.w == 1 || len >= LONG));
+        for (uint64_t m = big; m; m &= m - 1) {
+            const int t = __ffsll((unsigned long long)m) - 1;
+            const int row = __builtin_amdgcn_readlane(ent.x, t), y = __builtin_amdgcn_readlane(ent.y, t),
+                      z = __builtin_amdgcn_readlane(ent.z, t), sp = __builtin_amdgcn_readlane(ent.w, t);
             float acc[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) acc[i] = 0.0f;
-            int out_row = -1;
-            if (e < a.n_items) {
-                const int4 it = reinterpret_cast<const int4 *>(a.items)[e];
-                if (it.w < 0) {          // a whole row (chunk items of split rows were run beforehand)
-                    out_row = it.x;
-                    const int e0 = it.y, e1 = it.z;
-                    // the group fetches G neighbour ids and coefficients at a time with one coalesced
-                    // load, the next G being requested before these are used (as the aggregation kernel)
-                    int idx_next = 0;
-                    float c_next = 0.0f;
-                    if (e0 + gl < e1) {
-                        idx_next = a.nbr[e0 + gl];
-                        c_next = a.coef ? a.coef[e0 + gl] : 1.0f;
-                    }
-                    for (int base = e0; base < e1; base += G) {
-                        const int idx = idx_next;
-                        const float c = c_next;
-                        const int en = base + G + gl;
-                        idx_next = 0;
-                        c_next = 0.0f;
-                        if (en < e1) {
-                            idx_next = a.nbr[en];
-                            c_next = a.coef ? a.coef[en] : 1.0f;
-                        }
-                        const int cnt = (e1 - base) < G ? (e1 - base) : G;
-                        for (int j = 0; j < cnt; j += U) {
-                            raw_t v[U];
-                            float cj[U];
-#pragma unroll
-                            for (int u = 0; u < U; ++u) {
-                                const int jj = j + u;
-                                const int src = __shfl(idx, jj & (G - 1), G);
-                                cj[u] = __shfl(c, jj & (G - 1), G);
-                                const bool live = jj < cnt;
-                                if (!live) cj[u] = 0.0f;
-                                v[u] = raw_t{};
-                                if (live && col_live) v[u] = load_raw<T, V>(X + (int64_t)src * a.ldx + col);
-                            }
-#pragma unroll
-                            for (int u = 0; u < U; ++u) fma_raw(acc, cj[u], v[u]);
-                        }
-                    }
-                }
-            } else if (e < f.n_entries) {   // a split row: its partial rows in chunk order
-                const gt_split s = a.splits[e - a.n_items];
-                out_row = s.row;
-                for (int k = 0; k < s.count; ++k) {
-                    const float *P = a.partials + (int64_t)(s.first + k) * a.ldp + col;
+            int div = z - y;
+            if (sp) {
+                if (a.post_mode == 2) div = a.rowptr[row + 1] - a.rowptr[row];
+#pragma unroll 4
+                for (int k = y + grp; k < z; k += NG) {
+                    const float *P = a.partials + (int64_t)k * a.ldp + col;
                     if (col_live) {
 #pragma unroll
                         for (int q = 0; q < V / 4; ++q) {
@@ -167,19 +202,43 @@ __global__ void __launch_bounds__(NW * 64) k_fused_agg_combine(const AggArgs a, 
                         }
                     }
                 }
+            } else {
+                const int per = (z - y + NG - 1) / NG;
+                const int s0 = y + grp * per, s1 = s0 + per < z ? s0 + per : z;
+                const bool has = s0 + gl < s1;
+                gather(acc, s0, s1, has ? a.nbr[s0 + gl] : 0, has ? (a.coef ? a.coef[s0 + gl] : 1.0f) : 0.0f);
             }
-            if (out_row >= 0 && a.post_mode == 2) {   // mean: divide by the row's entry count
-                const int d = a.rowptr[out_row + 1] - a.rowptr[out_row];
 #pragma unroll
-                for (int i = 0; i < V; ++i) acc[i] = d > 0 ? acc[i] / (float)d : 0.0f;
+            for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+                for (int i = 0; i < V; ++i) acc[i] += __shfl_xor(acc[i], o, 64);
+            if (grp == 0) put_row(acc, t, div);
+        }
+        // ---- the others, NG at a time; the first ids of the next NG are requested before these are gathered
+        int e0n = 0, e1n = 0, tn = grp, idx_n = 0;
+        float c_n = 0.0f;
+        auto lookup = [&](int r) {
+            tn = r * NG + grp;
+            e0n = __shfl(ent.y, tn, 64);
+            e1n = __shfl(ent.z, tn, 64);
+            if ((big >> tn) & 1) { tn = -1; e1n = e0n; }     // done above
+            idx_n = 0;
+            c_n = 0.0f;
+            if (e0n + gl < e1n) {
+                idx_n = a.nbr[e0n + gl];
+                c_n = a.coef ? a.coef[e0n + gl] : 1.0f;
             }
-            // columns at or past K must be exact zeros in the tile (a 16-byte load may have brought in
-            // row padding of X or of a partial row, whatever that holds)
+        };
+        lookup(0);
+        for (int r = 0; r < 32 / NG; ++r) {
+            const int t = tn, e0 = e0n, e1 = e1n, idx = idx_n;
+            const float c = c_n;
+            if (r + 1 < 32 / NG) lookup(r + 1);
+            float acc[V];
 #pragma unroll
-            for (int i = 0; i < V; ++i)
-                if (col + i >= K) acc[i] = 0.0f;
-            *reinterpret_cast<uint4 *>(As + trow * STR + col) = pack_row(acc);
-            if (gl == 0) rowid[trow] = out_row;
+            for (int i = 0; i < V; ++i) acc[i] = 0.0f;
+            gather(acc, e0, e1, idx, c);
+            if (t >= 0) put_row(acc, t, e1 - e0);
         }
         __asm__ volatile("" ::: "memory");   // LDS operations of a wavefront run in program order
         // ---- multiply the tile by the weights
@@ -289,7 +348,7 @@ gt_status fused_launch(const AggArgs &a, const FusedArgs &f, hipStream_t st) {
     const bool fast = f.N % OW == 0 && f.N == NB * 32 && a.ldy % ve == 0 && (((uintptr_t)a.Y & 15) == 0);
     const int64_t nblk = (f.n_entries + 31) / 32;
     int64_t gx = (nblk + NW - 1) / NW;
-    const int per_cu = lds <= 80 * 1024 ? 2 : 1;
+    const int per_cu = lds <= 80 * 1024 && NW <= 8 ? 2 : 1;
     if (gx > 256 * per_cu) gx = 256 * per_cu;
     if (gx < 1) gx = 1;
 #define GT_FUSED_GO(FAST_)                                                                                            \
@@ -306,21 +365,27 @@ gt_status fused_launch(const AggArgs &a, const FusedArgs &f, hipStream_t st) {
     return GT_OK;
 }
 
-// NB from the output width, NS from the input width, NW = 8 wavefronts where the tiles fit, else 4
+// NB from the output width, NS from the input width; as many wavefronts (16, 12, 8, 6 or 4) as weights and tiles leave room for:
+// they are what hides the latency of the gathers.  Fewer where that would leave CUs without a workgroup (12 K rows, 128 -> 64
+// bf16: 50 us with 16, 36 with 4).  NB = 8 keeps 128 accumulators: two wavefronts per SIMD at most.
+template <typename T, int NB, int NS, int NW>
+gt_status fused_pick_nw(const AggArgs &a, const FusedArgs &f, hipStream_t st) {
+    if constexpr (fused_lds_bytes<T, NB, NS, NW>() <= 160 * 1024 && (NB < 8 || NW <= 8)) {
+        if (NW == 4 || (f.n_entries + 31) / 32 >= 256 * NW) return fused_launch<T, NB, NS, NW>(a, f, st);
+    }
+    if constexpr (NW == 16) return fused_pick_nw<T, NB, NS, 12>(a, f, st);
+    else if constexpr (NW == 12) return fused_pick_nw<T, NB, NS, 8>(a, f, st);
+    else if constexpr (NW == 8) return fused_pick_nw<T, NB, NS, 6>(a, f, st);
+    else if constexpr (NW == 6) return fused_pick_nw<T, NB, NS, 4>(a, f, st);
+    else return gt_fail(GT_ERR_UNSUPPORTED, "gt_aggregate_combine_fwd: weights and tiles exceed the LDS");
+}
+
 template <typename T, int NB>
 gt_status fused_pick_ns(const AggArgs &a, const FusedArgs &f, hipStream_t st) {
     const int64_t slices = (a.F + FusedGeom<T>::SK - 1) / FusedGeom<T>::SK;
-    constexpr size_t cap = 160 * 1024;
-#define GT_FUSED_NS(NS_)                                                                          \
-    do {                                                                                          \
-        if constexpr (fused_lds_bytes<T, NB, NS_, 8>() <= cap) return fused_launch<T, NB, NS_, 8>(a, f, st); \
-        else if constexpr (fused_lds_bytes<T, NB, NS_, 4>() <= cap) return fused_launch<T, NB, NS_, 4>(a, f, st); \
-        else return gt_fail(GT_ERR_UNSUPPORTED, "gt_aggregate_combine_fwd: weights and tiles exceed the LDS"); \
-    } while (0)
-    if (slices <= 1) GT_FUSED_NS(1);
-    if (slices <= 2) GT_FUSED_NS(2);
-    GT_FUSED_NS(4);
-#undef GT_FUSED_NS
+    if (slices <= 1) return fused_pick_nw<T, NB, 1, 16>(a, f, st);
+    if (slices <= 2) return fused_pick_nw<T, NB, 2, 16>(a, f, st);
+    return fused_pick_nw<T, NB, 4, 16>(a, f, st);
 }
 
 template <typename T>
