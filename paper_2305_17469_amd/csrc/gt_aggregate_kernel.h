@@ -258,15 +258,16 @@ static inline int agg_xcd_run(int64_t gx) {
     return run;
 }
 
-// Instances with cooperative workgroups for the long items (single column tile, eight row loads in flight)
+// Instances with cooperative workgroups for the long items (single column tile)
 template <int U, int NP, int VWM>
-constexpr bool agg_coop() { return U == 8 && NP == 1 && VWM == 0; }
+constexpr bool agg_coop() { return NP == 1 && VWM == 0; }
 
 // One group of G lanes per work item; 64/G items per wavefront; 4 wavefronts per workgroup.
 // blockIdx.y selects a column tile of G*V*NP columns.
 // MK: an output mask is present (its values are fetched when the item starts; a separate instance so
 // that the registers they occupy during the gather cost the unmasked kernel nothing)
-template <typename T, int V, int G, int NP, int U, int VWM = VWM_NONE, bool MK = false, bool SH = false>
+// COOP: long items are shared out (a separate instance for the same reason)
+template <typename T, int V, int G, int NP, int U, int VWM, bool MK, bool SH, bool COOP>
 __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63;
@@ -282,7 +283,6 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     // (100 K vertices, 3 M edges, 15 fp32 columns, both directions: 247 -> 101 us).  The first n_coop workgroups therefore
     // give each of their items all groups of the workgroup, or of one wavefront where a workgroup's share would be less than
     // four entries per group: every group sums a slice, and the slices are added in a fixed order.
-    constexpr bool COOP = agg_coop<U, NP, VWM>();
     const bool coop = COOP && (int)blockIdx.x < a.n_coop;   // uniform over the workgroup
     const bool one_wave = COOP && a.coop_waves == 1;
     const int64_t item_id = coop ? (one_wave ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x)
@@ -525,20 +525,29 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
         AggArgs b = a;
         b.coop_waves = a.chunk >= 16 * NG ? 4 : 1;
         const int64_t ipc = b.coop_waves == 1 ? 4 : 1;   // items per cooperative workgroup
-        // A launch that gathers more than 2 GB has enough items to hide a long one behind, and slicing only costs locality
-        // (1.9 GB, 41 fp32 columns: 215 us alone, 192 us cooperative; 2.1 GB, 128 bf16 columns: 244 and 256 us).
-        const bool coop = agg_coop<U, NP, VWM>() && (double)a.n_edges * (double)a.F * sizeof(T) <= 2.0e9;
+        // A launch that gathers more than 2 GB (4 GB with two loads in flight, whose chains are four times as long) has enough
+        // items to hide a long one behind, and slicing only costs locality (1.9 GB, 41 fp32 columns: 215 us alone, 192 us
+        // cooperative; 2.1 GB, 128 bf16 columns: 244 and 256 us; two in flight, 2.1 GB, 64 bf16 columns: 836 us alone, 585 us cooperative).
+        const bool coop = agg_coop<U, NP, VWM>() && (double)a.n_edges * (double)a.F * sizeof(T) <= (U == 8 ? 2.0e9 : 4.0e9);
         b.n_coop = coop ? (int)((a.n_long + ipc - 1) / ipc) : 0;
         const int64_t left = a.n_items > b.n_coop * ipc ? a.n_items - b.n_coop * ipc : 0;
         const int64_t gi = (left + 4 * NG - 1) / (4 * NG), gx = b.n_coop + gi;
         b.xcd_run = agg_xcd_run(gi);
         const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
         gt_trace_variant(tr, V, G, NP, U, VWM == VWM_NONE && a.mask != nullptr);
+        const dim3 grid((unsigned)gx, gy);
         if constexpr (VWM == VWM_NONE) {
-            if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
-            else k_aggregate<T, V, G, NP, U, VWM, false, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
+            if (b.n_coop > 0) {
+                if constexpr (agg_coop<U, NP, VWM>()) {
+                    if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, true><<<grid, 256, 0, st>>>(b);
+                    else k_aggregate<T, V, G, NP, U, VWM, false, SH, true><<<grid, 256, 0, st>>>(b);
+                }
+            } else {
+                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, false><<<grid, 256, 0, st>>>(b);
+                else k_aggregate<T, V, G, NP, U, VWM, false, SH, false><<<grid, 256, 0, st>>>(b);
+            }
         } else {
-            k_aggregate<T, V, G, NP, U, VWM, false, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(b);
+            k_aggregate<T, V, G, NP, U, VWM, false, SH, false><<<grid, 256, 0, st>>>(b);
         }
         gt_trace_close(tr, st);
         GT_LAUNCH_CHECK("k_aggregate");

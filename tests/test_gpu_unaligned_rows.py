@@ -138,3 +138,28 @@ def test_long_rows_summed_by_many_groups(F, dtype, hub):
         bound = hub * 2.0 ** -24 * mag + (2.0 ** -8 * ref.abs() if dtype == "bf16" else 0)
         assert bool(((Y.double() - ref).abs() <= bound).all())
         assert torch.equal(Y, B.gt_aggregate_fwd(g, "sum", X))
+
+
+@pytest.mark.parametrize("n,F,dtype", [(530000, 64, "bf16"), (60000, 200, "f32"), (530000, 17, "f32"), (90000, 256, "bf16")])
+def test_long_rows_of_large_tables(n, F, dtype):
+    """The same where the table is past 32 MiB (two rows in flight): mean of rows of 63 to 5,000 entries, bound as above."""
+    from paper_2305_17469_amd import binding as B
+    hubs = [63, 64, 65, 96, 127, 129, 700, 5000]
+    rng = np.random.default_rng(n)
+    dst = np.concatenate([np.repeat(np.arange(0, n, 4), 2)] + [np.full(h, 11 * (i + 1)) for i, h in enumerate(hubs)])
+    src = np.concatenate([rng.integers(0, n, dst.size - sum(hubs))] + [rng.choice(n, h, replace=False) for h in hubs])
+    rp, ci = graphs.csr_from_pairs(src, dst, n, n)
+    g = B.Graph(up_i32(rp), up_i32(ci), n)
+    announce("long rows, large table", dtype, "F", F, "n", n)
+    v = 8 if dtype == "bf16" else 4
+    X = torch.randn((n, (F + v - 1) // v * v), device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(n))
+    X = (X.to(torch.bfloat16) if dtype == "bf16" else X)[:, :F]
+    Y = B.gt_aggregate_fwd(g, "mean", X)
+    deg = up_i32(np.diff(rp)).long()
+    rows = torch.repeat_interleave(torch.arange(n, device="cuda:0"), deg)
+    t = X.double()[up_i32(ci).long()]
+    zero = torch.zeros((n, F), dtype=torch.float64, device="cuda:0")
+    ref, mag = zero.index_add(0, rows, t) / deg.clamp(min=1)[:, None], zero.index_add(0, rows, t.abs()) / deg.clamp(min=1)[:, None]
+    bound = (deg[:, None] + 1) * 2.0 ** -24 * mag + (2.0 ** -8 * ref.abs() if dtype == "bf16" else 0)
+    assert bool(((Y.double() - ref).abs() <= bound).all())
+    assert torch.equal(Y, B.gt_aggregate_fwd(g, "mean", X))
