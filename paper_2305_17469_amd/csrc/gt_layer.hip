@@ -272,21 +272,19 @@ bool ranges_overlap(const void *a, size_t a_elems, const void *b, size_t b_elems
     return a0 < b0 + b_elems * es && b0 < a0 + a_elems * es;
 }
 
-// Forward-only aggregation-first layers: where the fused aggregation + combination kernel is used
-// instead of the two kernels.  Measured on MI355X (ms, two kernels / fused): input rows of 64 bytes on a
-// 2^20-vertex uniform graph, 16 -> 64 fp32 0.49 / 0.37, 16 -> 256 0.63 / 0.55: the gather of such
-// rows is bound by the number of memory requests, and writing and re-reading A X costs as much as
-// gathering it.  Wider rows lose: one workgroup per CU holds the weights, and eight wavefronts hide
-// less gather latency than the aggregation kernel's two dozen (2^21-vertex power-law graph, bf16
-// 100 -> 256: 1.96 / 2.52; 2^18 vertices, fp32 128 -> 41: 0.52 / 1.10; 41 -> 128: 0.27 / 0.57).  So do
-// narrow rows of a table small enough to sit in the L2s, where the aggregation kernel is not request
-// bound (2^18 vertices, 16 -> 64 fp32, a 16 MB table: 0.24 / 0.36; 2^21 vertices, 16 -> 64 bf16, 64 MB:
-// 1.09 / 1.03).  Hence: rows of at most 64 bytes AND a gathered table of at least 32 MiB.
+// Forward-only aggregation-first layers: where the fused aggregation + combination kernel is used instead of the two kernels:
+// rows of at most 64 bytes of a table of at least 32 MiB, on graphs with next to no long rows.  Measured on MI355X (us, fused /
+// two kernels): uniform graphs of 2^20 vertices, 16 M edges, fp32 16 -> 64 394 / 410, 16 -> 8 347 / 381, bf16 32 -> 64
+// 373 / 382 (the gather of such rows is bound by the number of memory requests, and writing and re-reading A X adds to them),
+// and of 2^18 vertices, a 16 MB table, 16 -> 64 fp32 85 / 83, 8 -> 32 73 / 66.  On power-law graphs the two kernels win, whose
+// long rows are shared out over whole workgroups: 2^20 vertices, fp32 16 -> 64 313 / 275, 16 -> 256 634 / 447, bf16 16 -> 64
+// 325 / 236; 2^21 vertices, fp32 16 -> 64 821 / 726.  Wider rows lose there as well (bf16 64 -> 128 412 / 352, 128 -> 64
+// 718 / 387 against the combination-first order) and gain little on uniform ones (64 -> 128 409 / 437, 128 -> 64 656 / 452).
 bool fused_preferred(const gt_graph *g, const gt_layer_desc *d, const void *X, int64_t ldx) {
     const int ve = d->dtype == GT_BF16 ? 8 : 4;
     if (!gt_fused_applicable(d->dtype, d->in_dim, d->out_dim) || ((uintptr_t)X & 15) || ldx % ve) return false;
     const int64_t row_bytes = d->in_dim * (int64_t)gt_dtype_size(d->dtype);
-    return row_bytes <= 64 && g->n_src * row_bytes >= ((int64_t)32 << 20);
+    return row_bytes <= 64 && g->n_src * row_bytes >= ((int64_t)32 << 20) && g->fwd.n_long * 1024 <= g->n_dst;
 }
 
 void decide(const gt_graph *g, const gt_layer_desc *d, gt_order *fwd, gt_order *bwd) {

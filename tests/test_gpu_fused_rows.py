@@ -46,3 +46,29 @@ def test_rows_at_the_edges(n, hub, dtype, fi, fo):
         again = torch.empty_like(out)
         B.gt_aggregate_combine_fwd(g, reduce, X, W, b, False, out=again)
         assert torch.equal(out, again)
+
+
+@pytest.mark.parametrize("hubs", [0, 512, 513, 2000])
+def test_inference_layer_on_both_sides_of_the_rule(hubs):
+    """Forward-only aggregation-first layer on a 32 MiB table of 64-byte rows: one kernel up to one long row in 1,024, two
+    beyond.  Bound as above."""
+    from paper_2305_17469_amd import binding as B
+    n, fi, fo = 524288, 16, 24
+    rng = np.random.default_rng(hubs)
+    dst = np.concatenate([np.repeat(np.arange(0, n, 2), 2), np.repeat(np.arange(hubs) * 200 + 1, 90)])
+    rp, ci = graphs.csr_from_pairs(rng.integers(0, n, dst.size), dst, n, n)
+    g = B.Graph(up_i32(rp), up_i32(ci), n)
+    gen = torch.Generator(device="cuda:0").manual_seed(hubs)
+    X, W = torch.randn((n, fi), device="cuda:0", generator=gen), torch.randn((fi, fo), device="cuda:0", generator=gen)
+    b = torch.randn(fo, device="cuda:0", generator=gen)
+    d = B.make_desc("mean", "f32", False, fi, fo, need_dx=False, dy_is_dz=True)
+    announce("inference layer, hubs", hubs)
+    Y, used = B.gt_layer_fwd(g, d, X, W, b, B.LayerBuffers(g, d), "agg_first", inference=True)
+    deg = up_i32(np.diff(rp)).long()
+    at = torch.repeat_interleave(torch.arange(n, device="cuda:0"), deg)
+    t = X.double()[up_i32(ci).long()]
+    zero = torch.zeros((n, fi), dtype=torch.float64, device="cuda:0")
+    div = deg.clamp(min=1)[:, None].double()
+    ref = zero.index_add(0, at, t) / div @ W.double() + b.double()
+    mag = zero.index_add(0, at, t.abs()) / div @ W.double().abs() + b.double().abs()
+    assert used == "agg_first" and bool(((Y.double() - ref).abs() <= (int(deg.max()) + fi + 4) * 2.0 ** -24 * mag).all())
