@@ -80,9 +80,16 @@ def kernel_source_sha16():
 
 
 def agg_kernel_name(dt, V, G, NP, U, masked):
-    """The aggregation kernel instance as a profiler lists it."""
+    """The aggregation kernel instance as a profiler lists it, without the last two template arguments (see agg_short_name)."""
     return "k_aggregate<%s, %d, %d, %d, %d, 0, %s>" % ("unsigned short" if dt == "bf16" else "float", V, G, NP, U,
                                                       "true" if masked else "false")
+
+
+def agg_short_name(name):
+    """A profiler's name of an aggregation kernel without its argument list and its last two template arguments (shifted row
+    ends, shared-out long items: the same gather, chosen by alignment and by the graph's longest rows)."""
+    args_ = name.split("k_aggregate<")[1].split(">")[0].split(", ")
+    return "k_aggregate<%s>" % ", ".join(args_[:7])
 
 
 def measure_traffic(args):
@@ -149,16 +156,16 @@ def measure_traffic(args):
     line = [l for l in open(os.path.join(out_dir, "plain_%s.log" % tag)) if l.startswith('{"metric')][-1]
     plain = json.loads(line)
     inst = {}
-    for name in fetch:
-        if "k_aggregate<" not in name:
-            continue
-        short = name.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0]
-        fv, wv = fetch[name], write.get(name, [0.0])
-        st = [r for r in stats if r["Name"] == name]
+    for short in sorted({agg_short_name(n) for n in fetch if "k_aggregate<" in n}):
+        same = lambda n: "k_aggregate<" in n and agg_short_name(n) == short   # noqa: E731
+        fv = [v for n in fetch if same(n) for v in fetch[n]]
+        wv = [v for n in fetch if same(n) for v in write.get(n, [0.0])]
+        st = [r for r in stats if same(r["Name"])]
         ev = [k for k in plain.get("aggregation_kernels", []) if k["kernel"] == short]
         inst[short] = dict(dispatches=len(fv), fetch_kib_per_dispatch=sum(fv) / len(fv), write_kib_per_dispatch=sum(wv) / len(wv),
                            hbm_bytes_per_launch=(sum(fv) / len(fv) * fs + sum(wv) / len(wv) * ws) * 1024.0,
-                           avg_us_rocprof_kernel_trace=float(st[0]["AverageNs"]) / 1e3 if st else None,
+                           avg_us_rocprof_kernel_trace=sum(float(r["TotalDurationNs"]) for r in st)
+                           / sum(int(r["Calls"]) for r in st) / 1e3 if st else None,
                            avg_ms_hip_events=ev[0]["avg_ms"] if ev else None)
     # the matrix kernels of the same runs: bytes past L2 per launch, duration, matrix-pipe utilisation
     mm = {}
