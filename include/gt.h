@@ -14,8 +14,8 @@
  * Conventions (hold for every entry point unless it says otherwise)
  *   Layout     matrices are row-major, nodes x features; `ld*` is the row stride in ELEMENTS
  *              (>= the logical width).  Rows whose stride in bytes and base address are
- *              multiples of 16 take the vectorised kernels; anything else takes a slower
- *              element-wise path with identical results up to summation order.
+ *              multiples of 16 are the fastest; anything else is read and written in whole
+ *              vectors as well, with identical results up to summation order.
  *   Pointers   every data pointer is a DEVICE pointer unless marked "host".  The caller owns
  *              all device memory (inputs, outputs, workspaces); the library never allocates or
  *              frees device memory and never keeps a pointer beyond what is stated.
