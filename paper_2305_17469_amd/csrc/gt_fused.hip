@@ -30,7 +30,7 @@
 // What bounds it is the latency of the gathers: a wavefront's block lasts as long as its longest row, and no other work
 // hides that.  Blocks of 32 consecutive entries, eight wavefronts and one group per row took (us) 3059 for a 2^20-vertex
 // power-law graph, bf16 256 -> 64, and 1331 + 184 (chunk items) for one of 2^20 vertices and 16 M edges, 128 -> 64; this form
-// 1364 and, both kernels, 710.
+// 1210 and, both kernels, 639.
 #include "gt_aggregate_kernel.h"
 #include "gt_combine.h"
 
@@ -175,7 +175,10 @@ __global__ void __launch_bounds__(NW * 64) k_fused_agg_combine(const AggArgs a, 
     };
     constexpr int LONG = 4 * G < 64 ? 64 : 4 * G;   // rows from here on are summed by all groups of the wavefront together
 
-    int64_t blk = (int64_t)blockIdx.x * NW + wave;
+    // (numbered across the workgroups: a last round that is not full is spread over all CUs; 167 K rows, 2.7 M edges, uniform,
+    // bf16 60 -> 24: 71 -> 58 us; power law, 2^20 vertices, bf16 128 -> 64: 721 -> 639 us; on uniform graphs of many rounds
+    // with narrow rows the lost locality costs up to 4 % against workgroups of neighbouring blocks)
+    int64_t blk = (int64_t)wave * gridDim.x + blockIdx.x;
     int4 next = fetch_entry(blk);
     for (; blk < nblk; blk += (int64_t)gridDim.x * NW) {
         __asm__ volatile("" ::: "memory");   // this block's tile writes stay below the previous block's tile reads
