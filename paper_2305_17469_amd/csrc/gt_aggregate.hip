@@ -2,12 +2,6 @@
 // host side of gt_aggregate_fwd / gt_aggregate_bwd.  The kernels live in gt_aggregate_kernel.h.
 #include "gt_aggregate_kernel.h"
 
-// tables above this size are gathered in column passes (the MI355X last-level cache holds 256 MiB)
-static const int64_t GT_COLUMN_PASS_TABLE_BYTES = (int64_t)256 << 20;
-// ... and only when a pass gathers about a gigabyte or more: below that the extra launches cost more
-// than the passes save (a sampled block with 4,353-wide rows would run 68 launches of 11 MB each)
-static const int64_t GT_COLUMN_PASS_MIN_EDGES = (int64_t)4 << 20;
-
 size_t gt_aggregate_ws_bytes(const gt_graph *g, int64_t F) {
     const int64_t ldp = (F + 7) / 8 * 8;
     const int64_t parts = g->fwd.n_partials > g->bwd.n_partials ? g->fwd.n_partials : g->bwd.n_partials;
@@ -75,31 +69,7 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
     const int ve = in_dtype == GT_F32 ? 4 : 8;
     const bool vec = aligned16(X) && aligned16(Y) && (ldx % ve == 0) && (ldy % ve == 0) &&
                      (!mask || (aligned16(mask) && ldmask % ve == 0));
-    // A gathered table far larger than the last-level cache, with rows of 512 bytes or more, is
-    // aggregated in column passes of 256 bytes, one launch each: every pass gathers from a table
-    // slice a fraction of the size, so more of the popular rows stay cached, and the narrow launch
-    // shape keeps more loads in flight (measured on MI355X: 1 GiB bf16 table, 512-byte rows,
-    // 3.93 -> 3.65 ms; 4.3 GB fp32 table, 4 KB rows, 12.0 -> 10.2 ms).  Results are unchanged:
-    // columns are independent.  Rows without alignment lose by it: a slice's edges share their lines with the next one's
-    // (5.6 M edges, 161 fp32 columns 709 us whole, 944 in passes; 10 M edges, 301 bf16 columns 1068 and 1397).
-    int64_t pass = F;
-    if (vec && a.table_bytes > GT_COLUMN_PASS_TABLE_BYTES && F * (int64_t)es >= 512 && g->n_edges >= GT_COLUMN_PASS_MIN_EDGES)
-        pass = 256 / (int64_t)es;
-    // what one launch gathers from: the slice of a pass, not the whole table (picks the unroll)
-    if (pass < F) a.table_bytes = n_in * pass * (int64_t)es;
-    for (int64_t c0 = 0; c0 < F; c0 += pass) {
-        const int64_t fp = F - c0 < pass ? F - c0 : pass;
-        a.X = static_cast<const char *>(X) + c0 * es;
-        a.Y = static_cast<char *>(Y) + c0 * es;
-        a.F = fp;
-        a.ldp = (fp + 7) / 8 * 8;
-        a.bias = bias ? bias + c0 : nullptr;
-        a.mask = mask ? static_cast<const char *>(mask) + c0 * es : nullptr;
-        gt_status s;
-        s = gt_agg_launch(a, in_dtype, vec, st);
-        if (s != GT_OK) return s;
-    }
-    return GT_OK;
+    return gt_agg_launch(a, in_dtype, vec, st);
 }
 
 extern "C" gt_status gt_aggregate_ws_size(const gt_graph *g, int64_t F, size_t *ws_bytes) {

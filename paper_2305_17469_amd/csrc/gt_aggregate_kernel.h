@@ -20,6 +20,8 @@
 #include "gt_internal.h"
 #include "gt_trace.h"
 
+#include <type_traits>
+
 struct AggArgs {
     const gt_item *items;
     int64_t n_items;
@@ -52,6 +54,8 @@ struct AggArgs {
     int n_coop;              // set at launch: the first n_coop workgroups give their items a whole workgroup each
     int coop_waves;          // (4) or a whole wavefront each (1)
     int xcd_run;             // item blocks per XCD run (0 or 1: plain order)
+    int slices_lg;           // set at launch: 1 << slices_lg column tiles are shared out over the XCDs (see launch)
+    int n_blocks;            // set at launch: workgroups per column tile
     int only_split;          // run only the chunk items of split rows (the whole-row items are someone else's)
     int no_reduce;           // host-side: do not launch the kernel that adds the partial rows
     int trace_kind;          // host-side bookkeeping of the optional kernel timing
@@ -168,8 +172,14 @@ __device__ inline void store_vec<bf16_t, 1>(bf16_t *p, const float (&v)[1], int 
 // SH: rows without 16-byte alignment.  The lane that holds a row's ragged end takes the row's last V columns instead of
 // starting at its own column: it repeats some of its neighbour's (and stores the same values there), and every
 // access is a whole vector inside the row.  Needs F >= V.
+// Lanes past the row's end get its last vector.
 template <bool SH, int V>
-__device__ inline int64_t agg_col(const AggArgs &a, int64_t own) { return SH && own > a.F - V ? a.F - V : own; }
+__device__ inline int64_t agg_col(int64_t F, int64_t own) {
+    const int64_t last = SH ? F - V : (F - 1) / V * V;
+    return own > last ? last : own;
+}
+template <bool SH, int V>
+__device__ inline int64_t agg_col(const AggArgs &a, int64_t own) { return agg_col<SH, V>(a.F, own); }
 
 // the mask values of this lane's segments of output row `row` (16-byte loads where the segment is whole);
 // issued early by the callers so that the load is not a dependent round trip at the end of the item
@@ -235,19 +245,12 @@ __device__ inline void finish_row(const AggArgs &a, int row, int gl, int64_t col
     }
 }
 
-// Item block of this workgroup under the XCD-run order (run <= 1: plain order).  The remapping is
-// a bijection on the blocks of every complete group of 8 * run blocks; the ragged end of the grid
-// keeps the plain order.
-__device__ inline int64_t agg_item_block(int run, int first = 0) {   // first: blocks before the item blocks
-    int64_t bx = (int64_t)blockIdx.x - first;
-    if (gridDim.y == 1 && run > 1) {
-        const int64_t super = 8 * (int64_t)run;
-        const int64_t full = ((int64_t)gridDim.x - first) / super * super;
-        if (bx < full) {
-            const int64_t w = bx % super;
-            bx = bx - w + (w & 7) * run + (w >> 3);
-        }
-    }
+// Item block of workgroup `bx` of `n` under the XCD-run order (run: a power of two, 1: plain order), where consecutive workgroups go
+// to 1 << xcds_lg XCDs in turn.  The remapping is a bijection on the blocks of every complete group of run blocks per XCD; the
+// ragged end of the grid keeps the plain order.
+__device__ inline int agg_item_block(int run, int bx, int n, int xcds_lg) {
+    const int super = run << xcds_lg, w = bx & (super - 1);
+    if (run > 1 && bx < (n & ~(super - 1))) bx = bx - w + (w & ((1 << xcds_lg) - 1)) * run + (w >> xcds_lg);
     return bx;
 }
 
@@ -290,10 +293,19 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     // (100 K vertices, 3 M edges, 15 fp32 columns, both directions: 247 -> 101 us).  The first n_coop workgroups therefore
     // give each of their items all groups of the workgroup or of one wavefront (coop_waves, see launch): every group sums a slice,
     // and the slices are added in a fixed order.
-    const bool coop = COOP && (int)blockIdx.x < a.n_coop;   // uniform over the workgroup
+    // Column tiles may be shared out over the XCDs (slices_lg, see launch): the XCDs of one tile then walk the whole list.
+    int bx = blockIdx.x, slice = 0;
+    if (a.slices_lg > 0) {
+        const int xcd = bx & 7;
+        slice = xcd & ((1 << a.slices_lg) - 1);
+        bx = ((bx >> 3) << (3 - a.slices_lg)) + (xcd >> a.slices_lg);
+    }
+    const bool coop = COOP && bx < a.n_coop;   // uniform over the workgroup
     const bool one_wave = COOP && a.coop_waves == 1;
-    const int64_t item_id = coop ? (one_wave ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x)
-                                 : (COOP ? (int64_t)a.n_coop * (one_wave ? 4 : 1) : 0) + (agg_item_block(a.xcd_run, COOP ? a.n_coop : 0) * 4 + wave) * NG + grp;
+    const int first = COOP ? a.n_coop : 0;
+    const int64_t item_id = coop ? (one_wave ? (int64_t)bx * 4 + wave : (int64_t)bx)
+                                 : (int64_t)first * (one_wave ? 4 : 1) +
+                                       ((int64_t)agg_item_block(a.xcd_run, bx - first, a.n_blocks - first, 3 - a.slices_lg) * 4 + wave) * NG + grp;
     if (item_id >= a.n_items) return;   // whole groups leave together; the only barrier below is the cooperative one
     const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
     int row = raw.x, e0 = raw.y, e1 = raw.z, slot = raw.w;
@@ -311,7 +323,7 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         e1 = __builtin_amdgcn_readfirstlane(e1);
         slot = __builtin_amdgcn_readfirstlane(slot);
     }
-    const int64_t col0 = (int64_t)blockIdx.y * (G * V * NP);
+    const int64_t col0 = ((int64_t)blockIdx.y * (1 << a.slices_lg) + slice) * (G * V * NP);
     const T *X = static_cast<const T *>(a.X);
 
     float acc[NP][V];
@@ -358,34 +370,43 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         for (int k = 0; k < IPL; ++k) { idx[k] = idx_next[k]; ei[k] = ei_next[k]; c[k] = c_next[k]; }
         fetch(base + GB);
         const int cnt = (e1 - base) < GB ? (e1 - base) : GB;
-        auto step = [&](int j) {   // entries j .. j + U - 1 of the batch (j is a constant where IPL > 1)
+        // entries j .. j + U - 1 of the batch (j is a constant where IPL > 1); ALL: every one of them is there, and the loads are
+        // branch free (with a branch around each, the exchange that brings its id and the load wait for one another)
+        auto step = [&](int j, auto all) {
+            constexpr bool ALL = decltype(all)::value;
             raw_t v[U][NP];
             raw_t w[VWM == VWM_NONE ? 1 : U][VWM == VWM_NONE ? 1 : NP];
             float cj[U];
+            int src[U], we[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int jj = j + u, k = IPL > 1 ? jj / G : 0;
-                int src, we = 0;
+                we[u] = 0;
                 if constexpr (G == 64) {   // wave-uniform: scalar broadcast, scalar row base
-                    src = __builtin_amdgcn_readlane(idx[0], jj & 63);
+                    src[u] = __builtin_amdgcn_readlane(idx[0], jj & 63);
                     cj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c[0]), jj & 63));
-                    if constexpr (VWM != VWM_NONE) we = __builtin_amdgcn_readlane(ei[0], jj & 63);
+                    if constexpr (VWM != VWM_NONE) we[u] = __builtin_amdgcn_readlane(ei[0], jj & 63);
                 } else {
-                    src = __shfl(idx[k], jj & (G - 1), G);
+                    src[u] = __shfl(idx[k], jj & (G - 1), G);
                     cj[u] = __shfl(c[k], jj & (G - 1), G);
-                    if constexpr (VWM != VWM_NONE) we = __shfl(ei[k], jj & (G - 1), G);
+                    if constexpr (VWM != VWM_NONE) we[u] = __shfl(ei[k], jj & (G - 1), G);
                 }
-                const bool live = jj < cnt;
-                if (!live) cj[u] = 0.0f;
-                const T *xr = X + (int64_t)src * a.ldx;
+                if (!ALL && jj >= cnt) cj[u] = 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool live = ALL || j + u < cnt;
+                const T *xr = X + (int64_t)src[u] * a.ldx;
 #pragma unroll
                 for (int p = 0; p < NP; ++p) {
-                    const int64_t own = col0 + (int64_t)(p * G + gl) * V, col = agg_col<SH, V>(a, own);
-                    v[u][p] = raw_t{};
-                    if (live && own < a.F) v[u][p] = load_raw<T, V>(xr + col);
+                    const int64_t own = col0 + (int64_t)(p * G + gl) * V;
+                    // (a lane past the row's end repeats its last vector: a line that is read anyway, sums that nobody stores)
+                    const int64_t col = agg_col<SH, V>(a, own);
+                    if constexpr (!ALL) v[u][p] = raw_t{};
+                    if (live) v[u][p] = load_raw<T, V>(xr + col);
                     if constexpr (VWM != VWM_NONE) {
-                        w[u][p] = raw_t{};
-                        if (live && own < a.F) w[u][p] = load_raw<T, V>(VWp + (int64_t)we * a.ldvw + col);
+                        if constexpr (!ALL) w[u][p] = raw_t{};
+                        if (live) w[u][p] = load_raw<T, V>(VWp + (int64_t)we[u] * a.ldvw + col);
                     }
                 }
             }
@@ -397,12 +418,20 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
                     else fma_vw<VWM, V>(acc[p], cj[u], v[u][p], w[u][p]);
                 }
         };
+        // (two rows in flight: a remainder step of its own costs nothing.  With eight it is a round trip more for every batch that is no
+        // multiple of eight: power law, 1.5 M edges, 280 bf16 columns shared out, 99 us without it, 126 with it.)
+        constexpr bool BY_ALL = U == 2 && VWM == VWM_NONE;
         if constexpr (IPL == 1) {
-            for (int j = 0; j < cnt; j += U) step(j);
+            int j = 0;
+            if constexpr (BY_ALL)
+                for (; j + U <= cnt; j += U) step(j, std::true_type{});
+            for (; j < cnt; j += U) step(j, std::false_type{});
         } else {
 #pragma unroll
-            for (int j = 0; j < GB; j += U)
-                if (j < cnt) step(j);
+            for (int j = 0; j < GB; j += U) {
+                if (j + U <= cnt) step(j, std::true_type{}); else
+                if (j < cnt) step(j, std::false_type{});
+            }
         }
     }
 
@@ -566,28 +595,74 @@ static inline bool agg_vectors_pay(const AggArgs &a, double bytes) {
     return a.n_edges >= 12 * a.n_items && agg_long_batches(a, 4, bytes);
 }
 
+// Rows of more than 256 bytes may be cut into column tiles of 256 bytes (G = 16) or 512 (G = 32): the groups read shorter pieces of more
+// rows at a time, and what an L2 has to hold of a popular row is one tile of it.  The tiles of a launch either follow one another
+// (grid.y), or, in pairs, share out the XCDs (slices_lg = 1): four XCDs walk the list for one tile, four for the other, so each L2
+// holds twice as many rows and no tile has to wait for the long items of the one before.  us, whole rows / tiles, one direction:
+// power law, 262 K rows, 12 M edges, 128 fp32 columns 415 / 367, 256 columns 1067 / 776; 524 K rows, 13 M edges, 256 bf16 columns 687 / 582;
+// 66 K rows, 1 M edges, 256 fp32 columns 103 / 73; uniform, 66 K rows, 1.6 M edges, 128 fp32 columns 94 / 75, 512 columns 455 / 296;
+// 1 M rows, 17 M edges, 128 columns 1240 / 1263.
+//  * Only where a tile begins and ends with a line: otherwise each end costs a line more (uniform, 200 K rows, 3 M edges, 300 fp32
+//    columns 545 / 728; power law, 262 K rows, 6.5 M edges, 200 columns 451 / 501).  Rows wider than three of a wavefront's vectors
+//    per lane lose more by that width: 512-byte tiles there (power law, 602 fp32 columns, 12 M edges 2869 / 2146, 1.6 M edges 327 / 285), and
+//    power-law tables past 512 MB, where only the L2s are left to hit (629 MB, 300 columns 1333 / 1234).
+//  * The two tiles of a pair have to be nearly full (96 fp32 columns, power law, 262 K rows 267 / 278).
+//  * Pairs share out the XCDs on skewed graphs of tables up to 600 MB (537 MB, 256 bf16 columns 1229, one after the other 1250; 1.07 GB
+//    3384 and 3193) and in small launches of uniform ones (16 K rows, 262 K edges 13.7 and 15.1; 131 K rows, 3.3 M edges 201 and 193).
+//  * Skewed launches below half a gigabyte keep whole rows, eight in flight and shared out (33 K rows, 0.8 M edges, 128 fp32 columns 29 / 32).
+//  * Eight rows in flight and long items shared out where the chains of long items matter: tiles that gather at most 2.9 GB one after the
+//    other from at most 300 MB (us, that / two rows in flight alone: 131 K rows, 3.3 M edges, 128 columns 103 / 120; 262 K rows, 12 M edges, 160 columns
+//    464 / 504; 6.5 M edges, 128 columns, 3.4 GB 260 / 224; 302 MB, 144 columns 600 / 573).  Beyond, two in flight, shared out from 32 entries per item on
+//    (12 M edges, degree 45, symmetric norm 429 / 449; 6.5 M edges, degree 25 250 / 224).
+struct AggTiles { int G, U, slices_lg; bool share; };   // G 0: the row whole
+static inline AggTiles agg_tiles(const AggArgs &a, int64_t nvec, size_t es, double bytes) {
+    const bool lines = (a.ldx * (int64_t)es) % 128 == 0 && ((uintptr_t)a.X & 127) == 0;
+    const int64_t tiles = (nvec + 15) / 16;
+    const AggTiles whole = {0, 0, 0, false};
+    if (nvec < 28) return whole;
+    if (!agg_skewed(a)) {
+        if (!lines) return whole;
+        const bool few = a.n_long > 0 && a.n_items * 16 <= 1792 * 64;
+        return {16, 2, tiles % 2 == 0 && bytes < 0.3e9 ? 1 : 0, few};
+    }
+    if (bytes < 0.5e9) return whole;
+    if (!lines) {
+        if (nvec > 128) return {32, 2, 0, false};
+        if (nvec >= 64 && a.table_bytes > ((int64_t)512 << 20)) return {16, 2, 0, false};
+        return whole;
+    }
+    const int lg = tiles % 2 == 0 && a.table_bytes <= ((int64_t)600 << 20) ? 1 : 0;
+    if (bytes * (1 << lg) <= 2.9e9 * (double)tiles && a.table_bytes <= ((int64_t)300 << 20)) return {16, 8, lg, true};
+    return {16, 2, lg, a.n_long > 0 && a.n_edges >= 32 * a.n_items};
+}
+
+// tiled: the row is cut into several column tiles of this launch (see agg_tiles); share: whether its long items are shared out
 template <typename T, int V, int G, int NP, int U, int VWM, bool SH>
-gt_status launch(const AggArgs &a, hipStream_t st) {
+gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slices_lg = 0, bool share = false) {
     constexpr int NG = 64 / G;
     const int64_t tile = (int64_t)G * V * NP;
-    const unsigned gy = (unsigned)((a.F + tile - 1) / tile);
+    const unsigned tiles = (unsigned)((a.F + tile - 1) / tile);
     if (a.n_items > 0) {
         AggArgs b = a;
+        b.slices_lg = slices_lg;
         const double bytes = agg_bytes<T>(a);
         // A whole wavefront per long item where its groups then sum a few dozen entries each; a whole workgroup where a row has only
         // a group or two per wavefront's width to share it, or the chains are four times as long (U == 2).  us, one wavefront / a workgroup
         // per item, power-law graphs: 4 M edges, 64 bf16 columns 47 / 58, 32 columns 54 / 67, 41 fp32 columns 62 / 65; 12 M edges,
         // 41 fp32 columns 173 / 162; 17 M edges, 64 bf16 columns (U == 2) 270 / 247.
-        b.coop_waves = G == 64 || (U == 2 && G >= 8) || (G == 16 && bytes > 1.0e9) ? 4 : 1;
+        b.coop_waves = tiled || G == 64 || (U == 2 && G >= 8) || (G == 16 && bytes > 1.0e9) ? 4 : 1;
+        bool coop = agg_coop<NP, VWM>() && (tiled ? share : agg_share_out(a, G, U, bytes));
         const int64_t ipc = b.coop_waves == 1 ? 4 : 1;   // items per cooperative workgroup
-        const bool coop = agg_coop<NP, VWM>() && agg_share_out(a, G, U, bytes);
         b.n_coop = coop ? (int)((a.n_long + ipc - 1) / ipc) : 0;
         const int64_t left = a.n_items > b.n_coop * ipc ? a.n_items - b.n_coop * ipc : 0;
-        const int64_t gi = (left + 4 * NG - 1) / (4 * NG), gx = b.n_coop + gi;
+        const int64_t gi = (left + 4 * NG - 1) / (4 * NG), gb = b.n_coop + gi;
+        b.n_blocks = (int)gb;
         b.xcd_run = agg_xcd_run(gi);
+        const int S = 1 << b.slices_lg;
+        const int64_t gx = S > 1 ? (gb + 8 / S - 1) / (8 / S) * 8 : gb;
         const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
         gt_trace_variant(tr, V, G, NP, U, VWM == VWM_NONE && a.mask != nullptr);
-        const dim3 grid((unsigned)gx, gy);
+        const dim3 grid((unsigned)gx, (tiles + S - 1) / S);
         // (narrow groups hold several ids per lane where items are shared out to 64 / G groups of four lanes)
         constexpr int MANY = NP == 1 && VWM == VWM_NONE ? agg_many_ids(G) : 1, MANY_COOP = G == 4 ? MANY : 1;
         if constexpr (VWM == VWM_NONE) {
@@ -596,7 +671,8 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
                     if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, true, MANY_COOP><<<grid, 256, 0, st>>>(b);
                     else k_aggregate<T, V, G, NP, U, VWM, false, SH, true, MANY_COOP><<<grid, 256, 0, st>>>(b);
                 }
-            } else if (MANY > 1 && agg_long_batches(a, G, bytes)) {
+            } else if (MANY > 1 && (
+                agg_long_batches(a, G, bytes))) {
                 if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, false, MANY><<<grid, 256, 0, st>>>(b);
                 else k_aggregate<T, V, G, NP, U, VWM, false, SH, false, MANY><<<grid, 256, 0, st>>>(b);
             } else {
@@ -611,7 +687,7 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
     }
     if (a.n_splits > 0 && !a.no_reduce) {
         const int64_t gx = (a.n_splits + 3) / 4;
-        k_reduce_partials<T, V, G, NP, SH><<<dim3((unsigned)gx, gy), 256, 0, st>>>(a);
+        k_reduce_partials<T, V, G, NP, SH><<<dim3((unsigned)gx, tiles), 256, 0, st>>>(a);
         GT_LAUNCH_CHECK("k_reduce_partials");
     }
     return GT_OK;
@@ -619,14 +695,17 @@ gt_status launch(const AggArgs &a, hipStream_t st) {
 
 // Row loads kept in flight per lane.  Measured on MI355X: two are enough (and best) once the gathered table lives in HBM (2^18
 // vertices, 134 MB, 512-byte rows: 503 us, with four 527); rows of up to 256 bytes of a table that fits the last-level cache gain from
-// eight.  Wider ones only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
+// eight on skewed graphs, whose long rows are chains.  On uniform ones the L2s lose what eight spread (us, two / eight: 131 K rows, 3.3 M
+// edges, 64 fp32 columns 97 / 112, 47 bf16 columns 48 / 63; 300 K rows, 6 M edges, 12 fp32 columns 78 / 100), as long as a group has
+// a batch of ids to walk (G = 8, 66 K rows, 1 M edges, 32 fp32 columns 17.1 / 16.0).  Wider ones only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
 // 128 fp32 columns: 95 us with two, 42 with eight and items shared out); elsewhere eight spread the rows that the
 // resident groups read at a time, and the L2s lose them (uniform graphs, 128 fp32 columns: 65,536 vertices of degree 16
 // 68 us, with eight 73; degree 130, 4 M edges 87 and 174).
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
     if constexpr (NP == 1 && VWM == VWM_NONE) {
-        const bool eight = G <= 16 ? a.table_bytes <= ((int64_t)96 << 20)
+        const bool two = V > 1 && !agg_skewed(a) && (G == 16 || agg_long_batches(a, G, agg_bytes<T>(a)));
+        const bool eight = G <= 16 ? a.table_bytes <= ((int64_t)96 << 20) && !two
                                    : agg_share_out(a, G, 8, agg_bytes<T>(a)) && a.table_bytes <= ((int64_t)32 << 20);
         if (eight) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
     }
@@ -647,6 +726,12 @@ gt_status dispatch(const AggArgs &a, hipStream_t st) {
     }
     if constexpr (V == 1) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
     if (nvec <= 16) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
+    if constexpr (VWM == VWM_NONE) {
+        const AggTiles t = agg_tiles(a, nvec, sizeof(T), agg_bytes<T>(a));
+        if (t.G == 32) return launch<T, V, 32, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);
+        if (t.G == 16 && t.U == 8) return launch<T, V, 16, 1, 8, VWM, SH>(a, st, true, t.slices_lg, t.share);
+        if (t.G == 16) return launch<T, V, 16, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);
+    }
     if (nvec <= 32) return launch_u<T, V, 32, 1, VWM, SH>(a, st);
     if (nvec <= 64) return launch_u<T, V, 64, 1, VWM, SH>(a, st);
     if (nvec <= 128) return launch_u<T, V, 64, 2, VWM, SH>(a, st);

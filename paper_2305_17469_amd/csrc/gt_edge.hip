@@ -36,7 +36,7 @@ enum { EO_MUL = 0, EO_BCAST = 1 };
 
 // SH: rows without 16-byte alignment, see agg_col
 template <bool SH, int V>
-__device__ inline int64_t edge_col(const EdgeArgs &a, int64_t own) { return SH && own > a.F - V ? a.F - V : own; }
+__device__ inline int64_t edge_col(const EdgeArgs &a, int64_t own) { return agg_col<SH, V>(a.F, own); }
 
 // W[e, :] = s_r * R[r, :] (.) X[nbr[e], :]   (EO_MUL)   or   s_r * R[r, :]   (EO_BCAST)
 template <typename T, int V, int G, int NP, int MODE, bool SH>
@@ -44,7 +44,7 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gl = lane & (G - 1), grp = lane / G;
-    const int64_t item_id = (agg_item_block(a.xcd_run) * 4 + wave) * NG + grp;
+    const int64_t item_id = ((int64_t)agg_item_block(gridDim.y == 1 ? a.xcd_run : 1, blockIdx.x, gridDim.x, 3) * 4 + wave) * NG + grp;
     if (item_id >= a.n_items) return;
     const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
     const int row = raw.x, e0 = raw.y, e1 = raw.z;
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gl = lane & (G - 1), grp = lane / G;
-    const int64_t item_id = (agg_item_block(a.xcd_run) * 4 + wave) * NG + grp;
+    const int64_t item_id = ((int64_t)agg_item_block(gridDim.y == 1 ? a.xcd_run : 1, blockIdx.x, gridDim.x, 3) * 4 + wave) * NG + grp;
     if (item_id >= a.n_items) return;
     const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
     const int row = raw.x, e0 = raw.y, e1 = raw.z;
