@@ -29,7 +29,9 @@ struct EdgeArgs {
     int64_t ldw;
     int64_t F;
     int xcd_run;          // item blocks per XCD run (set at launch)
-    int skewed;              // host-side: see agg_skewed
+    int skewed;           // host-side: see agg_skewed
+    int64_t n_long;       // host-side: the first n_long items are long ones
+    int64_t n_cut;        // set at launch: the first n_cut items are cut into EDGE_CUT work items each
 };
 
 enum { EO_MUL = 0, EO_BCAST = 1 };
@@ -38,16 +40,33 @@ enum { EO_MUL = 0, EO_BCAST = 1 };
 template <bool SH, int V>
 __device__ inline int64_t edge_col(const EdgeArgs &a, int64_t own) { return agg_col<SH, V>(a.F, own); }
 
+// The row and the entries of this group's work item.  An entry's result depends on no other entry, so long items may be cut into
+// EDGE_CUT parts (whole batches of G entries), each of them a work item: on skewed graphs the longest items' chains outlast the
+// rest (dot product and scaled aggregation, both derivatives, power law, 900 K edges, 24 bf16 columns 248 -> 150 us; 1.5 M edges, 60 columns 331 -> 253).
+constexpr int EDGE_CUT = 4;
+template <int G>
+__device__ inline bool edge_item(const EdgeArgs &a, int run, int grp, int wave, int &row, int &e0, int &e1) {
+    const int64_t v = ((int64_t)agg_item_block(run, blockIdx.x, gridDim.x, 3) * 4 + wave) * (64 / G) + grp;
+    const bool cut = v < a.n_cut * EDGE_CUT;
+    const int64_t id = cut ? v / EDGE_CUT : v - a.n_cut * (EDGE_CUT - 1);
+    if (id >= a.n_items) return false;
+    const int4 raw = reinterpret_cast<const int4 *>(a.items)[id];
+    row = raw.x; e0 = raw.y; e1 = raw.z;
+    if (cut) {
+        const int per = ((e1 - e0 + EDGE_CUT - 1) / EDGE_CUT + G - 1) / G * G, part = (int)(v % EDGE_CUT);
+        e0 += part * per;
+        e1 = e0 + per < e1 ? e0 + per : e1;
+    }
+    return e0 < e1;
+}
+
 // W[e, :] = s_r * R[r, :] (.) X[nbr[e], :]   (EO_MUL)   or   s_r * R[r, :]   (EO_BCAST)
 template <typename T, int V, int G, int NP, int MODE, bool SH>
 __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
-    constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gl = lane & (G - 1), grp = lane / G;
-    const int64_t item_id = ((int64_t)agg_item_block(gridDim.y == 1 ? a.xcd_run : 1, blockIdx.x, gridDim.x, 3) * 4 + wave) * NG + grp;
-    if (item_id >= a.n_items) return;
-    const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
-    const int row = raw.x, e0 = raw.y, e1 = raw.z;
+    int row, e0, e1;
+    if (!edge_item<G>(a, gridDim.y == 1 ? a.xcd_run : 1, grp, wave, row, e0, e1)) return;
     const int64_t col0 = (int64_t)blockIdx.y * (G * V * NP);
     const T *X = static_cast<const T *>(a.X);
     const T *R = static_cast<const T *>(a.R) + (int64_t)row * a.ldr;
@@ -71,23 +90,23 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
     constexpr int U = NP == 1 ? (G >= 8 && V > 1 ? 8 : 4) : 2;
     int idx = 0, idx_next = 0;
     auto fetch = [&](int e) { return MODE == EO_MUL && e < e1 ? a.nbr[e] : 0; };
-    auto load = [&](raw_t (&v)[U][NP], int j, int left) {   // entries j .. j + U - 1 of the current ids
+    // entries j .. j + U - 1 of the current ids (branch free: one past the end stands for row 0 and is not stored)
+    auto load = [&](raw_t (&v)[U][NP], int j) {
+        int src[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) src[u] = __shfl(idx, (j + u) & (G - 1), G);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int src = __shfl(idx, (j + u) & (G - 1), G);
-            const T *xr = X + (int64_t)src * a.ldx;
+            const T *xr = X + (int64_t)src[u] * a.ldx;
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int64_t own = col0 + (int64_t)(p * G + gl) * V;
-                if (u < left && own < a.F) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, own));
-            }
+            for (int p = 0; p < NP; ++p) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, col0 + (int64_t)(p * G + gl) * V));
         }
     };
     raw_t v[U][NP];
     if constexpr (MODE == EO_MUL) {
         idx = fetch(e0 + gl);
         idx_next = fetch(e0 + G + gl);
-        load(v, 0, e1 - e0);
+        load(v, 0);
     }
     for (int e = e0; e < e1; e += U) {
         raw_t nx[U][NP];
@@ -98,7 +117,7 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
                     idx = idx_next;
                     idx_next = fetch(e + U + G + gl);
                 }
-                load(nx, jn, e1 - e - U);
+                load(nx, jn);
             }
         }
 #pragma unroll
@@ -151,16 +170,38 @@ __device__ inline float group_sum(float x) {
     return x;
 }
 
-// w[e] = s_r * <R[r, :], X[nbr[e], :]>   (all columns inside one column tile).  U: row loads in flight per lane
-template <typename T, int V, int G, int NP, bool SH, int U>
+// The elements of a raw vector that take part in a dot product: all ones or all zeros per element, so that a masked vector adds exact
+// zeros whatever the row's padding holds
+template <int V>
+__device__ inline uint4 dot_mask(int64_t col, int64_t own, int64_t F) {
+    uint32_t m[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if constexpr (V == 4) {
+            m[q] = col + q >= own && col + q < F ? ~0u : 0u;
+        } else {
+            m[q] = (col + 2 * q >= own && col + 2 * q < F ? 0xffffu : 0u) | (col + 2 * q + 1 >= own && col + 2 * q + 1 < F ? 0xffff0000u : 0u);
+        }
+    }
+    return make_uint4(m[0], m[1], m[2], m[3]);
+}
+__device__ inline float4 mask_raw(const float4 &v, const uint4 &m) {
+    return make_float4(__uint_as_float(__float_as_uint(v.x) & m.x), __uint_as_float(__float_as_uint(v.y) & m.y),
+                       __uint_as_float(__float_as_uint(v.z) & m.z), __uint_as_float(__float_as_uint(v.w) & m.w));
+}
+__device__ inline uint4 mask_raw(const uint4 &v, const uint4 &m) { return make_uint4(v.x & m.x, v.y & m.y, v.z & m.z, v.w & m.w); }
+__device__ inline float mask_raw(const float &v, const uint4 &m) { return __uint_as_float(__float_as_uint(v) & m.x); }
+__device__ inline bf16_t mask_raw(const bf16_t &v, const uint4 &m) { return v & (bf16_t)m.x; }
+
+// w[e] = s_r * <R[r, :], X[nbr[e], :]>   (all columns inside one column tile).  U: row loads in flight per lane.  WIDE: rows of more
+// than one column tile are walked tile by tile, the row operand read again per tile and batch; otherwise it stays in registers
+// (read per batch, it was a round trip in front of every batch's rows; power law, 8.4 M edges, 128 bf16 columns 216 -> 177 us).
+template <typename T, int V, int G, int NP, bool SH, int U, bool WIDE>
 __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
-    constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gl = lane & (G - 1), grp = lane / G;
-    const int64_t item_id = ((int64_t)agg_item_block(gridDim.y == 1 ? a.xcd_run : 1, blockIdx.x, gridDim.x, 3) * 4 + wave) * NG + grp;
-    if (item_id >= a.n_items) return;
-    const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
-    const int row = raw.x, e0 = raw.y, e1 = raw.z;
+    int row, e0, e1;
+    if (!edge_item<G>(a, a.xcd_run, grp, wave, row, e0, e1)) return;
     const T *X = static_cast<const T *>(a.X);
     const T *R = static_cast<const T *>(a.R) + (int64_t)row * a.ldr;
     float *W = static_cast<float *>(a.W);
@@ -168,49 +209,50 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
 
     const float s = a.rscale ? a.rscale[row] : 1.0f;
     constexpr int TILE = G * V * NP;
+    raw_t r[NP];
+    uint4 m[NP];
+    int64_t col[NP];
+    auto tile = [&](int64_t c0) {   // this lane's columns of the tile at c0: which of them count, and the row operand
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int64_t own = c0 + (int64_t)(p * G + gl) * V;
+            col[p] = edge_col<SH, V>(a, own);
+            if constexpr (V == 1) m[p].x = own < a.F ? ~0u : 0u;
+            else m[p] = dot_mask<V>(col[p], own, a.F);
+            r[p] = mask_raw(load_raw<T, V>(R + col[p]), m[p]);
+        }
+    };
+    if (!WIDE && a.F > 0) tile(0);
     int idx_next = e0 + gl < e1 ? a.nbr[e0 + gl] : 0;
     for (int base = e0; base < e1; base += G) {
         const int idx = idx_next;
         idx_next = base + G + gl < e1 ? a.nbr[base + G + gl] : 0;   // requested before this batch's rows are used
         const int cnt = (e1 - base) < G ? (e1 - base) : G;
         float mine = 0.0f;   // lane gl keeps the result of edge base + gl
-        // rows wider than one column tile are walked tile by tile; the row operand is re-read per
-        // tile (it stays in the vector cache), the common single-tile case reads it once per batch
-        for (int64_t c0 = 0; c0 < a.F; c0 += TILE) {
-            float r[NP][V];
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int64_t own = c0 + (int64_t)(p * G + gl) * V;
-                raw_t rv = raw_t{};
-                if (own < a.F) rv = load_raw<T, V>(R + edge_col<SH, V>(a, own));
-                unpack_raw(rv, r[p]);
-            }
+        for (int64_t c0 = 0; c0 < (WIDE ? a.F : a.F > 0 ? 1 : 0); c0 += TILE) {
+            if constexpr (WIDE) tile(c0);
             for (int j = 0; j < cnt; j += U) {
+                // (branch free: an entry past the end stands for row 0 and its product is not kept)
+                int src[U];
                 raw_t v[U][NP];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int jj = j + u;
-                    const int src = __shfl(idx, jj & (G - 1), G);
-                    const T *xr = X + (int64_t)src * a.ldx;
+                for (int u = 0; u < U; ++u) src[u] = __shfl(idx, (j + u) & (G - 1), G);
 #pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        const int64_t own = c0 + (int64_t)(p * G + gl) * V;
-                        v[u][p] = raw_t{};
-                        if (jj < cnt && own < a.F) v[u][p] = load_raw<T, V>(xr + edge_col<SH, V>(a, own));
-                    }
+                for (int u = 0; u < U; ++u) {
+                    const T *xr = X + (int64_t)src[u] * a.ldx;
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) v[u][p] = load_raw<T, V>(xr + col[p]);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     float part = 0.0f;
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
-                        float x[V];
-                        unpack_raw(v[u][p], x);
-                        const int64_t own = c0 + (int64_t)(p * G + gl) * V, col = edge_col<SH, V>(a, own);
+                        float x[V], y[V];
+                        unpack_raw(mask_raw(v[u][p], m[p]), x);
+                        unpack_raw(r[p], y);
 #pragma unroll
-                        for (int i = 0; i < V; ++i)   // padding elements of the last vector may hold anything, and a
-                                                      // shifted vector starts with its neighbour's columns
-                            part += (col + i < a.F && col + i >= own) ? r[p][i] * x[i] : 0.0f;
+                        for (int i = 0; i < V; ++i) part = fmaf(y[i], x[i], part);
                     }
                     part = group_sum<G>(part);
                     if (gl == ((j + u) & (G - 1))) mine += part;
@@ -227,19 +269,28 @@ gt_status launch_edge(const EdgeArgs &a, int kind, hipStream_t st) {
     if (a.n_items <= 0) return GT_OK;
     const int64_t tile = (int64_t)G * V * NP;
     const unsigned gy = kind == 2 ? 1u : (unsigned)((a.F + tile - 1) / tile);
-    const int64_t gx = (a.n_items + 4 * NG - 1) / (4 * NG);
-    const dim3 grid((unsigned)gx, gy);
     EdgeArgs b = a;
+    b.n_cut = a.skewed ? a.n_long : 0;
+    const int64_t gx = (a.n_items + b.n_cut * (EDGE_CUT - 1) + 4 * NG - 1) / (4 * NG);
+    const dim3 grid((unsigned)gx, gy);
     b.xcd_run = agg_xcd_run(gx);
     if (kind == 0) k_edge_out<T, V, G, NP, EO_MUL, SH><<<grid, 256, 0, st>>>(b);
     else if (kind == 1) k_edge_out<T, V, G, NP, EO_BCAST, SH><<<grid, 256, 0, st>>>(b);
     else {
         // Many rows in flight hide the chain of a long row; where there is none, two do, and keep the rows that are read at a time
         // in the L2s (us, two / eight: power law, 4 M edges, 64 fp32 columns 153 / 108; uniform, 2 M edges of degree 6, 128 bf16
-        // columns 81 / 86, 7.5 M edges, 40 bf16 columns 203 / 217)
-        constexpr int MANY = NP == 1 ? (G >= 8 ? 8 : 4) : 2;
-        if (a.skewed) k_edge_dot<T, V, G, NP, SH, MANY><<<grid, 256, 0, st>>>(b);
-        else k_edge_dot<T, V, G, NP, SH, 2><<<grid, 256, 0, st>>>(b);
+        // columns 81 / 86, 7.5 M edges, 40 bf16 columns 203 / 217).  Rows of a whole or half a wavefront need fewer (both derivatives too,
+        // four / eight: 1.5 M edges, 151 fp32 columns 566 / 584; 2.4 M edges, 128 columns 868 / 900).
+        constexpr int MANY = NP == 1 ? (G == 8 || G == 16 ? 8 : 4) : 2;
+        if constexpr (NP == 4) {   // (the widest shape also walks what is wider still)
+            if (a.F > tile) {
+                k_edge_dot<T, V, G, NP, SH, 2, true><<<grid, 256, 0, st>>>(b);
+                GT_LAUNCH_CHECK("k_edge");
+                return GT_OK;
+            }
+        }
+        if (a.skewed) k_edge_dot<T, V, G, NP, SH, MANY, false><<<grid, 256, 0, st>>>(b);
+        else k_edge_dot<T, V, G, NP, SH, 2, false><<<grid, 256, 0, st>>>(b);
     }
     GT_LAUNCH_CHECK("k_edge");
     return GT_OK;
@@ -272,6 +323,7 @@ gt_status run_edge(const gt_graph *g, int kind, gt_dtype t, int64_t F, const voi
     a.R = R; a.ldr = ldr; a.rscale = rscale; a.X = X; a.ldx = ldx; a.W = W; a.ldw = ldw; a.F = F;
     const bool vec = vec_ok(t, R, ldr) && vec_ok(t, X, ldx) && (kind == 2 || vec_ok(t, W, ldw));
     const int ve = t == GT_F32 ? 4 : 8;
+    a.n_long = g->fwd.n_long;
     a.skewed = agg_skewed(g->fwd.n_splits, g->fwd.n_long, g->fwd.n_items);
     // Narrow rows without alignment: element by element, whose neighbouring lanes share a line, where two to four lanes with shifted
     // vectors per edge leave most of a wavefront's loads idle (us, vectors / elements: 7.5 M uniform edges, 13 fp32 columns, product 301 / 245,
