@@ -118,8 +118,9 @@ __device__ inline void unpack_raw(const uint4 &v, float (&o)[8]) {
 __device__ inline void unpack_raw(const bf16_t &v, float (&o)[1]) { o[0] = __uint_as_float((uint32_t)v << 16); }
 
 // Vector-weight modes of the gather (paper: the function h that transforms the source embedding
-// with the edge weight before the aggregation): 1: acc += c * (x + w),  2: acc += c * (x * w)
-enum { VWM_NONE = 0, VWM_ADD = 1, VWM_MUL = 2 };
+// with the edge weight before the aggregation): 1: acc += c * (x + w),  2: acc += c * (x * w); VWM_NT beside either: the weights are
+// streamed past the caches (see edge_streams)
+enum { VWM_NONE = 0, VWM_ADD = 1, VWM_MUL = 2, VWM_NT = 4 };
 template <int VWM, int V, typename RawT>
 __device__ inline void fma_vw(float (&acc)[V], float c, const RawT &x, const RawT &w) {
     float xf[V], wf[V];
@@ -127,7 +128,7 @@ __device__ inline void fma_vw(float (&acc)[V], float c, const RawT &x, const Raw
     unpack_raw(w, wf);
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-        const float t = (VWM == VWM_ADD) ? xf[i] + wf[i] : xf[i] * wf[i];
+        const float t = ((VWM & 3) == VWM_ADD) ? xf[i] + wf[i] : xf[i] * wf[i];
         acc[i] = fmaf(c, t, acc[i]);
     }
 }
@@ -167,6 +168,28 @@ __device__ inline void store_vec<bf16_t, 8>(bf16_t *p, const float (&v)[8], int 
 template <>
 __device__ inline void store_vec<bf16_t, 1>(bf16_t *p, const float (&v)[1], int n) {
     if (n > 0) p[0] = (bf16_t)f32_to_bf16(v[0]);
+}
+
+// The same for data that is read or written once per launch and is larger than the caches (see edge_streams): it leaves the rows
+// that are gathered beside it in them.  Aligned whole vectors.
+typedef uint32_t nt_vec __attribute__((ext_vector_type(4)));
+template <typename T, int V>
+__device__ inline void store_vec_nt(T *p, const float (&v)[V], int n) {
+    if (n < V) {
+        store_vec<T, V>(p, v, n);
+        return;
+    }
+    nt_vec o;
+    if constexpr (V == 4) o = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    else o = {gt_pack_bf16(v[0], v[1]), gt_pack_bf16(v[2], v[3]), gt_pack_bf16(v[4], v[5]), gt_pack_bf16(v[6], v[7])};
+    __builtin_nontemporal_store(o, reinterpret_cast<nt_vec *>(p));
+}
+template <typename T, int V>
+__device__ inline typename Raw<T, V>::type load_raw_nt(const T *p) {
+    const nt_vec o = __builtin_nontemporal_load(reinterpret_cast<const nt_vec *>(p));
+    typename Raw<T, V>::type r;
+    __builtin_memcpy(&r, &o, sizeof(r));
+    return r;
 }
 
 // SH: rows without 16-byte alignment.  The lane that holds a row's ragged end takes the row's last V columns instead of
@@ -406,7 +429,11 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
                     if (live) v[u][p] = load_raw<T, V>(xr + col);
                     if constexpr (VWM != VWM_NONE) {
                         if constexpr (!ALL) w[u][p] = raw_t{};
-                        if (live) w[u][p] = load_raw<T, V>(VWp + (int64_t)we[u] * a.ldvw + col);
+                        if (live) {
+                            const T *wr = VWp + (int64_t)we[u] * a.ldvw + col;
+                            if constexpr ((VWM & VWM_NT) != 0) w[u][p] = load_raw_nt<T, V>(wr);
+                            else w[u][p] = load_raw<T, V>(wr);
+                        }
                     }
                 }
             }
@@ -419,8 +446,9 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
                 }
         };
         // (two rows in flight: a remainder step of its own costs nothing.  With eight it is a round trip more for every batch that is no
-        // multiple of eight: power law, 1.5 M edges, 280 bf16 columns shared out, 99 us without it, 126 with it.)
-        constexpr bool BY_ALL = U == 2 && VWM == VWM_NONE;
+        // multiple of eight: power law, 1.5 M edges, 280 bf16 columns shared out, 99 us without it, 126 with it; with weights' vectors beside
+        // the rows it pays all the same, 4.2 M edges, 64 fp32 columns, 1254 and 1220.)
+                constexpr bool BY_ALL = U == 2 || VWM != VWM_NONE;
         if constexpr (IPL == 1) {
             int j = 0;
             if constexpr (BY_ALL)

@@ -30,6 +30,7 @@ struct EdgeArgs {
     int64_t F;
     int xcd_run;          // item blocks per XCD run (set at launch)
     int skewed;           // host-side: see agg_skewed
+    int stream;           // host-side: see edge_streams
     int64_t n_long;       // host-side: the first n_long items are long ones
     int64_t n_cut;        // set at launch: the first n_cut items are cut into EDGE_CUT work items each
 };
@@ -60,8 +61,8 @@ __device__ inline bool edge_item(const EdgeArgs &a, int run, int grp, int wave, 
     return e0 < e1;
 }
 
-// W[e, :] = s_r * R[r, :] (.) X[nbr[e], :]   (EO_MUL)   or   s_r * R[r, :]   (EO_BCAST)
-template <typename T, int V, int G, int NP, int MODE, bool SH>
+// W[e, :] = s_r * R[r, :] (.) X[nbr[e], :]   (EO_MUL)   or   s_r * R[r, :]   (EO_BCAST).  NT: W is streamed past the caches
+template <typename T, int V, int G, int NP, int MODE, bool SH, bool NT>
 __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gl = lane & (G - 1), grp = lane / G;
@@ -140,7 +141,8 @@ __global__ void __launch_bounds__(256) k_edge_out(const EdgeArgs a) {
 #pragma unroll
                     for (int i = 0; i < V; ++i) o[i] = r[p][i];
                 }
-                store_vec<T, V>(wr + col, o, n);
+                if constexpr (NT) store_vec_nt<T, V>(wr + col, o, n);
+                else store_vec<T, V>(wr + col, o, n);
             }
         }
         if constexpr (MODE == EO_MUL) {
@@ -274,8 +276,16 @@ gt_status launch_edge(const EdgeArgs &a, int kind, hipStream_t st) {
     const int64_t gx = (a.n_items + b.n_cut * (EDGE_CUT - 1) + 4 * NG - 1) / (4 * NG);
     const dim3 grid((unsigned)gx, gy);
     b.xcd_run = agg_xcd_run(gx);
-    if (kind == 0) k_edge_out<T, V, G, NP, EO_MUL, SH><<<grid, 256, 0, st>>>(b);
-    else if (kind == 1) k_edge_out<T, V, G, NP, EO_BCAST, SH><<<grid, 256, 0, st>>>(b);
+    if constexpr (V > 1 && !SH) {
+        if (kind < 2 && a.stream) {
+            if (kind == 0) k_edge_out<T, V, G, NP, EO_MUL, SH, true><<<grid, 256, 0, st>>>(b);
+            else k_edge_out<T, V, G, NP, EO_BCAST, SH, true><<<grid, 256, 0, st>>>(b);
+            GT_LAUNCH_CHECK("k_edge");
+            return GT_OK;
+        }
+    }
+    if (kind == 0) k_edge_out<T, V, G, NP, EO_MUL, SH, false><<<grid, 256, 0, st>>>(b);
+    else if (kind == 1) k_edge_out<T, V, G, NP, EO_BCAST, SH, false><<<grid, 256, 0, st>>>(b);
     else {
         // Many rows in flight hide the chain of a long row; where there is none, two do, and keep the rows that are read at a time
         // in the L2s (us, two / eight: power law, 4 M edges, 64 fp32 columns 153 / 108; uniform, 2 M edges of degree 6, 128 bf16
@@ -315,6 +325,17 @@ bool vec_ok(gt_dtype t, const void *p, int64_t ld) {
     return p == nullptr || (aligned16(p) && ld % ve == 0);
 }
 
+// Whether a tensor of one row per edge is streamed past the caches, which keeps the vertices' rows in them: from about 100 MB on, below
+// which its next reader finds it there (us, element-wise product and aggregation with all derivatives, plain / streamed: power
+// law, 64 fp32 columns, 1.07 GB 1497 / 1220, 154 MB 285 / 265, 77 MB 120 / 134; uniform, 128 MB 236 / 227), with rows of whole lines or, since a
+// line of two rows is then written twice, long ones for the writer (33 columns 1262 / 1486, 304-byte rows 1022 / 1067, 480-byte rows
+// 2839 / 2566), and with rows of a line or more for the reader (33 columns 508 / 548, 304-byte rows 1022 / 985).
+bool edge_streams(int64_t E, const void *W, int64_t ldw, gt_dtype t, bool vec, bool write) {
+    const int64_t row = ldw * (int64_t)gt_dtype_size(t);
+    if (!vec || row < 128 || E * row < ((int64_t)96 << 20)) return false;
+    return !write || row >= 400 || (row % 128 == 0 && ((uintptr_t)W & 127) == 0);
+}
+
 // kind: 0 edge-out product, 1 edge-out broadcast, 2 edge-dot
 gt_status run_edge(const gt_graph *g, int kind, gt_dtype t, int64_t F, const void *R, int64_t ldr, const float *rscale,
                    const void *X, int64_t ldx, void *W, int64_t ldw, hipStream_t st) {
@@ -322,6 +343,7 @@ gt_status run_edge(const gt_graph *g, int kind, gt_dtype t, int64_t F, const voi
     a.items = g->fwd.items; a.n_items = g->fwd.n_items; a.nbr = g->colidx;
     a.R = R; a.ldr = ldr; a.rscale = rscale; a.X = X; a.ldx = ldx; a.W = W; a.ldw = ldw; a.F = F;
     const bool vec = vec_ok(t, R, ldr) && vec_ok(t, X, ldx) && (kind == 2 || vec_ok(t, W, ldw));
+    a.stream = kind < 2 && edge_streams(g->n_edges, W, ldw, t, vec, true);
     const int ve = t == GT_F32 ? 4 : 8;
     a.n_long = g->fwd.n_long;
     a.skewed = agg_skewed(g->fwd.n_splits, g->fwd.n_long, g->fwd.n_items);
@@ -361,10 +383,14 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
                     (via_perm || (vwm == VWM_NONE && !agg_vectors_pay(a, (double)a.n_edges * (double)F * gt_dtype_size(t))));
     if (vwm == VWM_NONE) return gt_agg_launch(a, t, vec, st, el);
 #define GT_GATHER_EL(T_) (vwm == VWM_ADD ? dispatch<T_, 1, VWM_ADD>(a, st) : dispatch<T_, 1, VWM_MUL>(a, st))
+#define GT_GATHER_NT(T_)                                                                                                         \
+    (vwm == VWM_ADD ? dispatch<T_, 16 / (int)sizeof(T_), VWM_ADD | VWM_NT>(a, st) : dispatch<T_, 16 / (int)sizeof(T_), VWM_MUL | VWM_NT>(a, st))
+    if (edge_streams(g->n_edges, VW, ldvw, t, vec, false)) return t == GT_F32 ? GT_GATHER_NT(float) : GT_GATHER_NT(bf16_t);
 #define GT_GATHER(T_) (vwm == VWM_ADD ? agg_dispatch<T_, VWM_ADD>(a, vec, st) : agg_dispatch<T_, VWM_MUL>(a, vec, st))
     if (el) return t == GT_F32 ? GT_GATHER_EL(float) : GT_GATHER_EL(bf16_t);
     return t == GT_F32 ? GT_GATHER(float) : GT_GATHER(bf16_t);
 #undef GT_GATHER_EL
+#undef GT_GATHER_NT
 #undef GT_GATHER
 }
 

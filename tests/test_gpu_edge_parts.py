@@ -43,3 +43,41 @@ def test_parts(F, dtype):
     assert torch.equal(dw, w)   # the same products in the same order
     _, dw = B.gt_pull_bwd(g, "sum", "add", Xd, Xs, m)
     assert torch.equal(dw, Xd[dst])
+
+
+@pytest.mark.parametrize("dtype,F", [(torch.float32, 64), (torch.float32, 60), (torch.float32, 132), (torch.bfloat16, 128), (torch.bfloat16, 72),
+                                     (torch.bfloat16, 520)], ids=str)
+def test_streamed_edge_tensor(dtype, F):
+    """Edge tensors just below and above 96 MiB (the larger is streamed past the caches; 60 columns for the reader only):
+    the same edges give the same results bit for bit, and all are within (n + 2) 2^-24 sum |terms| and one bf16 rounding of 64 bits."""
+    from paper_2305_17469_amd import binding as B
+    es = 4 if dtype == torch.float32 else 2
+    n, E = 5000, (96 << 20) // (F * es) + 1000
+    rng = np.random.default_rng(F)
+    dst = torch.from_numpy(np.sort(rng.integers(0, n, E))).cuda()
+    src = torch.from_numpy(rng.integers(0, n, E)).cuda()
+    gen = torch.Generator(device="cuda:0").manual_seed(F)
+    Xs, Xd, dY = (torch.randn((n, F), device="cuda:0", generator=gen).to(dtype) for _ in range(3))
+
+    def graph(m):
+        rowptr = torch.zeros(n + 1, dtype=torch.int64, device="cuda:0")
+        rowptr[1:] = torch.cumsum(torch.bincount(dst[:m], minlength=n), 0)
+        return B.Graph(rowptr.int(), src[:m].int(), n)
+
+    big, less = graph(E), graph(E - 2000)
+    announce("streamed", dtype, F, E)
+    r = 2.0 ** -8 if dtype == torch.bfloat16 else 0.0
+    m = B.gt_neighbor_apply_fwd(big, "mul", Xs, Xd)
+    p = Xs.double()[src] * Xd.double()[dst]
+    assert bool(((m.double() - p).abs() <= (r or 2.0 ** -23) * p.abs() + 1e-38).all())
+    assert torch.equal(m[:E - 2000], B.gt_neighbor_apply_fwd(less, "mul", Xs, Xd))
+    cnt = torch.bincount(dst, minlength=n).double()[:, None]
+    kept = dst[E - 2000]   # rows before this one are the same in both graphs
+    for h in ("add", "mul"):
+        y = B.gt_pull_fwd(big, "sum", h, Xs, m)
+        t = Xs.double()[src] + m.double() if h == "add" else Xs.double()[src] * m.double()
+        ref, mag = (torch.zeros((n, F), dtype=torch.float64, device="cuda:0").index_add_(0, dst, x) for x in (t, t.abs()))
+        assert bool(((y.double() - ref).abs() <= (cnt + 2) * 2.0 ** -23 * mag + r * ref.abs()).all()), h
+        assert torch.equal(y[:kept], B.gt_pull_fwd(less, "sum", h, Xs, m[:E - 2000].contiguous())[:kept])
+    _, dw = B.gt_pull_bwd(big, "sum", "add", dY, Xs, m)
+    assert torch.equal(dw, dY[dst])
