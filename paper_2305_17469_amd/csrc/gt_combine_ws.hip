@@ -361,31 +361,38 @@ __global__ void __launch_bounds__((ws_waves<T, NB, NS>() * 64), (ws_per_cu<T, NB
                     *reinterpret_cast<uint4 *>(Ws + n * WSTR + k) = ws_mask<T>(v[u], ok ? (left < VE ? (int)left : VE) : 0);
             }
         }
-    } else if (g.vecB && g.vecA) {   // B[k][n]: a vector holds VE columns of one k, scattered to VE rows
-        // (rows of A without alignment take the element form below, whose LDS writes collide less: 40,000 x 47 -> 256 bf16 20.6 us
-        // this way, 13.8 by element)
-        constexpr int VPR = BN / VE, TOTAL = KP * VPR;
-        for (int base = threadIdx.x; base < TOTAL; base += NT * 8) {
-            uint4 v[8];
+    } else if (g.vecB) {   // B[k][n]: patches of four k and VE columns, transposed in registers
+        // (scattering a vector's columns to their rows one by one put the lanes of a wavefront on two banks: 256 x 256 bf16 weights took
+        // 25 us of a launch, 30,000 rows 40 -> 18 us.)  KQ patches along k per row of the LDS write, then along n: 64 bytes of a row of B.
+        constexpr int KQ = KP / 4 < 16 ? KP / 4 : 16, RQ = BN / VE, TOTAL = KP / 4 * RQ;
+        for (int base = threadIdx.x; base < TOTAL; base += NT * 2) {
+            uint4 v[2][4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 2; ++u) {
                 const int idx = base + u * NT;
-                const int k = idx / VPR, n = (idx % VPR) * VE;
-                const bool ok = idx < TOTAL && n0 + n < g.N && k < g.K;
-                v[u] = *reinterpret_cast<const uint4 *>(B + (ok ? (int64_t)k * g.ldb + n0 + n : 0));
+                const int n = idx / KQ % RQ * VE, k = (idx / KQ / RQ * KQ + idx % KQ) * 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool ok = idx < TOTAL && n0 + n < g.N && k + i < g.K;
+                    v[u][i] = *reinterpret_cast<const uint4 *>(B + (ok ? (int64_t)(k + i) * g.ldb + n0 + n : 0));
+                }
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 2; ++u) {
                 const int idx = base + u * NT;
-                const int k = idx / VPR, n = (idx % VPR) * VE;
-                const bool ok = n0 + n < g.N && k < g.K;
+                const int n = idx / KQ % RQ * VE, k = (idx / KQ / RQ * KQ + idx % KQ) * 4;
+                if (idx >= TOTAL) continue;
                 const int64_t left = g.N - (n0 + n);
-                const uint4 m = ws_mask<T>(v[u], ok ? (left < VE ? (int)left : VE) : 0);
-                T e[VE];
-                __builtin_memcpy(e, &m, 16);
-                if (idx < TOTAL) {
+                T e[4][VE];
 #pragma unroll
-                    for (int q = 0; q < VE; ++q) Ws[(n + q) * WSTR + k] = e[q];
+                for (int i = 0; i < 4; ++i) {
+                    const uint4 m = ws_mask<T>(v[u][i], left > 0 && k + i < g.K ? (left < VE ? (int)left : VE) : 0);
+                    __builtin_memcpy(e[i], &m, 16);
+                }
+#pragma unroll
+                for (int q = 0; q < VE; ++q) {
+                    const T col[4] = {e[0][q], e[1][q], e[2][q], e[3][q]};
+                    __builtin_memcpy(__builtin_assume_aligned(Ws + (n + q) * WSTR + k, 4 * sizeof(T)), col, 4 * sizeof(T));
                 }
             }
         }
@@ -547,7 +554,41 @@ __global__ void __launch_bounds__(256, (ws_x3_per_cu<NB, NS>())) k_gemm_ws_x3(co
     // the weight slice, once, as three planes: Wp[plane][n][k] = piece of op(B)(k, n0 + n), zero
     // outside (K, N).  A thread takes quads of four elements that are consecutive in memory, eight
     // quads in flight.
-    {
+    if (g.vecB && !transB) {   // B[k][n]: patches of four k and four columns, transposed in registers (see k_gemm_ws)
+        constexpr int KQ = KP / 4 < 16 ? KP / 4 : 16, RQ = BN / 4, TOTAL = KP / 4 * RQ;
+        for (int base = threadIdx.x; base < TOTAL; base += 256 * 2) {
+            float4 v[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int idx = base + u * 256;
+                const int n = idx / KQ % RQ * 4, k = (idx / KQ / RQ * KQ + idx % KQ) * 4;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool ok = idx < TOTAL && n0 + n < g.N && k + i < g.K;
+                    v[u][i] = *reinterpret_cast<const float4 *>(B + (ok ? (int64_t)(k + i) * g.ldb + n0 + n : 0));
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int idx = base + u * 256;
+                const int n = idx / KQ % RQ * 4, k = (idx / KQ / RQ * KQ + idx % KQ) * 4;
+                if (idx >= TOTAL) continue;
+                float x[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) __builtin_memcpy(x[i], &v[u][i], 16);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t hi[4], mi[4], lo[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) ws_split3(n0 + n + q < g.N && k + i < g.K ? x[i][q] : 0.0f, hi[i], mi[i], lo[i]);
+                    bf16_t *d = Wp + (n + q) * WSTR + k;
+                    *reinterpret_cast<uint2 *>(d) = make_uint2(ws_pack_hi16(hi[0], hi[1]), ws_pack_hi16(hi[2], hi[3]));
+                    *reinterpret_cast<uint2 *>(d + PLANE) = make_uint2(ws_pack_hi16(mi[0], mi[1]), ws_pack_hi16(mi[2], mi[3]));
+                    *reinterpret_cast<uint2 *>(d + 2 * PLANE) = make_uint2(ws_pack_hi16(lo[0], lo[1]), ws_pack_hi16(lo[2], lo[3]));
+                }
+            }
+        }
+    } else {
         constexpr int TOTAL = BN * KP / 4;
         for (int base = threadIdx.x; base < TOTAL; base += 256 * 8) {
             float4 v[8];
