@@ -725,14 +725,15 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
 // vertices, 134 MB, 512-byte rows: 503 us, with four 527); rows of up to 256 bytes of a table that fits the last-level cache gain from
 // eight on skewed graphs, whose long rows are chains.  On uniform ones the L2s lose what eight spread (us, two / eight: 131 K rows, 3.3 M
 // edges, 64 fp32 columns 97 / 112, 47 bf16 columns 48 / 63; 300 K rows, 6 M edges, 12 fp32 columns 78 / 100), as long as a group has
-// a batch of ids to walk (G = 8, 66 K rows, 1 M edges, 32 fp32 columns 17.1 / 16.0).  Wider ones only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
+// a batch of ids to walk (G = 8, 66 K rows, 1 M edges, 32 fp32 columns 17.1 / 16.0) and the launch fills the chip (a sampled block of 300 rows,
+// 64 fp32 columns 9.3 / 7.5).  Wider ones only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
 // 128 fp32 columns: 95 us with two, 42 with eight and items shared out); elsewhere eight spread the rows that the
 // resident groups read at a time, and the L2s lose them (uniform graphs, 128 fp32 columns: 65,536 vertices of degree 16
 // 68 us, with eight 73; degree 130, 4 M edges 87 and 174).
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
     if constexpr (NP == 1 && VWM == VWM_NONE) {
-        const bool two = V > 1 && !agg_skewed(a) && (G == 16 || agg_long_batches(a, G, agg_bytes<T>(a)));
+        const bool two = V > 1 && !agg_skewed(a) && a.n_items * G > 1792 * 64 && (G == 16 || agg_long_batches(a, G, agg_bytes<T>(a)));
         const bool eight = G <= 16 ? a.table_bytes <= ((int64_t)96 << 20) && !two
                                    : agg_share_out(a, G, 8, agg_bytes<T>(a)) && a.table_bytes <= ((int64_t)32 << 20);
         if (eight) return launch<T, V, G, NP, 8, VWM, SH>(a, st);

@@ -278,6 +278,7 @@ extern "C" gt_status gt_reindex(const int32_t *dst, int64_t n_dst, const int32_t
     const uint32_t *vin = nullptr;   // first pass: value = position
     SortPasses sp{};
     sp.passes = passes;
+    sp.bits = 8 * passes;   // (whole bytes: ids at or past n_vertices stay in order as far as these reach)
     for (int p = 0; p < passes; ++p) {
         sp.kin[p] = kA; sp.vin[p] = vin; sp.kout[p] = kB; sp.vout[p] = vB;
         uint32_t *t = kA; kA = kB; kB = t;

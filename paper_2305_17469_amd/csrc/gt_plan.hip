@@ -62,25 +62,6 @@ namespace {
 constexpr int PT = 256;
 inline unsigned nblocks(int64_t n, int per = PT) { return (unsigned)((n + per - 1) / per); }
 
-// rowptr_t from the sorted source keys: rowptr_t[u] = first position whose key >= u.
-__global__ void k_boundaries(const uint32_t *skeys, int64_t E, int64_t n_src, int32_t *rowptr_t) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k > E) return;
-    // position k closes the gap (key[k-1], key[k]]; k == E closes (key[E-1], n_src]
-    int64_t lo = (k == 0) ? -1 : (int64_t)skeys[k - 1];
-    const int64_t hi = (k == E) ? n_src : (int64_t)skeys[k];
-    // short gaps by their own thread, long ones (runs of vertices without out-edges) by all lanes that are here
-    const uint64_t here = __ballot(1), all = __ballot(hi - lo > 4);
-    const int lane = threadIdx.x & 63, lanes = __popcll(here), mine = __popcll(here & ((1ull << lane) - 1));
-    if (hi - lo <= 4)
-        for (int64_t u = lo + 1; u <= hi; ++u) rowptr_t[u] = (int32_t)k;
-    for (uint64_t m = all; m; m &= m - 1) {
-        const int l = __ffsll((unsigned long long)m) - 1;
-        const int64_t a = __shfl(lo, l), b = __shfl(hi, l), kk = __shfl(k, l);
-        for (int64_t u = a + 1 + mine; u <= b; u += lanes) rowptr_t[u] = (int32_t)kk;
-    }
-}
-
 // Row of every entry of a CSR, written coalesced, and (square graphs) the symmetric-norm coefficient
 // w_e / sqrt(d(src) d(dst)) of every entry in the given order.  A workgroup takes ROWS_TILE consecutive entries: it finds the
 // row of its first entry by a 64-way search, marks in LDS where the rows of its range begin, and fills in between with a running
@@ -169,38 +150,88 @@ __global__ void __launch_bounds__(PT) k_entry_rows(const int32_t *rowptr, int64_
     }
 }
 
-// Per transposed entry k (position e = perm[k] in the given CSR, source u = skeys[k]): its destination, its weight, and
-// the per-entry coefficients of the normalised reduce modes in this order:
+// rowptr_t from the sorted source keys (rowptr_t[u] = first position whose key >= u), and per transposed entry k (position e = perm[k] in
+// the given CSR, source u = skeys[k]): its destination, its weight, and the per-entry coefficients of the normalised reduce modes in this order:
 //   symmetric norm  w_e / sqrt(d(src) d(dst))   (coef_sym_b[k]; square graphs)
-//   mean, backward  w_e / indeg(dst)            (as bits in the place of the key, which its thread has read)
+//   mean, backward  w_e / indeg(dst)            (coef_mean_b[k])
 // row_of null: the destinations have travelled through the sort and are in colidx_t already (looking each one up by its
 // entry is a random 4-byte read from an array of E: 25 M entries 0.51 ms, carried along 0.28 ms more in the sort).
-__global__ void k_transposed_entries(const int32_t *perm, uint32_t *skeys, const int32_t *row_of, int64_t E, const float *ew,
-                                     const int32_t *in_deg, int square, int32_t *colidx_t, float *ew_t, float *coef_sym_b) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= E) return;
-    const uint32_t u = skeys[k];
-    int32_t v;
-    float w = 1.0f;
-    if (row_of) {
-        const int32_t e = perm[k];
-        v = row_of[e];
-        colidx_t[k] = v;
+// A thread has four consecutive entries (25 M entries, with the row ends, which had a launch of their own, 212 -> 186 us).
+__global__ void __launch_bounds__(PT) k_transposed_entries(const int32_t *perm, const uint32_t *skeys, const int32_t *row_of, int64_t E, int64_t n_src,
+                                                           const float *ew, const int32_t *in_deg, int square, int32_t *rowptr_t, int32_t *colidx_t,
+                                                           float *ew_t, float *coef_sym_b, float *coef_mean_b) {
+    const int lane = threadIdx.x & 63;
+    const int64_t k0 = ((int64_t)blockIdx.x * PT + threadIdx.x) * 4;
+    const bool whole = k0 + 4 <= E;   // (all arrays are aligned)
+    uint32_t u[4];
+    if (whole) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(skeys + k0);
+        u[0] = x.x; u[1] = x.y; u[2] = x.z; u[3] = x.w;
     } else {
-        v = colidx_t[k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = k0 + i < E ? skeys[k0 + i] : 0u;
+    }
+    // position k closes the gap (key[k-1], key[k]]; k == E closes (key[E-1], n_src].  Short gaps by their own thread, long ones (runs of
+    // vertices without out-edges) by the whole wavefront; lanes past E stay for the exchanges
+    int64_t lo = (int64_t)(uint32_t)__shfl_up((int)u[3], 1, 64);
+    if (k0 == 0) lo = -1;
+    else if (lane == 0 && k0 <= E) lo = skeys[k0 - 1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t k = k0 + i, hi = k < E ? (int64_t)u[i] : k == E ? n_src : lo;   // (past E: no gap)
+        if (hi - lo <= 4)
+            for (int64_t r = lo + 1; r <= hi; ++r) rowptr_t[r] = (int32_t)k;
+        for (uint64_t m = __ballot(hi - lo > 4); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const int64_t a = __shfl(lo, l), b = __shfl(hi, l), kk = __shfl(k, l);
+            for (int64_t r = a + 1 + lane; r <= b; r += 64) rowptr_t[r] = (int32_t)kk;
+        }
+        lo = hi;
+    }
+    if (k0 >= E) return;
+    int32_t v[4];
+    float w[4] = {1.0f, 1.0f, 1.0f, 1.0f}, cs[4], cm[4];
+    if (!row_of && whole) {
+        const int4 x = *reinterpret_cast<const int4 *>(colidx_t + k0);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = 0;
+            if (k0 + i >= E) continue;
+            v[i] = row_of ? row_of[perm[k0 + i]] : colidx_t[k0 + i];
+            if (row_of) colidx_t[k0 + i] = v[i];
+        }
     }
     if (ew_t) {
-        w = ew[perm[k]];
-        ew_t[k] = w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (k0 + i < E) ew_t[k0 + i] = w[i] = ew[perm[k0 + i]];
     }
     // (the reciprocals from the degree, as k_row_counts forms them: one gather per vertex instead of two)
-    const int32_t d = in_deg[v];
-    if (square) {
-        const int32_t du = in_deg[u];
-        const float iu = du > 0 ? 1.0f / sqrtf((float)du) : 0.0f, iv = d > 0 ? 1.0f / sqrtf((float)d) : 0.0f;
-        coef_sym_b[k] = (w * iu) * iv;
+    int32_t d[4], du[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        d[i] = in_deg[v[i]];
+        du[i] = square ? in_deg[u[i]] : 0;
     }
-    skeys[k] = __float_as_uint(w * (d > 0 ? 1.0f / (float)d : 0.0f));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float iu = du[i] > 0 ? 1.0f / sqrtf((float)du[i]) : 0.0f, iv = d[i] > 0 ? 1.0f / sqrtf((float)d[i]) : 0.0f;
+        cs[i] = (w[i] * iu) * iv;
+        cm[i] = w[i] * (d[i] > 0 ? 1.0f / (float)d[i] : 0.0f);
+    }
+    if (whole) {
+        if (square) *reinterpret_cast<float4 *>(coef_sym_b + k0) = make_float4(cs[0], cs[1], cs[2], cs[3]);
+        *reinterpret_cast<float4 *>(coef_mean_b + k0) = make_float4(cm[0], cm[1], cm[2], cm[3]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (k0 + i >= E) continue;
+            if (square) coef_sym_b[k0 + i] = cs[i];
+            coef_mean_b[k0 + i] = cm[i];
+        }
+    }
 }
 
 // per row: degree (with its reciprocal and reciprocal square root where wanted) and item / partial / split / long-item counts
@@ -337,7 +368,7 @@ struct PlanLayout {
     size_t ca2, cb2, cc2, cd2;           // the same for the transposed direction
     size_t items_tmp, item_keys, item_keys2, item_idx, item_idx2;   // unsorted items, sort keys / indices
     size_t k0, k1, v1, e1;               // sort ping-pong (E each), with perm and colidx_t as the other halves of v1 and e1;
-                                         // one of k0 / k1, and v1, hold coefficients afterwards
+                                         // one of k0 / k1 (not the sorted keys), and v1, hold coefficients afterwards
     size_t coef_f;                       // symmetric-norm coefficients of the given order
     size_t hist, scan_tmp;
     size_t total;
@@ -414,9 +445,9 @@ gt_status build_direction(const int32_t *rowptr, const int32_t *nbr, int64_t n_i
     GT_LAUNCH_CHECK("k_fill_items");
     if (!sorted) return GT_OK;
     SortTmp t{at<int32_t>(ws, L.hist), at<int32_t>(ws, L.scan_tmp)};
-    gt_status s = radix_pass(keys, nullptr, keys2, idx, n_items, 0, t, st);      // neighbour range
+    gt_status s = radix_pass(keys, nullptr, keys2, idx, n_items, 0, 8, t, st);      // neighbour range
     if (s != GT_OK) return s;
-    s = radix_pass(keys2, idx, keys, idx2, n_items, 8, t, st);                   // length class (stable)
+    s = radix_pass(keys2, idx, keys, idx2, n_items, 8, 8, t, st);                   // length class (stable)
     if (s != GT_OK) return s;
     k_gather_items<<<nblocks(n_items), PT, 0, st>>>(tmp, idx2, n_items, items_out);
     GT_LAUNCH_CHECK("k_gather_items");
@@ -505,6 +536,7 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
         const uint32_t *vin = nullptr, *ein = carry ? reinterpret_cast<const uint32_t *>(row_of) : nullptr;
         SortPasses sp{};
         sp.passes = passes;
+        sp.bits = bits;
         for (int p = 0; p < passes; ++p) {
             const int other = (passes - 1 - p) & 1;
             sp.kin[p] = kin; sp.vin[p] = vin; sp.ein[p] = ein;
@@ -515,19 +547,14 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
         }
         if ((s = radix_sort(sp, E, t, st)) != GT_OK) return fail(s);
     }
-    k_boundaries<<<nblocks(E + 1), PT, 0, st>>>(sorted_keys, E, n_src, g->rowptr_t);
-    PLAN_LAUNCH("k_boundaries");
+    // the sort's ping-pong buffers are dead from here on, except the sorted keys: v1 and the other key buffer hold coefficients
+    g->coef_sym_b = g->dinv && E > 0 ? reinterpret_cast<float *>(v1) : nullptr;
+    g->coef_mean_b = E > 0 ? reinterpret_cast<float *>(sorted_keys == k0 ? k1 : k0) : nullptr;
+    k_transposed_entries<<<nblocks(E + 1, 4 * PT), PT, 0, st>>>(g->perm, sorted_keys, carry ? nullptr : row_of, E, n_src, ew, g->in_deg, g->dinv ? 1 : 0,
+                                                                g->rowptr_t, g->colidx_t, g->ew_t, g->coef_sym_b, g->coef_mean_b);
+    PLAN_LAUNCH("k_transposed_entries");
     k_row_counts<<<nblocks(n_src + 1), PT, 0, st>>>(g->rowptr_t, n_src, chunk, long_min, g->out_deg, nullptr, nullptr, ca2, cb2, cc2, cd2);
     PLAN_LAUNCH("k_row_counts(out)");
-    if (E > 0) {
-        // the sort's ping-pong buffers are dead from here on, except the sorted keys (k0 or k1), which each entry's thread
-        // reads before it writes its mean coefficient in their place
-        g->coef_sym_b = g->dinv ? reinterpret_cast<float *>(v1) : nullptr;
-        g->coef_mean_b = reinterpret_cast<float *>(sorted_keys);
-        k_transposed_entries<<<nblocks(E), PT, 0, st>>>(g->perm, sorted_keys, carry ? nullptr : row_of, E, ew, g->in_deg, g->dinv ? 1 : 0,
-                                                        g->colidx_t, g->ew_t, g->coef_sym_b);
-        PLAN_LAUNCH("k_transposed_entries");
-    }
     // work-list sizes of both directions: the exclusive scans over n_rows + 1 entries (last input 0) leave the totals in element
     // n_rows; read back once
     int32_t *d_counts = at<int32_t>(ws, L.counts);

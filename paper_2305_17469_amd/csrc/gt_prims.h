@@ -48,17 +48,46 @@ __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
     return base + inc - v;
 }
 
+// SCAN_PER_THREAD consecutive elements from p0 on, zeros from n on (16-byte accesses where the array is aligned and they are all there:
+// element by element a wavefront's sixteen loads each touched 32 lines; the 3 x 1.5 M counts and 4 M row counts of a plan over 25 M entries 94 -> 31 us)
+__device__ inline void scan_load(const int32_t *in, int64_t p0, int64_t n, int32_t (&v)[SCAN_PER_THREAD]) {
+    if (((uintptr_t)in & 15) == 0 && p0 + SCAN_PER_THREAD <= n) {
+#pragma unroll
+        for (int i = 0; i < SCAN_PER_THREAD; i += 4) {
+            const int4 x = *reinterpret_cast<const int4 *>(in + p0 + i);
+            v[i] = x.x; v[i + 1] = x.y; v[i + 2] = x.z; v[i + 3] = x.w;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < SCAN_PER_THREAD; ++i) v[i] = p0 + i < n ? in[p0 + i] : 0;
+    }
+}
+__device__ inline void scan_store(int32_t *out, int64_t p0, int64_t n, int32_t ex, const int32_t (&v)[SCAN_PER_THREAD]) {
+    int32_t o[SCAN_PER_THREAD];
+#pragma unroll
+    for (int i = 0; i < SCAN_PER_THREAD; ++i) {
+        o[i] = ex;
+        ex += v[i];
+    }
+    if (((uintptr_t)out & 15) == 0 && p0 + SCAN_PER_THREAD <= n) {
+#pragma unroll
+        for (int i = 0; i < SCAN_PER_THREAD; i += 4) *reinterpret_cast<int4 *>(out + p0 + i) = make_int4(o[i], o[i + 1], o[i + 2], o[i + 3]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < SCAN_PER_THREAD; ++i)
+            if (p0 + i < n) out[p0 + i] = o[i];
+    }
+}
+
 // sums[tile] of array blockIdx.y
 __global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(const ScanBatch b) {
     const int k = blockIdx.y;
     const int64_t n = b.n[k], base = (int64_t)blockIdx.x * SCAN_TILE;
     if (base >= n) return;
-    int32_t s = 0;
+    int32_t v[SCAN_PER_THREAD], s = 0;
+    scan_load(b.in[k], base + (int64_t)threadIdx.x * SCAN_PER_THREAD, n, v);
 #pragma unroll
-    for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-        const int64_t p = base + i * SCAN_THREADS + threadIdx.x;
-        s += p < n ? b.in[k][p] : 0;
-    }
+    for (int i = 0; i < SCAN_PER_THREAD; ++i) s += v[i];
     int32_t total;
     block_exclusive_scan<SCAN_THREADS / 64>(s, &total);
     if (threadIdx.x == 0) b.sums[k][blockIdx.x] = total;
@@ -83,18 +112,12 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_apply(const ScanBatch b, 
     const int64_t p0 = base + (int64_t)threadIdx.x * SCAN_PER_THREAD;
     int32_t v[SCAN_PER_THREAD];
     int32_t s = 0;
+    scan_load(b.in[k], p0, n, v);
 #pragma unroll
-    for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-        v[i] = p0 + i < n ? b.in[k][p0 + i] : 0;
-        s += v[i];
-    }
+    for (int i = 0; i < SCAN_PER_THREAD; ++i) s += v[i];
     int32_t total;
-    int32_t ex = off + block_exclusive_scan<SCAN_THREADS / 64>(s, &total);
-#pragma unroll
-    for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-        if (p0 + i < n) b.out[k][p0 + i] = ex;
-        ex += v[i];
-    }
+    const int32_t ex = off + block_exclusive_scan<SCAN_THREADS / 64>(s, &total);
+    scan_store(b.out[k], p0, n, ex, v);
 }
 
 // int32 of scratch one array of n elements takes (a batch: the sum over its arrays)
@@ -121,18 +144,12 @@ __global__ void __launch_bounds__(SCAN_SMALL_THREADS) k_scan_small(const ScanBat
         const int64_t p0 = t0 + (int64_t)threadIdx.x * SCAN_PER_THREAD;
         int32_t v[SCAN_PER_THREAD];
         int32_t s = 0;
+        scan_load(b.in[k], p0, n, v);
 #pragma unroll
-        for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-            v[i] = p0 + i < n ? b.in[k][p0 + i] : 0;
-            s += v[i];
-        }
+        for (int i = 0; i < SCAN_PER_THREAD; ++i) s += v[i];
         int32_t total;
-        int32_t ex = carry + block_exclusive_scan<SCAN_SMALL_THREADS / 64>(s, &total);
-#pragma unroll
-        for (int i = 0; i < SCAN_PER_THREAD; ++i) {
-            if (p0 + i < n) b.out[k][p0 + i] = ex;
-            ex += v[i];
-        }
+        const int32_t ex = carry + block_exclusive_scan<SCAN_SMALL_THREADS / 64>(s, &total);
+        scan_store(b.out[k], p0, n, ex, v);
         carry += total;
     }
 }
@@ -180,14 +197,15 @@ gt_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *tm
 }
 
 // ---------------------------------------------------------------------------------------------
-// stable LSD radix sort of (key, value) pairs, 8 bits per pass
+// stable LSD radix sort of (key, value) pairs, at most 8 bits per pass
 // ---------------------------------------------------------------------------------------------
 // A pass = per-tile digit counts, their offsets, and a scatter that ranks a tile's items (wavefront by wavefront, 64 items at a
 // time, in order, so equal digits keep their order), sorts the tile in LDS and writes it out from there: the runs of a
 // digit leave as consecutive stores (scattering from registers wrote 4-byte pieces: 25 M pairs 149 us per pass,
 // 58 us average over a plan with this).  Tiles: 8,192 pairs (8 wavefronts) on long inputs, where an XCD takes consecutive tiles so that
 // neighbouring runs of a digit meet in its L2; 4,096 and 1,024 pairs (4 wavefronts) on shorter ones, so that a few hundred thousand or
-// thousand pairs still spread over the compute units.  With at most RS_DIRECT tiles the scatter adds up the counts of the
+// thousand pairs still spread over the compute units.  The bits of a key are shared out evenly over the passes: 20 bits in 6, 7 and 7
+// leave a tile's digits in runs twice as long as 8, 8 and 4 do, and half the counts to scan (25 M triples 3 x 201 -> 3 x SCATUS us).  With at most RS_DIRECT tiles the scatter adds up the counts of the
 // tiles before its own itself: two launches per pass instead of four.
 template <int WAVES, int CH> constexpr int rs_tile() { return WAVES * CH * 64; }
 constexpr int RS_DIRECT = 128;
@@ -200,7 +218,7 @@ static inline unsigned rs_grid(int nblk) { return (unsigned)((nblk + 7) / 8 * 8)
 
 // counts of one tile: hist[tile][256] (direct) or hist[256][nblk] (to be scanned)
 template <int WAVES, int CH>
-__global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, int64_t n, int shift, int32_t *hist, int nblk,
+__global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, int64_t n, int shift, int nb, int32_t *hist, int nblk,
                                                         int direct) {
     constexpr int NT = WAVES * 64, TILE = rs_tile<WAVES, CH>();
     __shared__ int32_t h[256];
@@ -217,9 +235,9 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, in
     }
 #pragma unroll
     for (int i = 0; i < CH; ++i)
-        if (base + (int64_t)i * NT < n) atomicAdd(&h[(k[i] >> shift) & 255u], 1);
+        if (base + (int64_t)i * NT < n) atomicAdd(&h[(k[i] >> shift) & ((1u << nb) - 1u)], 1);
     __syncthreads();
-    if (threadIdx.x < 256) hist[direct ? tile * 256 + threadIdx.x : (int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
+    if (threadIdx.x < (direct ? 256 : 1 << nb)) hist[direct ? tile * 256 + threadIdx.x : (int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
 }
 
 template <int WAVES, int CH, bool EXTRA>
@@ -229,7 +247,7 @@ constexpr size_t rs_lds_bytes() { return (size_t)rs_tile<WAVES, CH>() * (EXTRA ?
 template <int WAVES, int CH, bool EXTRA>
 __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_in, const uint32_t *vals_in, const uint32_t *ext_in,
                                                            uint32_t *keys_out, uint32_t *vals_out, uint32_t *ext_out, int64_t n,
-                                                           int shift, const int32_t *hist, int nblk, int direct) {
+                                                           int shift, int nb, const int32_t *hist, int nblk, int direct) {
     constexpr int NT = WAVES * 64, TILE = rs_tile<WAVES, CH>();
     extern __shared__ __align__(16) unsigned char rs_smem[];
     uint32_t *lk = reinterpret_cast<uint32_t *>(rs_smem), *lv = lk + TILE;   // the tile, sorted
@@ -241,6 +259,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
     if (tile >= nblk) return;   // whole workgroups leave
     for (int i = threadIdx.x; i < WAVES * 256; i += NT) cnt[i] = 0;
     const int64_t t0 = tile * TILE, wstart = t0 + (int64_t)wave * CH * 64;
+    const uint32_t dmask = (1u << nb) - 1u;
     uint32_t key[CH], val[CH], ext[EXTRA ? CH : 1];
     int32_t rank[CH];
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -263,7 +282,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
                 all += x;
             }
         } else {
-            goff = hist[(int64_t)d * nblk + tile];
+            goff = d < (1 << nb) ? hist[(int64_t)d * nblk + tile] : 0;
         }
     }
     int32_t unused;
@@ -274,7 +293,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
         rank[c] = 0;
         if (wstart + (int64_t)c * 64 >= n) continue;   // wavefront-uniform: the chunk is empty
         const bool valid = wstart + (int64_t)c * 64 + lane < n;
-        const uint32_t digit = (key[c] >> shift) & 255u;
+        const uint32_t digit = (key[c] >> shift) & dmask;
         uint64_t m = __ballot(valid);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -309,7 +328,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         if (wstart + (int64_t)c * 64 + lane < n) {
-            const int pos = cnt[wave * 256 + ((key[c] >> shift) & 255u)] + rank[c];
+            const int pos = cnt[wave * 256 + ((key[c] >> shift) & dmask)] + rank[c];
             lk[pos] = key[c];
             lv[pos] = val[c];
             if constexpr (EXTRA) le[pos] = ext[c];
@@ -319,7 +338,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
     const int m = n - t0 < TILE ? (int)(n - t0) : TILE;
     for (int i = threadIdx.x; i < m; i += NT) {
         const uint32_t k = lk[i];
-        const int64_t dst = (int64_t)gdelta[(k >> shift) & 255u] + i;
+        const int64_t dst = (int64_t)gdelta[(k >> shift) & dmask] + i;
         keys_out[dst] = k;
         vals_out[dst] = lv[i];
         if constexpr (EXTRA) ext_out[dst] = le[i];
@@ -349,12 +368,15 @@ struct SortPasses {
     uint32_t *vout[RS_MAX_PASSES];
     const uint32_t *ein[RS_MAX_PASSES];   // second value, or null (multi-launch sorts only: n > RS_ONE_MAX)
     uint32_t *eout[RS_MAX_PASSES];
-    int passes;                           // pass p sorts by bits [8p, 8p + 8)
+    int passes;                           // at least bits / 8
+    int bits;                             // of a key, shared out over the passes (see sort_shift)
 };
+
+__host__ __device__ inline int sort_shift(int bits, int passes, int p) { return p * bits / passes; }   // pass p sorts by the bits from here on
 
 __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *keys_in, const uint32_t *vals_in,
                                                                 uint32_t *keys_out, uint32_t *vals_out, int64_t n,
-                                                                int passes) {
+                                                                int passes, int bits) {
     extern __shared__ __align__(16) unsigned char rs_one_smem[];
     uint32_t *lk = reinterpret_cast<uint32_t *>(rs_one_smem);       // [RS_ONE_MAX]
     uint32_t *lv = lk + RS_ONE_MAX;                                  // [RS_ONE_MAX]
@@ -373,7 +395,8 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
         val[c] = (q < nn && vals_in) ? vals_in[q] : (uint32_t)q;
     }
     for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
+        const int shift = sort_shift(bits, passes, p), nb = sort_shift(bits, passes, p + 1) - shift;
+        const uint32_t dmask = (1u << nb) - 1u;
         for (int i = threadIdx.x; i < RS_ONE_WAVES * 256; i += RS_ONE_THREADS) cnt[i] = 0;
         if (p > 0) {
 #pragma unroll
@@ -390,11 +413,11 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
             rank[c] = 0;
             if (wstart + c * 64 >= nn) continue;   // wavefront-uniform: the chunk is empty
             const bool valid = wstart + c * 64 + lane < nn;
-            const uint32_t digit = (key[c] >> shift) & 255u;
+            const uint32_t digit = (key[c] >> shift) & dmask;
             uint64_t m = __ballot(valid);
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                const bool bit = (digit >> b) & 1u;
+                    const bool bit = (digit >> b) & 1u;
                 const uint64_t bal = __ballot(valid && bit);
                 m &= bit ? bal : ~bal;
             }
@@ -436,7 +459,7 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
         for (int c = 0; c < RS_CHUNKS; ++c) {
             const int q = wstart + c * 64 + lane;
             if (q < nn) {
-                const uint32_t digit = (key[c] >> shift) & 255u;
+                const uint32_t digit = (key[c] >> shift) & dmask;
                 const int dst = (int)wbase[wave * 256 + digit] + rank[c];
                 lk[dst] = key[c];
                 lv[dst] = val[c];
@@ -472,55 +495,56 @@ size_t rs_hist_ints(int64_t n) { return (size_t)256 * (size_t)((n + RS_T2 - 1) /
 
 template <int WAVES, int CH, bool EXTRA>
 gt_status radix_pass_t(const uint32_t *kin, const uint32_t *vin, const uint32_t *ein, uint32_t *kout, uint32_t *vout, uint32_t *eout,
-                       int64_t n, int shift, const SortTmp &t, hipStream_t st) {
+                       int64_t n, int shift, int nb, const SortTmp &t, hipStream_t st) {
     constexpr int64_t TILE = rs_tile<WAVES, CH>();
     constexpr size_t lds = rs_lds_bytes<WAVES, CH, EXTRA>();
     const int nblk = (int)((n + TILE - 1) / TILE);
     const int direct = nblk <= RS_DIRECT;
     const unsigned grid = rs_grid(nblk);
-    k_rs_hist<WAVES, CH><<<grid, WAVES * 64, 0, st>>>(kin, n, shift, t.hist, nblk, direct);
+    k_rs_hist<WAVES, CH><<<grid, WAVES * 64, 0, st>>>(kin, n, shift, nb, t.hist, nblk, direct);
     GT_LAUNCH_CHECK("k_rs_hist");
     if (!direct) {
-        const gt_status s = scan_exclusive(t.hist, t.hist, (int64_t)256 * nblk, t.scan_tmp, st);
+        const gt_status s = scan_exclusive(t.hist, t.hist, (int64_t)nblk << nb, t.scan_tmp, st);
         if (s != GT_OK) return s;
     }
     if (lds > 64 * 1024)
         GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rs_scatter<WAVES, CH, EXTRA>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    k_rs_scatter<WAVES, CH, EXTRA><<<grid, WAVES * 64, lds, st>>>(kin, vin, ein, kout, vout, eout, n, shift, t.hist, nblk, direct);
+    k_rs_scatter<WAVES, CH, EXTRA><<<grid, WAVES * 64, lds, st>>>(kin, vin, ein, kout, vout, eout, n, shift, nb, t.hist, nblk, direct);
     GT_LAUNCH_CHECK("k_rs_scatter");
     return GT_OK;
 }
 
 gt_status radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout, int64_t n,
-                     int shift, const SortTmp &t, hipStream_t st, const uint32_t *ein = nullptr, uint32_t *eout = nullptr) {
+                     int shift, int nb, const SortTmp &t, hipStream_t st, const uint32_t *ein = nullptr, uint32_t *eout = nullptr) {
     if (n <= 0) return GT_OK;
     const int64_t tile = rs_tile_for(n);
     if (ein) {   // (8,192 triples leave a CU one workgroup: 228 us a pass over 25 M with 16 wavefronts, 202 with 4,096)
-        if (tile == RS_T1) return radix_pass_t<4, 4, true>(kin, vin, ein, kout, vout, eout, n, shift, t, st);
-        return radix_pass_t<8, 8, true>(kin, vin, ein, kout, vout, eout, n, shift, t, st);
+        if (tile == RS_T1) return radix_pass_t<4, 4, true>(kin, vin, ein, kout, vout, eout, n, shift, nb, t, st);
+        return radix_pass_t<8, 8, true>(kin, vin, ein, kout, vout, eout, n, shift, nb, t, st);
     }
-    if (tile == RS_T1) return radix_pass_t<4, 4, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, t, st);
-    if (tile == RS_T2) return radix_pass_t<4, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, t, st);
-    return radix_pass_t<8, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, t, st);
+    if (tile == RS_T1) return radix_pass_t<4, 4, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
+    if (tile == RS_T2) return radix_pass_t<4, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
+    return radix_pass_t<8, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
 }
 
 // Runs the passes of `a` in order: one launch when the input is short, one pass at a time otherwise.
 gt_status radix_sort(const SortPasses &a, int64_t n, const SortTmp &t, hipStream_t st) {
     if (n <= 0 || a.passes <= 0) return GT_OK;
-    if (a.passes > RS_MAX_PASSES) return gt_fail(GT_ERR_INTERNAL, "radix_sort: too many passes");
+    if (a.passes > RS_MAX_PASSES || a.bits > 8 * a.passes || a.bits < a.passes) return gt_fail(GT_ERR_INTERNAL, "radix_sort: too many passes");
     if (n <= RS_ONE_MAX) {
         if (a.ein[0]) return gt_fail(GT_ERR_INTERNAL, "radix_sort: a second value on a one-launch sort");
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_rs_sort_one),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)RS_ONE_LDS);
         if (e != hipSuccess) return gt_hip_fail(e, "hipFuncSetAttribute(k_rs_sort_one)");
         k_rs_sort_one<<<1, RS_ONE_THREADS, RS_ONE_LDS, st>>>(a.kin[0], a.vin[0], a.kout[a.passes - 1],
-                                                              a.vout[a.passes - 1], n, a.passes);
+                                                              a.vout[a.passes - 1], n, a.passes, a.bits);
         GT_LAUNCH_CHECK("k_rs_sort_one");
         return GT_OK;
     }
     for (int p = 0; p < a.passes; ++p) {
-        const gt_status s = radix_pass(a.kin[p], a.vin[p], a.kout[p], a.vout[p], n, 8 * p, t, st, a.ein[p], a.eout[p]);
+        const int shift = sort_shift(a.bits, a.passes, p), nb = sort_shift(a.bits, a.passes, p + 1) - shift;
+        const gt_status s = radix_pass(a.kin[p], a.vin[p], a.kout[p], a.vout[p], n, shift, nb, t, st, a.ein[p], a.eout[p]);
         if (s != GT_OK) return s;
     }
     return GT_OK;
