@@ -205,7 +205,7 @@ gt_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *tm
 // 58 us average over a plan with this).  Tiles: 8,192 pairs (8 wavefronts) on long inputs, where an XCD takes consecutive tiles so that
 // neighbouring runs of a digit meet in its L2; 4,096 and 1,024 pairs (4 wavefronts) on shorter ones, so that a few hundred thousand or
 // thousand pairs still spread over the compute units.  The bits of a key are shared out evenly over the passes: 20 bits in 6, 7 and 7
-// leave a tile's digits in runs twice as long as 8, 8 and 4 do, and half the counts to scan (25 M triples 3 x 201 -> 3 x SCATUS us).  With at most RS_DIRECT tiles the scatter adds up the counts of the
+// leave a tile's digits in runs twice as long as 8, 8 and 4 do, and half the counts to scan.  With at most RS_DIRECT tiles the scatter adds up the counts of the
 // tiles before its own itself: two launches per pass instead of four.
 template <int WAVES, int CH> constexpr int rs_tile() { return WAVES * CH * 64; }
 constexpr int RS_DIRECT = 128;
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, in
 }
 
 template <int WAVES, int CH, bool EXTRA>
-constexpr size_t rs_lds_bytes() { return (size_t)rs_tile<WAVES, CH>() * (EXTRA ? 12 : 8) + (size_t)WAVES * 256 * 4 + 256 * 4; }
+constexpr size_t rs_lds_bytes() { return (size_t)rs_tile<WAVES, CH>() * 4 + (size_t)WAVES * 256 * 4 + 256 * 4; }
 
 // vals_in == nullptr means value = position (iota).  EXTRA: a second value travels along.
 template <int WAVES, int CH, bool EXTRA>
@@ -250,10 +250,9 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
                                                            int shift, int nb, const int32_t *hist, int nblk, int direct) {
     constexpr int NT = WAVES * 64, TILE = rs_tile<WAVES, CH>();
     extern __shared__ __align__(16) unsigned char rs_smem[];
-    uint32_t *lk = reinterpret_cast<uint32_t *>(rs_smem), *lv = lk + TILE;   // the tile, sorted
-    uint32_t *le = lv + TILE;                                                // (EXTRA only)
-    int32_t *cnt = reinterpret_cast<int32_t *>(EXTRA ? le + TILE : le);      // [WAVES][256] counts, then bases
-    int32_t *gdelta = cnt + WAVES * 256;                                     // output position minus tile position, per digit
+    uint32_t *lx = reinterpret_cast<uint32_t *>(rs_smem);        // the tile's keys, sorted; then its values; then the second ones
+    int32_t *cnt = reinterpret_cast<int32_t *>(lx + TILE);       // [WAVES][256] counts, then bases
+    int32_t *gdelta = cnt + WAVES * 256;                         // output position minus tile position, per digit
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, d = threadIdx.x;
     const int64_t tile = rs_tile_of_block(nblk);
     if (tile >= nblk) return;   // whole workgroups leave
@@ -325,24 +324,40 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
         for (int w = 0; w < WAVES; ++w) cnt[w * 256 + d] = start + wb[w];
     }
     __syncthreads();
+    // One array at a time goes through LDS: with room for all of them a CU held two workgroups (25 M triples 198 us a pass,
+    // 130 this way; 16 items per thread 135, and more where the tiles are few)
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         if (wstart + (int64_t)c * 64 + lane < n) {
-            const int pos = cnt[wave * 256 + ((key[c] >> shift) & dmask)] + rank[c];
-            lk[pos] = key[c];
-            lv[pos] = val[c];
-            if constexpr (EXTRA) le[pos] = ext[c];
+            rank[c] += cnt[wave * 256 + ((key[c] >> shift) & dmask)];
+            lx[rank[c]] = key[c];
         }
     }
     __syncthreads();
     const int m = n - t0 < TILE ? (int)(n - t0) : TILE;
-    for (int i = threadIdx.x; i < m; i += NT) {
-        const uint32_t k = lk[i];
-        const int64_t dst = (int64_t)gdelta[(k >> shift) & dmask] + i;
-        keys_out[dst] = k;
-        vals_out[dst] = lv[i];
-        if constexpr (EXTRA) ext_out[dst] = le[i];
+    int32_t dst[CH];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+        const int i = j * NT + threadIdx.x;
+        dst[j] = 0;
+        if (i < m) {
+            const uint32_t k = lx[i];
+            dst[j] = gdelta[(k >> shift) & dmask] + i;
+            keys_out[dst[j]] = k;
+        }
     }
+    auto carry = [&](const uint32_t *x, uint32_t *out) {
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            if (wstart + (int64_t)c * 64 + lane < n) lx[rank[c]] = x[c];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+            if (j * NT + (int)threadIdx.x < m) out[dst[j]] = lx[j * NT + threadIdx.x];
+    };
+    carry(val, vals_out);
+    if constexpr (EXTRA) carry(ext, ext_out);
 }
 
 // All passes of a sort of at most 16,384 pairs in one launch: a single workgroup of 16 wavefronts,
@@ -519,7 +534,7 @@ gt_status radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, u
                      int shift, int nb, const SortTmp &t, hipStream_t st, const uint32_t *ein = nullptr, uint32_t *eout = nullptr) {
     if (n <= 0) return GT_OK;
     const int64_t tile = rs_tile_for(n);
-    if (ein) {   // (8,192 triples leave a CU one workgroup: 228 us a pass over 25 M with 16 wavefronts, 202 with 4,096)
+    if (ein) {
         if (tile == RS_T1) return radix_pass_t<4, 4, true>(kin, vin, ein, kout, vout, eout, n, shift, nb, t, st);
         return radix_pass_t<8, 8, true>(kin, vin, ein, kout, vout, eout, n, shift, nb, t, st);
     }
