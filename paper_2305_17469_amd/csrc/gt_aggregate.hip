@@ -46,7 +46,7 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
     }
 
     AggArgs a{};
-    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long;
+    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len;
     a.rowptr = sc.rowptr; a.nbr = sc.nbr;
     a.coef = sc.wt; a.post_mode = 0;
     if (reduce == GT_MEAN) {

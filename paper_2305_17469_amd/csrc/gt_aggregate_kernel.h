@@ -53,6 +53,8 @@ struct AggArgs {
     int64_t n_long;          // host-side: the first n_long items are long ones (gt_long_min)
     int n_coop;              // set at launch: the first n_coop workgroups give their items a whole workgroup each
     int coop_waves;          // (4) or a whole wavefront each (1)
+    int n_whole;             // set at launch: before those, one workgroup per split row, which sums the whole row (see agg_whole_rows)
+    int64_t max_len;         // host-side: entries of the longest split row
     int xcd_run;             // item blocks per XCD run (0 or 1: plain order)
     int slices_lg;           // set at launch: 1 << slices_lg column tiles are shared out over the XCDs (see launch)
     int n_blocks;            // set at launch: workgroups per column tile
@@ -291,6 +293,12 @@ static inline int agg_xcd_run(int64_t gx) {
 template <int NP, int VWM>
 constexpr bool agg_coop() { return NP == 1 && VWM == 0; }
 
+// Whether a launch that shares its long items out gives each split row a workgroup instead of cutting it into chunks: the row is finished there,
+// and the launch that adds the partial rows is saved.  Up to rows of 64 entries per group, whose sum takes about as long as that
+// launch (us, partial rows / whole rows: 5 K rows, 50 K power-law edges, 16 fp32 columns, both directions 31.7 / 24.6; a training step on 4 K rows,
+// 61 K edges 77 / 68; with 256 entries per group 50 K rows, 500 K edges, 100 bf16 columns 41 / 78).
+static inline bool agg_whole_rows(const AggArgs &a, int G) { return a.n_splits > 0 && !a.only_split && !a.no_reduce && a.max_len > 0 && a.max_len * G <= 16384; }
+
 // Ids that a lane of a narrow group may hold per batch: sixteen per group
 constexpr int agg_many_ids(int G) { return G >= 16 ? 1 : 16 / G; }
 
@@ -298,9 +306,9 @@ constexpr int agg_many_ids(int G) { return G >= 16 ? 1 : 16 / G; }
 // blockIdx.y selects a column tile of G*V*NP columns.
 // MK: an output mask is present (its values are fetched when the item starts; a separate instance so
 // that the registers they occupy during the gather cost the unmasked kernel nothing)
-// COOP: long items are shared out (a separate instance for the same reason)
+// COOP: 1: long items are shared out; 2: and split rows are summed whole (separate instances for the same reason)
 // IPL: neighbour ids per lane and batch
-template <typename T, int V, int G, int NP, int U, int VWM, bool MK, bool SH, bool COOP, int IPL>
+template <typename T, int V, int G, int NP, int U, int VWM, bool MK, bool SH, int COOP, int IPL>
 __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63;
@@ -323,16 +331,28 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         slice = xcd & ((1 << a.slices_lg) - 1);
         bx = ((bx >> 3) << (3 - a.slices_lg)) + (xcd >> a.slices_lg);
     }
-    const bool coop = COOP && bx < a.n_coop;   // uniform over the workgroup
-    const bool one_wave = COOP && a.coop_waves == 1;
+    const int whole = COOP == 2 ? a.n_whole : 0;
+    const bool all_row = COOP == 2 && bx < whole;   // uniform over the workgroup, as the next two
+    bx -= whole;
+    const bool coop = COOP && bx < a.n_coop;
+    const bool one_wave = COOP && a.coop_waves == 1 && !all_row;
     const int first = COOP ? a.n_coop : 0;
     const int64_t item_id = coop ? (one_wave ? (int64_t)bx * 4 + wave : (int64_t)bx)
                                  : (int64_t)first * (one_wave ? 4 : 1) +
-                                       ((int64_t)agg_item_block(a.xcd_run, bx - first, a.n_blocks - first, 3 - a.slices_lg) * 4 + wave) * NG + grp;
-    if (item_id >= a.n_items) return;   // whole groups leave together; the only barrier below is the cooperative one
-    const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
-    int row = raw.x, e0 = raw.y, e1 = raw.z, slot = raw.w;
-    if (a.only_split && slot < 0) return;   // uniform within the group
+                                       ((int64_t)agg_item_block(a.xcd_run, bx - first, a.n_blocks - whole - first, 3 - a.slices_lg) * 4 + wave) * NG + grp;
+    int row, e0, e1, slot;
+    if (all_row) {
+        row = a.splits[bx + whole].row;
+        e0 = a.rowptr[row];
+        e1 = a.rowptr[row + 1];
+        slot = -1;
+    } else {
+        if (item_id >= a.n_items) return;   // whole groups leave together; the only barrier below is the cooperative one
+        const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
+        row = raw.x; e0 = raw.y; e1 = raw.z; slot = raw.w;
+        if (a.only_split && slot < 0) return;   // uniform within the group
+        if (COOP == 2 && slot >= 0) return;   // (summed with its row)
+    }
     if (coop) {   // this group's slice
         const int ng = one_wave ? NG : 4 * NG;
         const int per = (e1 - e0 + ng - 1) / ng;
@@ -463,7 +483,7 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         }
     }
 
-    if constexpr (COOP) {
+    if constexpr (COOP != 0) {
         __shared__ float red[4][G * V];
         if (coop) {
             // groups of a wavefront: exchanged pairwise; wavefronts: through LDS, in order
@@ -682,8 +702,9 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
         bool coop = agg_coop<NP, VWM>() && (tiled ? share : agg_share_out(a, G, U, bytes));
         const int64_t ipc = b.coop_waves == 1 ? 4 : 1;   // items per cooperative workgroup
         b.n_coop = coop ? (int)((a.n_long + ipc - 1) / ipc) : 0;
+        b.n_whole = coop && agg_whole_rows(a, G) ? (int)a.n_splits : 0;
         const int64_t left = a.n_items > b.n_coop * ipc ? a.n_items - b.n_coop * ipc : 0;
-        const int64_t gi = (left + 4 * NG - 1) / (4 * NG), gb = b.n_coop + gi;
+        const int64_t gi = (left + 4 * NG - 1) / (4 * NG), gb = b.n_whole + b.n_coop + gi;
         b.n_blocks = (int)gb;
         b.xcd_run = agg_xcd_run(gi);
         const int S = 1 << b.slices_lg;
@@ -696,22 +717,26 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
         if constexpr (VWM == VWM_NONE) {
             if (b.n_coop > 0) {
                 if constexpr (agg_coop<NP, VWM>()) {
-                    if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, true, MANY_COOP><<<grid, 256, 0, st>>>(b);
-                    else k_aggregate<T, V, G, NP, U, VWM, false, SH, true, MANY_COOP><<<grid, 256, 0, st>>>(b);
+                    if (b.n_whole > 0) {
+                        if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 2, MANY_COOP><<<grid, 256, 0, st>>>(b);
+                        else k_aggregate<T, V, G, NP, U, VWM, false, SH, 2, MANY_COOP><<<grid, 256, 0, st>>>(b);
+                    } else if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
+                    else k_aggregate<T, V, G, NP, U, VWM, false, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
                 }
             } else if (MANY > 1 && (
                 agg_long_batches(a, G, bytes))) {
-                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, false, MANY><<<grid, 256, 0, st>>>(b);
-                else k_aggregate<T, V, G, NP, U, VWM, false, SH, false, MANY><<<grid, 256, 0, st>>>(b);
+                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
+                else k_aggregate<T, V, G, NP, U, VWM, false, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
             } else {
-                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, false, 1><<<grid, 256, 0, st>>>(b);
-                else k_aggregate<T, V, G, NP, U, VWM, false, SH, false, 1><<<grid, 256, 0, st>>>(b);
+                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 0, 1><<<grid, 256, 0, st>>>(b);
+                else k_aggregate<T, V, G, NP, U, VWM, false, SH, 0, 1><<<grid, 256, 0, st>>>(b);
             }
         } else {
-            k_aggregate<T, V, G, NP, U, VWM, false, SH, false, 1><<<grid, 256, 0, st>>>(b);
+            k_aggregate<T, V, G, NP, U, VWM, false, SH, 0, 1><<<grid, 256, 0, st>>>(b);
         }
         gt_trace_close(tr, st);
         GT_LAUNCH_CHECK("k_aggregate");
+        if (b.n_whole > 0) return GT_OK;   // no partial rows
     }
     if (a.n_splits > 0 && !a.no_reduce) {
         const int64_t gx = (a.n_splits + 3) / 4;

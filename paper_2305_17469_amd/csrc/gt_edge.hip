@@ -363,7 +363,7 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
     const gt_sched &sc = transposed ? g->bwd : g->fwd;
     if (sc.n_rows == 0) return GT_OK;
     AggArgs a{};
-    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.rowptr = sc.rowptr; a.nbr = sc.nbr;
+    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len; a.rowptr = sc.rowptr; a.nbr = sc.nbr;
     a.coef = coef; a.eidx = via_perm ? g->perm : nullptr; a.coef2 = coef2;
     a.VW = VW; a.ldvw = ldvw; a.post_mode = post_mode;
     a.bias = nullptr; a.relu = 0;

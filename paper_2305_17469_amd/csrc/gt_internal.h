@@ -64,6 +64,7 @@ struct gt_sched {
     const gt_item *items = nullptr;
     const gt_split *splits = nullptr;
     int64_t n_rows = 0, n_items = 0, n_splits = 0, n_partials = 0, n_long = 0;
+    int64_t max_len = 0;              // entries of the longest split row, or 0
 };
 
 struct gt_graph {

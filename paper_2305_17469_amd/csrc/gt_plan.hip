@@ -234,10 +234,27 @@ __global__ void __launch_bounds__(PT) k_transposed_entries(const int32_t *perm, 
     }
 }
 
-// per row: degree (with its reciprocal and reciprocal square root where wanted) and item / partial / split / long-item counts
+// per row: degree (with its reciprocal and reciprocal square root where wanted) and item / partial / split / long-item counts.  The call for
+// the given CSR (other null) clears max_len[0..1]; the one for the transposed structure finds the longest split row of both directions
+// (other: the given CSR's n_other degrees), the given one's first, where asked (else both stay 0).  (An integer maximum: its value does not depend on the order.)
 __global__ void k_row_counts(const int32_t *rowptr, int64_t n_rows, int chunk, int long_min, int32_t *deg, float *rdeg, float *dinv,
-                             int32_t *c_items, int32_t *c_parts, int32_t *c_splits, int32_t *c_long) {
+                             int32_t *c_items, int32_t *c_parts, int32_t *c_splits, int32_t *c_long, int32_t *max_len, const int32_t *other,
+                             int64_t n_other) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (!other) {
+        if (r < 2) max_len[r] = 0;   // (again by the second call where nobody asks)
+    } else {
+        int32_t mx[2] = {r < n_other ? other[r] : 0, r < n_rows ? rowptr[r + 1] - rowptr[r] : 0};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (__ballot(mx[k] > chunk + chunk / 2) == 0) continue;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) mx[k] = max(mx[k], __shfl_xor(mx[k], o, 64));
+            // (most wavefronts find a longer one there already)
+            if ((threadIdx.x & 63) == 0 && mx[k] > __hip_atomic_load(&max_len[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&max_len[k], mx[k]);
+        }
+    }
     if (r > n_rows) return;
     if (r == n_rows) {   // the extra entry makes the exclusive scans end with the totals
         c_items[r] = 0; c_parts[r] = 0; c_splits[r] = 0; c_long[r] = 0;
@@ -363,7 +380,7 @@ __global__ void k_validate(const int32_t *rowptr, const int32_t *colidx, int64_t
 struct PlanLayout {
     size_t in_deg, out_deg, rowptr_t, colidx_t, perm, ew_t, dinv, rdeg;
     size_t items_f, splits_f, items_b, splits_b;
-    size_t counts;                       // 8 int32 read back by the host
+    size_t counts;                       // 10 int32 read back by the host
     size_t ca, cb, cc, cd;               // per-row count arrays (max(n_dst, n_src) + 1 each), forward direction
     size_t ca2, cb2, cc2, cd2;           // the same for the transposed direction
     size_t items_tmp, item_keys, item_keys2, item_idx, item_idx2;   // unsorted items, sort keys / indices
@@ -428,6 +445,7 @@ T *at(void *ws, size_t off) { return reinterpret_cast<T *>(static_cast<char *>(w
 
 // items of one direction, sorted longest first (stable, so equal lengths keep row order).
 constexpr int64_t GT_SORT_ITEMS_MIN = 16384;
+constexpr int64_t GT_ASK_MAX_EDGES = (int64_t)4 << 20;   // larger graphs do not ask for their longest split row (25 M edges: 30 us)
 gt_status build_direction(const int32_t *rowptr, const int32_t *nbr, int64_t n_in, int64_t n_rows, int chunk,
                           int64_t n_items, int64_t n_long, void *ws, const PlanLayout &L, bool transposed, gt_item *items_out,
                           gt_split *splits_out, hipStream_t st) {
@@ -510,8 +528,10 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
     g->chunk = chunk;
     int32_t *ca = at<int32_t>(ws, L.ca), *cb = at<int32_t>(ws, L.cb), *cc = at<int32_t>(ws, L.cc), *cd = at<int32_t>(ws, L.cd);
     int32_t *ca2 = at<int32_t>(ws, L.ca2), *cb2 = at<int32_t>(ws, L.cb2), *cc2 = at<int32_t>(ws, L.cc2), *cd2 = at<int32_t>(ws, L.cd2);
+    int32_t *d_counts = at<int32_t>(ws, L.counts);
     // degrees and work-list counts of the given CSR
-    k_row_counts<<<nblocks(n_dst + 1), PT, 0, st>>>(rowptr, n_dst, chunk, long_min, g->in_deg, g->rdeg, g->dinv, ca, cb, cc, cd);
+    k_row_counts<<<nblocks(n_dst + 1), PT, 0, st>>>(rowptr, n_dst, chunk, long_min, g->in_deg, g->rdeg, g->dinv, ca, cb, cc, cd, d_counts + 8,
+                                                nullptr, 0);
     PLAN_LAUNCH("k_row_counts");
     // transposed structure: stable sort of (source, position) pairs by source.  A sort that runs pass by pass carries the
     // entries' destinations along; the one-launch sort of a short list has its LDS full with the pairs.
@@ -553,12 +573,12 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
     k_transposed_entries<<<nblocks(E + 1, 4 * PT), PT, 0, st>>>(g->perm, sorted_keys, carry ? nullptr : row_of, E, n_src, ew, g->in_deg, g->dinv ? 1 : 0,
                                                                 g->rowptr_t, g->colidx_t, g->ew_t, g->coef_sym_b, g->coef_mean_b);
     PLAN_LAUNCH("k_transposed_entries");
-    k_row_counts<<<nblocks(n_src + 1), PT, 0, st>>>(g->rowptr_t, n_src, chunk, long_min, g->out_deg, nullptr, nullptr, ca2, cb2, cc2, cd2);
+    k_row_counts<<<nblocks((n_src > n_dst ? n_src : n_dst) + 1), PT, 0, st>>>(g->rowptr_t, n_src, chunk, long_min, g->out_deg, nullptr, nullptr, ca2, cb2, cc2,
+                                                                              cd2, d_counts + 8, E <= GT_ASK_MAX_EDGES ? g->in_deg : nullptr, n_dst);
     PLAN_LAUNCH("k_row_counts(out)");
     // work-list sizes of both directions: the exclusive scans over n_rows + 1 entries (last input 0) leave the totals in element
     // n_rows; read back once
-    int32_t *d_counts = at<int32_t>(ws, L.counts);
-    int32_t h_counts[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int32_t h_counts[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};   // forward: items, partials, splits, long items; transposed; longest split rows
     {
         int32_t *const arr[8] = {ca, cb, cc, cd, ca2, cb2, cc2, cd2};
         const int64_t len[8] = {n_dst + 1, n_dst + 1, n_dst + 1, n_dst + 1, n_src + 1, n_src + 1, n_src + 1, n_src + 1};
@@ -568,19 +588,19 @@ extern "C" gt_status gt_graph_create(gt_graph **out, int64_t n_dst, int64_t n_sr
         k_collect_counts<<<1, 64, 0, st>>>(counts, n_dst, n_src, d_counts);
         PLAN_LAUNCH("k_collect_counts");
     }
-    PLAN_HIP(hipMemcpyAsync(h_counts, d_counts, 8 * 4, hipMemcpyDeviceToHost, st));
+    PLAN_HIP(hipMemcpyAsync(h_counts, d_counts, 10 * 4, hipMemcpyDeviceToHost, st));
     PLAN_HIP(hipStreamSynchronize(st));
     g->fwd.rowptr = rowptr; g->fwd.nbr = colidx; g->fwd.wt = ew; g->fwd.n_rows = n_dst;
     g->fwd.coef_sym = g->coef_sym_f;
     g->fwd.n_items = h_counts[0]; g->fwd.n_partials = h_counts[1]; g->fwd.n_splits = h_counts[2];
-    g->fwd.n_long = h_counts[3];
+    g->fwd.n_long = h_counts[3]; g->fwd.max_len = h_counts[8];
     g->fwd.items = at<gt_item>(ws, L.items_f); g->fwd.splits = at<gt_split>(ws, L.splits_f);
     if (g->fwd.n_items > max_items(n_dst, E) || g->fwd.n_splits > max_splits(E))
         return fail(gt_fail(GT_ERR_INTERNAL, "gt_graph_create: forward work list exceeds its bound (is rowptr valid?)"));
     g->bwd.rowptr = g->rowptr_t; g->bwd.nbr = g->colidx_t; g->bwd.wt = g->ew_t; g->bwd.n_rows = n_src;
     g->bwd.coef_sym = g->coef_sym_b; g->bwd.coef_mean = g->coef_mean_b;
     g->bwd.n_items = h_counts[4]; g->bwd.n_partials = h_counts[5]; g->bwd.n_splits = h_counts[6];
-    g->bwd.n_long = h_counts[7];
+    g->bwd.n_long = h_counts[7]; g->bwd.max_len = h_counts[9];
     g->bwd.items = at<gt_item>(ws, L.items_b); g->bwd.splits = at<gt_split>(ws, L.splits_b);
     if (g->bwd.n_items > max_items(n_src, E) || g->bwd.n_splits > max_splits(E))
         return fail(gt_fail(GT_ERR_INTERNAL, "gt_graph_create: transposed work list exceeds its bound"));
