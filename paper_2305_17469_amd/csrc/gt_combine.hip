@@ -434,10 +434,36 @@ constexpr size_t tn_lds_bytes() {
     return tiles > stages ? tiles : stages;
 }
 
+// out[c] = sum over the splits' column sums, four columns per workgroup (block = which four), 64 lanes per column stride over
+// the splits, the lanes' sums are added in lane order (fixed order; a single thread per column walking
+// a few hundred splits one after the other took 0.1 ms)
+__device__ inline void colsum_of_splits(const float *partial, int splits, int64_t cols, float *out, int64_t block) {
+    __shared__ float red[256];
+    const int cl = threadIdx.x & 3, rl = threadIdx.x >> 2;
+    const int64_t c = block * 4 + cl;
+    float s = 0.0f;
+    if (c < cols)
+        for (int z = rl; z < splits; z += 64) s += partial[(int64_t)z * cols + c];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (rl == 0 && c < cols) {
+        float t = 0.0f;
+        for (int k = 0; k < 64; ++k) t += red[k * 4 + cl];
+        out[c] = t;
+    }
+}
+// The column sums of a split reduction, formed by the workgroups of its reducing launch past the first `blocks` (in launches of their own a
+// training step of a 4,096-vertex graph took 70 us, this way 65)
+struct ColsumPart { const float *partial; float *out; unsigned blocks; };
+
 // C = act(sum_z P[z] + C_in + bias), partials added in z order
 __global__ void __launch_bounds__(256) k_splitk_reduce(const float *P, int splits, int64_t M, int64_t N, void *C,
                                                        int64_t ldc, const void *Cin, int64_t ldcin, const float *bias,
-                                                       const float *rowscale, int relu, int c_bf16) {
+                                                       const float *rowscale, int relu, int c_bf16, const ColsumPart cs) {
+    if (blockIdx.x >= cs.blocks) {   // whole workgroups
+        colsum_of_splits(cs.partial, splits, N, cs.out, blockIdx.x - cs.blocks);
+        return;
+    }
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= M * N) return;
     const int64_t row = idx / N, col = idx % N;
@@ -467,7 +493,11 @@ __global__ void __launch_bounds__(256) k_splitk_reduce(const float *P, int split
 // walked 32 rounds of loads one after the other).
 __global__ void __launch_bounds__(256) k_splitk_reduce8(const float *P, int splits, int64_t M, int64_t N, void *C,
                                                         int64_t ldc, const void *Cin, int64_t ldcin, const float *bias,
-                                                        const float *rowscale, int relu, int c_bf16) {
+                                                        const float *rowscale, int relu, int c_bf16, const ColsumPart cs) {
+    if (blockIdx.x >= cs.blocks) {   // whole workgroups
+        colsum_of_splits(cs.partial, splits, N, cs.out, blockIdx.x - cs.blocks);
+        return;
+    }
     const int l = threadIdx.x & 7;
     const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3;
     const bool live = idx < M * N;
@@ -656,23 +686,8 @@ size_t gt_gemm_ws_bytes(int transA, int64_t M, int64_t N, int64_t K) {
            (transA ? gt_align_up((size_t)splits * (size_t)N * 4) : 0);
 }
 
-// out[c] = sum over the splits' column sums: 4 columns per workgroup, 64 lanes per column stride over
-// the splits, the lanes' sums are added in lane order (fixed order; a single thread per column walking
-// a few hundred splits one after the other took 0.1 ms)
 __global__ void __launch_bounds__(256) k_colsum_splits(const float *partial, int splits, int64_t cols, float *out) {
-    __shared__ float red[256];
-    const int cl = threadIdx.x & 3, rl = threadIdx.x >> 2;
-    const int64_t c = (int64_t)blockIdx.x * 4 + cl;
-    float s = 0.0f;
-    if (c < cols)
-        for (int z = rl; z < splits; z += 64) s += partial[(int64_t)z * cols + c];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (rl == 0 && c < cols) {
-        float t = 0.0f;
-        for (int k = 0; k < 64; ++k) t += red[k * 4 + cl];
-        out[c] = t;
-    }
+    colsum_of_splits(partial, splits, cols, out, blockIdx.x);
 }
 
 gt_status gt_gemm_run(const char *fn, gt_dtype dtype, int transA, int transB, int64_t M, int64_t N, int64_t K,
@@ -743,16 +758,17 @@ gt_status gt_gemm_run(const char *fn, gt_dtype dtype, int transA, int transB, in
     if (s != GT_OK) return s;
     if (p.splits > 1) {
         const int64_t n = M * N;
-        if (p.splits >= 64)
-            k_splitk_reduce8<<<(unsigned)((n * 8 + 255) / 256), 256, 0, st>>>(static_cast<const float *>(ws), p.splits, M, N,
-                                                                            C, ldc, Cin, ldcin, bias, rowscale, g.relu,
-                                                                            g.c_bf16);
+        const bool many = p.splits >= 64;
+        const ColsumPart cs{g.colsum, colsum_b, (unsigned)(((many ? n * 8 : n) + 255) / 256)};
+        const unsigned blocks = cs.blocks + (colsum_b ? (unsigned)((N + 3) / 4) : 0u);
+        if (many)
+            k_splitk_reduce8<<<blocks, 256, 0, st>>>(static_cast<const float *>(ws), p.splits, M, N, C, ldc, Cin, ldcin, bias, rowscale, g.relu,
+                                                     g.c_bf16, cs);
         else
-            k_splitk_reduce<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(static_cast<const float *>(ws), p.splits, M, N, C,
-                                                                         ldc, Cin, ldcin, bias, rowscale, g.relu, g.c_bf16);
+            k_splitk_reduce<<<blocks, 256, 0, st>>>(static_cast<const float *>(ws), p.splits, M, N, C, ldc, Cin, ldcin, bias, rowscale, g.relu,
+                                                    g.c_bf16, cs);
         GT_LAUNCH_CHECK("k_splitk_reduce");
-    }
-    if (colsum_b) {
+    } else if (colsum_b) {
         k_colsum_splits<<<(unsigned)((N + 3) / 4), 256, 0, st>>>(g.colsum, p.splits, N, colsum_b);
         GT_LAUNCH_CHECK("k_colsum_splits");
     }
