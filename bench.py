@@ -850,7 +850,7 @@ def main():
                 traffic, why = e["hbm_bytes_per_launch"], "profiles/" + os.path.basename(tpath)
         gather_gbs = dom["gather_model_bytes_per_launch"] / (avg_ms * 1e-3) / 1e9
         floor_gbs = dom["compulsory_bytes_per_launch"] / (avg_ms * 1e-3) / 1e9
-        table_mb = dom["gathered_slice_mb"]        # what one launch gathers from (a column pass reads a slice of the table)
+        table_mb = dom["gathered_slice_mb"]        # what one launch gathers from
         # `achieved`: bytes that crossed the L2 <-> memory-fabric boundary per launch (counters) over the
         # launch duration (HIP events, this run) when the stored counters apply; else the compulsory bytes
         # over the duration.  Neither can exceed the HBM peak.  The gather-model rate is printed beside

@@ -651,8 +651,8 @@ static inline bool agg_vectors_pay(const AggArgs &a, double bytes) {
 // 66 K rows, 1 M edges, 256 fp32 columns 103 / 73; uniform, 66 K rows, 1.6 M edges, 128 fp32 columns 94 / 75, 512 columns 455 / 296;
 // 1 M rows, 17 M edges, 128 columns 1240 / 1263.
 //  * Only where a tile begins and ends with a line: otherwise each end costs a line more (uniform, 200 K rows, 3 M edges, 300 fp32
-//    columns 545 / 728; power law, 262 K rows, 6.5 M edges, 200 columns 451 / 501).  Rows wider than three of a wavefront's vectors
-//    per lane lose more by that width: 512-byte tiles there (power law, 602 fp32 columns, 12 M edges 2869 / 2146, 1.6 M edges 327 / 285), and
+//    columns 545 / 728; power law, 262 K rows, 6.5 M edges, 200 columns 451 / 501).  Rows of more than two vectors per lane of
+//    a wavefront lose more by that width: 512-byte tiles there (power law, 602 fp32 columns, 12 M edges 2869 / 2146, 1.6 M edges 327 / 285), and
 //    power-law tables past 512 MB, where only the L2s are left to hit (629 MB, 300 columns 1333 / 1234).
 //  * The two tiles of a pair have to be nearly full (96 fp32 columns, power law, 262 K rows 267 / 278).
 //  * Pairs share out the XCDs on skewed graphs of tables up to 600 MB (537 MB, 256 bf16 columns 1229, one after the other 1250; 1.07 GB
