@@ -197,7 +197,7 @@ __device__ inline typename Raw<T, V>::type load_raw_nt(const T *p) {
 // SH: rows without 16-byte alignment.  The lane that holds a row's ragged end takes the row's last V columns instead of
 // starting at its own column: it repeats some of its neighbour's (and stores the same values there), and every
 // access is a whole vector inside the row.  Needs F >= V.
-// Lanes past the row's end get its last vector.
+// Lanes past the row's end get its last vector (see the row loads of k_aggregate).
 template <bool SH, int V>
 __device__ inline int64_t agg_col(int64_t F, int64_t own) {
     const int64_t last = SH ? F - V : (F - 1) / V * V;
@@ -406,6 +406,18 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
     };
     fetch(e0);
     const T *VWp = static_cast<const T *>(a.VW);
+    // This lane's columns, counted from the tile's first one.  Lanes past the row's end repeat its last vector, in sums that nobody stores: a line
+    // that is read anyway, and no branch around the load.  Where rows are not aligned that vector mostly lies in two lines, and these
+    // lanes load nothing (IDLE; power law, 6.5 M edges, 161 bf16 columns of 32 lanes 239 us without it, 214 with it; 100 K rows, 2 M edges, 81 / 72),
+    // except where what counts is how soon the loads leave (eight in flight or wide tiles; power law, 61 K edges, 602 fp32 columns 25 / 29).
+    constexpr bool IDLE = SH && (U == 1 || (U == 2 && NP == 1) || G == 32);
+    const T *Xt = X + col0, *VWt = VWp + col0;
+    constexpr int TILE = G * V * NP;
+    const int64_t left = a.F - col0, at = SH ? left - V : (left - 1) / V * V;
+    const int width = left < TILE ? (int)left : TILE, last = at < TILE ? (int)at : TILE;
+    int col[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) col[p] = (p * G + gl) * V > last ? last : (p * G + gl) * V;
     for (int base = e0; base < e1; base += GB) {
         int idx[IPL], ei[IPL];
         float c[IPL];
@@ -413,16 +425,17 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
         for (int k = 0; k < IPL; ++k) { idx[k] = idx_next[k]; ei[k] = ei_next[k]; c[k] = c_next[k]; }
         fetch(base + GB);
         const int cnt = (e1 - base) < GB ? (e1 - base) : GB;
-        // entries j .. j + U - 1 of the batch (j is a constant where IPL > 1); ALL: every one of them is there, and the loads are
+        // entries j .. j + N - 1 of the batch (j is a constant where IPL > 1); ALL: every one of them is there, and the loads are
         // branch free (with a branch around each, the exchange that brings its id and the load wait for one another)
-        auto step = [&](int j, auto all) {
+        auto step = [&](int j, auto n, auto all) {
+            constexpr int N = decltype(n)::value;
             constexpr bool ALL = decltype(all)::value;
-            raw_t v[U][NP];
-            raw_t w[VWM == VWM_NONE ? 1 : U][VWM == VWM_NONE ? 1 : NP];
-            float cj[U];
-            int src[U], we[U];
+            raw_t v[N][NP];
+            raw_t w[VWM == VWM_NONE ? 1 : N][VWM == VWM_NONE ? 1 : NP];
+            float cj[N];
+            int src[N], we[N];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const int jj = j + u, k = IPL > 1 ? jj / G : 0;
                 we[u] = 0;
                 if constexpr (G == 64) {   // wave-uniform: scalar broadcast, scalar row base
@@ -436,49 +449,72 @@ __global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
                 }
                 if (!ALL && jj >= cnt) cj[u] = 0.0f;
             }
+            auto load = [&](int u, int p, const T *xr) {
+                v[u][p] = load_raw<T, V>(xr + col[p]);
+                if constexpr (VWM != VWM_NONE) {
+                    const T *wr = VWt + (int64_t)we[u] * a.ldvw + col[p];
+                    if constexpr ((VWM & VWM_NT) != 0) w[u][p] = load_raw_nt<T, V>(wr);
+                    else w[u][p] = load_raw<T, V>(wr);
+                }
+            };
+            if constexpr (ALL && IDLE) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool live = ALL || j + u < cnt;
-                const T *xr = X + (int64_t)src[u] * a.ldx;
+                for (int u = 0; u < N; ++u)   // (ahead of all loads: a register that is zeroed between them waits for those in flight)
 #pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    const int64_t own = col0 + (int64_t)(p * G + gl) * V;
-                    // (a lane past the row's end repeats its last vector: a line that is read anyway, sums that nobody stores)
-                    const int64_t col = agg_col<SH, V>(a, own);
-                    if constexpr (!ALL) v[u][p] = raw_t{};
-                    if (live) v[u][p] = load_raw<T, V>(xr + col);
-                    if constexpr (VWM != VWM_NONE) {
-                        if constexpr (!ALL) w[u][p] = raw_t{};
-                        if (live) {
-                            const T *wr = VWp + (int64_t)we[u] * a.ldvw + col;
-                            if constexpr ((VWM & VWM_NT) != 0) w[u][p] = load_raw_nt<T, V>(wr);
-                            else w[u][p] = load_raw<T, V>(wr);
+                    for (int p = 0; p < NP; ++p) {
+                        v[u][p] = raw_t{};
+                        if constexpr (VWM != VWM_NONE) w[u][p] = raw_t{};
+                    }
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                    if ((p * G + gl) * V < width)
+#pragma unroll
+                        for (int u = 0; u < N; ++u) load(u, p, Xt + (int64_t)src[u] * a.ldx);
+            } else {
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const T *xr = Xt + (int64_t)src[u] * a.ldx;
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) {
+                        if constexpr (!ALL) {
+                            v[u][p] = raw_t{};
+                            if constexpr (VWM != VWM_NONE) w[u][p] = raw_t{};
                         }
+                        if (ALL || (j + u < cnt && (!IDLE || (p * G + gl) * V < width))) load(u, p, xr);
                     }
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < N; ++u)
 #pragma unroll
                 for (int p = 0; p < NP; ++p) {
                     if constexpr (VWM == VWM_NONE) fma_raw(acc[p], cj[u], v[u][p]);
                     else fma_vw<VWM, V>(acc[p], cj[u], v[u][p], w[u][p]);
                 }
         };
-        // (two rows in flight: a remainder step of its own costs nothing.  With eight it is a round trip more for every batch that is no
-        // multiple of eight: power law, 1.5 M edges, 280 bf16 columns shared out, 99 us without it, 126 with it; with weights' vectors beside
-        // the rows it pays all the same, 4.2 M edges, 64 fp32 columns, 1254 and 1220.)
-                constexpr bool BY_ALL = U == 2 || VWM != VWM_NONE;
+        // At most two rows in flight: a last entry of an odd number by itself.  With eight, a remainder step of its own is a round trip more for
+        // every batch that is no multiple of eight (power law, 1.5 M edges, 280 bf16 columns shared out, 99 us without it, 126 with it); with
+        // weights' vectors beside the rows it pays all the same (4.2 M edges, 64 fp32 columns, 1254 and 1220).
+        constexpr std::integral_constant<int, U> some{};
+        constexpr std::integral_constant<int, 1> single{};
         if constexpr (IPL == 1) {
             int j = 0;
-            if constexpr (BY_ALL)
-                for (; j + U <= cnt; j += U) step(j, std::true_type{});
-            for (; j < cnt; j += U) step(j, std::false_type{});
+            if constexpr (U <= 2 || VWM != VWM_NONE)
+                for (; j + U <= cnt; j += U) step(j, some, std::true_type{});
+            if constexpr (U <= 2) {
+                if (U == 2 && j < cnt) step(j, single, std::true_type{});
+            } else {
+                for (; j < cnt; j += U) step(j, some, std::false_type{});
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < GB; j += U) {
-                if (j + U <= cnt) step(j, std::true_type{}); else
-                if (j < cnt) step(j, std::false_type{});
+                if (j + U <= cnt) step(j, some, std::true_type{});
+                else if constexpr (U > 2) {
+                    if (j < cnt) step(j, some, std::false_type{});
+                } else if constexpr (U == 2) {
+                    if (j < cnt) step(j, single, std::true_type{});
+                }
             }
         }
     }
