@@ -661,7 +661,7 @@ static inline bool agg_share_out(const AggArgs &a, int G, int U, double bytes) {
     const double chunk = gt_chunk_for(a.n_edges);
     if (G >= 32) return bytes <= chunk * (a.table_bytes <= ((int64_t)32 << 20) ? 8.0e6 : 5.0e6);
     if (U == 8 && G >= 8 && a.table_bytes > ((int64_t)64 << 20)) return bytes <= chunk * 1.25e6;
-    return bytes <= (U == 2 && G <= 8 ? 3.0e9 : 2.0e9);
+    return bytes <= (U <= 2 && G <= 8 ? 3.0e9 : 2.0e9);
 }
 
 // Whether a narrow group holds several ids per lane (batches of 16 ids instead of 4 or 8, at the price of registers).  It pays on
@@ -678,6 +678,9 @@ static inline bool agg_long_batches(const AggArgs &a, int G, double bytes) {
 static inline bool agg_vectors_pay(const AggArgs &a, double bytes) {
     return a.n_edges >= 12 * a.n_items && agg_long_batches(a, 4, bytes);
 }
+
+// Whether rows of more than 256 bytes keep eight loads in flight (see launch_u)
+static inline bool agg_wide_eight(const AggArgs &a, int G, double bytes) { return agg_share_out(a, G, 8, bytes) && a.table_bytes <= ((int64_t)32 << 20); }
 
 // Rows of more than 256 bytes may be cut into column tiles of 256 bytes (G = 16) or 512 (G = 32): the groups read shorter pieces of more
 // rows at a time, and what an L2 has to hold of a popular row is one tile of it.  The tiles of a launch either follow one another
@@ -749,7 +752,7 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
         gt_trace_variant(tr, V, G, NP, U, VWM == VWM_NONE && a.mask != nullptr);
         const dim3 grid((unsigned)gx, (tiles + S - 1) / S);
         // (narrow groups hold several ids per lane where items are shared out to 64 / G groups of four lanes)
-        constexpr int MANY = NP == 1 && VWM == VWM_NONE ? agg_many_ids(G) : 1, MANY_COOP = G == 4 ? MANY : 1;
+        constexpr int MANY = NP == 1 && VWM == VWM_NONE && U != 2 ? agg_many_ids(G) : 1, MANY_COOP = G == 4 ? MANY : 1;
         if constexpr (VWM == VWM_NONE) {
             if (b.n_coop > 0) {
                 if constexpr (agg_coop<NP, VWM>()) {
@@ -782,22 +785,38 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
     return GT_OK;
 }
 
-// Row loads kept in flight per lane.  Measured on MI355X: two are enough (and best) once the gathered table lives in HBM (2^18
-// vertices, 134 MB, 512-byte rows: 503 us, with four 527); rows of up to 256 bytes of a table that fits the last-level cache gain from
-// eight on skewed graphs, whose long rows are chains.  On uniform ones the L2s lose what eight spread (us, two / eight: 131 K rows, 3.3 M
-// edges, 64 fp32 columns 97 / 112, 47 bf16 columns 48 / 63; 300 K rows, 6 M edges, 12 fp32 columns 78 / 100), as long as a group has
-// a batch of ids to walk (G = 8, 66 K rows, 1 M edges, 32 fp32 columns 17.1 / 16.0) and the launch fills the chip (a sampled block of 300 rows,
-// 64 fp32 columns 9.3 / 7.5).  Wider ones only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
-// 128 fp32 columns: 95 us with two, 42 with eight and items shared out); elsewhere eight spread the rows that the
-// resident groups read at a time, and the L2s lose them (uniform graphs, 128 fp32 columns: 65,536 vertices of degree 16
-// 68 us, with eight 73; degree 130, 4 M edges 87 and 174).
+// Row loads kept in flight per lane.  What they hide are the chains of long rows, on skewed graphs, and latency where the launch has few wavefronts;
+// what they cost is reuse: the more rows the resident groups read at a time, the fewer of them the caches still hold when they are wanted again.
+// us, one / two / eight (s.o.: several ids per lane):
+//  * Rows of up to 256 bytes: eight where the table fits the last-level cache (power law, 131 K rows, 1.3 M edges, 16 fp32 columns 58 / 44 / 30), and on
+//    uniform graphs where it fits the L2s (20 K rows of degree 25, 64 columns 17.6 / 12.9 / 11.2; 131 K rows of degree 25, 4 columns, backward s.o. 40 / 38 / 32) or the launch
+//    does not fill the chip (a sampled block of 300 rows, 64 columns - / 9.3 / 7.5).  Beyond the L2s, uniform rows of up to 128 bytes take one where
+//    a group has a batch of ids to walk (s.o.; 300 K rows of degree 20, 8 columns 55 / 61 / 75, backward 77 / 85 / 91; 1 M rows of degree 16, 4 columns
+//    196 / 229 / 243; 300 K rows, 32 columns 100 / 104 / 113; just past the L2s a direction may lose by it, 131 K rows of degree 25, 16 columns 31 / 30 / 37, backward
+//    47 / 44 / 44); those of 129 to 256 bytes two from eight entries on (131 K rows of degree 25, 64 columns 92 / 97 / 112; degree 4 27.7 / 27.7 / 26.1).
+//  * The same past the last-level cache: one for rows of up to 64 bytes that are shared out (2 M power-law rows, 52 M edges, 13 columns, backward 715 / 787 / 743)
+//    and for launches with several ids per lane (47 bf16 columns without padding 890 / 917 / 925), else two (1 M power-law rows, 16 M edges,
+//    64 bf16 columns, one row in flight takes 1.7 times as long).
+//  * Wider rows: eight only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
+//    128 fp32 columns: two 95, eight 42 with items shared out); elsewhere two.  Uniform graphs of whole-wavefront rows take one from ten entries on (30 K
+//    rows of degree 130, 300 columns 360 / 557; 131 K rows of degree 25, 200 columns, one vector per lane 386 / 405; degree 6, 300 K rows 276 / 261; 130 columns, 34 of 64
+//    lanes, 1 M rows of degree 8 1100 / 913), and four vectors per lane take one wherever rows are short (degree 5, 66 K rows, 1030 columns 275 / 283).
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
-    if constexpr (NP == 1 && VWM == VWM_NONE) {
-        const bool two = V > 1 && !agg_skewed(a) && a.n_items * G > 1792 * 64 && (G == 16 || agg_long_batches(a, G, agg_bytes<T>(a)));
-        const bool eight = G <= 16 ? a.table_bytes <= ((int64_t)96 << 20) && !two
-                                   : agg_share_out(a, G, 8, agg_bytes<T>(a)) && a.table_bytes <= ((int64_t)32 << 20);
-        if (eight) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
+    if constexpr (NP == 1 && VWM == VWM_NONE && G <= 16) {
+        const double bytes = agg_bytes<T>(a);
+        const bool fits = a.table_bytes <= ((int64_t)96 << 20);   // the last-level cache
+        const bool fills = !agg_skewed(a) && a.n_items * G > 1792 * 64 && a.table_bytes > ((int64_t)6 << 20);
+        if constexpr (G < 16)
+            if (agg_share_out(a, G, 1, bytes) ? G == 4 && !fits : (fills || !fits) && agg_long_batches(a, G, bytes)) return launch<T, V, G, NP, 1, VWM, SH>(a, st);
+        if (fits && !(V > 1 && G == 16 && fills && a.n_edges >= 8 * a.n_items)) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
+    } else if constexpr (NP == 1 && VWM == VWM_NONE) {
+        if (agg_wide_eight(a, G, agg_bytes<T>(a))) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
+    }
+    if constexpr (G == 64 && V > 1 && VWM == VWM_NONE) {
+        bool one = agg_skewed(a) ? NP == 4 && a.n_edges < 4 * a.n_items : NP == 4 || (a.n_edges >= 10 * a.n_items && a.n_edges >= 256 * 1024);
+        if constexpr (NP == 1) one = one && !SH && a.F >= 40 * V && a.table_bytes > ((int64_t)40 << 20) && a.table_bytes < ((int64_t)300 << 20);
+        if (one) return launch<T, V, G, NP, 1, VWM, SH>(a, st);
     }
     // per-entry vector weights stream from memory, each row once, and the gathered table beside them is smaller than they
     // are: eight in flight (4.2 M edges x 64 fp32: two 333 us, four 301, eight 296), four of the widest (1.8 M edges of degree 6,
