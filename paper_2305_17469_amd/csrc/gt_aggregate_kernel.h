@@ -690,37 +690,52 @@ static inline bool agg_wide_eight(const AggArgs &a, int G, double bytes) { retur
 // 66 K rows, 1 M edges, 256 fp32 columns 103 / 73; uniform, 66 K rows, 1.6 M edges, 128 fp32 columns 94 / 75, 512 columns 455 / 296;
 // 1 M rows, 17 M edges, 128 columns 1240 / 1263.
 //  * Only where a tile begins and ends with a line: otherwise each end costs a line more (uniform, 200 K rows, 3 M edges, 300 fp32
-//    columns 545 / 728; power law, 262 K rows, 6.5 M edges, 200 columns 451 / 501).  Rows of more than two vectors per lane of
-//    a wavefront lose more by that width: 512-byte tiles there (power law, 602 fp32 columns, 12 M edges 2869 / 2146, 1.6 M edges 327 / 285), and
-//    power-law tables past 512 MB, where only the L2s are left to hit (629 MB, 300 columns 1333 / 1234).
-//  * The two tiles of a pair have to be nearly full (96 fp32 columns, power law, 262 K rows 267 / 278).
+//    columns 545 / 728; power law, 262 K rows, 6.5 M edges, 200 columns 451 / 501).  Such power-law rows of more than two vectors per lane of
+//    a wavefront lose more by that width: 512-byte tiles there (602 fp32 columns, 12 M edges 2869 / 2146, 1.6 M edges 327 / 285) and, in tables past
+//    256 MB, from one on (304 MB, 602 bf16 columns 787 / 696); 256-byte ones on aligned rows past 512 MB, where only the L2s are left to hit (638 MB, 602
+//    bf16 columns 889 / 753, in 512-byte tiles 833).
+//  * Uniform graphs of few entries per row lose by tiles of whole wavefronts' rows as long as the table is beyond the L2s and not far beyond the
+//    last-level cache (degree 4, 66 K rows, 1024 fp32 columns 192 / 219, 131 K rows, 640 columns 237 / 264; 16 K rows, 1024 columns 51 / 41 and 1 M rows, 512 columns 1.00 / 0.84 gain
+//    all the same; 128 columns at any size 0.99 / 1.03), others by three or four tiles of such a table (262 K rows of degree 10, 224 columns
+//    350 / 377, 300 K rows of degree 20, 192 columns 628 / 665).  So do gathers that look their coefficients up by entry, once per tile (200 K rows of
+//    degree 10, 160 columns, backward 433 / 516).
+//  * The two tiles of the first pair have to be nearly full (96 fp32 columns, power law, 262 K rows 267 / 278); a half empty last one of
+//    four still pays (224 columns, 21 power-law graphs, geometric mean: paired 0.90 of the rows whole, one after the other 0.93).
 //  * Pairs share out the XCDs on skewed graphs of tables up to 600 MB (537 MB, 256 bf16 columns 1229, one after the other 1250; 1.07 GB
 //    3384 and 3193) and in small launches of uniform ones (16 K rows, 262 K edges 13.7 and 15.1; 131 K rows, 3.3 M edges 201 and 193).
-//  * Skewed launches below half a gigabyte keep whole rows, eight in flight and shared out (33 K rows, 0.8 M edges, 128 fp32 columns 29 / 32).
+//  * Skewed launches keep whole rows below half a gigabyte (33 K rows, 0.8 M edges, 128 fp32 columns 29 / 32) and where those have eight loads in
+//    flight (20 K rows, 0.5 M edges, 256 columns 36 / 58, 0.9 M edges 50 / 64).
 //  * Eight rows in flight and long items shared out where the chains of long items matter: tiles that gather at most 2.9 GB one after the
-//    other from at most 300 MB (us, that / two rows in flight alone: 131 K rows, 3.3 M edges, 128 columns 103 / 120; 262 K rows, 12 M edges, 160 columns
-//    464 / 504; 6.5 M edges, 128 columns, 3.4 GB 260 / 224; 302 MB, 144 columns 600 / 573).  Beyond, two in flight, shared out from 32 entries per item on
-//    (12 M edges, degree 45, symmetric norm 429 / 449; 6.5 M edges, degree 25 250 / 224).
+//    other from at most 450 MB (us, that / two rows in flight alone: 131 K rows, 3.3 M edges, 128 columns 103 / 120; 262 K rows, 12 M edges, 160 columns
+//    464 / 504; 262 K rows, 2.6 M edges, 320 columns 310 / 449; 6.5 M edges, 128 columns, 3.4 GB 260 / 224).  Chunks of graphs below a million edges
+//    make no chains (512 columns, 0.5 M edges 114 / 72, 0.66 M edges 123 / 116).  Beyond, two in flight, shared out from 32 entries per item on
+//    (12 M edges, degree 45, symmetric norm 429 / 449) and where a tile gathers up to 1.7 GB (524 K rows, 5.2 M edges, 160 columns, backward 476 alone,
+//    381; 10 M edges 725 and 775).
 struct AggTiles { int G, U, slices_lg; bool share; };   // G 0: the row whole
-static inline AggTiles agg_tiles(const AggArgs &a, int64_t nvec, size_t es, double bytes) {
+static inline AggTiles agg_tiles(const AggArgs &a, bool shifted, int64_t nvec, size_t es, double bytes) {
     const bool lines = (a.ldx * (int64_t)es) % 128 == 0 && ((uintptr_t)a.X & 127) == 0;
-    const int64_t tiles = (nvec + 15) / 16;
+    const int64_t tiles = (nvec + 15) / 16, MB = (int64_t)1 << 20;
     const AggTiles whole = {0, 0, 0, false};
     if (nvec < 28) return whole;
     if (!agg_skewed(a)) {
-        if (!lines) return whole;
+        if (!lines || a.eidx) return whole;
+        if (a.n_edges < 10 * a.n_items ? nvec <= 32 || (nvec >= 56 && a.table_bytes > 80 * MB && a.table_bytes < 600 * MB)
+                                      : nvec > 32 && nvec < 64 && a.table_bytes > (a.n_edges < 16 * a.n_items ? 80 : 140) * MB && a.table_bytes < 300 * MB)
+            return whole;
         const bool few = a.n_long > 0 && a.n_items * 16 <= 1792 * 64;
         return {16, 2, tiles % 2 == 0 && bytes < 0.3e9 ? 1 : 0, few};
     }
     if (bytes < 0.5e9) return whole;
+    const int lg = tiles % 2 == 0 && a.table_bytes <= 600 * MB ? 1 : 0;
+    const bool share = a.n_long > 0 && (a.n_edges >= 32 * a.n_items || (double)a.n_edges * 256 <= 1.7e9);
     if (!lines) {
-        if (nvec > 128) return {32, 2, 0, false};
-        if (nvec >= 64 && a.table_bytes > ((int64_t)512 << 20)) return {16, 2, 0, false};
-        return whole;
+        if (nvec < 64 || (nvec <= 128 && a.table_bytes <= 256 * MB)) return whole;
+        return nvec <= 128 && !shifted && a.table_bytes > 512 * MB ? AggTiles{16, 2, 0, share} : AggTiles{32, 2, 0, false};
     }
-    const int lg = tiles % 2 == 0 && a.table_bytes <= ((int64_t)600 << 20) ? 1 : 0;
-    if (bytes * (1 << lg) <= 2.9e9 * (double)tiles && a.table_bytes <= ((int64_t)300 << 20)) return {16, 8, lg, true};
-    return {16, 2, lg, a.n_long > 0 && a.n_edges >= 32 * a.n_items};
+    if (nvec <= 64 && agg_wide_eight(a, nvec <= 32 ? 32 : 64, bytes)) return whole;
+    if (a.n_edges < ((int64_t)1 << 20)) return {16, 2, lg, false};
+    if (bytes * (1 << lg) <= 2.9e9 * (double)tiles && a.table_bytes <= 450 * MB) return {16, 8, lg, true};
+    return {16, 2, lg, share};
 }
 
 // tiled: the row is cut into several column tiles of this launch (see agg_tiles); share: whether its long items are shared out
@@ -836,7 +851,7 @@ gt_status dispatch(const AggArgs &a, hipStream_t st) {
     if constexpr (V == 1) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
     if (nvec <= 16) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
     if constexpr (VWM == VWM_NONE) {
-        const AggTiles t = agg_tiles(a, nvec, sizeof(T), agg_bytes<T>(a));
+        const AggTiles t = agg_tiles(a, SH, nvec, sizeof(T), agg_bytes<T>(a));
         if (t.G == 32) return launch<T, V, 32, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);
         if (t.G == 16 && t.U == 8) return launch<T, V, 16, 1, 8, VWM, SH>(a, st, true, t.slices_lg, t.share);
         if (t.G == 16) return launch<T, V, 16, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);

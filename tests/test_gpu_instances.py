@@ -1,5 +1,5 @@
-"""Which instance of the aggregation kernel a shape takes (lanes per row, vectors per lane, rows in flight), on both sides of the rules for rows in
-flight; the results against 64 bits: |error| <= (n + 2) 2^-24 sum |x| for a row of n entries (any order of fp32 additions), one bf16
+"""Which instance of the aggregation kernel a shape takes (lanes per row, vectors per lane, rows in flight), on both sides of the rules for rows in flight
+and column tiles; the results against 64 bits: |error| <= (n + 2) 2^-24 sum |x| for a row of n entries (any order of fp32 additions), one bf16
 rounding more for bf16 results."""
 import numpy as np
 import pytest
@@ -11,9 +11,9 @@ pytestmark = pytest.mark.gpu
 
 # rows, entries per row, hub rows, their entries: graphs without hubs are uniform, those with hubs skewed
 GRAPHS = {"even20k": (20000, 25, 0, 0), "sparse66k": (66000, 4, 0, 0), "even66k": (66000, 16, 0, 0), "even131k": (131072, 25, 0, 0),
-          "even30k130": (30000, 130, 0, 0), "even1m": (1000003, 8, 0, 0), "hubs262k": (262144, 8, 60, 8000),
-          "hubs2m": (2097152, 11, 300, 9000)}
-# columns, stride, type, (lanes, vectors per lane, rows in flight)
+          "sparse131k": (131072, 4, 0, 0), "even30k130": (30000, 130, 0, 0), "even1m": (1000003, 8, 0, 0), "hubs20k": (20000, 22, 40, 1500),
+          "hubs33k": (33000, 26, 40, 2500), "hubs262k": (262144, 8, 60, 8000), "hubs2m": (2097152, 11, 300, 9000)}
+# columns, stride, type, (lanes, vectors per lane, rows in flight); strides of whole lines of 128 bytes may be cut into tiles of 16 lanes
 CASES = [("even131k", 4, 4, "f32", (4, 1, 8)),        # the table fits the L2s
          ("even131k", 16, 16, "f32", (4, 1, 1)),      # past them, several ids per lane
          ("even131k", 32, 32, "f32", (8, 1, 1)),
@@ -30,6 +30,14 @@ CASES = [("even131k", 4, 4, "f32", (4, 1, 8)),        # the table fits the L2s
          ("even30k130", 602, 602, "bf16", (64, 2, 1)),
          ("sparse66k", 300, 300, "f32", (64, 2, 2)),
          ("sparse66k", 1030, 1032, "f32", (64, 4, 1)),
+         ("even66k", 256, 256, "f32", (16, 1, 2)),    # tiles
+         ("sparse131k", 256, 256, "f32", (64, 1, 2)),   # few entries per row
+         ("sparse131k", 160, 160, "f32", (16, 1, 2)),
+         ("hubs20k", 256, 256, "f32", (64, 1, 8)),    # skewed: whole rows with eight in flight
+         ("hubs20k", 512, 512, "f32", (16, 1, 2)),    # no chains
+         ("hubs33k", 200, 224, "f32", (64, 1, 8)),
+         ("hubs262k", 320, 320, "f32", (16, 1, 8)),
+         ("hubs262k", 300, 300, "f32", (32, 1, 2)),   # no whole lines, past the last-level cache
          ("hubs262k", 200, 200, "f32", (64, 1, 2))]
 
 
