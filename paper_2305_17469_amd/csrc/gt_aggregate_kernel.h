@@ -705,6 +705,8 @@ static inline bool agg_wide_eight(const AggArgs &a, int G, double bytes) { retur
 //    3384 and 3193) and in small launches of uniform ones (16 K rows, 262 K edges 13.7 and 15.1; 131 K rows, 3.3 M edges 201 and 193).
 //  * Skewed launches keep whole rows below half a gigabyte (33 K rows, 0.8 M edges, 128 fp32 columns 29 / 32) and where those have eight loads in
 //    flight (20 K rows, 0.5 M edges, 256 columns 36 / 58, 0.9 M edges 50 / 64).
+//  * Uniform tiles keep two rows in flight; one where rows are long and the table beyond the L2s (131 K rows of degree 25, 256 columns 402 / 374, 1 M rows
+//    of degree 16, 1024 columns 10.5 / 10.1 ms; degree 8, 256 columns 1320 / 1340).
 //  * Eight rows in flight and long items shared out where the chains of long items matter: tiles that gather at most 2.9 GB one after the
 //    other from at most 450 MB (us, that / two rows in flight alone: 131 K rows, 3.3 M edges, 128 columns 103 / 120; 262 K rows, 12 M edges, 160 columns
 //    464 / 504; 262 K rows, 2.6 M edges, 320 columns 310 / 449; 6.5 M edges, 128 columns, 3.4 GB 260 / 224).  Chunks of graphs below a million edges
@@ -723,7 +725,7 @@ static inline AggTiles agg_tiles(const AggArgs &a, bool shifted, int64_t nvec, s
                                       : nvec > 32 && nvec < 64 && a.table_bytes > (a.n_edges < 16 * a.n_items ? 80 : 140) * MB && a.table_bytes < 300 * MB)
             return whole;
         const bool few = a.n_long > 0 && a.n_items * 16 <= 1792 * 64;
-        return {16, 2, tiles % 2 == 0 && bytes < 0.3e9 ? 1 : 0, few};
+        return {16, a.n_edges >= 16 * a.n_items && a.table_bytes > 80 * MB ? 1 : 2, tiles % 2 == 0 && bytes < 0.3e9 ? 1 : 0, few};
     }
     if (bytes < 0.5e9) return whole;
     const int lg = tiles % 2 == 0 && a.table_bytes <= 600 * MB ? 1 : 0;
@@ -813,9 +815,10 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
 //    and for launches with several ids per lane (47 bf16 columns without padding 890 / 917 / 925), else two (1 M power-law rows, 16 M edges,
 //    64 bf16 columns, one row in flight takes 1.7 times as long).
 //  * Wider rows: eight only where chains are the launch's time, i.e. where long items would be shared out (power law, 1 M edges,
-//    128 fp32 columns: two 95, eight 42 with items shared out); elsewhere two.  Uniform graphs of whole-wavefront rows take one from ten entries on (30 K
-//    rows of degree 130, 300 columns 360 / 557; 131 K rows of degree 25, 200 columns, one vector per lane 386 / 405; degree 6, 300 K rows 276 / 261; 130 columns, 34 of 64
-//    lanes, 1 M rows of degree 8 1100 / 913), and four vectors per lane take one wherever rows are short (degree 5, 66 K rows, 1030 columns 275 / 283).
+//    128 fp32 columns: two 95, eight 42 with items shared out); elsewhere two.  Uniform graphs of whole-wavefront rows take one from ten entries on,
+//    if there are wavefronts enough (30 K rows of degree 130, 300 columns 360 / 557; 131 K rows of degree 25, 200 columns, one vector per lane 386 / 405;
+//    degree 6, 300 K rows 276 / 261; 130 columns, 33 of 64 lanes, 1 M rows of degree 8 1100 / 913; 6 K rows of 600 entries, 602 bf16 columns 342 / 255),
+//    and four vectors per lane take one wherever rows are short (degree 5, 66 K rows, 1030 columns 275 / 283).
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
     if constexpr (NP == 1 && VWM == VWM_NONE && G <= 16) {
@@ -829,7 +832,7 @@ gt_status launch_u(const AggArgs &a, hipStream_t st) {
         if (agg_wide_eight(a, G, agg_bytes<T>(a))) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
     }
     if constexpr (G == 64 && V > 1 && VWM == VWM_NONE) {
-        bool one = agg_skewed(a) ? NP == 4 && a.n_edges < 4 * a.n_items : NP == 4 || (a.n_edges >= 10 * a.n_items && a.n_edges >= 256 * 1024);
+        bool one = agg_skewed(a) ? NP == 4 && a.n_edges < 4 * a.n_items : NP == 4 || (a.n_edges >= 10 * a.n_items && a.n_items >= 16384);
         if constexpr (NP == 1) one = one && !SH && a.F >= 40 * V && a.table_bytes > ((int64_t)40 << 20) && a.table_bytes < ((int64_t)300 << 20);
         if (one) return launch<T, V, G, NP, 1, VWM, SH>(a, st);
     }
@@ -854,6 +857,7 @@ gt_status dispatch(const AggArgs &a, hipStream_t st) {
         const AggTiles t = agg_tiles(a, SH, nvec, sizeof(T), agg_bytes<T>(a));
         if (t.G == 32) return launch<T, V, 32, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);
         if (t.G == 16 && t.U == 8) return launch<T, V, 16, 1, 8, VWM, SH>(a, st, true, t.slices_lg, t.share);
+        if (t.G == 16 && t.U == 1) return launch<T, V, 16, 1, 1, VWM, SH>(a, st, true, t.slices_lg, t.share);
         if (t.G == 16) return launch<T, V, 16, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);
     }
     if (nvec <= 32) return launch_u<T, V, 32, 1, VWM, SH>(a, st);

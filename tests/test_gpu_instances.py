@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 # rows, entries per row, hub rows, their entries: graphs without hubs are uniform, those with hubs skewed
 GRAPHS = {"even20k": (20000, 25, 0, 0), "sparse66k": (66000, 4, 0, 0), "even66k": (66000, 16, 0, 0), "even131k": (131072, 25, 0, 0),
-          "sparse131k": (131072, 4, 0, 0), "even30k130": (30000, 130, 0, 0), "even1m": (1000003, 8, 0, 0), "hubs20k": (20000, 22, 40, 1500),
+          "sparse131k": (131072, 4, 0, 0), "even30k130": (30000, 130, 0, 0), "even1m": (1000003, 8, 0, 0), "few6k600": (6000, 600, 0, 0), "hubs20k": (20000, 22, 40, 1500),
           "hubs33k": (33000, 26, 40, 2500), "hubs262k": (262144, 8, 60, 8000), "hubs2m": (2097152, 11, 300, 9000)}
 # columns, stride, type, (lanes, vectors per lane, rows in flight); strides of whole lines of 128 bytes may be cut into tiles of 16 lanes
 CASES = [("even131k", 4, 4, "f32", (4, 1, 8)),        # the table fits the L2s
@@ -31,6 +31,8 @@ CASES = [("even131k", 4, 4, "f32", (4, 1, 8)),        # the table fits the L2s
          ("sparse66k", 300, 300, "f32", (64, 2, 2)),
          ("sparse66k", 1030, 1032, "f32", (64, 4, 1)),
          ("even66k", 256, 256, "f32", (16, 1, 2)),    # tiles
+         ("even131k", 256, 256, "f32", (16, 1, 1)),   # ... of longer rows
+         ("few6k600", 301, 301, "f32", (64, 2, 2)),   # few long rows
          ("sparse131k", 256, 256, "f32", (64, 1, 2)),   # few entries per row
          ("sparse131k", 160, 160, "f32", (16, 1, 2)),
          ("hubs20k", 256, 256, "f32", (64, 1, 8)),    # skewed: whole rows with eight in flight
