@@ -302,6 +302,12 @@ static inline bool agg_whole_rows(const AggArgs &a, int G) { return a.n_splits >
 // Ids that a lane of a narrow group may hold per batch: sixteen per group
 constexpr int agg_many_ids(int G) { return G >= 16 ? 1 : 16 / G; }
 
+// Wavefronts per SIMD that the registers have to leave room for: eight where one register past 64 cost one (41 fp32 columns without
+// alignment, 262 K rows, 12 M edges, in a training step 190 us with 64, 192.5 with 65; rows of up to 64 bytes gain nothing by it, 2 M rows, 52 M edges, 8
+// columns, backward 644 with five wavefronts, 697 with six)
+template <typename T, int V, int G, int NP, int U, int VWM, bool MK>
+constexpr int agg_waves() { return V == 4 && (G == 16 || G == 32) && NP == 1 && U == 8 && VWM == VWM_NONE && !MK ? 8 : 1; }
+
 // One group of G lanes per work item; 64/G items per wavefront; 4 wavefronts per workgroup.
 // blockIdx.y selects a column tile of G*V*NP columns.
 // MK: an output mask is present (its values are fetched when the item starts; a separate instance so
@@ -309,7 +315,7 @@ constexpr int agg_many_ids(int G) { return G >= 16 ? 1 : 16 / G; }
 // COOP: 1: long items are shared out; 2: and split rows are summed whole (separate instances for the same reason)
 // IPL: neighbour ids per lane and batch
 template <typename T, int V, int G, int NP, int U, int VWM, bool MK, bool SH, int COOP, int IPL>
-__global__ void __launch_bounds__(256) k_aggregate(const AggArgs a) {
+__global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k_aggregate(const AggArgs a) {
     constexpr int NG = 64 / G;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
