@@ -325,15 +325,19 @@ bool vec_ok(gt_dtype t, const void *p, int64_t ld) {
     return p == nullptr || (aligned16(p) && ld % ve == 0);
 }
 
-// Whether a tensor of one row per edge is streamed past the caches, which keeps the vertices' rows in them: from about 100 MB on, below
-// which its next reader finds it there (us, element-wise product and aggregation with all derivatives, plain / streamed: power
-// law, 64 fp32 columns, 1.07 GB 1497 / 1220, 154 MB 285 / 265, 77 MB 120 / 134; uniform, 128 MB 236 / 227), with rows of whole lines or, since a
-// line of two rows is then written twice, long ones for the writer (33 columns 1262 / 1486, 304-byte rows 1022 / 1067, 480-byte rows
-// 2839 / 2566), and with rows of a line or more for the reader (33 columns 508 / 548, 304-byte rows 1022 / 985).
+// Whether a tensor of one row per edge is streamed past the caches, which keeps the vertices' rows in them (us, element-wise product and
+// aggregation with all derivatives; the reader alone is the tensor's next one and finds a small tensor in the last-level cache).
+//  * Rows of whole lines: read so from about 100 MB on (nowhere / reader / both: power law, 64 fp32 columns, 122 MB 180 / 175 / 191, 244 MB 375 / 370 / 347,
+//    1.07 GB 1435 / 1349 / 1208), written so from 224 MB on.
+//  * Other rows: read so from 224 MB on, if they are a line or more (100 columns, 191 MB 261 / 286 / 331, 305 MB 636 / 610 / 617; 33 columns and 304-byte
+//    rows, reader, 508 / 548 and 1022 / 985); written so where the part of a line at a row's end, which is then written twice, is little of the row
+//    and the tensor large (400-byte rows, 381 MB 711 / 682 / 690, 687 MB 918 / 924 / 1027; 480-byte rows 229 MB 330 / 334 / 361, 458 MB 822 / 774 / 744,
+//    1.1 GB 2308 / 2254 / 2196).
 bool edge_streams(int64_t E, const void *W, int64_t ldw, gt_dtype t, bool vec, bool write) {
-    const int64_t row = ldw * (int64_t)gt_dtype_size(t);
-    if (!vec || row < 128 || E * row < ((int64_t)96 << 20)) return false;
-    return !write || row >= 400 || (row % 128 == 0 && ((uintptr_t)W & 127) == 0);
+    const int64_t row = ldw * (int64_t)gt_dtype_size(t), MB = (int64_t)1 << 20;
+    if (!vec || row < 128) return false;
+    if (row % 128 == 0 && ((uintptr_t)W & 127) == 0) return E * row >= (write ? 224 : 96) * MB;
+    return (!write || row >= 440) && E * row >= (write ? 320 : 224) * MB;
 }
 
 // kind: 0 edge-out product, 1 edge-out broadcast, 2 edge-dot

@@ -45,14 +45,14 @@ def test_parts(F, dtype):
     assert torch.equal(dw, Xd[dst])
 
 
-@pytest.mark.parametrize("dtype,F", [(torch.float32, 64), (torch.float32, 60), (torch.float32, 132), (torch.bfloat16, 128), (torch.bfloat16, 72),
-                                     (torch.bfloat16, 520)], ids=str)
-def test_streamed_edge_tensor(dtype, F):
-    """Edge tensors just below and above 96 MiB (the larger is streamed past the caches; 60 columns for the reader only):
-    the same edges give the same results bit for bit, and all are within (n + 2) 2^-24 sum |terms| and one bf16 rounding of 64 bits."""
+@pytest.mark.parametrize("dtype,F,mib", [(torch.float32, 64, 96), (torch.float32, 64, 224), (torch.float32, 60, 224), (torch.float32, 116, 320),
+                                         (torch.bfloat16, 128, 96), (torch.bfloat16, 128, 224), (torch.bfloat16, 72, 224), (torch.bfloat16, 520, 320)], ids=str)
+def test_streamed_edge_tensor(dtype, F, mib):
+    """Edge tensors just below and above a line of the rule for streaming: rows of whole lines are read past the caches from 96 MiB on and
+    written past them from 224, others from 224 and, if long, 320.  The same edges give the same results bit for bit, and all are within (n + 2) 2^-24 sum |terms| and one bf16 rounding of 64 bits."""
     from paper_2305_17469_amd import binding as B
     es = 4 if dtype == torch.float32 else 2
-    n, E = 5000, (96 << 20) // (F * es) + 1000
+    n, E = 5000, (mib << 20) // (F * es) + 1000
     rng = np.random.default_rng(F)
     dst = torch.from_numpy(np.sort(rng.integers(0, n, E))).cuda()
     src = torch.from_numpy(rng.integers(0, n, E)).cuda()
@@ -65,7 +65,7 @@ def test_streamed_edge_tensor(dtype, F):
         return B.Graph(rowptr.int(), src[:m].int(), n)
 
     big, less = graph(E), graph(E - 2000)
-    announce("streamed", dtype, F, E)
+    announce("streamed", dtype, F, mib, E)
     r = 2.0 ** -8 if dtype == torch.bfloat16 else 0.0
     m = B.gt_neighbor_apply_fwd(big, "mul", Xs, Xd)
     p = Xs.double()[src] * Xd.double()[dst]
