@@ -205,5 +205,5 @@ int64_t gt_gemm_ws_tail_rows(gt_dtype dtype, int64_t K, int64_t lda, int vecA);
 gt_status gt_gemm_ws_launch(const GemmArgs &g, gt_dtype dtype, int transB, hipStream_t st);
 
 // Tall bf16 products past the weight-stationary kernels (gt_combine_rows.hip); no addend, row scale or split.
-bool gt_gemm_rows_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int64_t M, int64_t N, int64_t K, int vecA, int vecB, int vecC);
+bool gt_gemm_rows_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int vecA, int vecB, int vecC);
 gt_status gt_gemm_rows_launch(GemmArgs g, int transB, hipStream_t st);

@@ -200,16 +200,27 @@ gt_status launch_rows(const GemmArgs &g, hipStream_t st) {
 //  * K past 256 (tiled kernels): more than 128 columns (2^19 x 602 -> 256 435 / 310, transposed weights 1000 columns, 200 K rows -> 256 265 / 183,
 //    2 K rows, 602 -> 130 29 / 21); up to 128 columns, where half of the tile is padding, up to 50,000 rows (30 K rows, 602 -> 65
 //    29 / 22, 200 K rows 88 / 97).
-//  * Smaller K and fewer than 8,192 rows (tiled): more than 128 columns, or from 4,096 rows on (2 K rows, 200 -> 200 17 / 13, 64 -> 100 13.3 / 13.6;
-//    5 K rows, 256 -> 100 17 / 14).
-//  * Smaller K, more rows (weight-stationary, which holds 256 columns at a time and reads A once for each): more than 256 columns of more than
-//    128 terms up to 65,536 rows (30 K rows, 256 -> 300 28 / 19; 200 K rows 78 / 85), and, since rows leave this kernel 512 bytes at a time,
-//    large outputs whose rows are not aligned (2^19 rows, 256 -> 602 468 / 364, aligned 360 / 353, 128 -> 602 345 / 240; 200 K rows 141 / 140).
-bool gt_gemm_rows_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int64_t M, int64_t N, int64_t K, int vecA, int vecB, int vecC) {
+//  * Smaller K and fewer than 8,192 rows (tiled): from 4,096 rows on 0.53 to 0.74 of the time at any width; more than 128 columns from 2,000
+//    rows on, or where the output has as many elements (2 K rows, 100 -> 130 0.58 of the time, 1.5 K rows 1.30, -> 300 0.71; 1 K rows -> 300
+//    1.44, -> 602 0.61): below, the tiled kernel has more workgroups.
+//  * Smaller K, more rows (weight-stationary, which holds 256 columns at a time and reads A once for each), more than 256 columns:
+//    - more than 128 terms up to 65,536 rows (30 K rows, 256 -> 300 28 / 19; 70 K rows 1.07 of the time), unless the tiles are a round of
+//      workgroups and a part of the next (16 K rows, 200 -> 602, 375 tiles 16.3 / 17.6; -> 1001, 500 tiles 0.71 of the time);
+//    - large outputs whose rows are not aligned, since rows leave this kernel 512 bytes at a time: with up to 128 terms from 250 Mi elements
+//      on (2^19 rows, 128 -> 602 0.87 of the time, -> 402 1.00; 1 M rows -> 300 1.01, -> 402 0.90; 350 K rows, 128 -> 602, 201 Mi, 1.05), transposed
+//      weights from 200 Mi (2^19 rows, 128 -> 402 0.80, -> 602 0.67; 200 K rows, 100 -> 1001, 191 Mi, 1.03); with more terms
+//      transposed weights of more than 384 columns (2^19 rows, 256 -> 602 0.79 of the time, 200 -> 402 1.00; 1 M rows, 200 -> 300 1.09; weights as they are
+//      256 -> 402 1.10, -> 602 1.00).
+bool gt_gemm_rows_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int vecA, int vecB, int vecC) {
     if (dtype != GT_BF16 || c_dtype != GT_BF16 || transA || !vecA || !vecB || M < 1024 || N <= 64 || K < 64 || K >= ((int64_t)1 << 30)) return false;
     if (K > 256) return N > 128 || M <= 50000;
-    if (M < 8192) return N > 128 || M >= 4096;
-    return N > 256 && ((K > 128 && M <= 65536) || (!vecC && M * N >= ((int64_t)180 << 20)));
+    if (M < 8192) return M >= 4096 || (N > 128 && (M >= 2000 || M * N >= 420000));
+    if (N <= 256) return false;
+    const int64_t tiles = (M + BM - 1) / BM * ((N + BN - 1) / BN), Mi = (int64_t)1 << 20;
+    if (K > 128 && M <= 65536) return tiles <= 256 || tiles >= 448;
+    if (vecC) return false;
+    if (K > 128) return transB && N > 384 && M * N >= 200 * Mi;
+    return M * N >= (transB ? 200 : 250) * Mi;
 }
 
 gt_status gt_gemm_rows_launch(GemmArgs g, int transB, hipStream_t st) {

@@ -36,9 +36,10 @@ def _check(M, N, K, dtype, transB, bias, relu, ldc):
 
 
 @pytest.mark.parametrize("transB", [False, True], ids=["NN", "NT"])
-@pytest.mark.parametrize("M,N,K", [(1024, 129, 64), (1025, 256, 257), (1151, 257, 319), (4096, 65, 65), (4223, 130, 256), (8191, 200, 127),
-                                   (8192, 300, 129), (8193, 513, 255), (20001, 72, 602), (50001, 128, 602), (65537, 257, 200), (9001, 512, 1000),
-                                   (320001, 602, 66)])
+@pytest.mark.parametrize("M,N,K", [(1024, 129, 64), (1030, 602, 64), (1500, 279, 100), (1500, 281, 100), (2000, 129, 64), (1025, 256, 257), (1151, 257, 319),
+                                   (4095, 65, 65), (4096, 65, 65), (4223, 130, 256), (8191, 200, 127), (8192, 300, 129), (8193, 513, 255),
+                                   (16001, 602, 200), (20001, 72, 602), (50001, 128, 602), (65537, 257, 200), (9001, 512, 1000), (320001, 602, 66),
+                                   (350001, 602, 66), (440001, 602, 66), (350001, 602, 130)])
 def test_row_tiles(M, N, K, transB):
     v8 = (N + 7) // 8 * 8
     for bias, relu, ldc in ((True, True, N), (False, False, v8), (True, False, v8 + 8), (False, True, N + 1)):
