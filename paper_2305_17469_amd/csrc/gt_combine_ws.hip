@@ -365,6 +365,7 @@ __global__ void __launch_bounds__((ws_waves<T, NB, NS>() * 64), (ws_per_cu<T, NB
         // (scattering a vector's columns to their rows one by one put the lanes of a wavefront on two banks: 256 x 256 bf16 weights took
         // 25 us of a launch, 30,000 rows 40 -> 18 us.)  KQ patches along k per row of the LDS write, then along n: 64 bytes of a row of B.
         constexpr int KQ = KP / 4 < 16 ? KP / 4 : 16, RQ = BN / VE, TOTAL = KP / 4 * RQ;
+        static_assert(KP / 4 % KQ == 0, "the patches along k come in whole groups of KQ");
         for (int base = threadIdx.x; base < TOTAL; base += NT * 2) {
             uint4 v[2][4];
 #pragma unroll
@@ -556,6 +557,7 @@ __global__ void __launch_bounds__(256, (ws_x3_per_cu<NB, NS>())) k_gemm_ws_x3(co
     // quads in flight.
     if (g.vecB && !transB) {   // B[k][n]: patches of four k and four columns, transposed in registers (see k_gemm_ws)
         constexpr int KQ = KP / 4 < 16 ? KP / 4 : 16, RQ = BN / 4, TOTAL = KP / 4 * RQ;
+        static_assert(KP / 4 % KQ == 0, "the patches along k come in whole groups of KQ");
         for (int base = threadIdx.x; base < TOTAL; base += 256 * 2) {
             float4 v[2][4];
 #pragma unroll
