@@ -289,7 +289,7 @@ static inline int agg_xcd_run(int64_t gx) {
     return run;
 }
 
-// Instances with cooperative workgroups for the long items (single column tile)
+// Instances with cooperative workgroups for the long items
 template <int NP, int VWM>
 constexpr bool agg_coop() { return NP == 1 && VWM == 0; }
 
@@ -533,7 +533,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
             for (int o = G; o < 64; o <<= 1)
 #pragma unroll
                 for (int i = 0; i < V; ++i) acc[0][i] += __shfl_xor(acc[0][i], o, 64);
-            if (!one_wave) {   // uniform over the launch
+            if (!one_wave) {   // uniform over the workgroup
                 if (grp == 0) {
 #pragma unroll
                     for (int i = 0; i < V; ++i) red[wave][i * G + gl] = acc[0][i];
@@ -544,8 +544,8 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
             if (grp != 0) return;
             if (!one_wave)
 #pragma unroll
-            for (int i = 0; i < V; ++i)
-                acc[0][i] = ((red[0][i * G + gl] + red[1][i * G + gl]) + red[2][i * G + gl]) + red[3][i * G + gl];
+                for (int i = 0; i < V; ++i)
+                    acc[0][i] = ((red[0][i * G + gl] + red[1][i * G + gl]) + red[2][i * G + gl]) + red[3][i * G + gl];
         }
     }
     if (slot >= 0) {
@@ -785,8 +785,7 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
                     } else if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
                     else k_aggregate<T, V, G, NP, U, VWM, false, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
                 }
-            } else if (MANY > 1 && (
-                agg_long_batches(a, G, bytes))) {
+            } else if (MANY > 1 && agg_long_batches(a, G, bytes)) {
                 if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
                 else k_aggregate<T, V, G, NP, U, VWM, false, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
             } else {

@@ -452,7 +452,7 @@ gt_status gt_fused_run(const gt_graph *g, gt_reduce reduce, gt_dtype dtype, int6
         if (ws_bytes < need) return gt_fail(GT_ERR_WORKSPACE, "%s: ws_bytes %zu < required %zu", fn, ws_bytes, need);
     }
     AggArgs a{};
-    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len;
+    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long;
     a.rowptr = sc.rowptr; a.nbr = sc.nbr;
     a.coef = sc.wt; a.post_mode = 0;
     if (reduce == GT_MEAN) a.post_mode = 2;

@@ -216,7 +216,7 @@ __device__ inline int64_t rs_tile_of_block(int nblk) {   // consecutive tiles on
 }
 static inline unsigned rs_grid(int nblk) { return (unsigned)((nblk + 7) / 8 * 8); }
 
-// counts of one tile: hist[tile][256] (direct) or hist[256][nblk] (to be scanned)
+// counts of one tile, nb bits: hist[tile][256] (direct) or hist[1 << nb][nblk] (to be scanned)
 template <int WAVES, int CH>
 __global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, int64_t n, int shift, int nb, int32_t *hist, int nblk,
                                                         int direct) {
@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, in
     if (threadIdx.x < (direct ? 256 : 1 << nb)) hist[direct ? tile * 256 + threadIdx.x : (int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
 }
 
-template <int WAVES, int CH, bool EXTRA>
+template <int WAVES, int CH>
 constexpr size_t rs_lds_bytes() { return (size_t)rs_tile<WAVES, CH>() * 4 + (size_t)WAVES * 256 * 4 + 256 * 4; }
 
 // vals_in == nullptr means value = position (iota).  EXTRA: a second value travels along.
@@ -432,7 +432,7 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
             uint64_t m = __ballot(valid);
 #pragma unroll
             for (int b = 0; b < 8; ++b) {
-                    const bool bit = (digit >> b) & 1u;
+                const bool bit = (digit >> b) & 1u;
                 const uint64_t bal = __ballot(valid && bit);
                 m &= bit ? bal : ~bal;
             }
@@ -512,7 +512,8 @@ template <int WAVES, int CH, bool EXTRA>
 gt_status radix_pass_t(const uint32_t *kin, const uint32_t *vin, const uint32_t *ein, uint32_t *kout, uint32_t *vout, uint32_t *eout,
                        int64_t n, int shift, int nb, const SortTmp &t, hipStream_t st) {
     constexpr int64_t TILE = rs_tile<WAVES, CH>();
-    constexpr size_t lds = rs_lds_bytes<WAVES, CH, EXTRA>();
+    constexpr size_t lds = rs_lds_bytes<WAVES, CH>();
+    static_assert(lds <= 64 * 1024, "more needs the kernel's attribute set");
     const int nblk = (int)((n + TILE - 1) / TILE);
     const int direct = nblk <= RS_DIRECT;
     const unsigned grid = rs_grid(nblk);
@@ -522,9 +523,6 @@ gt_status radix_pass_t(const uint32_t *kin, const uint32_t *vin, const uint32_t 
         const gt_status s = scan_exclusive(t.hist, t.hist, (int64_t)nblk << nb, t.scan_tmp, st);
         if (s != GT_OK) return s;
     }
-    if (lds > 64 * 1024)
-        GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rs_scatter<WAVES, CH, EXTRA>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     k_rs_scatter<WAVES, CH, EXTRA><<<grid, WAVES * 64, lds, st>>>(kin, vin, ein, kout, vout, eout, n, shift, nb, t.hist, nblk, direct);
     GT_LAUNCH_CHECK("k_rs_scatter");
     return GT_OK;
