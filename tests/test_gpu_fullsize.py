@@ -160,7 +160,7 @@ def _check_full(got, ref, abs_terms, dtype, what):
 def test_aggregation_full_outputs_at_benchmark_size(which, widths):
     """gt_aggregate_fwd / gt_aggregate_bwd on the benchmark graphs at the widths the benchmark's
     layers aggregate at (config 2: both; config 3: the narrow last layer and the 256-wide hidden
-    layers, which run as column passes), symmetric normalisation, EVERY output element against
+    layers, which run in column tiles), symmetric normalisation, EVERY output element against
     the oracle."""
     from paper_2305_17469_amd import binding as B
     cfg = configs.reddit_like() if which == "c2" else configs.products_like()
@@ -251,29 +251,38 @@ def test_config3_full_size_bf16_power_law():
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_large_table_is_gathered_in_column_passes(dtype):
-    """A gathered table above the last-level cache size with rows of 512 bytes or more is
-    aggregated in 256-byte column passes; widths chosen so that the last pass is ragged.  Checked on
+def test_large_table_is_gathered_in_column_tiles(dtype):
+    """A gathered table above the last-level cache size, of rows that begin at lines and are more than 256 bytes
+    wide, is aggregated in column tiles; widths chosen so that the last tile is ragged.  Checked on
     sampled output rows (forward) and sampled source rows (transposed direction), all columns."""
     from paper_2305_17469_amd import binding as B
     from gt_inputs import graphs
     dev = torch.device("cuda:0")
-    F = 136 if dtype == "f32" else 264                      # 544 / 528 bytes per row: 2 full passes + 8 columns
+    F = 136 if dtype == "f32" else 264                      # 544 / 528 bytes per row: 2 full tiles + 8 columns
+    ld = 160 if dtype == "f32" else 320                     # (640 bytes: five lines)
     scale = 19 if dtype == "f32" else 20
     rp, ci = graphs.rmat_csr(scale, 12 if dtype == "f32" else 6, seed=12, self_loops=False)
-    n = rp.size - 1
-    # both conditions of the column-pass path: table above 256 MiB, at least 4 Mi edges
-    assert n * F * (4 if dtype == "f32" else 2) > (256 << 20) and ci.size >= (4 << 20)
-    announce("column passes:", dtype, "n", n, "F", F, "E", ci.size)
+    n, es = rp.size - 1, 4 if dtype == "f32" else 2
+    # what the tile rule asks of a skewed graph: half a gigabyte gathered, rows of whole lines; the table is beyond the cache
+    assert n * ld * es > (256 << 20) and ci.size * F * es >= 500_000_000 and ld * es % 128 == 0
+    announce("column tiles:", dtype, "n", n, "F", F, "E", ci.size)
     g = B.Graph(torch.from_numpy(rp).to(dev), torch.from_numpy(ci).to(dev), n)
     X = tensors.normal((n, F), seed=13)
     if dtype == "bf16":
         X = tensors.bf16_values(X)
-    Xd = _up(X, dtype, dev)
+    Xd = torch.zeros((n, ld), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device=dev)[:, :F]
+    Xd.copy_(_up(X, dtype, dev))
+    Yd = torch.empty_strided(Xd.shape, Xd.stride(), dtype=Xd.dtype, device=dev)
     rng = np.random.default_rng(14)
     deg_in, deg_out = np.diff(rp), np.bincount(ci, minlength=n)
     for reduce in ("sum", "mean"):
-        Y = B.gt_aggregate_fwd(g, reduce, Xd)
+        B.gt_trace_reset()
+        B.gt_trace_enable(True)
+        Y = B.gt_aggregate_fwd(g, reduce, Xd, Yd)
+        torch.cuda.synchronize()
+        B.gt_trace_enable(False)
+        assert [v[1:3] for v in B.gt_trace_variants()] == [(16, 1)]   # tiles of sixteen lanes
+        B.gt_trace_reset()
         rows = _sample(n, deg_in, 300, 8, rng)
         ref = oracle.aggregate_fwd(rp, ci, n, X, reduce, rows=rows)
         if dtype == "bf16":
