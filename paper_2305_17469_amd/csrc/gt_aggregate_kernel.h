@@ -702,7 +702,7 @@ static inline bool agg_wide_eight(const AggArgs &a, int G, double bytes) { retur
 //    bf16 columns 889 / 753, in 512-byte tiles 833).
 //  * Uniform graphs of few entries per row lose by tiles of whole wavefronts' rows as long as the table is beyond the L2s and not far beyond the
 //    last-level cache (degree 4, 66 K rows, 1024 fp32 columns 192 / 219, 131 K rows, 640 columns 237 / 264; 16 K rows, 1024 columns 51 / 41 and 1 M rows, 512 columns 1.00 / 0.84 gain
-//    all the same; 128 columns at any size 0.99 / 1.03), others by three or four tiles of such a table (262 K rows of degree 10, 224 columns
+//    all the same; 128 columns 0.99 / 1.03), others by three or four tiles of such a table (262 K rows of degree 10, 224 columns
 //    350 / 377, 300 K rows of degree 20, 192 columns 628 / 665).  So do gathers that look their coefficients up by entry, once per tile (200 K rows of
 //    degree 10, 160 columns, backward 433 / 516).
 //  * The two tiles of the first pair have to be nearly full (96 fp32 columns, power law, 262 K rows 267 / 278); a half empty last one of
@@ -727,11 +727,11 @@ static inline AggTiles agg_tiles(const AggArgs &a, bool shifted, int64_t nvec, s
     if (nvec < 28) return whole;
     if (!agg_skewed(a)) {
         if (!lines || a.eidx) return whole;
-        if (a.n_edges < 10 * a.n_items ? nvec <= 32 || (nvec >= 56 && a.table_bytes > 80 * MB && a.table_bytes < 600 * MB)
+        if (a.n_edges < 10 * a.n_items ? a.table_bytes < 600 * MB && (nvec <= 32 || (nvec >= 56 && a.table_bytes > 80 * MB))
                                       : nvec > 32 && nvec < 64 && a.table_bytes > (a.n_edges < 16 * a.n_items ? 80 : 140) * MB && a.table_bytes < 300 * MB)
             return whole;
         const bool few = a.n_long > 0 && a.n_items * 16 <= 1792 * 64;
-        return {16, a.n_edges >= 16 * a.n_items && a.table_bytes > 80 * MB ? 1 : 2, tiles % 2 == 0 && bytes < 0.3e9 ? 1 : 0, few};
+        return {16, a.n_edges >= 12 * a.n_items && a.table_bytes > 80 * MB ? 1 : 2, tiles % 2 == 0 && bytes < 0.3e9 ? 1 : 0, few};
     }
     if (bytes < 0.5e9) return whole;
     const int lg = tiles % 2 == 0 && a.table_bytes <= 600 * MB ? 1 : 0;
