@@ -207,3 +207,7 @@ gt_status gt_gemm_ws_launch(const GemmArgs &g, gt_dtype dtype, int transB, hipSt
 // Tall bf16 products past the weight-stationary kernels (gt_combine_rows.hip); no addend, row scale or split.
 bool gt_gemm_rows_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int vecA, int vecB, int vecC);
 gt_status gt_gemm_rows_launch(GemmArgs g, int transB, hipStream_t st);
+
+// Tall bf16 products whose weights fit the registers of a CU (gt_combine_reg.hip); no addend, row scale or split; rows of a mask aligned.
+bool gt_gemm_reg_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t lda, bool vec);
+gt_status gt_gemm_reg_launch(const GemmArgs &g, int transB, hipStream_t st);

@@ -740,15 +740,17 @@ gt_status gt_gemm_run(const char *fn, gt_dtype dtype, int transA, int transB, in
     int64_t tail = gt_gemm_ws_tail_rows(dtype, K, lda, g.vecA);
     if (!vec_mask && gt_gemm_ws_tail_rows(dtype, N, ldmask, 0) > tail) tail = gt_gemm_ws_tail_rows(dtype, N, ldmask, 0);
     if (dtype == GT_F32 && K > 128) tail = 0;
-    const bool rows_path = p.splits == 1 && !Cin && !rowscale &&
+    const bool reg_path = p.splits == 1 && !Cin && !rowscale && vec_mask && gt_gemm_reg_applicable(dtype, c_dtype, transA, transB, M, N, K, lda, g.vecA && g.vecB);
+    const bool rows_path = !reg_path && p.splits == 1 && !Cin && !rowscale &&
                            gt_gemm_rows_applicable(dtype, c_dtype, transA, transB, M, N, K, g.vecA, g.vecB, ((uintptr_t)C & 15) == 0 && ldc % 8 == 0);
-    const bool ws_path = !rows_path && p.splits == 1 && c_dtype == dtype && !Cin && !rowscale &&
+    const bool ws_path = !reg_path && !rows_path && p.splits == 1 && c_dtype == dtype && !Cin && !rowscale &&
                          gt_gemm_ws_applicable(dtype, transA, M - tail, N, K, g.vecA, x3);
     if (ws_path) {
         g.tail = (int)tail;
         g.M = M - tail;
     }
-    gt_status s = rows_path ? gt_gemm_rows_launch(g, transB, st)
+    gt_status s = reg_path ? gt_gemm_reg_launch(g, transB, st)
+                  : rows_path ? gt_gemm_rows_launch(g, transB, st)
                   : ws_path ? gt_gemm_ws_launch(g, dtype, transB, st)
                   : tn256 ? launch_tn256(g, p.splits, st)
                   : x3 ? gt_gemm_x3_launch(g, transA, transB, p.splits, st)
