@@ -8,6 +8,80 @@ size_t gt_aggregate_ws_bytes(const gt_graph *g, int64_t F) {
     return gt_align_up((size_t)parts * (size_t)ldp * 4);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Rows gathered from whole lines.  A gather beyond the L2s costs what it has of lines: a row of 94 bytes at a stride of 94 lies in
+// 1.73 of them on average, at 96 in 1.5, at 128 in one.  Where a uniform graph reads every row often enough, the table is copied
+// to such a stride (64 bytes for rows of up to 64, 128 for up to 128) into the caller's workspace before it is gathered.
+// ---------------------------------------------------------------------------------------------
+namespace {
+
+// Lines that a row of `rb` bytes lies in, on average over the rows of a table
+double mean_lines(uintptr_t base, int64_t stride, int64_t rb) {
+    int64_t step = 128;
+    for (int64_t b = stride % 128; b;) { const int64_t r = step % b; step = b; b = r; }   // gcd(stride, 128)
+    int64_t lines = 0, n = 0;
+    for (int64_t o = (int64_t)(base % (uintptr_t)step); o < 128; o += step, ++n) lines += (o % 128 + rb + 127) / 128;
+    return (double)lines / (double)n;
+}
+
+// Stride (bytes) of the copy that a gather of rows of `rb` bytes from `lines` lines each would be made from, or 0.  What the copy saves is lines of
+// misses (10 TB/s of them), what it costs are its bytes (4.5 TB/s); it has to be clearly ahead, and the table well past the L2s.  us, both
+// directions of the gather as it is / copied: 1 M rows of degree 16, 47 bf16 columns 1026 / 822, of degree 8 601 / 531, 61 columns 1175 / 845, 25 columns 840 /
+// 765; 300 K rows of degree 20, 47 columns 295 / 268; 1 M rows of degree 4, 47 columns 365 / 369; 65 K rows of degree 25 (6 MB) 68 / 70.
+// Power-law graphs find the rows they read most in the L2s at any stride (1 M rows of degree 16, 47 bf16 columns 633 / 640).
+int64_t repack_stride(const gt_sched &sc, int64_t n_in, int64_t n_edges, int64_t rb, double lines) {
+    if (rb <= 32 || rb > 128 || n_in * rb < ((int64_t)24 << 20) || agg_skewed(sc.n_splits, sc.n_long, sc.n_items)) return 0;
+    const int64_t stride = rb <= 64 ? 64 : 128;
+    return (double)n_edges * (lines - 1.0) * 30.0 > (double)n_in * (double)(rb + stride) ? stride : 0;
+}
+
+// out[row] (stride `stride`) = in[row] (stride `ld`), rb bytes each; L lanes per row, each 16 bytes, the last that the row needs ending with it (no
+// alignment past the elements').  Bound by memory.
+template <int L>
+__global__ void __launch_bounds__(256) k_repack(const unsigned char *in, int64_t ld, int rb, int64_t rows, unsigned char *out) {
+    const int l = threadIdx.x % L;
+    if (l * 16 >= rb) return;
+    const int off = l * 16 + 16 <= rb ? l * 16 : rb - 16;
+    constexpr int RPB = 256 / L;
+    const int64_t r0 = (int64_t)blockIdx.x * RPB * 4 + threadIdx.x / L;
+    uint4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t r = r0 + i * RPB < rows ? r0 + i * RPB : rows - 1;
+        __builtin_memcpy(&v[i], in + r * ld + off, 16);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t r = r0 + i * RPB;
+        if (r < rows) __builtin_memcpy(out + r * (L * 16) + off, &v[i], 16);
+    }
+}
+
+}  // namespace
+
+// Room for such a copy at width F, of whichever direction it may serve; 0 where no stride of the caller's could make it pay.
+size_t gt_aggregate_repack_bytes(const gt_graph *g, int64_t F, gt_dtype t) {
+    const int64_t rb = F * (int64_t)gt_dtype_size(t);
+    const double most = 1.0 + (double)(rb - 2) / 128.0;   // rows at every element of a line
+    const int64_t f = repack_stride(g->fwd, g->n_src, g->n_edges, rb, most) * g->n_src, b = repack_stride(g->bwd, g->n_dst, g->n_edges, rb, most) * g->n_dst;
+    return (size_t)(f > b ? f : b);
+}
+
+// Row stride (elements) of a table that the library writes itself and then gathers, `transposed` or not: 16-byte padding, or the next multiple of 64 or 128 bytes where
+// a uniform graph's rows then lie in fewer lines (1 M rows of degree 16, one direction, 47 bf16 columns at 96 bytes 467 us, at 128 364; 41 fp32 columns at 176
+// bytes 683, at 192 621; 101 bf16 columns at 208 bytes 755, at 256 623).
+int64_t gt_aggregate_table_ld(const gt_graph *g, bool transposed, int64_t F, gt_dtype t) {
+    const int64_t es = (int64_t)gt_dtype_size(t), rb = F * es, pad = (rb + 15) / 16 * 16;
+    const gt_sched &sc = transposed ? g->bwd : g->fwd;
+    if (rb <= 32 || agg_skewed(sc.n_splits, sc.n_long, sc.n_items)) return pad / es;
+    int64_t best = pad;
+    for (const int64_t to : {64, 128}) {
+        const int64_t s = (pad + to - 1) / to * to;
+        if (mean_lines(0, s, rb) < mean_lines(0, best, rb) - 0.01) best = s;
+    }
+    return best / es;
+}
+
 gt_status gt_agg_launch(const AggArgs &a, gt_dtype t, bool vec, hipStream_t st, bool by_element) {
     if (by_element) return t == GT_F32 ? dispatch<float, 1>(a, st) : dispatch<bf16_t, 1>(a, st);
     return t == GT_F32 ? agg_dispatch<float>(a, vec, st) : agg_dispatch<bf16_t>(a, vec, st);
@@ -45,6 +119,17 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
         if (ws_bytes < need) return gt_fail(GT_ERR_WORKSPACE, "%s: ws_bytes %zu < required %zu", fn, ws_bytes, need);
     }
 
+    const int64_t rb = F * (int64_t)es, stride = repack_stride(sc, n_in, g->n_edges, rb, mean_lines((uintptr_t)X, ldx * (int64_t)es, rb));
+    if (stride && ws && ((uintptr_t)ws & 255) == 0 && ws_bytes >= need + (size_t)(n_in * stride)) {
+        unsigned char *copy = static_cast<unsigned char *>(ws) + need;
+        const unsigned blocks = (unsigned)((n_in + 1024 / (stride / 16) - 1) / (1024 / (stride / 16)));
+        if (stride == 64) k_repack<4><<<blocks, 256, 0, st>>>(static_cast<const unsigned char *>(X), ldx * (int64_t)es, (int)rb, n_in, copy);
+        else k_repack<8><<<blocks, 256, 0, st>>>(static_cast<const unsigned char *>(X), ldx * (int64_t)es, (int)rb, n_in, copy);
+        GT_LAUNCH_CHECK("k_repack");
+        X = copy;
+        ldx = stride / (int64_t)es;
+    }
+
     AggArgs a{};
     a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len;
     a.rowptr = sc.rowptr; a.nbr = sc.nbr;
@@ -76,7 +161,8 @@ extern "C" gt_status gt_aggregate_ws_size(const gt_graph *g, int64_t F, size_t *
     if (!g || !ws_bytes) return gt_fail(GT_ERR_INVALID_ARG, "gt_aggregate_ws_size: null argument");
     if (F < 0) return gt_fail(GT_ERR_INVALID_ARG, "gt_aggregate_ws_size: F < 0");
     const bool any = g->fwd.n_partials > 0 || g->bwd.n_partials > 0;
-    *ws_bytes = any ? gt_aggregate_ws_bytes(g, F) : 0;
+    const size_t c16 = gt_aggregate_repack_bytes(g, F, GT_BF16), c32 = gt_aggregate_repack_bytes(g, F, GT_F32);   // (the type is not known here)
+    *ws_bytes = (any ? gt_aggregate_ws_bytes(g, F) : 0) + (c16 > c32 ? c16 : c32);
     return GT_OK;
 }
 
@@ -149,5 +235,5 @@ extern "C" gt_status gt_aggregate_fwd_static(const gt_graph *g, gt_reduce reduce
     // every partial slot is written by its work item before the second kernel reads it: nothing in
     // the array has to start at zero; kernel timing is off for this call (it would create events)
     return gt_aggregate_run(g, false, reduce, dtype, dtype, F, X, ldx, Y, ldy, nullptr, GT_ACT_NONE, ws,
-                            GT_STATIC_SCRATCH_BYTES, (hipStream_t)stream, false);
+                            need, (hipStream_t)stream, false);
 }

@@ -110,6 +110,8 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
 // pad_out: the output rows are padded and the padding is the library's to write (see gt_layer_desc.pad_writable)
 
 size_t gt_aggregate_ws_bytes(const gt_graph *g, int64_t F);
+size_t gt_aggregate_repack_bytes(const gt_graph *g, int64_t F, gt_dtype t);   // optional, after those
+int64_t gt_aggregate_table_ld(const gt_graph *g, bool transposed, int64_t F, gt_dtype t);
 
 // fused aggregation-first forward (gt_fused.hip): Y = act((A X) W + b) without writing A X
 bool gt_fused_applicable(gt_dtype dtype, int64_t in_dim, int64_t out_dim);

@@ -207,16 +207,17 @@ int64_t pad_ld(int64_t F, gt_dtype t) {
 
 struct LayerLayout {
     // scratch regions (bytes offsets); forward and backward use the same buffer at different times
-    size_t T;        // [n_src, ldo]  X W (combination-first forward)
-    size_t dZ;       // [n_dst, ldo]
+    size_t T;        // [n_src, ldt]  X W (combination-first forward)
+    size_t dZ;       // [n_dst, ldz]
     size_t S;        // [n_src, ldo]  A^T dZ
-    size_t dM;       // [n_dst, ldi]  dZ W^T
+    size_t dM;       // [n_dst, ldm]  dZ W^T
     size_t colsum;   // fp32 [ceil(n_dst / cs_rows(n_dst)), out]
     size_t agg_ws;   // aggregation partial rows
     size_t gemm_ws;  // split-k partials
     size_t total;
     size_t saved;    // bytes of `saved`: M = A X, [n_dst, ldi]
-    int64_t ldi, ldo;
+    int64_t ldi, ldo;        // rows padded to 16 bytes
+    int64_t ldt, ldz, ldm;   // of the tables that an aggregation gathers: rows in as few lines as possible
     size_t agg_ws_bytes, gemm_ws_bytes;
 };
 
@@ -225,15 +226,19 @@ LayerLayout layer_layout(const gt_graph *g, const gt_layer_desc *d) {
     const size_t es = gt_dtype_size(d->dtype);
     L.ldi = pad_ld(d->in_dim, d->dtype);
     L.ldo = pad_ld(d->out_dim, d->dtype);
+    L.ldt = gt_aggregate_table_ld(g, false, d->out_dim, d->dtype);
+    L.ldz = gt_aggregate_table_ld(g, true, d->out_dim, d->dtype);
+    L.ldm = gt_aggregate_table_ld(g, true, d->in_dim, d->dtype);
     size_t off = 0;
     auto take = [&](size_t b) { size_t o = off; off += gt_align_up(b ? b : 4); return o; };
-    L.T = take((size_t)g->n_src * L.ldo * es);
-    L.dZ = take((size_t)g->n_dst * L.ldo * es);
+    L.T = take((size_t)g->n_src * L.ldt * es);
+    L.dZ = take((size_t)g->n_dst * L.ldz * es);
     L.S = L.T;   // never live together: T belongs to the forward call, S to the backward call
-    L.dM = take((size_t)g->n_dst * L.ldi * es);
+    L.dM = take((size_t)g->n_dst * L.ldm * es);
     L.colsum = take((size_t)((g->n_dst + cs_rows(g->n_dst) - 1) / cs_rows(g->n_dst) + 1) * d->out_dim * 4);
     const int64_t fmax = d->in_dim > d->out_dim ? d->in_dim : d->out_dim;
-    L.agg_ws_bytes = gt_aggregate_ws_bytes(g, fmax);
+    const size_t ci = gt_aggregate_repack_bytes(g, d->in_dim, d->dtype), co = gt_aggregate_repack_bytes(g, d->out_dim, d->dtype);
+    L.agg_ws_bytes = gt_aggregate_ws_bytes(g, fmax) + (ci > co ? ci : co);
     L.agg_ws = take(L.agg_ws_bytes);
     // split-k partials: the largest need over every product either order may run
     L.gemm_ws_bytes = 0;
@@ -485,11 +490,11 @@ extern "C" gt_status gt_layer_fwd(const gt_graph *g, const gt_layer_desc *d, gt_
         // T = X W on n_src rows, then the aggregation at width out_dim with bias and activation
         // applied as the row is written
         void *T = at(scratch, L.T);
-        s = gt_gemm_run(fn, t, 0, 0, g->n_src, fo, fi, X, ldx, W, fo, nullptr, nullptr, GT_ACT_NONE, nullptr, 0, T, L.ldo,
+        s = gt_gemm_run(fn, t, 0, 0, g->n_src, fo, fi, X, ldx, W, fo, nullptr, nullptr, GT_ACT_NONE, nullptr, 0, T, L.ldt,
                         t, gws, L.gemm_ws_bytes, st, nullptr, 0, nullptr, /*pad_c (own buffer)*/ true);
         if (s != GT_OK) return s;
         const bool fuse = !d->has_root;
-        s = gt_aggregate_run(g, false, d->reduce, t, t, fo, T, L.ldo, Y, ldy, fuse ? b : nullptr,
+        s = gt_aggregate_run(g, false, d->reduce, t, t, fo, T, L.ldt, Y, ldy, fuse ? b : nullptr,
                              fuse ? d->act : GT_ACT_NONE, at(scratch, L.agg_ws), L.agg_ws_bytes, st, true, nullptr, 0,
                              pad_user);
         if (s != GT_OK || fuse) return s;
@@ -559,9 +564,9 @@ extern "C" gt_status gt_layer_bwd(const gt_graph *g, const gt_layer_desc *d, gt_
     float *partial = static_cast<float *>(at(scratch, L.colsum));
     if (d->act == GT_ACT_RELU && !d->dy_is_dz) {
         void *z = at(scratch, L.dZ);
-        s = (t == GT_F32) ? mask_colsum<float>(dY, lddy, Y, ldy, z, L.ldo, g->n_dst, fo, partial, db, st)
-                          : mask_colsum<bf16_t>(dY, lddy, Y, ldy, z, L.ldo, g->n_dst, fo, partial, db, st);
-        dZ = z; lddz = L.ldo;
+        s = (t == GT_F32) ? mask_colsum<float>(dY, lddy, Y, ldy, z, L.ldz, g->n_dst, fo, partial, db, st)
+                          : mask_colsum<bf16_t>(dY, lddy, Y, ldy, z, L.ldz, g->n_dst, fo, partial, db, st);
+        dZ = z; lddz = L.ldz;
     } else if (db) {
         // dZ is dY as it is.  Its column sums come for free from a weight-gradient product that streams
         // dZ as its second operand (the root term's, or (A X)^T dZ); only a combination-first forward
@@ -615,10 +620,10 @@ extern "C" gt_status gt_layer_bwd(const gt_graph *g, const gt_layer_desc *d, gt_
     } else {
         // dM = dZ W^T (the combination's derivative uses the transposed weight), dX = A^T dM
         void *dM = at(scratch, L.dM);
-        s = gt_gemm_run(fn, t, 0, 1, g->n_dst, fi, fo, dZ, lddz, W, fo, nullptr, nullptr, GT_ACT_NONE, nullptr, 0, dM, L.ldi,
+        s = gt_gemm_run(fn, t, 0, 1, g->n_dst, fi, fo, dZ, lddz, W, fo, nullptr, nullptr, GT_ACT_NONE, nullptr, 0, dM, L.ldm,
                         t, gws, L.gemm_ws_bytes, st, nullptr, 0, nullptr, /*pad_c (own buffer)*/ true);
         if (s != GT_OK) return s;
-        s = gt_aggregate_run(g, true, d->reduce, t, t, fi, dM, L.ldi, dX, lddx, nullptr, GT_ACT_NONE, aws, L.agg_ws_bytes, st,
+        s = gt_aggregate_run(g, true, d->reduce, t, t, fi, dM, L.ldm, dX, lddx, nullptr, GT_ACT_NONE, aws, L.agg_ws_bytes, st,
                              true, mk, ldx, d->pad_writable != 0);
     }
     if (s != GT_OK) return s;
