@@ -40,20 +40,20 @@ int64_t repack_stride(const gt_sched &sc, int64_t n_in, int64_t n_edges, int64_t
 template <int L>
 __global__ void __launch_bounds__(256) k_repack(const unsigned char *in, int64_t ld, int rb, int64_t rows, unsigned char *out) {
     const int l = threadIdx.x % L;
-    if (l * 16 >= rb) return;
-    const int off = l * 16 + 16 <= rb ? l * 16 : rb - 16;
+    const int off = l * 16 + 16 <= rb ? l * 16 : rb - 16, to = l * 16 < rb ? off : l * 16;
     constexpr int RPB = 256 / L;
     const int64_t r0 = (int64_t)blockIdx.x * RPB * 4 + threadIdx.x / L;
-    uint4 v[4];
+    typedef uint32_t vec __attribute__((ext_vector_type(4), aligned(2)));
+    vec v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int64_t r = r0 + i * RPB < rows ? r0 + i * RPB : rows - 1;
-        __builtin_memcpy(&v[i], in + r * ld + off, 16);
+        v[i] = *reinterpret_cast<const vec *>(in + r * ld + off);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int64_t r = r0 + i * RPB;
-        if (r < rows) __builtin_memcpy(out + r * (L * 16) + off, &v[i], 16);
+        if (r < rows) *reinterpret_cast<vec *>(out + r * (L * 16) + to) = v[i];
     }
 }
 
