@@ -434,6 +434,182 @@ constexpr size_t tn_lds_bytes() {
     return tiles > stages ? tiles : stages;
 }
 
+// The same for outputs past 256 x 256 and for operands without alignment: a workgroup of eight wavefronts owns 80 MFMA blocks (160 accumulators a
+// lane), so that the operands are read in fewer pieces (602 x 256: two tiles of 320 rows instead of three of 256, 602 x 100: one of 640 x 128
+// instead of five of 128 x 128).  Tiles of 32 k have two buffers in LDS and one set of registers: a tile is put into LDS while the one before it
+// is multiplied, A's patches and then B's, each followed at once by the loads of the tile after, so that the CU's queue
+// towards the L2 never runs dry.  Per step of 32 k a CU reads 36 KB and multiplies for 1,280 clocks; 2^19 rows take 1.7 us a step (602 x 256: 219 us,
+// 4.1 TB/s, 740 TFLOP/s; three tiles of 256 x 256 took 334, contiguous operands 596).  fp32 partial tiles leave from the registers, 128 bytes per half wavefront.
+template <int TM, int TN, int WGM, int WGN>
+__global__ void __launch_bounds__(512, 2) k_gemm_tn_wide(const GemmArgs g) {
+    constexpr int KT = 32, KQ = KT / 4, STR = KT + 8, BM = TM * WGM * 32, BN = TN * WGN * 32;
+    constexpr int PR = (BM + BN + 511) / 512;                        // patches (4 k of 8 columns) per thread; the first BM are A's
+    static_assert(WGM * WGN == 8 && BM % 64 == 0 && PR <= 2 && 2 * (BM + BN) * STR * 2 <= 160 * 1024, "tile");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    bf16_t *Ls = reinterpret_cast<bf16_t *>(smem);                   // [2][BM + BN][STR]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, h = lane >> 5;
+    const int wm = wave / WGN, wn = wave % WGN;
+    int tile_m, tile_n, split;
+    if (!gemm_tile_of_block(g, tile_m, tile_n, split)) return;
+    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+    const int64_t kbeg = (int64_t)split * g.k_per_split;
+    const int64_t kend = (kbeg + g.k_per_split < g.K) ? kbeg + g.k_per_split : g.K;
+
+    // patch i of this thread: operand (a wavefront's patches are one operand's: BM is a multiple of 64) and column
+    const int kq = threadIdx.x % KQ;
+    bool isB[PR], any[PR];
+    uint32_t off[PR];           // bytes from the operand's row k0 on
+    int dst[PR];
+#pragma unroll
+    for (int i = 0; i < PR; ++i) {
+        const int w0 = __builtin_amdgcn_readfirstlane(threadIdx.x) + 512 * i;
+        isB[i] = w0 >= BM;
+        any[i] = w0 < BM + BN;
+        const int octet = (threadIdx.x + 512 * i) / KQ;   // of BM / 8 + BN / 8
+        const int64_t c = isB[i] ? n0 + (octet - BM / 8) * 8 : m0 + octet * 8, lim = isB[i] ? g.N : g.M;
+        off[i] = (uint32_t)(kq * 4 * (isB[i] ? g.ldb : g.lda) + (any[i] && c < lim ? c : 0)) * 2;
+        dst[i] = (octet * 8) * STR + kq * 4;
+    }
+    floatx16 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
+    const bool do_cs = g.colsum && tile_m == 0;
+    float cs[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs[e] = 0.0f;
+
+    typedef uint32_t vec __attribute__((ext_vector_type(4), aligned(2)));
+    vec r[PR][4];
+    // The tile with the matrix's last row: rows past it repeat it, and a vector that would leave the matrix begins earlier.
+    auto at_end = [&](int i, int64_t k, int64_t &e, int64_t &last) {   // element where the vector of row k begins, and the last where one may
+        const int64_t ld = isB[i] ? g.ldb : g.lda, lim = isB[i] ? g.N : g.M;
+        e = k * ld + (int64_t)(off[i] / 2) - kq * 4 * ld;
+        last = (g.K - 1) * ld + lim - 8;
+    };
+    auto fetch = [&](int i, int64_t k0) {
+        const char *P = static_cast<const char *>(isB[i] ? g.B : g.A);
+        const int64_t ld = isB[i] ? g.ldb : g.lda;
+        if (k0 + KT < g.K) {   // uniform
+            P += k0 * ld * 2;
+#pragma unroll
+            for (int dk = 0; dk < 4; ++dk) r[i][dk] = *reinterpret_cast<const vec *>(P + dk * ld * 2 + off[i]);
+        } else {
+#pragma unroll
+            for (int dk = 0; dk < 4; ++dk) {
+                const int64_t k = k0 + kq * 4 + dk;
+                int64_t e, last;
+                at_end(i, k < g.K ? k : g.K - 1, e, last);
+                r[i][dk] = *reinterpret_cast<const vec *>(P + (e < last ? e : last) * 2);
+            }
+        }
+    };
+    auto put = [&](int i, int64_t k0, bf16_t *buf) {
+        if (k0 + KT > kend || k0 + KT >= g.K) {   // uniform: rows past the range are zeros, and a vector that was moved back to stay inside the matrix is put right
+#pragma unroll
+            for (int dk = 0; dk < 4; ++dk) {
+                const int64_t k = k0 + kq * 4 + dk;
+                vec &v = r[i][dk];
+                if (k >= kend) v = vec{0, 0, 0, 0};
+                else if (k == g.K - 1) {
+                    int64_t e, last;
+                    at_end(i, k, e, last);
+                    for (; e > last; --e) { v.x = v.x >> 16 | v.y << 16; v.y = v.y >> 16 | v.z << 16; v.z = v.z >> 16 | v.w << 16; v.w >>= 16; }
+                }
+            }
+        }
+        // (columns past the matrix hold anything: they only enter results that are not stored)
+        uint32_t w[4][4];
+#pragma unroll
+        for (int dk = 0; dk < 4; ++dk)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[dk][c] = r[i][dk][c];
+        if (do_cs && isB[i]) {
+#pragma unroll
+            for (int dk = 0; dk < 4; ++dk)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    cs[2 * c] += __uint_as_float(w[dk][c] << 16);
+                    cs[2 * c + 1] += __uint_as_float(w[dk][c] & 0xffff0000u);
+                }
+        }
+        bf16_t *d = buf + dst[i];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {   // columns 2c and 2c + 1 of the patch: their four k as one 8-byte run each
+            *reinterpret_cast<uint2 *>(d + (2 * c) * STR) = make_uint2(tn_lo(w[0][c], w[1][c]), tn_lo(w[2][c], w[3][c]));
+            *reinterpret_cast<uint2 *>(d + (2 * c + 1) * STR) = make_uint2(tn_hi(w[0][c], w[1][c]), tn_hi(w[2][c], w[3][c]));
+        }
+    };
+    // the next tile from registers to LDS, and the loads of the one after it
+    auto pass = [&](int64_t k0, bf16_t *buf) {
+#pragma unroll
+        for (int i = 0; i < PR; ++i) {
+            if (i * 512 + 512 > BM + BN && !any[i]) continue;   // whole wavefronts
+            put(i, k0, buf);
+            fetch(i, k0 + KT);
+        }
+    };
+    const bool live = m0 + wm * TM * 32 < g.M && n0 + wn * TN * 32 < g.N;   // a wavefront past the output multiplies nothing
+    auto multiply = [&](const bf16_t *buf) {
+        if (!live) return;
+        const bf16_t *A = buf + (wm * TM * 32 + l32) * STR + h * 8, *B = buf + (BM + wn * TN * 32 + l32) * STR + h * 8;
+#pragma unroll
+        for (int s = 0; s < KT / 16; ++s) {
+            bf16x8 af[TM], bf[TN];
+#pragma unroll
+            for (int a = 0; a < TM; ++a) af[a] = *reinterpret_cast<const bf16x8 *>(A + a * 32 * STR + s * 16);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) bf[b] = *reinterpret_cast<const bf16x8 *>(B + b * 32 * STR + s * 16);
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < PR; ++i) fetch(i, kbeg);
+    pass(kbeg, Ls);
+    __syncthreads();
+    int buf = 0;
+    for (int64_t k0 = kbeg; k0 < kend; k0 += KT, buf ^= 1) {
+        multiply(Ls + buf * (BM + BN) * STR);
+        pass(k0 + KT, Ls + (buf ^ 1) * (BM + BN) * STR);   // (past kend: zeros that nobody multiplies)
+        __syncthreads();
+    }
+    if (do_cs) {   // uniform over the workgroup: the KQ k-groups that share a column octet are added in order
+        float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+        for (int i = 0; i < PR; ++i)
+            if (any[i] && isB[i]) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) red[(threadIdx.x + 512 * i - BM) * 8 + e] = cs[e];
+            }
+        __syncthreads();
+        if ((int)threadIdx.x < BN) {
+            const int q = threadIdx.x >> 3, e = threadIdx.x & 7;
+            float sum = 0.0f;
+            for (int k = 0; k < KQ; ++k) sum += red[(q * KQ + k) * 8 + e];
+            if (n0 + threadIdx.x < g.N) g.colsum[(int64_t)split * g.N + n0 + threadIdx.x] = sum;
+        }
+    }
+    float *out = static_cast<float *>(g.C) + (int64_t)split * g.M * g.N;
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            const int64_t col = n0 + (wn * TN + b) * 32 + l32;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int64_t row = m0 + (wm * TM + a) * 32 + 8 * (i / 4) + 4 * h + i % 4;
+                if (row < g.M && col < g.N) out[row * g.N + col] = acc[a][b][i];
+            }
+        }
+}
+
 // out[c] = sum over the splits' column sums, four columns per workgroup (block = which four), 64 lanes per column stride over
 // the splits, the lanes' sums are added in lane order (fixed order; a single thread per column walking
 // a few hundred splits one after the other took 0.1 ms)
@@ -576,9 +752,49 @@ bool tn256_shape(int transA, int transB, int64_t M, int64_t N, int64_t K) {
     return tiles <= 8 && 5 * reads(128) >= 8 * reads(256) && K >= (tiles >= 4 ? 65536 : 98304);
 }
 
-SplitPlan plan_split(int transA, int64_t M, int64_t N, int64_t K, bool x3, bool tn256 = false) {
+// Tiles of k_gemm_tn_wide for an output: the shape that covers it in the fewest tiles, of those the smallest.  No tile: bm 0.
+struct WideTile { int64_t bm, bn; };
+WideTile tn_wide_tile(int64_t M, int64_t N) {
+    WideTile best{0, 0};
+    int64_t most = 0;
+    for (const WideTile t : {WideTile{320, 256}, WideTile{256, 320}, WideTile{640, 128}}) {
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (!best.bm || tiles < most) { best = t; most = tiles; }
+    }
+    return best;
+}
+int64_t tn_wide_tiles(int64_t M, int64_t N) {
+    const WideTile t = tn_wide_tile(M, N);
+    return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+}
+// Where it covers the output in fewer tiles than 256 x 256 ones do, over reductions of 98,304 rows and more (us, the other bf16 weight gradients / this one: 602 x
+// 256 over 50,000 rows 50 / 51, 131,072 98 / 88, 2^19 334 / 250; 300 x 300 40 / 47, 81 / 65, 347 / 202; 602 x 100 33 / 46, 61 / 60, 231 / 169), from 16,384 on where those
+// would be more than six (1024 x 320 over 20,000 rows 52 / 45, 2^19 726 / 434); in as many tiles it is even or behind (256 x 256 over 2^21 rows 460 / 471,
+// 512 x 256 over 2^19 242 / 251).  Operands without alignment (vec false), which the others read by the element in LDS: from 49,152 rows on, in as
+// many tiles as well from 98,304 unless the output is one tile of 128 x 128 (602 x 256 over 50,000 rows 66 / 50, 2^19 596 / 237; 100 x 256 30 / 33, 125 / 95;
+// 100 x 100 over 2^19 rows 73 / 79).
+bool tn_wide_shape(int transA, int transB, int64_t M, int64_t N, int64_t K, bool vec) {
+    if (!transA || transB || M <= 64 || N <= 64 || (double)M * (double)N * (double)K < 268435456.0) return false;
+    const int64_t tiles = tn_wide_tiles(M, N), tiles256 = tn256_tiles(M, N);
+    if (tiles > 8) return false;
+    if (tiles < tiles256) return K >= (tiles256 > 6 ? 16384 : vec ? 98304 : 49152);
+    return !vec && K >= 98304 && (M > 128 || N > 128);
+}
+
+SplitPlan plan_split(int transA, int64_t M, int64_t N, int64_t K, bool x3, bool tn256 = false, bool wide = false) {
     TileShape t = pick_tile(M, N, K);
     if (x3) { gt_gemm_x3_tile(M, N, &t.bm, &t.bn); t.small = false; }
+    if (wide) {
+        const int64_t tiles = tn_wide_tiles(M, N);
+        SplitPlan p{1, (K + KT - 1) / KT * KT};
+        int64_t want = 256 / tiles, max_by_len = K / (8 * KT);
+        if (want > max_by_len) want = max_by_len;           // (at least 32: always partial tiles)
+        if (tiles > 1) want = want / 8 * 8;                 // whole k-ranges per XCD (gemm_split_xcd)
+        const int64_t kps = ((K + want - 1) / want + KT - 1) / KT * KT;
+        p.splits = (int)((K + kps - 1) / kps);
+        p.k_per_split = kps;
+        return p;
+    }
     if (tn256) {
         SplitPlan p{1, (K + KT - 1) / KT * KT};
         int64_t want = 256 / tn256_tiles(M, N), max_by_len = K / (4 * KT);
@@ -662,6 +878,22 @@ gt_status launch_tn256(GemmArgs g, int splits, hipStream_t st) {
     return GT_OK;
 }
 
+template <int TM, int TN, int WGM, int WGN>
+gt_status launch_tn_wide_as(const GemmArgs &g, int splits, hipStream_t st) {
+    constexpr size_t lds = (size_t)2 * (TM * WGM + TN * WGN) * 32 * 40 * 2;
+    GT_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_tn_wide<TM, TN, WGM, WGN>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    k_gemm_tn_wide<TM, TN, WGM, WGN><<<dim3((unsigned)(g.ntm * g.ntn), 1, (unsigned)splits), 512, lds, st>>>(g);
+    GT_LAUNCH_CHECK("k_gemm_tn_wide");
+    return GT_OK;
+}
+gt_status launch_tn_wide(GemmArgs g, int splits, hipStream_t st) {
+    const WideTile t = tn_wide_tile(g.M, g.N);
+    g.ntm = (int)((g.M + t.bm - 1) / t.bm); g.ntn = (int)((g.N + t.bn - 1) / t.bn);
+    g.split_xcd = gemm_split_xcd(g.ntm, g.ntn, splits);
+    return t.bm == 320 ? launch_tn_wide_as<5, 2, 2, 4>(g, splits, st) : t.bm == 256 ? launch_tn_wide_as<2, 5, 4, 2>(g, splits, st)
+                                                                                  : launch_tn_wide_as<5, 2, 4, 2>(g, splits, st);
+}
+
 template <typename T>
 gt_status launch_gemm_t(const GemmArgs &g, int transA, int transB, int splits, hipStream_t st) {
     if (!transA && !transB) return launch_gemm<T, false, false>(g, splits, st);
@@ -679,6 +911,10 @@ size_t gt_gemm_ws_bytes(int transA, int64_t M, int64_t N, int64_t K) {
     int splits = p.splits > q.splits ? p.splits : q.splits;
     if (tn256_shape(transA, 0, M, N, K)) {
         const SplitPlan r = plan_split(transA, M, N, K, false, true);
+        if (r.splits > splits) splits = r.splits;
+    }
+    if (tn_wide_shape(transA, 0, M, N, K, false) || tn_wide_shape(transA, 0, M, N, K, true)) {
+        const SplitPlan r = plan_split(transA, M, N, K, false, false, true);
         if (r.splits > splits) splits = r.splits;
     }
     // partial tiles of a split reduction, plus (weight-gradient shape) room for the column sums of B per split
@@ -708,9 +944,10 @@ gt_status gt_gemm_run(const char *fn, gt_dtype dtype, int transA, int transB, in
         return gt_fail(GT_ERR_INVALID_ARG, "%s: pointer misaligned for dtype", fn);
     const bool x3 = use_x3(dtype, transA, M, N, K);
     const int ve0 = dtype == GT_BF16 ? 8 : 4;
-    const bool tn256 = dtype == GT_BF16 && tn256_shape(transA, transB, M, N, K) && ((uintptr_t)A & 15) == 0 &&
-                       ((uintptr_t)B & 15) == 0 && lda % ve0 == 0 && ldb % ve0 == 0;
-    const SplitPlan p = plan_split(transA, M, N, K, x3, tn256);
+    const bool vec = ((uintptr_t)A & 15) == 0 && ((uintptr_t)B & 15) == 0 && lda % ve0 == 0 && ldb % ve0 == 0;
+    const bool wide = dtype == GT_BF16 && lda < ((int64_t)1 << 25) && ldb < ((int64_t)1 << 25) && tn_wide_shape(transA, transB, M, N, K, vec);   // (offsets in 32 bits)
+    const bool tn256 = dtype == GT_BF16 && !wide && vec && tn256_shape(transA, transB, M, N, K);
+    const SplitPlan p = plan_split(transA, M, N, K, x3, tn256, wide);
     if (colsum_b && (!transA || transB)) return gt_fail(GT_ERR_INTERNAL, "%s: column sums of B need the A^T B shape", fn);
     const size_t need_part = p.splits > 1 ? gt_align_up((size_t)p.splits * (size_t)M * (size_t)N * 4) : 0;
     const size_t need = need_part + (colsum_b ? gt_align_up((size_t)p.splits * (size_t)N * 4) : 0);
@@ -752,6 +989,7 @@ gt_status gt_gemm_run(const char *fn, gt_dtype dtype, int transA, int transB, in
     gt_status s = reg_path ? gt_gemm_reg_launch(g, transB, st)
                   : rows_path ? gt_gemm_rows_launch(g, transB, st)
                   : ws_path ? gt_gemm_ws_launch(g, dtype, transB, st)
+                  : wide ? launch_tn_wide(g, p.splits, st)
                   : tn256 ? launch_tn256(g, p.splits, st)
                   : x3 ? gt_gemm_x3_launch(g, transA, transB, p.splits, st)
                        : (dtype == GT_F32) ? launch_gemm_t<float>(g, transA, transB, p.splits, st)
