@@ -265,6 +265,149 @@ __global__ void __launch_bounds__(256) k_edge_dot(const EdgeArgs a) {
     }
 }
 
+// Both derivatives of the scaled aggregation from one gather, over the transposed structure:  Y[u] = sum_e c_e X[v],
+// dW[perm e] = f_e <X[v], R[u]>  (X: the upstream gradient, R: the source embeddings; c_e = W[perm e] f_e).  The same rows of X that the sum reads give the
+// products, which otherwise take a pass of their own that gathers R for every edge; what it costs is that they leave by the permutation, a line each.
+// One entry's product is formed as in k_edge_dot (same lanes, same order).  Long items may be shared out as in k_aggregate, whose items, partial rows and
+// row ends these are.  Power law, 8.4 M edges, 128 bf16 columns: 268 + 187 us apart (a gather, a product).
+template <typename T, int V, int G, bool SH, int U>
+__global__ void __launch_bounds__(256) k_scale_bwd(const AggArgs a, const void *R, int64_t ldr, float *dW) {
+    constexpr int NG = 64 / G;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gl = lane & (G - 1), grp = lane / G;
+    const int bx = blockIdx.x;
+    const bool coop = bx < a.n_coop, one_wave = a.coop_waves == 1;   // uniform over the workgroup
+    const int64_t item_id = coop ? (one_wave ? (int64_t)bx * 4 + wave : (int64_t)bx)
+                                 : (int64_t)a.n_coop * (one_wave ? 4 : 1) + ((int64_t)agg_item_block(a.xcd_run, bx - a.n_coop, a.n_blocks - a.n_coop, 3) * 4 + wave) * NG + grp;
+    if (item_id >= a.n_items) return;   // whole groups (in a cooperative workgroup: all, or whole wavefronts that meet no barrier)
+    const int4 raw = reinterpret_cast<const int4 *>(a.items)[item_id];
+    const int row = raw.x, slot = raw.w;
+    int e0 = raw.y, e1 = raw.z;
+    if (coop) {   // this group's slice
+        const int ng = one_wave ? NG : 4 * NG, per = (e1 - e0 + ng - 1) / ng;
+        e0 += (one_wave ? grp : wave * NG + grp) * per;
+        e1 = e0 + per < e1 ? e0 + per : e1;   // (may lie before e0: an empty slice)
+    }
+    typedef typename Raw<T, V>::type raw_t;
+    const T *X = static_cast<const T *>(a.X);
+    const int64_t own = (int64_t)gl * V, col = agg_col<SH, V>(a, own);
+    const uint4 m = dot_mask<V>(col, own, a.F);
+    const raw_t r = mask_raw(load_raw<T, V>(static_cast<const T *>(R) + (int64_t)row * ldr + col), m);
+    float acc[1][V], msk[1][V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) { acc[0][i] = 0.0f; msk[0][i] = 1.0f; }
+    int idx_next, ei_next;
+    float c_next, f_next;
+    auto fetch = [&](int e) {   // this lane's entry of a batch
+        idx_next = 0; ei_next = 0; c_next = 0.0f; f_next = 1.0f;
+        if (e < e1) {
+            idx_next = a.nbr[e];
+            ei_next = a.eidx[e];
+            if (a.coef2) f_next = a.coef2[e];
+            c_next = a.coef[ei_next] * f_next;
+        }
+    };
+    fetch(e0 + gl);
+    for (int base = e0; base < e1; base += G) {
+        const int idx = idx_next, ei = ei_next;
+        const float c = c_next, f = f_next;
+        fetch(base + G + gl);   // requested before this batch's rows are used
+        const int cnt = (e1 - base) < G ? (e1 - base) : G;
+        float mine = 0.0f;   // lane gl keeps the product of entry base + gl
+        for (int j = 0; j < cnt; j += U) {
+            // (branch free: an entry past the end stands for row 0, with a coefficient of zero on a vector of zeros)
+            raw_t v[U];
+            float cj[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cj[u] = __shfl(c, (j + u) & (G - 1), G);
+                v[u] = load_raw<T, V>(X + (int64_t)__shfl(idx, (j + u) & (G - 1), G) * a.ldx + col);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j + u >= cnt) { v[u] = raw_t{}; cj[u] = 0.0f; }
+                fma_raw(acc[0], cj[u], v[u]);
+                float x[V], y[V], part = 0.0f;
+                unpack_raw(mask_raw(v[u], m), x);
+                unpack_raw(r, y);
+#pragma unroll
+                for (int i = 0; i < V; ++i) part = fmaf(y[i], x[i], part);
+                part = group_sum<G>(part);
+                if (gl == ((j + u) & (G - 1))) mine += part;
+            }
+        }
+        if (base + gl < e1) dW[ei] = f * mine;
+    }
+    if (coop) {
+        __shared__ float red[4][G * V];
+        // groups of a wavefront: exchanged pairwise; wavefronts: through LDS, in order
+#pragma unroll
+        for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[0][i] += __shfl_xor(acc[0][i], o, 64);
+        if (!one_wave) {   // uniform over the workgroup
+            if (grp == 0) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) red[wave][i * G + gl] = acc[0][i];
+            }
+            __syncthreads();
+            if (wave != 0) return;
+        }
+        if (grp != 0) return;
+        if (!one_wave)
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[0][i] = ((red[0][i * G + gl] + red[1][i * G + gl]) + red[2][i * G + gl]) + red[3][i * G + gl];
+    }
+    if (slot < 0) {
+        finish_row<T, V, G, 1, SH>(a, row, gl, 0, acc, msk);
+    } else if (own < a.F) {   // (partial rows are padded to 8 floats: a whole vector always fits)
+        float *P = a.partials + (int64_t)slot * a.ldp + col;
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q) {
+            const float4 x = make_float4(acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]);
+            __builtin_memcpy(P + 4 * q, &x, 16);
+        }
+    }
+}
+
+template <typename T, int V, int G, bool SH, int U>
+gt_status launch_scale_bwd(const AggArgs &a, const void *R, int64_t ldr, float *dW, hipStream_t st) {
+    constexpr int NG = 64 / G;
+    AggArgs b = a;
+    const double bytes = agg_bytes<T>(a);
+    b.coop_waves = G == 64 || (U == 2 && G >= 8) || (G == 16 && bytes > 1.0e9) ? 4 : 1;   // (as in the plain gather)
+    const int64_t ipc = b.coop_waves == 1 ? 4 : 1;   // items per cooperative workgroup
+    b.n_coop = agg_share_out(a, G, U, bytes) ? (int)((a.n_long + ipc - 1) / ipc) : 0;
+    const int64_t left = a.n_items > b.n_coop * ipc ? a.n_items - b.n_coop * ipc : 0, gi = (left + 4 * NG - 1) / (4 * NG);
+    b.n_blocks = (int)(b.n_coop + gi);
+    b.xcd_run = agg_xcd_run(gi);
+    const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
+    gt_trace_variant(tr, V, G, 1, U, false);
+    if (b.n_blocks > 0) k_scale_bwd<T, V, G, SH, U><<<(unsigned)b.n_blocks, 256, 0, st>>>(b, R, ldr, dW);
+    gt_trace_close(tr, st);
+    GT_LAUNCH_CHECK("k_scale_bwd");
+    if (a.n_splits > 0) {
+        k_reduce_partials<T, V, G, 1, SH><<<(unsigned)((a.n_splits + 3) / 4), 256, 0, st>>>(a);
+        GT_LAUNCH_CHECK("k_reduce_partials");
+    }
+    return GT_OK;
+}
+
+template <typename T, bool SH>
+gt_status dispatch_scale_bwd(const AggArgs &a, const void *R, int64_t ldr, float *dW, hipStream_t st) {
+    constexpr int V = 16 / (int)sizeof(T);
+    const int64_t nvec = (a.F + V - 1) / V;
+    const bool many = agg_skewed(a);   // rows in flight as in the edge product (see launch_edge)
+#define GT_SCALE_BWD(G_, U_) (many ? launch_scale_bwd<T, V, G_, SH, U_>(a, R, ldr, dW, st) : launch_scale_bwd<T, V, G_, SH, 2>(a, R, ldr, dW, st))
+    if (nvec <= 4) return GT_SCALE_BWD(4, 4);
+    if (nvec <= 8) return GT_SCALE_BWD(8, 8);
+    if (nvec <= 16) return GT_SCALE_BWD(16, 8);
+    if (a.n_edges < 8 * a.n_items) return nvec <= 32 ? launch_scale_bwd<T, V, 32, SH, 2>(a, R, ldr, dW, st) : launch_scale_bwd<T, V, 64, SH, 2>(a, R, ldr, dW, st);
+    if (nvec <= 32) return GT_SCALE_BWD(32, 4);
+    return GT_SCALE_BWD(64, 4);
+#undef GT_SCALE_BWD
+}
+
 template <typename T, int V, int G, int NP, bool SH>
 gt_status launch_edge(const EdgeArgs &a, int kind, hipStream_t st) {
     constexpr int NG = 64 / G;
@@ -398,6 +541,34 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
 #undef GT_GATHER
 }
 
+// Whether both derivatives of the scaled aggregation come from one gather: rows of at most a wavefront's vectors.  Narrow ones without alignment
+// stay with the element-wise kernels; rows of up to 128 bytes on skewed graphs whose scores are beyond the L2s find the rows they read there, and not the places
+// of their products (us, two passes / one: power law, 8.4 M edges, 32 bf16 columns 410 / 435, 128 columns 507 / 455; 2.6 M edges, 32 columns 1.0; uniform, 8.4 M edges, 32
+// columns 541 / 496, 128 columns 772 / 567; 1 M edges, 150 fp32 columns 220 / 143; 60 K edges 14.0 / 9.0).
+bool scale_bwd_joined(const gt_graph *g, gt_dtype t, int64_t F, const void *dY, int64_t lddy, const void *Xs, int64_t ldxs, const void *dXs, int64_t lddxs) {
+    const int ve = t == GT_F32 ? 4 : 8;
+    const bool vec = vec_ok(t, dY, lddy) && vec_ok(t, Xs, ldxs) && vec_ok(t, dXs, lddxs);
+    if (agg_skewed(g->bwd.n_splits, g->bwd.n_long, g->bwd.n_items) && g->n_edges > ((int64_t)4 << 20) && F * (int64_t)gt_dtype_size(t) <= 128) return false;
+    return g->n_edges > 0 && F <= 64 * ve && (vec || F > 16);
+}
+
+gt_status run_scale_bwd(const gt_graph *g, gt_dtype t, int64_t F, const void *dY, int64_t lddy, const void *Xs, int64_t ldxs, const float *W,
+                        const float *cmean, void *dXs, int64_t lddxs, float *dW, void *ws, hipStream_t st) {
+    const gt_sched &sc = g->bwd;
+    AggArgs a{};
+    a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len; a.rowptr = sc.rowptr; a.nbr = sc.nbr;
+    a.coef = W; a.eidx = g->perm; a.coef2 = cmean;
+    a.X = dY; a.ldx = lddy; a.Y = dXs; a.ldy = lddxs; a.F = F;
+    a.partials = static_cast<float *>(ws); a.ldp = (F + 7) / 8 * 8;
+    a.splits = sc.splits; a.n_splits = sc.n_splits;
+    a.table_bytes = g->n_dst * lddy * (int64_t)gt_dtype_size(t);
+    a.trace_kind = GT_TRACE_AGG_BWD;
+    a.n_rows = sc.n_rows; a.n_edges = g->n_edges;
+    const bool vec = vec_ok(t, dY, lddy) && vec_ok(t, Xs, ldxs) && vec_ok(t, dXs, lddxs);
+    if (t == GT_F32) return vec ? dispatch_scale_bwd<float, false>(a, Xs, ldxs, dW, st) : dispatch_scale_bwd<float, true>(a, Xs, ldxs, dW, st);
+    return vec ? dispatch_scale_bwd<bf16_t, false>(a, Xs, ldxs, dW, st) : dispatch_scale_bwd<bf16_t, true>(a, Xs, ldxs, dW, st);
+}
+
 gt_status check_common(const char *fn, const gt_graph *g, gt_dtype t, int64_t F, void *ws, size_t ws_bytes,
                        bool needs_ws) {
     if (!g) return gt_fail(GT_ERR_INVALID_ARG, "%s: g is null", fn);
@@ -497,6 +668,8 @@ extern "C" gt_status gt_pull_bwd(const gt_graph *g, gt_reduce reduce, gt_weight_
     const float *cmean = (mean && g->n_edges > 0) ? g->coef_mean_b : nullptr;   // 1 / indeg(dst) per transposed entry
     const float *rdeg = mean ? g->rdeg : nullptr;                                // 1 / indeg per destination row
     // gradient of the source embeddings: outputs on the source vertices, transposed structure
+    if (h == GT_H_SCALE && scale_bwd_joined(g, t, F, dY, lddy, Xs, ldxs, dXs, lddxs))
+        return run_scale_bwd(g, t, F, dY, lddy, Xs, ldxs, static_cast<const float *>(W), cmean, dXs, lddxs, static_cast<float *>(dW), ws, st);
     if (h == GT_H_SCALE) {
         s = run_gather(g, true, t, F, dY, lddy, dXs, lddxs, static_cast<const float *>(W), true, cmean, nullptr, 0,
                        VWM_NONE, 0, ws, st);
