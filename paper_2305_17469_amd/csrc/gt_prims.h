@@ -274,11 +274,18 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
     int32_t goff = 0, before = 0, all = 0;
     if (d < 256) {
         if (direct) {
-#pragma unroll 8
-            for (int t = 0; t < nblk; ++t) {
-                const int32_t x = hist[t * 256 + d];
-                before += t < (int)tile ? x : 0;
-                all += x;
+            // 32 counts in flight, none of them in a remainder loop (each of whose rounds waits for its load: 300 K pairs, 75 tiles,
+            // eight in flight and a remainder 18.4 us a pass, 12.6 this way with eight wavefronts of eight
+            // chunks instead of four of sixteen)
+            for (int t0 = 0; t0 < nblk; t0 += 32) {
+                int32_t x[32];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) x[u] = hist[(t0 + u < nblk ? t0 + u : 0) * 256 + d];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) {
+                    before += t0 + u < (int)tile ? x[u] : 0;
+                    all += t0 + u < nblk ? x[u] : 0;
+                }
             }
         } else {
             goff = d < (1 << nb) ? hist[(int64_t)d * nblk + tile] : 0;
@@ -361,7 +368,7 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
 }
 
 // All passes of a sort of at most 16,384 pairs in one launch: a single workgroup of 16 wavefronts,
-// each owning 1,024 consecutive items, keeps keys and values in LDS (128 KB) between the passes:
+// each owning a sixteenth of the items (up to 1,024 consecutive ones), keeps keys and values in LDS (128 KB) between the passes:
 // a pass reads its items from LDS in order, ranks them exactly as k_rs_scatter does (so the
 // order is the same stable one) and writes them back to LDS at their sorted positions; the last
 // pass is followed by one coalesced copy to the caller's output.  A sampled batch sorts a few
@@ -400,14 +407,15 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
     __shared__ int32_t wsum[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int wstart = wave * RS_WAVE_ITEMS;
     const int nn = (int)n;
+    const int per = ((nn + RS_ONE_WAVES - 1) / RS_ONE_WAVES + 63) / 64 * 64, wstart = wave * per;   // a wavefront's items (at most RS_WAVE_ITEMS)
+    const int wend = wstart + per < nn ? wstart + per : nn;
     uint32_t key[RS_CHUNKS], val[RS_CHUNKS];
 #pragma unroll
     for (int c = 0; c < RS_CHUNKS; ++c) {
         const int q = wstart + c * 64 + lane;
-        key[c] = q < nn ? keys_in[q] : 0u;
-        val[c] = (q < nn && vals_in) ? vals_in[q] : (uint32_t)q;
+        key[c] = q < wend ? keys_in[q] : 0u;
+        val[c] = (q < wend && vals_in) ? vals_in[q] : (uint32_t)q;
     }
     for (int p = 0; p < passes; ++p) {
         const int shift = sort_shift(bits, passes, p), nb = sort_shift(bits, passes, p + 1) - shift;
@@ -417,8 +425,8 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
 #pragma unroll
             for (int c = 0; c < RS_CHUNKS; ++c) {
                 const int q = wstart + c * 64 + lane;
-                key[c] = q < nn ? lk[q] : 0u;
-                val[c] = q < nn ? lv[q] : 0u;
+                key[c] = q < wend ? lk[q] : 0u;
+                val[c] = q < wend ? lv[q] : 0u;
             }
         }
         __syncthreads();
@@ -426,8 +434,8 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
 #pragma unroll
         for (int c = 0; c < RS_CHUNKS; ++c) {
             rank[c] = 0;
-            if (wstart + c * 64 >= nn) continue;   // wavefront-uniform: the chunk is empty
-            const bool valid = wstart + c * 64 + lane < nn;
+            if (wstart + c * 64 >= wend) continue;   // wavefront-uniform: the chunk is empty
+            const bool valid = wstart + c * 64 + lane < wend;
             const uint32_t digit = (key[c] >> shift) & dmask;
             uint64_t m = __ballot(valid);
 #pragma unroll
@@ -473,7 +481,7 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
 #pragma unroll
         for (int c = 0; c < RS_CHUNKS; ++c) {
             const int q = wstart + c * 64 + lane;
-            if (q < nn) {
+            if (q < wend) {
                 const uint32_t digit = (key[c] >> shift) & dmask;
                 const int dst = (int)wbase[wave * 256 + digit] + rank[c];
                 lk[dst] = key[c];
@@ -486,7 +494,7 @@ __global__ void __launch_bounds__(RS_ONE_THREADS) k_rs_sort_one(const uint32_t *
 #pragma unroll
         for (int c = 0; c < RS_CHUNKS; ++c) {
             const int q = wstart + c * 64 + lane;
-            if (q < nn) { keys_out[q] = key[c]; vals_out[q] = val[c]; }
+            if (q < wend) { keys_out[q] = key[c]; vals_out[q] = val[c]; }
         }
         return;
     }
@@ -537,7 +545,7 @@ gt_status radix_pass(const uint32_t *kin, const uint32_t *vin, uint32_t *kout, u
         return radix_pass_t<8, 8, true>(kin, vin, ein, kout, vout, eout, n, shift, nb, t, st);
     }
     if (tile == RS_T1) return radix_pass_t<4, 4, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
-    if (tile == RS_T2) return radix_pass_t<4, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
+    if (tile == RS_T2) return radix_pass_t<8, 8, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
     return radix_pass_t<8, 16, false>(kin, vin, nullptr, kout, vout, nullptr, n, shift, nb, t, st);
 }
 
