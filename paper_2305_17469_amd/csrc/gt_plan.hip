@@ -66,7 +66,8 @@ inline unsigned nblocks(int64_t n, int per = PT) { return (unsigned)((n + per - 
 // w_e / sqrt(d(src) d(dst)) of every entry in the given order.  A workgroup takes ROWS_TILE consecutive entries: it finds the
 // row of its first entry by a 64-way search, marks in LDS where the rows of its range begin, and fills in between with a running
 // maximum.  (Looking up the row of each transposed entry by binary search over rowptr instead, 20 dependent loads
-// per entry, took 1.70 ms on 1 M vertices and 25 M entries; this takes 0.19 and the pass below 0.17.)  Where a tile spans more
+// per entry, took 1.70 ms on 1 M vertices and 25 M entries; this takes 0.16 and the pass below 0.16.)  Both passes are bound by one random read of a
+// vertex's degree per entry: what they stream goes past the caches, which keeps the degrees in the L2s (188 -> 157 us and 198 -> 161).  Where a tile spans more
 // than ROWS_WALK rows, almost all of them empty, walking them would be one workgroup's work of the whole launch
 // (16 M rows, 100,000 entries in the first and last 200: plan 24.7 ms walked, 1.2 searched): its entries are searched for instead, a thread's eight at a time.
 constexpr int ROWS_PER = 8, ROWS_TILE = PT * ROWS_PER, ROWS_WALK = 32768;
@@ -145,8 +146,8 @@ __global__ void __launch_bounds__(PT) k_entry_rows(const int32_t *rowptr, int64_
         const int64_t e = base + i * PT + threadIdx.x;
         if (e >= end) continue;
         const int32_t r = mark[i * PT + threadIdx.x];
-        row_of[e] = r;
-        if (dinv) coef_sym[e] = ((ew ? ew[e] : 1.0f) * dinv[colidx[e]]) * dinv[r];
+        __builtin_nontemporal_store(r, row_of + e);
+        if (dinv) __builtin_nontemporal_store(((ew ? ew[e] : 1.0f) * dinv[__builtin_nontemporal_load(colidx + e)]) * dinv[r], coef_sym + e);
     }
 }
 
@@ -165,7 +166,8 @@ __global__ void __launch_bounds__(PT) k_transposed_entries(const int32_t *perm, 
     const bool whole = k0 + 4 <= E;   // (all arrays are aligned)
     uint32_t u[4];
     if (whole) {
-        const uint4 x = *reinterpret_cast<const uint4 *>(skeys + k0);
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const u4 x = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(skeys + k0));
         u[0] = x.x; u[1] = x.y; u[2] = x.z; u[3] = x.w;
     } else {
 #pragma unroll
@@ -192,7 +194,8 @@ __global__ void __launch_bounds__(PT) k_transposed_entries(const int32_t *perm, 
     int32_t v[4];
     float w[4] = {1.0f, 1.0f, 1.0f, 1.0f}, cs[4], cm[4];
     if (!row_of && whole) {
-        const int4 x = *reinterpret_cast<const int4 *>(colidx_t + k0);
+        typedef int32_t i4 __attribute__((ext_vector_type(4)));
+        const i4 x = __builtin_nontemporal_load(reinterpret_cast<const i4 *>(colidx_t + k0));
         v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     } else {
 #pragma unroll
@@ -222,8 +225,9 @@ __global__ void __launch_bounds__(PT) k_transposed_entries(const int32_t *perm, 
         cm[i] = w[i] * (d[i] > 0 ? 1.0f / (float)d[i] : 0.0f);
     }
     if (whole) {
-        if (square) *reinterpret_cast<float4 *>(coef_sym_b + k0) = make_float4(cs[0], cs[1], cs[2], cs[3]);
-        *reinterpret_cast<float4 *>(coef_mean_b + k0) = make_float4(cm[0], cm[1], cm[2], cm[3]);
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        if (square) __builtin_nontemporal_store(f4{cs[0], cs[1], cs[2], cs[3]}, reinterpret_cast<f4 *>(coef_sym_b + k0));
+        __builtin_nontemporal_store(f4{cm[0], cm[1], cm[2], cm[3]}, reinterpret_cast<f4 *>(coef_mean_b + k0));
     } else {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

@@ -221,10 +221,13 @@ template <int WAVES, int CH>
 __global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, int64_t n, int shift, int nb, int32_t *hist, int nblk,
                                                         int direct) {
     constexpr int NT = WAVES * 64, TILE = rs_tile<WAVES, CH>();
-    __shared__ int32_t h[256];
+    // eight counters per digit, by lane: the lanes of a wavefront that meet on one (most, in the upper digits of a power-law graph's ids) take
+    // turns (25 M keys 30 us a pass with one counter per digit, 22 with eight)
+    constexpr int COPIES = 8, HSTR = 257;
+    __shared__ int32_t h[COPIES * HSTR];
     const int64_t tile = rs_tile_of_block(nblk);
     if (tile >= nblk) return;
-    if (threadIdx.x < 256) h[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < COPIES * HSTR; i += NT) h[i] = 0;
     __syncthreads();
     const int64_t base = tile * TILE + threadIdx.x;
     uint32_t k[CH];
@@ -233,11 +236,18 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_hist(const uint32_t *keys, in
         const int64_t p = base + (int64_t)i * NT;
         k[i] = p < n ? keys[p] : 0u;
     }
+    int32_t *mine = h + (threadIdx.x % COPIES) * HSTR;
 #pragma unroll
     for (int i = 0; i < CH; ++i)
-        if (base + (int64_t)i * NT < n) atomicAdd(&h[(k[i] >> shift) & ((1u << nb) - 1u)], 1);
+        if (base + (int64_t)i * NT < n) atomicAdd(&mine[(k[i] >> shift) & ((1u << nb) - 1u)], 1);
     __syncthreads();
-    if (threadIdx.x < (direct ? 256 : 1 << nb)) hist[direct ? tile * 256 + threadIdx.x : (int64_t)threadIdx.x * nblk + tile] = h[threadIdx.x];
+    const int d = threadIdx.x;
+    if (d < (direct ? 256 : 1 << nb)) {
+        int32_t sum = 0;
+#pragma unroll
+        for (int c = 0; c < COPIES; ++c) sum += h[c * HSTR + d];
+        hist[direct ? tile * 256 + d : (int64_t)d * nblk + tile] = sum;
+    }
 }
 
 template <int WAVES, int CH>
@@ -262,13 +272,14 @@ __global__ void __launch_bounds__(WAVES * 64) k_rs_scatter(const uint32_t *keys_
     uint32_t key[CH], val[CH], ext[EXTRA ? CH : 1];
     int32_t rank[CH];
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    // all loads first, so that their latencies overlap instead of adding up chunk by chunk
+    // all loads first, so that their latencies overlap instead of adding up chunk by chunk; past the caches, which keeps the lines there that
+    // the tiles' runs are filling (25 M triples 128 us a pass, 122 so)
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const int64_t p = wstart + (int64_t)c * 64 + lane;
-        key[c] = p < n ? keys_in[p] : 0u;
-        val[c] = vals_in ? (p < n ? vals_in[p] : 0u) : (uint32_t)p;
-        if constexpr (EXTRA) ext[c] = p < n ? ext_in[p] : 0u;
+        key[c] = p < n ? __builtin_nontemporal_load(keys_in + p) : 0u;
+        val[c] = vals_in ? (p < n ? __builtin_nontemporal_load(vals_in + p) : 0u) : (uint32_t)p;
+        if constexpr (EXTRA) ext[c] = p < n ? __builtin_nontemporal_load(ext_in + p) : 0u;
     }
     // digit d (threads 0..255): output position of the tile's first item with it
     int32_t goff = 0, before = 0, all = 0;
