@@ -29,7 +29,7 @@ struct AggArgs {
     const int32_t *nbr;
     const float *coef;       // per-entry coefficient (edge weight x normalisation) or null (= 1)
     const int32_t *eidx;     // entry -> position in coef / VW (the transposed structure's perm), or null (= entry)
-    const float *coef2;      // second per-entry factor, indexed by the entry itself, or null (= 1)
+    const float *coef2;      // per-entry factor, indexed by the entry itself, or null (= 1): beside coef with VWM_SCORE, instead of it with vector weights
     const void *VW;          // per-entry vector weights [E][ldvw] (type T) for the VWM modes, or null
     int64_t ldvw;
     int post_mode;           // 0 none, 2 divide by the row's entry count (mean, forward)
@@ -121,8 +121,9 @@ __device__ inline void unpack_raw(const bf16_t &v, float (&o)[1]) { o[0] = __uin
 
 // Vector-weight modes of the gather (paper: the function h that transforms the source embedding
 // with the edge weight before the aggregation): 1: acc += c * (x + w),  2: acc += c * (x * w); VWM_NT beside either: the weights are
-// streamed past the caches (see edge_streams)
-enum { VWM_NONE = 0, VWM_ADD = 1, VWM_MUL = 2, VWM_NT = 4 };
+// streamed past the caches (see edge_streams).  VWM_SCORE: no vectors, one coefficient per entry, found through the permutation.
+enum { VWM_NONE = 0, VWM_ADD = 1, VWM_MUL = 2, VWM_NT = 4, VWM_SCORE = 8 };
+constexpr bool agg_plain(int vwm) { return (vwm & 3) == 0; }   // no vectors beside the rows
 template <int VWM, int V, typename RawT>
 __device__ inline void fma_vw(float (&acc)[V], float c, const RawT &x, const RawT &w) {
     float xf[V], wf[V];
@@ -291,7 +292,7 @@ static inline int agg_xcd_run(int64_t gx) {
 
 // Instances with cooperative workgroups for the long items
 template <int NP, int VWM>
-constexpr bool agg_coop() { return NP == 1 && VWM == 0; }
+constexpr bool agg_coop() { return NP == 1 && agg_plain(VWM); }
 
 // Whether a launch that shares its long items out gives each split row a workgroup instead of cutting it into chunks: the row is finished there,
 // and the launch that adds the partial rows is saved.  Up to rows of 64 entries per group, whose sum takes about as long as that
@@ -393,23 +394,54 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
     // The group fetches GB neighbour ids and coefficients with coalesced loads and walks them; the next GB are requested
     // before the current ones are used, so the id fetch of the next batch overlaps the row gathers of this one.
     constexpr int GB = G * IPL;
+    // A coefficient that is looked up through the permutation (VWM_SCORE) waits for its place there: the places are requested a batch
+    // earlier still, and the two factors of an entry are multiplied when they are used, so that no load waits for another between the row loads
+    // (both gathers of a dot product's derivative, of which one looks up, us, places in the batch before / earlier: power law, 8.4 M edges,
+    // 8 fp32 columns 308 / 261, 1 M edges 82 / 65; uniform, 131 K rows, 8.4 M edges, 32 bf16 columns 349 / 304; not where eight lanes hold two ids each: 47 bf16 columns 380 / 410; what
+    // bounds rows of 256 bytes are the lines of the scores: 482 / 477).
+    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = !(G == 8 && IPL > 1);
     int idx_next[IPL], ei_next[IPL];
-    float c_next[IPL];
+    float c_next[IPL], f_next[IPL];
+    if constexpr (SCORE) {
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) {   // the first batch's places; the second's follow
+            const int e = e0 + k * G + gl;
+            ei_next[k] = 0;
+            if (e < e1) ei_next[k] = a.eidx[e];
+        }
+    }
+    int ei_later[IPL];
+    auto places = [&](int base, int ahead) {
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) {
+            const int d = ahead + k * G + gl;
+            ei_later[k] = 0;
+            if (d < e1 - base) ei_later[k] = a.eidx[base + d];
+        }
+    };
     auto fetch = [&](int e_first) {
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {
             const int e = e_first + k * G + gl;
             idx_next[k] = 0;
-            ei_next[k] = 0;
             c_next[k] = 0.0f;
+            f_next[k] = 1.0f;
+            if constexpr (!SCORE) ei_next[k] = 0;
             if (e < e1) {
                 idx_next[k] = a.nbr[e];
-                ei_next[k] = a.eidx ? a.eidx[e] : e;
-                c_next[k] = a.coef ? a.coef[ei_next[k]] : 1.0f;
-                if (a.coef2) c_next[k] *= a.coef2[e];
+                if constexpr (SCORE) {
+                    c_next[k] = a.coef[ei_next[k]];
+                    if (a.coef2) f_next[k] = a.coef2[e];
+                } else if constexpr (VWM == VWM_NONE) {
+                    c_next[k] = a.coef ? a.coef[e] : 1.0f;
+                } else {
+                    ei_next[k] = a.eidx ? a.eidx[e] : e;
+                    c_next[k] = a.coef2 ? a.coef2[e] : 1.0f;
+                }
             }
         }
     };
+    if constexpr (SCORE && EARLY) places(e0, GB);
     fetch(e0);
     const T *VWp = static_cast<const T *>(a.VW);
     // This lane's columns, counted from the tile's first one.  Lanes past the row's end repeat its last vector, in sums that nobody stores: a line
@@ -427,9 +459,16 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
     for (int base = e0; base < e1; base += GB) {
         int idx[IPL], ei[IPL];
         float c[IPL];
+        if constexpr (SCORE && !EARLY) places(base, GB);
 #pragma unroll
-        for (int k = 0; k < IPL; ++k) { idx[k] = idx_next[k]; ei[k] = ei_next[k]; c[k] = c_next[k]; }
+        for (int k = 0; k < IPL; ++k) {
+            idx[k] = idx_next[k];
+            ei[k] = ei_next[k];
+            c[k] = SCORE ? c_next[k] * f_next[k] : c_next[k];
+            if constexpr (SCORE) ei_next[k] = ei_later[k];
+        }
         fetch(base + GB);
+        if constexpr (SCORE && EARLY) places(base, 2 * GB);
         const int cnt = (e1 - base) < GB ? (e1 - base) : GB;
         // entries j .. j + N - 1 of the batch (j is a constant where IPL > 1); ALL: every one of them is there, and the loads are
         // branch free (with a branch around each, the exchange that brings its id and the load wait for one another)
@@ -437,7 +476,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
             constexpr int N = decltype(n)::value;
             constexpr bool ALL = decltype(all)::value;
             raw_t v[N][NP];
-            raw_t w[VWM == VWM_NONE ? 1 : N][VWM == VWM_NONE ? 1 : NP];
+            raw_t w[agg_plain(VWM) ? 1 : N][agg_plain(VWM) ? 1 : NP];
             float cj[N];
             int src[N], we[N];
 #pragma unroll
@@ -447,17 +486,17 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
                 if constexpr (G == 64) {   // wave-uniform: scalar broadcast, scalar row base
                     src[u] = __builtin_amdgcn_readlane(idx[0], jj & 63);
                     cj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c[0]), jj & 63));
-                    if constexpr (VWM != VWM_NONE) we[u] = __builtin_amdgcn_readlane(ei[0], jj & 63);
+                    if constexpr (!agg_plain(VWM)) we[u] = __builtin_amdgcn_readlane(ei[0], jj & 63);
                 } else {
                     src[u] = __shfl(idx[k], jj & (G - 1), G);
                     cj[u] = __shfl(c[k], jj & (G - 1), G);
-                    if constexpr (VWM != VWM_NONE) we[u] = __shfl(ei[k], jj & (G - 1), G);
+                    if constexpr (!agg_plain(VWM)) we[u] = __shfl(ei[k], jj & (G - 1), G);
                 }
                 if (!ALL && jj >= cnt) cj[u] = 0.0f;
             }
             auto load = [&](int u, int p, const T *xr) {
                 v[u][p] = load_raw<T, V>(xr + col[p]);
-                if constexpr (VWM != VWM_NONE) {
+                if constexpr (!agg_plain(VWM)) {
                     const T *wr = VWt + (int64_t)we[u] * a.ldvw + col[p];
                     if constexpr ((VWM & VWM_NT) != 0) w[u][p] = load_raw_nt<T, V>(wr);
                     else w[u][p] = load_raw<T, V>(wr);
@@ -469,7 +508,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
 #pragma unroll
                     for (int p = 0; p < NP; ++p) {
                         v[u][p] = raw_t{};
-                        if constexpr (VWM != VWM_NONE) w[u][p] = raw_t{};
+                        if constexpr (!agg_plain(VWM)) w[u][p] = raw_t{};
                     }
 #pragma unroll
                 for (int p = 0; p < NP; ++p)
@@ -484,7 +523,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
                     for (int p = 0; p < NP; ++p) {
                         if constexpr (!ALL) {
                             v[u][p] = raw_t{};
-                            if constexpr (VWM != VWM_NONE) w[u][p] = raw_t{};
+                            if constexpr (!agg_plain(VWM)) w[u][p] = raw_t{};
                         }
                         if (ALL || (j + u < cnt && (!IDLE || (p * G + gl) * V < width))) load(u, p, xr);
                     }
@@ -494,7 +533,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
             for (int u = 0; u < N; ++u)
 #pragma unroll
                 for (int p = 0; p < NP; ++p) {
-                    if constexpr (VWM == VWM_NONE) fma_raw(acc[p], cj[u], v[u][p]);
+                    if constexpr (agg_plain(VWM)) fma_raw(acc[p], cj[u], v[u][p]);
                     else fma_vw<VWM, V>(acc[p], cj[u], v[u][p], w[u][p]);
                 }
         };
@@ -505,7 +544,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
         constexpr std::integral_constant<int, 1> single{};
         if constexpr (IPL == 1) {
             int j = 0;
-            if constexpr (U <= 2 || VWM != VWM_NONE)
+            if constexpr (U <= 2 || !agg_plain(VWM))
                 for (; j + U <= cnt; j += U) step(j, some, std::true_type{});
             if constexpr (U <= 2) {
                 if (U == 2 && j < cnt) step(j, single, std::true_type{});
@@ -752,6 +791,8 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
     constexpr int NG = 64 / G;
     const int64_t tile = (int64_t)G * V * NP;
     const unsigned tiles = (unsigned)((a.F + tile - 1) / tile);
+    if (a.n_edges > 0 && (VWM == VWM_NONE ? a.eidx || a.coef2 : VWM == VWM_SCORE ? !a.eidx || !a.coef || a.mask : a.coef != nullptr))
+        return gt_fail(GT_ERR_INTERNAL, "k_aggregate: coefficients that this mode does not read");
     if (a.n_items > 0) {
         AggArgs b = a;
         b.slices_lg = slices_lg;
@@ -772,24 +813,25 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
         const int S = 1 << b.slices_lg;
         const int64_t gx = S > 1 ? (gb + 8 / S - 1) / (8 / S) * 8 : gb;
         const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
-        gt_trace_variant(tr, V, G, NP, U, VWM == VWM_NONE && a.mask != nullptr);
+        gt_trace_variant(tr, V, G, NP, U, agg_plain(VWM) && a.mask != nullptr);
         const dim3 grid((unsigned)gx, (tiles + S - 1) / S);
         // (narrow groups hold several ids per lane where items are shared out to 64 / G groups of four lanes)
-        constexpr int MANY = NP == 1 && VWM == VWM_NONE && U != 2 ? agg_many_ids(G) : 1, MANY_COOP = G == 4 ? MANY : 1;
-        if constexpr (VWM == VWM_NONE) {
+        constexpr int MANY = NP == 1 && agg_plain(VWM) && U != 2 ? agg_many_ids(G) : 1, MANY_COOP = G == 4 ? MANY : 1;
+        constexpr bool MASKED = VWM == VWM_NONE;   // (a score comes with no mask)
+        if constexpr (agg_plain(VWM)) {
             if (b.n_coop > 0) {
                 if constexpr (agg_coop<NP, VWM>()) {
                     if (b.n_whole > 0) {
-                        if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 2, MANY_COOP><<<grid, 256, 0, st>>>(b);
+                        if (b.mask) k_aggregate<T, V, G, NP, U, VWM, MASKED, SH, 2, MANY_COOP><<<grid, 256, 0, st>>>(b);
                         else k_aggregate<T, V, G, NP, U, VWM, false, SH, 2, MANY_COOP><<<grid, 256, 0, st>>>(b);
-                    } else if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
+                    } else if (b.mask) k_aggregate<T, V, G, NP, U, VWM, MASKED, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
                     else k_aggregate<T, V, G, NP, U, VWM, false, SH, 1, MANY_COOP><<<grid, 256, 0, st>>>(b);
                 }
             } else if (MANY > 1 && agg_long_batches(a, G, bytes)) {
-                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
+                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, MASKED, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
                 else k_aggregate<T, V, G, NP, U, VWM, false, SH, 0, MANY><<<grid, 256, 0, st>>>(b);
             } else {
-                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, true, SH, 0, 1><<<grid, 256, 0, st>>>(b);
+                if (b.mask) k_aggregate<T, V, G, NP, U, VWM, MASKED, SH, 0, 1><<<grid, 256, 0, st>>>(b);
                 else k_aggregate<T, V, G, NP, U, VWM, false, SH, 0, 1><<<grid, 256, 0, st>>>(b);
             }
         } else {
@@ -826,17 +868,17 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
 //    and four vectors per lane take one wherever rows are short (degree 5, 66 K rows, 1030 columns 275 / 283).
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
-    if constexpr (NP == 1 && VWM == VWM_NONE && G <= 16) {
+    if constexpr (NP == 1 && agg_plain(VWM) && G <= 16) {
         const double bytes = agg_bytes<T>(a);
         const bool fits = a.table_bytes <= ((int64_t)96 << 20);   // the last-level cache
         const bool fills = !agg_skewed(a) && a.n_items * G > 1792 * 64 && a.table_bytes > ((int64_t)6 << 20);
         if constexpr (G < 16)
             if (agg_share_out(a, G, 1, bytes) ? G == 4 && !fits : (fills || !fits) && agg_long_batches(a, G, bytes)) return launch<T, V, G, NP, 1, VWM, SH>(a, st);
         if (fits && !(V > 1 && G == 16 && fills && a.n_edges >= 8 * a.n_items)) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
-    } else if constexpr (NP == 1 && VWM == VWM_NONE) {
+    } else if constexpr (NP == 1 && agg_plain(VWM)) {
         if (agg_wide_eight(a, G, agg_bytes<T>(a))) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
     }
-    if constexpr (G == 64 && V > 1 && VWM == VWM_NONE) {
+    if constexpr (G == 64 && V > 1 && agg_plain(VWM)) {
         bool one = agg_skewed(a) ? NP == 4 && a.n_edges < 4 * a.n_items : NP == 4 || (a.n_edges >= 10 * a.n_items && a.n_items >= 16384);
         if constexpr (NP == 1) one = one && !SH && a.F >= 40 * V && a.table_bytes > ((int64_t)40 << 20) && a.table_bytes < ((int64_t)300 << 20);
         if (one) return launch<T, V, G, NP, 1, VWM, SH>(a, st);
@@ -844,7 +886,7 @@ gt_status launch_u(const AggArgs &a, hipStream_t st) {
     // per-entry vector weights stream from memory, each row once, and the gathered table beside them is smaller than they
     // are: eight in flight (4.2 M edges x 64 fp32: two 333 us, four 301, eight 296), four of the widest (1.8 M edges of degree 6,
     // 130 fp32 columns: two 344 us, four 339, eight 368)
-    if constexpr (NP == 1 && VWM != VWM_NONE) return launch<T, V, G, NP, (G == 64 ? 4 : 8), VWM, SH>(a, st);
+    if constexpr (NP == 1 && !agg_plain(VWM)) return launch<T, V, G, NP, (G == 64 ? 4 : 8), VWM, SH>(a, st);
     else return launch<T, V, G, NP, 2, VWM, SH>(a, st);
 }
 
@@ -853,12 +895,12 @@ gt_status dispatch(const AggArgs &a, hipStream_t st) {
     const int64_t nvec = (a.F + V - 1) / V;   // lanes needed to cover one row
     if (nvec <= 4) return launch_u<T, V, 4, 1, VWM, SH>(a, st);
     if (nvec <= 8) return launch_u<T, V, 8, 1, VWM, SH>(a, st);
-    if constexpr (V == 1 && sizeof(T) == 4 && VWM == VWM_NONE) {   // (see agg_dispatch)
+    if constexpr (V == 1 && sizeof(T) == 4 && agg_plain(VWM)) {   // (see agg_dispatch)
         if (nvec > 16) return launch_u<T, V, 64, 3, VWM, SH>(a, st);
     }
     if constexpr (V == 1) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
     if (nvec <= 16) return launch_u<T, V, 16, 1, VWM, SH>(a, st);
-    if constexpr (VWM == VWM_NONE) {
+    if constexpr (agg_plain(VWM)) {
         const AggTiles t = agg_tiles(a, SH, nvec, sizeof(T), agg_bytes<T>(a));
         if (t.G == 32) return launch<T, V, 32, 1, 2, VWM, SH>(a, st, true, t.slices_lg, t.share);
         if (t.G == 16 && t.U == 8) return launch<T, V, 16, 1, 8, VWM, SH>(a, st, true, t.slices_lg, t.share);
@@ -884,7 +926,7 @@ gt_status agg_dispatch(const AggArgs &a, bool vec, hipStream_t st) {
     constexpr int V = 16 / (int)sizeof(T);
     if (vec) return dispatch<T, V, VWM>(a, st);
     if (a.F < V) return dispatch<T, 1, VWM>(a, st);
-    if constexpr (sizeof(T) == 4 && VWM == VWM_NONE) {
+    if constexpr (sizeof(T) == 4 && agg_plain(VWM)) {
         if (a.F <= 16 && !agg_skewed(a) && !agg_vectors_pay(a, agg_bytes<T>(a))) return dispatch<T, 1, VWM>(a, st);
         if (a.F > 128 && a.F <= 176 && !agg_share_out(a, 64, 2, agg_bytes<T>(a))) return dispatch<T, 1, VWM>(a, st);
     }

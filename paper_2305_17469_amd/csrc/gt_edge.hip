@@ -296,22 +296,30 @@ __global__ void __launch_bounds__(256) k_scale_bwd(const AggArgs a, const void *
     float acc[1][V], msk[1][V];
 #pragma unroll
     for (int i = 0; i < V; ++i) { acc[0][i] = 0.0f; msk[0][i] = 1.0f; }
-    int idx_next, ei_next;
+    int idx_next, ei_next = 0, ei_later;   // places of the next batch and of the one after: the scores are not waited for between the row loads
     float c_next, f_next;
+    if (e0 + gl < e1) ei_next = a.eidx[e0 + gl];
+    auto place = [&](int base, int ahead) {
+        ei_later = 0;
+        if (ahead + gl < e1 - base) ei_later = a.eidx[base + ahead + gl];
+    };
     auto fetch = [&](int e) {   // this lane's entry of a batch
-        idx_next = 0; ei_next = 0; c_next = 0.0f; f_next = 1.0f;
+        idx_next = 0; c_next = 0.0f; f_next = 1.0f;
         if (e < e1) {
             idx_next = a.nbr[e];
-            ei_next = a.eidx[e];
             if (a.coef2) f_next = a.coef2[e];
-            c_next = a.coef[ei_next] * f_next;
+            c_next = a.coef[ei_next];
         }
     };
+    if constexpr (G < 64) place(e0, G);
     fetch(e0 + gl);
     for (int base = e0; base < e1; base += G) {
         const int idx = idx_next, ei = ei_next;
-        const float c = c_next, f = f_next;
+        const float f = f_next, c = c_next * f;
+        if constexpr (G == 64) place(base, G);   // (long batches hide the places' latency, and the register costs: 150 fp32 columns, power law, 4 M edges 459 / 464 us)
+        ei_next = ei_later;
         fetch(base + G + gl);   // requested before this batch's rows are used
+        if constexpr (G < 64) place(base, 2 * G);
         const int cnt = (e1 - base) < G ? (e1 - base) : G;
         float mine = 0.0f;   // lane gl keeps the product of entry base + gl
         for (int j = 0; j < cnt; j += U) {
@@ -512,6 +520,7 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
     AggArgs a{};
     a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len; a.rowptr = sc.rowptr; a.nbr = sc.nbr;
     a.coef = coef; a.eidx = via_perm ? g->perm : nullptr; a.coef2 = coef2;
+    if (!coef && vwm == VWM_NONE) { a.coef = coef2; a.coef2 = nullptr; }   // (one factor per entry)
     a.VW = VW; a.ldvw = ldvw; a.post_mode = post_mode;
     a.bias = nullptr; a.relu = 0;
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.F = F;
@@ -528,7 +537,10 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
     // those random reads (us, vectors / elements: 7.5 M uniform edges, 13 bf16 columns, scaled aggregation backward 498 / 426).
     const bool el = !vec && F <= 16 && !agg_skewed(a) &&
                     (via_perm || (vwm == VWM_NONE && !agg_vectors_pay(a, (double)a.n_edges * (double)F * gt_dtype_size(t))));
-    if (vwm == VWM_NONE) return gt_agg_launch(a, t, vec, st, el);
+    if (vwm == VWM_NONE && !via_perm) return gt_agg_launch(a, t, vec, st, el);
+#define GT_SCORE(T_) (el ? dispatch<T_, 1, VWM_SCORE>(a, st) : agg_dispatch<T_, VWM_SCORE>(a, vec, st))
+    if (vwm == VWM_NONE) return t == GT_F32 ? GT_SCORE(float) : GT_SCORE(bf16_t);
+#undef GT_SCORE
 #define GT_GATHER_EL(T_) (vwm == VWM_ADD ? dispatch<T_, 1, VWM_ADD>(a, st) : dispatch<T_, 1, VWM_MUL>(a, st))
 #define GT_GATHER_NT(T_)                                                                                                         \
     (vwm == VWM_ADD ? dispatch<T_, 16 / (int)sizeof(T_), VWM_ADD | VWM_NT>(a, st) : dispatch<T_, 16 / (int)sizeof(T_), VWM_MUL | VWM_NT>(a, st))
@@ -542,13 +554,18 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
 }
 
 // Whether both derivatives of the scaled aggregation come from one gather: rows of at most a wavefront's vectors.  Narrow ones without alignment
-// stay with the element-wise kernels; rows of up to 128 bytes on skewed graphs whose scores are beyond the L2s find the rows they read there, and not the places
-// of their products (us, two passes / one: power law, 8.4 M edges, 32 bf16 columns 410 / 435, 128 columns 507 / 455; 2.6 M edges, 32 columns 1.0; uniform, 8.4 M edges, 32
-// columns 541 / 496, 128 columns 772 / 567; 1 M edges, 150 fp32 columns 220 / 143; 60 K edges 14.0 / 9.0).
+// stay with the element-wise kernels.  Where the L2s hold the rows but not the scores, the rows are found there and the places of the products
+// are not, and two passes are ahead: rows of up to 128 bytes on skewed graphs from 4 Mi edges on, of up to 64 from 3 Mi on; on uniform graphs of
+// tables up to 16 MB from 2 Mi on (us, two passes / one: power law, 8.4 M edges, 32 bf16 columns 410 / 435, 128 columns 507 / 455; 4 M edges, 32 columns
+// 209 / 227, 2.5 M 140 / 140; uniform, 131 K rows, 8.4 M edges, 8 fp32 columns 319 / 437, 32 bf16 columns 375 / 462, 24 fp32 columns 387 / 481, 32 fp32 columns 361 / 437; 90 K rows, 2.3 M edges, 20 fp32 columns 104 / 119;
+// 262 K rows, 5 M edges, 47 bf16 columns 381 / 326; 262 K rows, 2.5 M edges, 8 columns 133 / 144, 32 bf16
+// columns 151 / 149; 500 K rows, 12 M edges 713 / 728, 774 / 735; 262 K rows, 8.4 M edges, 128 columns 772 / 567; 1 M edges, 150 fp32 columns 220 / 143; 60 K edges 14.0 / 9.0).
 bool scale_bwd_joined(const gt_graph *g, gt_dtype t, int64_t F, const void *dY, int64_t lddy, const void *Xs, int64_t ldxs, const void *dXs, int64_t lddxs) {
     const int ve = t == GT_F32 ? 4 : 8;
     const bool vec = vec_ok(t, dY, lddy) && vec_ok(t, Xs, ldxs) && vec_ok(t, dXs, lddxs);
-    if (agg_skewed(g->bwd.n_splits, g->bwd.n_long, g->bwd.n_items) && g->n_edges > ((int64_t)4 << 20) && F * (int64_t)gt_dtype_size(t) <= 128) return false;
+    const int64_t rb = F * (int64_t)gt_dtype_size(t), Mi = (int64_t)1 << 20;
+    if (agg_skewed(g->bwd.n_splits, g->bwd.n_long, g->bwd.n_items) ? rb <= 128 && g->n_edges > (rb <= 64 ? 3 : 4) * Mi
+                                                                  : rb <= 128 && g->n_edges > 2 * Mi && g->n_dst * rb <= 16 * Mi) return false;
     return g->n_edges > 0 && F <= 64 * ve && (vec || F > 16);
 }
 
