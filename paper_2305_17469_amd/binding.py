@@ -173,7 +173,6 @@ class Graph:
         _check(lib.gt_graph_create(byref(h), self.n_dst, self.n_src, self.n_edges, _ptr(self.rowptr), _ptr(self.colidx),
                                    _ptr(self.edge_weight), _ptr(self.ws), self.ws.numel(), _stream()))
         self.handle = h
-        self._agg_ws = None
 
     def __del__(self):
         h = getattr(self, "handle", None)
@@ -205,11 +204,11 @@ class Graph:
         return n.value
 
     def aggregate_ws(self, F):
+        """Scratch of one call at width F, from torch's allocator: ordered with the current stream, and a captured graph's own.  Calls
+        on other streams and captured graphs may be at work in theirs, so nothing of it is kept on the Graph."""
         need = c_size_t()
         _check(lib.gt_aggregate_ws_size(self.handle, int(F), byref(need)))
-        if self._agg_ws is None or self._agg_ws.numel() < need.value:
-            self._agg_ws = _ws(need.value, self.device)
-        return self._agg_ws
+        return _ws(need.value, self.device)
 
 
 def gt_aggregate_fwd(g: Graph, reduce, X, out=None, F=None):
