@@ -21,7 +21,7 @@
  *              all device memory (inputs, outputs, workspaces); the library never allocates or
  *              frees device memory and never keeps a pointer beyond what is stated.
  *   Streams    `stream` is a hipStream_t passed as void* (NULL = the default stream).  Compute
- *              calls only enqueue work and return; gt_graph_create synchronises the stream (twice).
+ *              calls only enqueue work and return; gt_graph_create synchronises the stream.
  *   dtype      GT_F32: fp32 storage and arithmetic.  GT_BF16: bf16 storage (round-to-nearest-
  *              even on store), fp32 accumulation.
  *   Errors     every call returns a gt_status; nothing throws, aborts or prints.  Arguments
@@ -87,8 +87,9 @@ gt_status gt_graph_plan_size(int64_t n_dst, int64_t n_src, int64_t n_edges, int 
 /* rowptr[n_dst+1], colidx[n_edges] (source ids in [0, n_src)), edge_weight[n_edges] or NULL:
  * device, int32/fp32, borrowed until gt_graph_destroy.  ws: device, 256-byte aligned, at
  * least gt_graph_plan_size bytes, borrowed likewise (it holds the plan).  Enqueues the plan
- * kernels on `stream` and synchronises it twice: once to read back the work-list sizes, once
- * before returning, so that the finished plan may be used from any stream.
+ * kernels on `stream` and synchronises it: to read back the work-list sizes, and, on graphs of more
+ * than some 16 K work items, whose lists are sorted after that, once more before returning.  The
+ * finished plan may be used from any stream.
  * Errors: INVALID_ARG (null/negative), UNSUPPORTED (n_edges or n_* >= 2^31 - 1024), WORKSPACE, HIP. */
 gt_status gt_graph_create(gt_graph **g /* host out */, int64_t n_dst, int64_t n_src, int64_t n_edges,
                           const int32_t *rowptr, const int32_t *colidx, const float *edge_weight,
@@ -121,9 +122,19 @@ gt_status gt_graph_validate(const gt_graph *g, int64_t *n_violations /* host */,
  * split long rows; 0 if no row is split).  Covers both directions. */
 gt_status gt_aggregate_ws_size(const gt_graph *g, int64_t F, size_t *ws_bytes /* host */);
 
+/* Bytes of scratch with which gt_aggregate_fwd (transposed = 0) or gt_aggregate_bwd (transposed != 0)
+ * is fastest on the table X, ldx: at least gt_aggregate_ws_size, and more where the call, given the room,
+ * gathers from a copy of the table whose rows lie in fewer 128-byte lines (rows of 33 to 128 bytes at
+ * strides that cross lines, tables of 24 MB and more, graphs without few rows much longer than the rest;
+ * 64 or 128 bytes per row of the table).  The extra bytes are optional; with and without them results
+ * agree up to summation order.  X is not read, only its alignment counts. */
+gt_status gt_aggregate_best_ws_size(const gt_graph *g, int transposed, gt_dtype dtype, int64_t F,
+                                    const void *X, int64_t ldx, size_t *ws_bytes /* host */);
+
 /* Y[n_dst, F] = A X,  X[n_src, F];  see gt_reduce.  X and Y must not overlap.  ws: device
  * scratch of at least gt_aggregate_ws_size bytes (may be NULL when that is 0), 256-byte aligned;
- * its contents are overwritten.  Errors: INVALID_ARG, UNSUPPORTED (SYMNORM on a non-square
+ * its contents are overwritten, and calls that may overlap in time need one each; more may save
+ * time (gt_aggregate_best_ws_size).  Errors: INVALID_ARG, UNSUPPORTED (SYMNORM on a non-square
  * graph), WORKSPACE.  n_dst == 0 or F == 0 is a valid no-op; empty rows give zeros. */
 gt_status gt_aggregate_fwd(const gt_graph *g, gt_reduce reduce, gt_dtype dtype, int64_t F,
                            const void *X, int64_t ldx, void *Y, int64_t ldy,
@@ -139,9 +150,10 @@ gt_status gt_aggregate_bwd(const gt_graph *g, gt_reduce reduce, gt_dtype dtype, 
  * loops, harnesses that forbid hipMalloc): gt_aggregate_fwd with the scratch for the partial
  * rows of split long rows taken from a fixed array inside the library (32 MiB per GPU, held from
  * library load until the process ends) instead of a caller workspace.  Same arguments, checks,
- * kernels and results (bit for bit) as gt_aggregate_fwd.  Calls no hipMalloc / hipFree or other
- * allocating routine and records no kernel-timing events.  If the graph's partial rows at width
- * F need more than gt_aggregate_static_capacity() bytes (compare gt_aggregate_ws_size), returns
+ * kernels and results (bit for bit) as gt_aggregate_fwd with gt_aggregate_ws_size bytes of scratch:
+ * X is gathered where it lies, never from a copy.  Calls no hipMalloc / hipFree or other allocating
+ * routine and records no kernel-timing events.  If the graph's partial rows at width F need more
+ * than gt_aggregate_static_capacity() bytes (compare gt_aggregate_ws_size), returns
  * GT_ERR_WORKSPACE and launches nothing.  The GPU that is current at the call must be the one
  * that holds the graph and the tensors.  All calls on one GPU share the one array: calls that
  * may overlap in time on the same GPU (different streams or threads) race on it and must be
@@ -301,7 +313,11 @@ gt_status gt_cost_benefits(const gt_cost_coeffs *c, int64_t n_src, int64_t n_dst
 gt_status gt_layer_decide(const gt_graph *g, const gt_layer_desc *d, gt_order *fwd, gt_order *bwd);
 
 /* Device bytes for `saved` (activations the backward needs, written by gt_layer_fwd) and for
- * `scratch` (temporaries of either call), for any order. */
+ * `scratch` (temporaries of either call), for any order.  Scratch holds X W [n_src, out_dim],
+ * dZ [n_dst, out_dim] and dZ W^T [n_dst, in_dim], rows padded to 16 bytes or, on graphs without few
+ * rows much longer than the rest, up to the next 128; column sums; the aggregation's partial rows
+ * and, on such graphs, room for the copy of gt_aggregate_best_ws_size (64 or 128 bytes per row where
+ * in_dim or out_dim has rows of 33 to 128 bytes); and the split products' partial tiles. */
 gt_status gt_layer_ws_size(const gt_graph *g, const gt_layer_desc *d,
                            size_t *saved_bytes /* host */, size_t *scratch_bytes /* host */);
 

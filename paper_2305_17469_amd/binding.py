@@ -49,7 +49,7 @@ class GtError(RuntimeError):
 
 
 EXPORTS = ["gt_graph_plan_size", "gt_graph_create", "gt_graph_destroy", "gt_graph_outputs", "gt_graph_info",
-           "gt_graph_validate", "gt_aggregate_ws_size", "gt_aggregate_fwd", "gt_aggregate_bwd",
+           "gt_graph_validate", "gt_aggregate_ws_size", "gt_aggregate_best_ws_size", "gt_aggregate_fwd", "gt_aggregate_bwd",
            "gt_aggregate_static_capacity", "gt_aggregate_fwd_static", "gt_aggregate_combine_supported",
            "gt_aggregate_combine_fwd", "gt_combine_ws_size",
            "gt_combine", "gt_neighbor_apply_fwd", "gt_neighbor_apply_bwd", "gt_pull_fwd", "gt_pull_bwd", "gt_cost_get", "gt_cost_set", "gt_cost_get_dtype", "gt_cost_set_dtype", "gt_cost_benefits", "gt_layer_decide", "gt_layer_ws_size",
@@ -71,6 +71,7 @@ lib.gt_graph_outputs.argtypes = [c_void_p] + [POINTER(c_void_p)] * 5
 lib.gt_graph_info.argtypes = [c_void_p] + [POINTER(c_int64)] * 7
 lib.gt_graph_validate.argtypes = [c_void_p, POINTER(c_int64), c_void_p]
 lib.gt_aggregate_ws_size.argtypes = [c_void_p, c_int64, POINTER(c_size_t)]
+lib.gt_aggregate_best_ws_size.argtypes = [c_void_p, c_int, c_int, c_int64, c_void_p, c_int64, POINTER(c_size_t)]
 _AGG = [c_void_p, c_int, c_int, c_int64, c_void_p, c_int64, c_void_p, c_int64, c_void_p, c_size_t, c_void_p]
 lib.gt_aggregate_fwd.argtypes = _AGG
 lib.gt_aggregate_bwd.argtypes = _AGG
@@ -203,11 +204,15 @@ class Graph:
         _check(lib.gt_graph_validate(self.handle, byref(n), _stream()))
         return n.value
 
-    def aggregate_ws(self, F):
+    def aggregate_ws(self, F, table=None, transposed=False):
         """Scratch of one call at width F, from torch's allocator: ordered with the current stream, and a captured graph's own.  Calls
-        on other streams and captured graphs may be at work in theirs, so nothing of it is kept on the Graph."""
+        on other streams and captured graphs may be at work in theirs, so nothing of it is kept on the Graph.  What such a call needs, or, for the
+        plain aggregation of `table`, what it is fastest with."""
         need = c_size_t()
-        _check(lib.gt_aggregate_ws_size(self.handle, int(F), byref(need)))
+        if table is None:
+            _check(lib.gt_aggregate_ws_size(self.handle, int(F), byref(need)))
+        else:
+            _check(lib.gt_aggregate_best_ws_size(self.handle, int(transposed), _dtype(table), int(F), _ptr(table), _rows2d(table), byref(need)))
         return _ws(need.value, self.device)
 
 
@@ -215,7 +220,7 @@ def gt_aggregate_fwd(g: Graph, reduce, X, out=None, F=None):
     """Y[n_dst, F] = A X.  `out` may be a preallocated (possibly wider-strided) tensor."""
     F = X.shape[1] if F is None else F
     Y = torch.empty((g.n_dst, F), dtype=X.dtype, device=X.device) if out is None else out
-    ws = g.aggregate_ws(F)
+    ws = g.aggregate_ws(F, X)
     _check(lib.gt_aggregate_fwd(g.handle, REDUCE[reduce], _dtype(X), F, _ptr(X), _rows2d(X), _ptr(Y), _rows2d(Y),
                                 _ptr(ws), ws.numel(), _stream()))
     return Y
@@ -251,7 +256,7 @@ def gt_aggregate_bwd(g: Graph, reduce, dY, out=None, F=None):
     """dX[n_src, F] = A^T dY."""
     F = dY.shape[1] if F is None else F
     dX = torch.empty((g.n_src, F), dtype=dY.dtype, device=dY.device) if out is None else out
-    ws = g.aggregate_ws(F)
+    ws = g.aggregate_ws(F, dY, transposed=True)
     _check(lib.gt_aggregate_bwd(g.handle, REDUCE[reduce], _dtype(dY), F, _ptr(dY), _rows2d(dY), _ptr(dX), _rows2d(dX),
                                 _ptr(ws), ws.numel(), _stream()))
     return dX

@@ -35,6 +35,11 @@ int64_t repack_stride(const gt_sched &sc, int64_t n_in, int64_t n_edges, int64_t
     return (double)n_edges * (lines - 1.0) * 30.0 > (double)n_in * (double)(rb + stride) ? stride : 0;
 }
 
+// That of a table as it is given
+int64_t table_copy_stride(const gt_sched &sc, int64_t n_in, int64_t n_edges, int64_t rb, const void *X, int64_t stride) {
+    return repack_stride(sc, n_in, n_edges, rb, mean_lines((uintptr_t)X, stride, rb));
+}
+
 // out[row] (stride `stride`) = in[row] (stride `ld`), rb bytes each; L lanes per row, each 16 bytes, the last that the row needs ending with it (no
 // alignment past the elements').  Bound by memory.
 template <int L>
@@ -119,7 +124,7 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
         if (ws_bytes < need) return gt_fail(GT_ERR_WORKSPACE, "%s: ws_bytes %zu < required %zu", fn, ws_bytes, need);
     }
 
-    const int64_t rb = F * (int64_t)es, stride = repack_stride(sc, n_in, g->n_edges, rb, mean_lines((uintptr_t)X, ldx * (int64_t)es, rb));
+    const int64_t rb = F * (int64_t)es, stride = table_copy_stride(sc, n_in, g->n_edges, rb, X, ldx * (int64_t)es);
     if (stride && ws && ((uintptr_t)ws & 255) == 0 && ws_bytes >= need + (size_t)(n_in * stride)) {
         unsigned char *copy = static_cast<unsigned char *>(ws) + need;
         const unsigned blocks = (unsigned)((n_in + 1024 / (stride / 16) - 1) / (1024 / (stride / 16)));
@@ -161,8 +166,23 @@ extern "C" gt_status gt_aggregate_ws_size(const gt_graph *g, int64_t F, size_t *
     if (!g || !ws_bytes) return gt_fail(GT_ERR_INVALID_ARG, "gt_aggregate_ws_size: null argument");
     if (F < 0) return gt_fail(GT_ERR_INVALID_ARG, "gt_aggregate_ws_size: F < 0");
     const bool any = g->fwd.n_partials > 0 || g->bwd.n_partials > 0;
-    const size_t c16 = gt_aggregate_repack_bytes(g, F, GT_BF16), c32 = gt_aggregate_repack_bytes(g, F, GT_F32);   // (the type is not known here)
-    *ws_bytes = (any ? gt_aggregate_ws_bytes(g, F) : 0) + (c16 > c32 ? c16 : c32);
+    *ws_bytes = any ? gt_aggregate_ws_bytes(g, F) : 0;
+    return GT_OK;
+}
+
+extern "C" gt_status gt_aggregate_best_ws_size(const gt_graph *g, int transposed, gt_dtype dtype, int64_t F, const void *X, int64_t ldx,
+                                               size_t *ws_bytes) {
+    const char *fn = "gt_aggregate_best_ws_size";
+    size_t least = 0;
+    const gt_status s = gt_aggregate_ws_size(g, F, &least);
+    if (s != GT_OK) return s;
+    if (!ws_bytes) return gt_fail(GT_ERR_INVALID_ARG, "%s: null argument", fn);
+    if (dtype != GT_F32 && dtype != GT_BF16) return gt_fail(GT_ERR_INVALID_ARG, "%s: unknown dtype", fn);
+    const gt_sched &sc = transposed ? g->bwd : g->fwd;
+    const int64_t es = (int64_t)gt_dtype_size(dtype), rb = F * es, n_in = transposed ? g->n_dst : g->n_src;
+    const size_t copy = ldx < F ? 0 : (size_t)(n_in * table_copy_stride(sc, n_in, g->n_edges, rb, X, ldx * es));   // (the call refuses such a table)
+    const size_t best = copy ? copy + (sc.n_partials > 0 ? gt_aggregate_ws_bytes(g, F) : 0) : 0;
+    *ws_bytes = best > least ? best : least;
     return GT_OK;
 }
 

@@ -1,6 +1,8 @@
 """The scratch of the aggregation's entry points: each call has its own, so one Graph serves several streams at a time, and a captured graph keeps to
 its own memory whatever is called afterwards.  Tables are of a uniform graph whose narrow rows are copied into the scratch and gathered from there; every
 result is bit for bit that of the same call without room for the copy."""
+import ctypes
+
 import pytest
 import torch
 
@@ -36,7 +38,8 @@ def _in_place(g, X, transposed=False):
 
 
 def test_blocks_of_two_calls_are_apart(graph):
-    a, b = graph.aggregate_ws(47), graph.aggregate_ws(47)
+    X = _table(47, 1)
+    a, b = graph.aggregate_ws(47, X), graph.aggregate_ws(47, X)
     assert a.data_ptr() + a.numel() <= b.data_ptr() or b.data_ptr() + b.numel() <= a.data_ptr()
 
 
@@ -81,3 +84,40 @@ def test_captured_call_keeps_to_its_memory(graph):
         torch.cuda.synchronize()
         assert torch.equal(Y, want)
     assert all(bool((t == 3 + i // 4).all()) for i, t in enumerate(held))
+
+
+def test_sizes(graph):
+    """What a call needs is what it refuses to go without; the room for a copy comes on top, for the table at hand alone."""
+    from paper_2305_17469_amd import binding as B
+    least, best = ctypes.c_size_t(), ctypes.c_size_t()
+    assert graph.info()["fwd_split_rows"] == 0 and graph.info()["bwd_split_rows"] == 0
+
+    def sizes(g, X, F, dtype, ld, transposed=0):
+        assert B.lib.gt_aggregate_ws_size(g.handle, F, ctypes.byref(least)) == 0
+        assert B.lib.gt_aggregate_best_ws_size(g.handle, transposed, dtype, F, X, ld, ctypes.byref(best)) == 0
+        return least.value, best.value
+    for transposed in (0, 1):
+        assert sizes(graph, 4096, 47, 1, 47, transposed) == (0, N * 128)
+        assert sizes(graph, 4096, 28, 1, 28, transposed) == (0, N * 64)
+        assert sizes(graph, 4096, 47, 1, 64, transposed) == (0, 0)             # one line per row as it is
+        assert sizes(graph, 4096 + 64, 47, 1, 64, transposed) == (0, N * 128)  # two
+        assert sizes(graph, 4096, 47, 0, 47, transposed) == (0, 0)             # rows past 128 bytes
+        assert sizes(graph, 4096, 12, 1, 12, transposed) == (0, 0)             # and of up to 32
+    assert B.lib.gt_aggregate_best_ws_size(graph.handle, 0, 7, 47, 4096, 47, ctypes.byref(best)) == 1
+    assert B.lib.gt_aggregate_best_ws_size(graph.handle, 0, 1, 47, 4096, 47, None) == 1
+    assert B.lib.gt_aggregate_best_ws_size(None, 0, 1, 47, 4096, 47, ctypes.byref(best)) == 1
+    # a graph with split rows: partial rows are needed, its tables are not copied
+    rowptr = torch.arange(3, device="cuda:0", dtype=torch.int32) * 4000
+    skewed = B.Graph(rowptr, torch.randint(0, N, (8000,), device="cuda:0", dtype=torch.int32), N)
+    need, most = sizes(skewed, 4096, 47, 1, 47)
+    assert 0 < need <= most
+    X, Y = _table(47, 5), torch.zeros((2, 47), dtype=torch.bfloat16, device="cuda:0")
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    announce("aggregation, least scratch")
+    call = B.lib.gt_aggregate_fwd
+    assert call(skewed.handle, 0, 1, 47, X.data_ptr(), 47, Y.data_ptr(), 47, ws.data_ptr(), need, None) == 0
+    assert call(skewed.handle, 0, 1, 47, X.data_ptr(), 47, Y.data_ptr(), 47, ws.data_ptr(), need - 1, None) == 3
+    # the entry point without scratch takes every graph whose partial rows fit, and gathers in place
+    out = torch.empty_like(X)
+    B.gt_aggregate_fwd_static(graph, "mean", X, out)
+    assert torch.equal(out, _in_place(graph, X))
