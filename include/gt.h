@@ -421,7 +421,8 @@ gt_status gt_lookup(gt_dtype dtype, const void *table, int64_t n_rows, int64_t l
  *   kind: 0 aggregation (given CSR), 1 aggregation (transposed), 2 combination, 3 fused
  *   aggregation + combination (width = in_dim)
  *   width: feature width F (aggregation) or N (combination); rows: output rows;
- *   work: edges gathered (aggregation) or M*N*K (combination); ms: kernel duration.
+ *   work: edges gathered (aggregation) or M*N*K (combination); ms: kernel duration, an
+ *   aggregation's with the copy of its table where one is made (gt_aggregate_best_ws_size).
  * gt_trace_get synchronises on the record's end event.
  * ------------------------------------------------------------------------------------------ */
 gt_status gt_trace_enable(int on);
@@ -431,7 +432,8 @@ gt_status gt_trace_get(int64_t i, int *kind, int64_t *width, int64_t *rows, int6
 /* Which instance of the aggregation kernel record i timed: V elements per lane and load, G lanes
  * per work item, NP column tiles per lane, U row loads in flight, and whether it applies an output
  * mask (all 0 for a combination record).  Together with the data type these are the kernel's
- * template arguments, i.e. its name in a profiler's kernel list. */
+ * template arguments, i.e. its name in a profiler's kernel list; where gt_pull_bwd forms both
+ * derivatives of GT_H_SCALE in one kernel, they are that kernel's. */
 gt_status gt_trace_get_variant(int64_t i, int *V, int *G, int *NP, int *U, int *masked);
 
 const char *gt_status_string(gt_status s);

@@ -123,19 +123,25 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
         if (!ws || ((uintptr_t)ws & 255)) return gt_fail(GT_ERR_WORKSPACE, "%s: ws null or not 256-byte aligned", fn);
         if (ws_bytes < need) return gt_fail(GT_ERR_WORKSPACE, "%s: ws_bytes %zu < required %zu", fn, ws_bytes, need);
     }
+    if (mask && ldmask < F) return gt_fail(GT_ERR_INVALID_ARG, "%s: mask leading dimension smaller than F", fn);
 
+    AggArgs a{};
+    a.trace_kind = !traced ? -1 : transposed ? GT_TRACE_AGG_BWD : GT_TRACE_AGG_FWD;
+    a.n_rows = n_out; a.n_edges = g->n_edges;
     const int64_t rb = F * (int64_t)es, stride = table_copy_stride(sc, n_in, g->n_edges, rb, X, ldx * (int64_t)es);
     if (stride && ws && ((uintptr_t)ws & 255) == 0 && ws_bytes >= need + (size_t)(n_in * stride)) {
         unsigned char *copy = static_cast<unsigned char *>(ws) + need;
         const unsigned blocks = (unsigned)((n_in + 1024 / (stride / 16) - 1) / (1024 / (stride / 16)));
+        a.trace_open = 1 + gt_trace_open(a.trace_kind, F, n_out, g->n_edges, st);   // (the gather's time has the copy in it)
         if (stride == 64) k_repack<4><<<blocks, 256, 0, st>>>(static_cast<const unsigned char *>(X), ldx * (int64_t)es, (int)rb, n_in, copy);
         else k_repack<8><<<blocks, 256, 0, st>>>(static_cast<const unsigned char *>(X), ldx * (int64_t)es, (int)rb, n_in, copy);
-        GT_LAUNCH_CHECK("k_repack");
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) {
+            gt_trace_close(a.trace_open - 1, st);
+            return gt_hip_fail(e, "k_repack");
+        }
         X = copy;
         ldx = stride / (int64_t)es;
     }
-
-    AggArgs a{};
     a.items = sc.items; a.n_items = sc.n_items; a.n_long = sc.n_long; a.max_len = sc.max_len;
     a.rowptr = sc.rowptr; a.nbr = sc.nbr;
     a.coef = sc.wt; a.post_mode = 0;
@@ -148,13 +154,10 @@ gt_status gt_aggregate_run(const gt_graph *g, bool transposed, gt_reduce reduce,
     a.bias = bias; a.relu = (act == GT_ACT_RELU);
     a.mask = mask; a.ldmask = ldmask;
     a.pad_out = pad_out ? 1 : 0;
-    if (mask && ldmask < F) return gt_fail(GT_ERR_INVALID_ARG, "%s: mask leading dimension smaller than F", fn);
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.F = F;
     a.partials = static_cast<float *>(ws); a.ldp = (F + 7) / 8 * 8;
     a.splits = sc.splits; a.n_splits = sc.n_splits;
     a.table_bytes = n_in * ldx * (int64_t)es;
-    a.trace_kind = !traced ? -1 : transposed ? GT_TRACE_AGG_BWD : GT_TRACE_AGG_FWD;
-    a.n_rows = n_out; a.n_edges = g->n_edges;
 
     const int ve = in_dtype == GT_F32 ? 4 : 8;
     const bool vec = aligned16(X) && aligned16(Y) && (ldx % ve == 0) && (ldy % ve == 0) &&

@@ -61,6 +61,7 @@ struct AggArgs {
     int only_split;          // run only the chunk items of split rows (the whole-row items are someone else's)
     int no_reduce;           // host-side: do not launch the kernel that adds the partial rows
     int trace_kind;          // host-side bookkeeping of the optional kernel timing
+    int trace_open;          // 1 + the record that the caller has opened for this launch, or 0
     int64_t n_rows, n_edges;
 };
 
@@ -812,7 +813,7 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
         b.xcd_run = agg_xcd_run(gi);
         const int S = 1 << b.slices_lg;
         const int64_t gx = S > 1 ? (gb + 8 / S - 1) / (8 / S) * 8 : gb;
-        const int tr = gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
+        const int tr = a.trace_open > 0 ? a.trace_open - 1 : gt_trace_open(a.trace_kind, a.F, a.n_rows, a.n_edges, st);
         gt_trace_variant(tr, V, G, NP, U, agg_plain(VWM) && a.mask != nullptr);
         const dim3 grid((unsigned)gx, (tiles + S - 1) / S);
         // (narrow groups hold several ids per lane where items are shared out to 64 / G groups of four lanes)

@@ -121,3 +121,34 @@ def test_sizes(graph):
     out = torch.empty_like(X)
     B.gt_aggregate_fwd_static(graph, "mean", X, out)
     assert torch.equal(out, _in_place(graph, X))
+
+
+def test_timing_record_has_the_copy_in_it():
+    """The record of a gather from a copy spans both kernels.  Degree 12, where the copy is some 12 % of the call: the record has to reach 95 % of what events
+    around the call measure (launch overhead is 1 %)."""
+    from paper_2305_17469_amd import binding as B
+    n, deg = 2_000_000, 12
+    gen = torch.Generator(device="cuda:0").manual_seed(9)
+    g = B.Graph((torch.arange(n + 1, device="cuda:0") * deg).int(), torch.randint(0, n, (n * deg,), device="cuda:0", generator=gen).int(), n)
+    X = torch.randn((n, 47), device="cuda:0", generator=gen).bfloat16()
+    assert g.aggregate_ws(47, X).numel() == n * 128
+    Y, shares = torch.empty_like(X), []
+    announce("aggregation, timing record")
+    for _ in range(3):
+        B.gt_aggregate_fwd(g, "sum", X, out=Y)
+    for _ in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        B.gt_trace_reset()
+        B.gt_trace_enable(True)
+        try:
+            a.record()
+            B.gt_aggregate_fwd(g, "sum", X, out=Y)
+            b.record()
+            recs = B.gt_trace_records()
+        finally:
+            B.gt_trace_enable(False)
+            B.gt_trace_reset()
+        b.synchronize()
+        assert len(recs) == 1 and recs[0][0] == 0
+        shares.append(recs[0][4] / a.elapsed_time(b))
+    assert 0.95 <= sorted(shares)[4] <= 1.001, shares
