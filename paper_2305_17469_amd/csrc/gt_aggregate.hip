@@ -64,10 +64,11 @@ __global__ void __launch_bounds__(256) k_repack(const unsigned char *in, int64_t
 
 }  // namespace
 
-// Room for such a copy at width F, of whichever direction it may serve; 0 where no stride of the caller's could make it pay.
+// Room for such a copy at width F, of whichever direction it may serve and at whichever stride the table is given; 0 where no stride could make
+// it pay.  The most lines that a row lies in are those of one that begins with a line's last element, and at a stride of whole lines all rows may.
 size_t gt_aggregate_repack_bytes(const gt_graph *g, int64_t F, gt_dtype t) {
     const int64_t rb = F * (int64_t)gt_dtype_size(t);
-    const double most = 1.0 + (double)(rb - 2) / 128.0;   // rows at every element of a line
+    const double most = (double)((128 - (int64_t)gt_dtype_size(t) + rb + 127) / 128);
     const int64_t f = repack_stride(g->fwd, g->n_src, g->n_edges, rb, most) * g->n_src, b = repack_stride(g->bwd, g->n_dst, g->n_edges, rb, most) * g->n_dst;
     return (size_t)(f > b ? f : b);
 }

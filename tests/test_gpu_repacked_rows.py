@@ -113,3 +113,37 @@ def test_layers(graph, dt, fi, fo):
         for name, got, ref in (("Y", Y, Z.clamp(min=0)), ("dX", r["dX"], dX), ("dW", r["dW"], M.T @ dZ), ("db", r["db"], dZ.sum(0))):
             err = float((got.double() - ref).norm() / ref.norm())
             assert err <= tol, (order, name, err)
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+def test_layer_has_room_for_rows_across_two_lines(transposed):
+    """Rows of 94 bytes at a stride of 128 that all lie in two lines: at 9 entries per row the copy pays for these, not for rows at every offset (1.73 lines).  The
+    layer's scratch, sized without the stride, has the room: the copy's first rows are found there."""
+    from paper_2305_17469_amd import binding as B
+    n, deg, fi, fo = 300_000, 9, (120, 47)[not transposed], (47, 120)[not transposed]
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    g = B.Graph((torch.arange(n + 1, device="cuda:0") * deg).int(), torch.randint(0, n, (n * deg,), device="cuda:0", generator=gen).int(), n)
+
+    def rows(F, across):
+        buf = torch.zeros(n * 128 + 64, dtype=torch.bfloat16, device="cuda:0")
+        t = buf[20:20 + n * 64].view(n, 64)[:, :F] if across else buf[:n * 120].view(n, 120)[:, :F]
+        return t.copy_(torch.randn((n, F), device="cuda:0", generator=gen))
+    X, dY = rows(fi, not transposed), rows(fo, transposed)
+    W = torch.randn((fi, fo), device="cuda:0", generator=gen).bfloat16()
+    desc = B.make_desc("sum", "bf16", False, fi, fo)
+    bufs = B.LayerBuffers(g, desc)
+    announce("room in a layer's scratch", transposed)
+    order = "comb_first" if transposed else "agg_first"
+    Y, used = B.gt_layer_fwd(g, desc, X, W, None, bufs, order)
+    bufs.scratch.fill_(7)
+    if transposed:
+        B.gt_layer_bwd(g, desc, used, dY, X, W, Y, bufs, order)
+        table = dY
+    else:
+        B.gt_layer_fwd(g, desc, X, W, None, bufs, order)
+        table = X
+    torch.cuda.synchronize()
+    lines = bufs.scratch[:bufs.scratch.numel() // 128 * 128].view(-1, 128)[:, :94]
+    first = table[:3].contiguous().view(torch.uint8)
+    at = (lines == first[0]).all(1).nonzero().flatten().tolist()
+    assert any(torch.equal(lines[i:i + 3], first) for i in at)
