@@ -60,6 +60,7 @@ struct AggArgs {
     int n_blocks;            // set at launch: workgroups per column tile
     int only_split;          // run only the chunk items of split rows (the whole-row items are someone else's)
     int no_reduce;           // host-side: do not launch the kernel that adds the partial rows
+    int64_t chunk_entries;   // host-side: entries of the chunk items where these are all that the launch gathers and they set its form (see launch_u), or 0
     int trace_kind;          // host-side bookkeeping of the optional kernel timing
     int trace_open;          // 1 + the record that the caller has opened for this launch, or 0
     int64_t n_rows, n_edges;
@@ -680,8 +681,9 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AggArgs a) {
 }
 
 // What a launch gathers
+static inline int64_t agg_entries(const AggArgs &a) { return a.chunk_entries > 0 ? a.chunk_entries : a.n_edges; }
 template <typename T>
-static inline double agg_bytes(const AggArgs &a) { return (double)a.n_edges * (double)a.F * sizeof(T); }
+static inline double agg_bytes(const AggArgs &a) { return (double)agg_entries(a) * (double)a.F * sizeof(T); }
 
 // Skewed: rows longer than 1.5 chunks exist, and most items are not long.  A long item is then a chain of up to 1.5 chunk / U round
 // trips while the other items of the launch are soon done; where every row is long (and about as long as the next one), no
@@ -704,6 +706,7 @@ static inline bool agg_skewed(const AggArgs &a) { return agg_skewed(a.n_splits, 
 static inline bool agg_share_out(const AggArgs &a, int G, int U, double bytes) {
     if (a.n_long > 0 && a.n_items * G <= 1792 * 64) return true;
     if (!agg_skewed(a)) return false;
+    if (a.chunk_entries > 0) return bytes <= 2.0e9;   // (nothing else in the launch hides them, whatever the table)
     const double chunk = gt_chunk_for(a.n_edges);
     if (G >= 32) return bytes <= chunk * (a.table_bytes <= ((int64_t)32 << 20) ? 8.0e6 : 5.0e6);
     if (U == 8 && G >= 8 && a.table_bytes > ((int64_t)64 << 20)) return bytes <= chunk * 1.25e6;
@@ -717,7 +720,7 @@ static inline bool agg_share_out(const AggArgs &a, int G, int U, double bytes) {
 // 339 / 329) and no chain of a long row is lengthened by it: next to no long rows, or a launch that hides them (power law, 47 bf16
 // columns 52 M edges 798 / 777, 64 bf16 columns 26 M edges 306 / 327; degree 130, 12 M edges, 32 bf16 columns 77 / 89).
 static inline bool agg_long_batches(const AggArgs &a, int G, double bytes) {
-    return a.n_edges >= ((int64_t)2 << 20) && a.n_edges >= (G == 4 ? 4 : 12) * a.n_items && a.n_long * 4 <= a.n_items &&
+    return agg_entries(a) >= ((int64_t)2 << 20) && agg_entries(a) >= (G == 4 ? 4 : 12) * a.n_items && a.n_long * 4 <= a.n_items &&
            (G == 4 || a.n_long * 1024 <= a.n_rows || bytes > 4.0e9);
 }
 // ... and with rows long enough that vectors and long batches outdo elements on narrow fp32 rows without alignment (see agg_dispatch)
@@ -867,9 +870,11 @@ gt_status launch(const AggArgs &a, hipStream_t st, bool tiled = false, int slice
 //    if there are wavefronts enough (30 K rows of degree 130, 300 columns 360 / 557; 131 K rows of degree 25, 200 columns, one vector per lane 386 / 405;
 //    degree 6, 300 K rows 276 / 261; 130 columns, 33 of 64 lanes, 1 M rows of degree 8 1100 / 913; 6 K rows of 600 entries, 602 bf16 columns 342 / 255),
 //    and four vectors per lane take one wherever rows are short (degree 5, 66 K rows, 1030 columns 275 / 283).
+//  * The chunks of long rows alone (chunk_entries, the launch before a fused layer): eight, whatever the table (see gt_fused_run).
 template <typename T, int V, int G, int NP, int VWM, bool SH>
 gt_status launch_u(const AggArgs &a, hipStream_t st) {
     if constexpr (NP == 1 && agg_plain(VWM) && G <= 16) {
+        if (a.chunk_entries > 0) return launch<T, V, G, NP, 8, VWM, SH>(a, st);
         const double bytes = agg_bytes<T>(a);
         const bool fits = a.table_bytes <= ((int64_t)96 << 20);   // the last-level cache
         const bool fills = !agg_skewed(a) && a.n_items * G > 1792 * 64 && a.table_bytes > ((int64_t)6 << 20);

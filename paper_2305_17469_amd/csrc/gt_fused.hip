@@ -471,14 +471,13 @@ gt_status gt_fused_run(const gt_graph *g, gt_reduce reduce, gt_dtype dtype, int6
         c.only_split = 1;   // whole-row items are skipped ...
         c.no_reduce = 1;    // ... and the partial rows are left for the fused kernel to add
         c.Y = nullptr;
-        // What this launch gathers are the chunks alone.  By the whole graph's bytes and table their chains would pass for hidden behind other items:
-        // rows of up to 256 bytes of a table past 72 MB take the rules for the chunks' bytes, and eight loads in flight
+        // What this launch gathers are the chunks alone.  By the whole graph's bytes and table their chains would pass for hidden behind other items: for
+        // rows of up to 256 bytes of a table past 72 MB they are shared out by their own bytes, with eight loads in flight
         // (the whole call, us, before / now: power law, 1 M rows, 17 M edges, 128 -> 64 bf16 620 / 568, of which the chunks 166 / 107; 1.2 M rows, 8 M edges, 64 -> 64 fp32
         // 433 / 371; 600 K rows, 6 M edges, 64 -> 32 bf16 196 / 150; 262 K rows, a 67 MB table, 120 / 125; 512-byte rows 1228 / 1257).
         if (c.table_bytes > ((int64_t)72 << 20) && fi * (int64_t)es <= 256) {
             const int64_t chunks = sc.n_partials * (int64_t)g->chunk;
-            if (chunks < c.n_edges) c.n_edges = chunks;
-            c.table_bytes = (int64_t)64 << 20;
+            c.chunk_entries = chunks < c.n_edges ? chunks : c.n_edges;
         }
         const gt_status s = gt_agg_launch(c, dtype, true, st);
         if (s != GT_OK) return s;
