@@ -399,12 +399,14 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
     // A coefficient that is looked up through the permutation (VWM_SCORE) waits for its place there: the places are requested a batch
     // earlier still, and the two factors of an entry are multiplied when they are used, so that no load waits for another between the row loads
     // (both gathers of a dot product's derivative, of which one looks up, us, places in the batch before / earlier: power law, 8.4 M edges,
-    // 8 fp32 columns 308 / 261, 1 M edges 82 / 65; uniform, 131 K rows, 8.4 M edges, 32 bf16 columns 349 / 304; not where eight lanes hold two ids each: 47 bf16 columns 380 / 410; what
-    // bounds rows of 256 bytes are the lines of the scores: 482 / 477).
-    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = !(G == 8 && IPL > 1);
+    // 8 fp32 columns 308 / 261, 1 M edges 82 / 65; uniform, 131 K rows, 8.4 M edges, 32 bf16 columns 349 / 304; what bounds rows of 256 bytes are the lines
+    // of the scores: 482 / 477).  Not where eight lanes hold two ids each: these have the rows in flight without it, and every score is waited for before the next
+    // place is asked for, which leaves the L2s to the rows (uniform, 131 K rows, 8.4 M edges, 47 bf16 columns without alignment, both gathers
+    // 444 not waited for, 417 waited for, 444 with places a batch earlier; 100 K rows, 4.8 M edges, 25 fp32 columns 227, 220 and 226).
+    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = SCORE && !(G == 8 && IPL > 1);
     int idx_next[IPL], ei_next[IPL];
     float c_next[IPL], f_next[IPL];
-    if constexpr (SCORE) {
+    if constexpr (EARLY) {
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {   // the first batch's places; the second's follow
             const int e = e0 + k * G + gl;
@@ -428,12 +430,17 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
             idx_next[k] = 0;
             c_next[k] = 0.0f;
             f_next[k] = 1.0f;
-            if constexpr (!SCORE) ei_next[k] = 0;
+            if constexpr (!EARLY) ei_next[k] = 0;
             if (e < e1) {
                 idx_next[k] = a.nbr[e];
-                if constexpr (SCORE) {
+                if constexpr (EARLY) {
                     c_next[k] = a.coef[ei_next[k]];
                     if (a.coef2) f_next[k] = a.coef2[e];
+                } else if constexpr (SCORE) {
+                    ei_next[k] = a.eidx[e];
+                    c_next[k] = a.coef[ei_next[k]];
+                    if (a.coef2) c_next[k] *= a.coef2[e];
+                    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
                 } else if constexpr (VWM == VWM_NONE) {
                     c_next[k] = a.coef ? a.coef[e] : 1.0f;
                 } else {
@@ -443,7 +450,7 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
             }
         }
     };
-    if constexpr (SCORE && EARLY) places(e0, GB);
+    if constexpr (EARLY) places(e0, GB);
     fetch(e0);
     const T *VWp = static_cast<const T *>(a.VW);
     // This lane's columns, counted from the tile's first one.  Lanes past the row's end repeat its last vector, in sums that nobody stores: a line
@@ -461,16 +468,15 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
     for (int base = e0; base < e1; base += GB) {
         int idx[IPL], ei[IPL];
         float c[IPL];
-        if constexpr (SCORE && !EARLY) places(base, GB);
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {
             idx[k] = idx_next[k];
             ei[k] = ei_next[k];
-            c[k] = SCORE ? c_next[k] * f_next[k] : c_next[k];
-            if constexpr (SCORE) ei_next[k] = ei_later[k];
+            c[k] = EARLY ? c_next[k] * f_next[k] : c_next[k];
+            if constexpr (EARLY) ei_next[k] = ei_later[k];
         }
         fetch(base + GB);
-        if constexpr (SCORE && EARLY) places(base, 2 * GB);
+        if constexpr (EARLY) places(base, 2 * GB);
         const int cnt = (e1 - base) < GB ? (e1 - base) : GB;
         // entries j .. j + N - 1 of the batch (j is a constant where IPL > 1); ALL: every one of them is there, and the loads are
         // branch free (with a branch around each, the exchange that brings its id and the load wait for one another)
