@@ -396,14 +396,14 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
     // The group fetches GB neighbour ids and coefficients with coalesced loads and walks them; the next GB are requested
     // before the current ones are used, so the id fetch of the next batch overlaps the row gathers of this one.
     constexpr int GB = G * IPL;
-    // A coefficient that is looked up through the permutation (VWM_SCORE) waits for its place there: the places are requested a batch
-    // earlier still, and the two factors of an entry are multiplied when they are used, so that no load waits for another between the row loads
-    // (both gathers of a dot product's derivative, of which one looks up, us, places in the batch before / earlier: power law, 8.4 M edges,
-    // 8 fp32 columns 308 / 261, 1 M edges 82 / 65; uniform, 131 K rows, 8.4 M edges, 32 bf16 columns 349 / 304; what bounds rows of 256 bytes are the lines
-    // of the scores: 482 / 477).  Not where eight lanes hold two ids each: these have the rows in flight without it, and every score is waited for before the next
-    // place is asked for, which leaves the L2s to the rows (uniform, 131 K rows, 8.4 M edges, 47 bf16 columns without alignment, both gathers
-    // 444 not waited for, 417 waited for, 444 with places a batch earlier; 100 K rows, 4.8 M edges, 25 fp32 columns 227, 220 and 226).
-    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = SCORE && !(G == 8 && IPL > 1);
+    // A coefficient that is looked up through the permutation (VWM_SCORE) waits for its place there.  EARLY: the places are requested a batch
+    // earlier still, and the two factors of an entry are multiplied when they are used, so that no load waits for another between the row loads.  That is
+    // ahead in groups of four lanes, and of eight with eight rows in flight.  The others have rows in flight without it, and wait for every score
+    // before the next place is asked for, which leaves the L2s to the rows.  The transposed gather alone, us, places early / waited for: power law, 262 K rows, 8.4 M edges,
+    // 4 to 16 fp32 columns 0.84, 32 fp32 columns 0.96 of the time; uniform, 500 K rows, 8 M edges, 16 fp32 columns 304 / 328, 60 K rows, 2.2 M edges 49 / 55 (with exactly 36 entries
+    // each 44 / 41); 131 K rows, 8.4 M edges, 47 bf16 columns without alignment 264 / 238; 64 bf16 columns and more, 32 fp32 columns and more: uniform 1.00 to 1.21, power law
+    // 0.99 to 1.00 of the time.
+    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = SCORE && (G == 4 || (G == 8 && U == 8 && IPL == 1));
     int idx_next[IPL], ei_next[IPL];
     float c_next[IPL], f_next[IPL];
     if constexpr (EARLY) {
