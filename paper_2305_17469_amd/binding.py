@@ -130,11 +130,11 @@ def _check(status):
 
 
 def _stream():
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype(t):
@@ -174,6 +174,7 @@ class Graph:
         _check(lib.gt_graph_create(byref(h), self.n_dst, self.n_src, self.n_edges, _ptr(self.rowptr), _ptr(self.colidx),
                                    _ptr(self.edge_weight), _ptr(self.ws), self.ws.numel(), _stream()))
         self.handle = h
+        self._sizes = {}
 
     def __del__(self):
         h = getattr(self, "handle", None)
@@ -204,25 +205,50 @@ class Graph:
         _check(lib.gt_graph_validate(self.handle, byref(n), _stream()))
         return n.value
 
+    def _scratch_bytes(self, F, table=None, transposed=False):
+        """Bytes of scratch that a call at width F needs, or, for the plain aggregation of `table`, is fastest with.  Sizes follow from the plan
+        and from what their keys say, so each is asked for once."""
+        key = F if table is None else (F, transposed, table.dtype)
+        n = self._sizes.get(key)
+        if n is not None:
+            return n
+        need = c_size_t()
+        _check(lib.gt_aggregate_ws_size(self.handle, int(F), byref(need)))
+        n = need.value
+        if table is not None:
+            def best(ptr, ld):
+                _check(lib.gt_aggregate_best_ws_size(self.handle, int(transposed), _dtype(table), int(F), ptr, ld, byref(need)))
+                return need.value
+            # no table of this width gains by more room than one whose every row begins with the last element of a line
+            if best(128 - table.element_size(), (int(F) + 63) // 64 * 64) > n:
+                return best(table.data_ptr(), _rows2d(table))
+        if len(self._sizes) >= 1024:
+            self._sizes.clear()
+        self._sizes[key] = n
+        return n
+
     def aggregate_ws(self, F, table=None, transposed=False):
         """Scratch of one call at width F, from torch's allocator: ordered with the current stream, and a captured graph's own.  Calls
         on other streams and captured graphs may be at work in theirs, so nothing of it is kept on the Graph.  What such a call needs, or, for the
         plain aggregation of `table`, what it is fastest with."""
-        need = c_size_t()
-        if table is None:
-            _check(lib.gt_aggregate_ws_size(self.handle, int(F), byref(need)))
-        else:
-            _check(lib.gt_aggregate_best_ws_size(self.handle, int(transposed), _dtype(table), int(F), _ptr(table), _rows2d(table), byref(need)))
-        return _ws(need.value, self.device)
+        return _ws(self._scratch_bytes(F, table, transposed), self.device)
+
+    def _scratch(self, F, table=None, transposed=False):
+        """(tensor, pointer, bytes) of that scratch, nothing where the call needs none: an allocation is a quarter of the smallest call's host time."""
+        n = self._scratch_bytes(F, table, transposed)
+        if n == 0:
+            return None, None, 0
+        ws = self.ws.new_empty(n)
+        return ws, ws.data_ptr(), n
 
 
 def gt_aggregate_fwd(g: Graph, reduce, X, out=None, F=None):
     """Y[n_dst, F] = A X.  `out` may be a preallocated (possibly wider-strided) tensor."""
     F = X.shape[1] if F is None else F
     Y = torch.empty((g.n_dst, F), dtype=X.dtype, device=X.device) if out is None else out
-    ws = g.aggregate_ws(F, X)
+    ws, ws_ptr, ws_bytes = g._scratch(F, X)
     _check(lib.gt_aggregate_fwd(g.handle, REDUCE[reduce], _dtype(X), F, _ptr(X), _rows2d(X), _ptr(Y), _rows2d(Y),
-                                _ptr(ws), ws.numel(), _stream()))
+                                ws_ptr, ws_bytes, _stream()))
     return Y
 
 
@@ -244,10 +270,10 @@ def gt_aggregate_combine_fwd(g: Graph, reduce, X, W, b=None, relu=False, out=Non
     """Y = act((A X) W + b) in one fused kernel (inference: A X is not kept)."""
     fi, fo = W.shape
     Y = torch.empty((g.n_dst, fo), dtype=X.dtype, device=X.device) if out is None else out
-    ws = g.aggregate_ws(fi)
+    ws, ws_ptr, ws_bytes = g._scratch(fi)
     assert W.is_contiguous()
     _check(lib.gt_aggregate_combine_fwd(g.handle, REDUCE[reduce], _dtype(X), fi, fo, _ptr(X), _rows2d(X), _ptr(W), _ptr(b),
-                                        GT_ACT_RELU if relu else GT_ACT_NONE, _ptr(Y), _rows2d(Y), _ptr(ws), ws.numel(),
+                                        GT_ACT_RELU if relu else GT_ACT_NONE, _ptr(Y), _rows2d(Y), ws_ptr, ws_bytes,
                                         _stream()))
     return Y
 
@@ -256,9 +282,9 @@ def gt_aggregate_bwd(g: Graph, reduce, dY, out=None, F=None):
     """dX[n_src, F] = A^T dY."""
     F = dY.shape[1] if F is None else F
     dX = torch.empty((g.n_src, F), dtype=dY.dtype, device=dY.device) if out is None else out
-    ws = g.aggregate_ws(F, dY, transposed=True)
+    ws, ws_ptr, ws_bytes = g._scratch(F, dY, True)
     _check(lib.gt_aggregate_bwd(g.handle, REDUCE[reduce], _dtype(dY), F, _ptr(dY), _rows2d(dY), _ptr(dX), _rows2d(dX),
-                                _ptr(ws), ws.numel(), _stream()))
+                                ws_ptr, ws_bytes, _stream()))
     return dX
 
 
@@ -301,19 +327,19 @@ def gt_neighbor_apply_bwd(g: Graph, fn, dW, Xs, Xd, out_dXs=None, out_dXd=None):
     F = Xs.shape[1]
     dXs = torch.empty((g.n_src, F), dtype=Xs.dtype, device=Xs.device) if out_dXs is None else out_dXs
     dXd = torch.empty((g.n_dst, F), dtype=Xs.dtype, device=Xs.device) if out_dXd is None else out_dXd
-    ws = g.aggregate_ws(F)
+    ws, ws_ptr, ws_bytes = g._scratch(F)
     _check(lib.gt_neighbor_apply_bwd(g.handle, EDGE_FN[fn], _dtype(Xs), F, _ptr(dW), _ld(dW), _ptr(Xs), _rows2d(Xs),
                                      _ptr(Xd), _rows2d(Xd), _ptr(dXs), _rows2d(dXs), _ptr(dXd), _rows2d(dXd),
-                                     _ptr(ws), ws.numel(), _stream()))
+                                     ws_ptr, ws_bytes, _stream()))
     return dXs, dXd
 
 
 def gt_pull_fwd(g: Graph, reduce, h, Xs, W, out=None):
     F = Xs.shape[1]
     Y = torch.empty((g.n_dst, F), dtype=Xs.dtype, device=Xs.device) if out is None else out
-    ws = g.aggregate_ws(F)
+    ws, ws_ptr, ws_bytes = g._scratch(F)
     _check(lib.gt_pull_fwd(g.handle, REDUCE[reduce], WEIGHT_FN[h], _dtype(Xs), F, _ptr(Xs), _rows2d(Xs), _ptr(W), _ld(W),
-                           _ptr(Y), _rows2d(Y), _ptr(ws), ws.numel(), _stream()))
+                           _ptr(Y), _rows2d(Y), ws_ptr, ws_bytes, _stream()))
     return Y
 
 
@@ -321,10 +347,10 @@ def gt_pull_bwd(g: Graph, reduce, h, dY, Xs, W, out_dXs=None, out_dW=None):
     F = Xs.shape[1]
     dXs = torch.empty((g.n_src, F), dtype=Xs.dtype, device=Xs.device) if out_dXs is None else out_dXs
     dW = torch.empty_like(W) if out_dW is None else out_dW
-    ws = g.aggregate_ws(F)
+    ws, ws_ptr, ws_bytes = g._scratch(F)
     _check(lib.gt_pull_bwd(g.handle, REDUCE[reduce], WEIGHT_FN[h], _dtype(Xs), F, _ptr(dY), _rows2d(dY), _ptr(Xs),
-                           _rows2d(Xs), _ptr(W), _ld(W), _ptr(dXs), _rows2d(dXs), _ptr(dW), _ld(dW), _ptr(ws),
-                           ws.numel(), _stream()))
+                           _rows2d(Xs), _ptr(W), _ld(W), _ptr(dXs), _rows2d(dXs), _ptr(dW), _ld(dW), ws_ptr,
+                           ws_bytes, _stream()))
     return dXs, dW
 
 

@@ -123,6 +123,19 @@ def test_sizes(graph):
     assert torch.equal(out, _in_place(graph, X))
 
 
+def test_calls_take_what_they_need(graph):
+    """Sizes are asked for once per width, or per table where its stride and alignment count; a call that needs nothing allocates nothing."""
+    buf = torch.empty(20 + N * 64, dtype=torch.bfloat16, device="cuda:0")
+    lines, across = buf[:N * 64].view(N, 64)[:, :47], buf[20:20 + N * 64].view(N, 64)[:, :47]
+    packed, wide = buf[:N * 47].view(N, 47), torch.empty((N, 80), dtype=torch.bfloat16, device="cuda:0")
+    for _ in range(2):
+        assert graph._scratch(47) == (None, None, 0)
+        for table, want in ((lines, 0), (across, N * 128), (packed, N * 128), (lines, 0), (packed[:, :28], N * 64), (wide, 0), (wide.float(), 0)):
+            for transposed in (False, True):
+                ws, ptr, n = graph._scratch(table.shape[1], table, transposed)
+                assert n == want and ((ws, ptr) == (None, None) if want == 0 else ws.numel() == n and ptr == ws.data_ptr() and ptr % 256 == 0)
+
+
 def test_timing_record_has_the_copy_in_it():
     """The record of a gather from a copy spans both kernels.  Degree 12, where the copy is some 12 % of the call: the record has to reach 95 % of what events
     around the call measure (launch overhead is 1 %)."""
