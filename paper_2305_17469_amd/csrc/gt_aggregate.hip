@@ -28,7 +28,7 @@ double mean_lines(uintptr_t base, int64_t stride, int64_t rb) {
 // misses (10 TB/s of them), what it costs are its bytes (4.5 TB/s); it has to be clearly ahead, and the table well past the L2s.  us, both
 // directions of the gather as it is / copied: 1 M rows of degree 16, 47 bf16 columns 1026 / 822, of degree 8 601 / 531, 61 columns 1175 / 845, 25 columns 840 /
 // 765; 300 K rows of degree 20, 47 columns 295 / 268; 1 M rows of degree 4, 47 columns 365 / 369; 65 K rows of degree 25 (6 MB) 68 / 70.
-// Power-law graphs find the rows they read most in the L2s at any stride (1 M rows of degree 16, 47 bf16 columns 633 / 640).
+// On power-law graphs, whose rows read most are hits, it saves what it costs (1 M rows of degree 16, 47 bf16 columns 633 / 640).
 int64_t repack_stride(const gt_sched &sc, int64_t n_in, int64_t n_edges, int64_t rb, double lines) {
     if (rb <= 32 || rb > 128 || n_in * rb < ((int64_t)24 << 20) || agg_skewed(sc.n_splits, sc.n_long, sc.n_items)) return 0;
     const int64_t stride = rb <= 64 ? 64 : 128;
@@ -75,7 +75,9 @@ size_t gt_aggregate_repack_bytes(const gt_graph *g, int64_t F, gt_dtype t) {
 
 // Row stride (elements) of a table that the library writes itself and then gathers, `transposed` or not: 16-byte padding, or the next multiple of 64 or 128 bytes where
 // a uniform graph's rows then lie in fewer lines (1 M rows of degree 16, one direction, 47 bf16 columns at 96 bytes 467 us, at 128 364; 41 fp32 columns at 176
-// bytes 683, at 192 621; 101 bf16 columns at 208 bytes 755, at 256 623).
+// bytes 683, at 192 621; 101 bf16 columns at 208 bytes 755, at 256 623).  On power-law graphs fewer lines are not always ahead, because the table grows in the L2s
+// and a power of two maps the rows read most to few channels: 262 K rows, 12 M edges, one direction, 41 fp32 columns at 176 bytes 171 us, at 192 161; 47 bf16
+// columns at 96 bytes 120, at 128 112; 101 bf16 columns at 208 bytes 227, at 256 277; 70 bf16 columns at 144 bytes 188, at 256 245: they keep 16-byte padding.
 int64_t gt_aggregate_table_ld(const gt_graph *g, bool transposed, int64_t F, gt_dtype t) {
     const int64_t es = (int64_t)gt_dtype_size(t), rb = F * es, pad = (rb + 15) / 16 * 16;
     const gt_sched &sc = transposed ? g->bwd : g->fwd;

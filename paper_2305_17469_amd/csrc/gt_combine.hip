@@ -752,14 +752,15 @@ bool tn256_shape(int transA, int transB, int64_t M, int64_t N, int64_t K) {
     return tiles <= 8 && 5 * reads(128) >= 8 * reads(256) && K >= (tiles >= 4 ? 65536 : 98304);
 }
 
-// Tiles of k_gemm_tn_wide for an output: the shape that covers it in the fewest tiles, of those the smallest.  No tile: bm 0.
+// Tiles of k_gemm_tn_wide for an output: the shape that covers it in the fewest tiles, the first listed of those (all three hold 81,920 results).  There is none of 128 x 640:
+// outputs of up to 128 rows and more than 320 columns take two tiles.
 struct WideTile { int64_t bm, bn; };
 WideTile tn_wide_tile(int64_t M, int64_t N) {
     WideTile best{0, 0};
-    int64_t most = 0;
+    int64_t fewest = 0;
     for (const WideTile t : {WideTile{320, 256}, WideTile{256, 320}, WideTile{640, 128}}) {
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-        if (!best.bm || tiles < most) { best = t; most = tiles; }
+        if (!best.bm || tiles < fewest) { best = t; fewest = tiles; }
     }
     return best;
 }
