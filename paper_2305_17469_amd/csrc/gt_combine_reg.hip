@@ -283,35 +283,59 @@ gt_status launch_reg(const GemmArgs &g, int transB, const Slices &s, hipStream_t
 
 // Which products come here.  us, the kernel that would take it otherwise / this one, weights as they are stored [k][n] unless said; setting the weights up
 // costs 8 to 12 us (transposed ones 3 to 5, unaligned transposed ones up to 25), so the middle of the range of M stays with the row tiles
-// (operands' rows aligned and padded to 16 bytes: vec) wherever a round or two of them is enough:
+// (operands' rows aligned and padded to 16 bytes: vec) wherever a round or two of them is enough.  With few terms a block of A is 4 to 8 KB, too little in flight
+// to hide its latency behind, so that a tile's round is ahead until the tiles fill many rounds; at up to 512 columns only five to seven of the eight wavefronts
+// have columns besides.  The lines below are those of 16,000 random products (K 64 to 1,024, N 65 to 1,280, M 1,024 to 600,000, both orders of the weights, padded and
+// contiguous) and of 1,800 at round sizes: this kernel takes 0.68 and 0.79 of the time of the others in the geometric mean of what it is given; 2 % of them are slower by more than 3 %.
 //  * Rows without that alignment, which the general tiles read by element at the matrix's ends and hold a tile of weights four times as long: from 2,000
-//    rows on, 1,024 with more than 256 terms (2 K rows, 602 -> 255 33.1 / 23.0, 131 K rows 166 / 69, 257 -> 602 230 / 84; 4 K rows, 65 -> 300 14.5 / 9.4); transposed
-//    weights of more than 256 columns and others of more than 640 from 32,768 (16 K rows, 257 -> 602 transposed 29.4 / 34.7, 33 K rows 52.6 / 45.2; 16 K
-//    rows, 101 -> 1000 14.8 / 22.1, 33 K rows 33.8 / 31.9), with fewer than 100 terms from 65,536 (53 K rows, 67 -> 307 18.9 / 22.3).
-//  * K past 640 and more than 128 columns (two slices of 128, A read twice): up to 16,384 rows, which are too few row tiles (4 K rows, 800 -> 130 23.0 /
-//    13.5, 16 K rows 23.7 / 19.5; 33 K rows 25.1 / 27.0, 400 K rows, 700 -> 200 245 / 263).
-//  * K up to 256 and more than 256 columns (weight-stationary from LDS, 256 columns at a time, or tiles): from 49,152 rows on (65 K rows, 128 -> 602 46.2 /
-//    29.7, 256 -> 1000 66 / 55; 33 K rows, 256 -> 602 27.8 / 28.6; 400 K rows 295 / 178), with fewer than 100 terms from 98,304 (75 K rows, 78 -> 411 28.4 /
-//    31.6; 131 K rows, 65 -> 270 36.4 / 32.3), past 640 columns from 131,072 (64 -> 1000, 65 K rows 39.1 / 39.8, 400 K rows 338 / 208).
-//  * K past 256, several slices: from 49,152 rows on (65 K rows, 512 -> 400 53 / 47, 320 -> 640 55 / 46; 16 K rows 20.7 / 21.8).
-//  * K past 256, more than 256 columns in one slice: from 32,768 rows on (65 K rows, 400 -> 300 54 / 38; 16 K rows 17.4 / 19.5), transposed weights always
-//    (16 K rows 15.9 / 12.9).
-//  * K past 256, 129 to 256 columns: up to 12,288 rows (4 K rows, 602 -> 256 18.9 / 16.1, transposed 17.0 / 10.4) and from 65,536 on (50 K rows, 512 -> 256
-//    26.7 / 29.3), with more than 512 terms from 98,304 (80 K rows, 600 -> 129 44.5 / 47.9; 131 K rows, 602 -> 256 64.9 / 58.3, 2^19 rows 306 / 211).
-//  * K past 256, up to 128 columns: from 2,000 rows on (4 K rows, 300 -> 128 12.0 / 7.7, 1000 -> 70 27.0 / 13.9; 400 K rows 124 / 92, 287 / 170).
+//    rows on, 1,024 with more than 256 terms (2 K rows, 602 -> 255 33.1 / 23.0, 131 K rows 166 / 69, 257 -> 602 230 / 84; 4 K rows, 65 -> 300 14.5 / 9.4); more than
+//    384 columns in one slice past 18,432 with more than 256 terms (3 K rows, 320 -> 443 1.24 of the time), more than 512 from 8,192 (2.5 K rows, 150 -> 560 1.2);
+//    transposed weights of more than 256 columns and others of more than 640 from 32,768 (16 K rows, 257 -> 602 transposed 29.4 / 34.7, 33 K rows 52.6 / 45.2; 16 K
+//    rows, 101 -> 1000 14.8 / 22.1, 33 K rows 33.8 / 31.9).  Up to 128 terms (transposed weights past 32,768 rows only): 257 to 320 columns up to 18,432 rows and past 32,768 (32,768 rows, 75 -> 257 1.12 of
+//    the time, 50 K 0.84), 321 to 512 up to 8,192, past 32,768 up to 98,304 (163,840 past 448 columns) and from 393,216 (16 K rows, 100 -> 401 1.09, 32,768 1.28, 50 K 0.96, 169 K 1.09, 2^19 0.81), 513 to 640 up to
+//    8,192 and from 24,576 (12 K rows 1.1, 32,768 0.65), 641 to 768 past 32,768 but for 163,840 to 262,144 (1.0 to 1.06), more past 32,768.
+//  * K past 640 and more than 128 columns (two slices of 128, A read twice): up to 8,192 rows, 16,384 of transposed weights, which are too few row tiles (4 K rows, 800 -> 130 23.0 /
+//    13.5, 12 K rows 1.1 of the time; 33 K rows 25.1 / 27.0, 400 K rows, 700 -> 200 245 / 263).
+//  * K up to 128 and more than 256 columns (weight-stationary from LDS, 256 columns at a time, or tiles): widths whose rows of C end inside a line, which those write in pieces: up to
+//    512 columns from 2^19 rows on (128 -> 300 166 / 122, 128 -> 320 even, 154 K rows, 64 -> 325 transposed 1.8 of the time), 513 to 768 from 393,216 (2^19 rows, 100 -> 602 0.71, 64 -> 768 1.13; 131 K rows, 64 ->
+//    602 1.19), more from 196,608 (2^18 rows, 128 -> 1000 0.64, 128 -> 1024 1.05; 131 K rows, 64 -> 1000 1.17).
+//  * K of 129 to 256 and more than 256 columns: past 49,152 rows (400 K rows, 256 -> 602 295 / 178; 33 K rows 27.8 / 28.6), past 384 columns past 65,536 (65,536 rows, which are two full
+//    rounds of tiles, 160 -> 512 1.15 of the time), past 640 from 131,072.
+//  * K past 256, several slices: from 49,152 rows on (65 K rows, 512 -> 400 41.6 / 43, 320 -> 640 55 / 46, 2^18 rows 0.7 to 0.8 of the time; 16 K rows 20.7 / 21.8).
+//  * K past 256, more than 256 columns in one slice: past 32,768 rows (65 K rows, 400 -> 300 54 / 38; 32,768 rows, 400 -> 384 1.20 of the time), past 384 columns past 65,536 (8 K to
+//    16 K rows of transposed weights 1.2 to 1.3).
+//  * K past 256, 129 to 256 columns: up to 8,192 rows of transposed weights (4 K rows, 602 -> 256 17.0 / 10.4; 10 K rows 1.03 to 1.14 of the time), 4,096 of others with up to 512 terms
+//    (4,096 rows, 400 -> 256 1.11), and past 65,536 (65,536 rows, 512 -> 256 1.23, 2^18 rows 0.7), with more than 512 terms past 98,304 (131 K rows, 602 -> 256 64.9 / 58.3, 2^19 rows 306 / 211).
+//  * K past 256, up to 128 columns: from 2,000 rows on (4 K rows, 300 -> 128 12.0 / 7.7, 1000 -> 70 27.0 / 13.9; 400 K rows 124 / 92, 287 / 170), but not where the row tiles come to one full
+//    round, past 18,432 rows and up to 32,768 (32,768 rows, 300 -> 128 1.23 of the time, 400 -> 128 1.06; 513 to 640 terms 0.9, more of transposed weights 0.95), and with fewer than 320 terms up to 98,304
+//    (50 K rows, 300 -> 128 1.13, 100 K rows 0.83), fewer than 288 up to 262,144 (1.0 to 1.2).
 bool gt_gemm_reg_applicable(gt_dtype dtype, gt_dtype c_dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t lda, bool vec) {
     if (dtype != GT_BF16 || c_dtype != GT_BF16 || transA || N <= 64 || K < 64 || K > 1024 || N > 2048) return false;
     if (M < 1024 || M >= ((int64_t)1 << 35) || lda >= ((int64_t)1 << 25)) return false;   // (block numbers and offsets inside a block in 32 bits)
     if (K <= 256 && N <= 256) return false;
     const int slices = pick(N, K).slices;
     if (!slices || slices > 2) return false;
-    if (!vec) return M >= (N > (transB ? 256 : 640) ? (K < 100 ? 65536 : 32768) : K > 256 ? 1024 : 2000);
-    if (K > 640 && N > 128) return M <= 16384;
-    if (K <= 256) return M >= (N > 640 ? 131072 : K < 100 ? 98304 : 49152);
+    if (!vec) {
+        if (K <= 128 && N > 256) {
+            if (M <= 32768 && (transB || N > 640)) return false;
+            if (N <= 320) return M > 32768 || (M >= 2000 && M <= 18432);
+            if (N <= 512) return M >= 393216 || (M > 32768 && M < (N <= 448 ? 98304 : 163840)) || (M >= 2000 && M < 8192);
+            if (N <= 640) return M >= 24576 || (M >= 2000 && M < 8192);
+            return N > 768 || M < 163840 || M >= 262144;
+        }
+        if (N > (transB ? 256 : 640)) return M >= 32768;
+        if (slices == 1 && N > 384) return M >= (K > 256 ? 18433 : N > 512 ? 8192 : 2000);
+        return M >= (K > 256 ? 1024 : 2000);
+    }
+    if (K > 640 && N > 128) return M <= (transB ? 16384 : 8192);
+    if (K <= 128) return N % 64 != 0 && M >= (N <= 512 ? 524288 : N <= 768 ? 393216 : 196608);
+    if (K <= 256) return N > 640 ? M >= 131072 : M > (N > 384 ? 65536 : 49152);
     if (slices > 1) return M >= 49152;
-    if (N > 256) return transB || M >= 32768;
-    if (N > 128) return M <= 12288 || M >= (K > 512 ? 98304 : 65536);
-    return M >= 2000;
+    if (N > 256) return M > (N > 384 ? 65536 : 32768);
+    if (N > 128) return M > (K > 512 ? 98304 : 65536) || (transB ? M < 8192 : M < 4096 && K <= 512);
+    if (M <= 18432) return M >= 2000;
+    if (K < 320) return M >= (K < 288 ? 262144 : 98304);
+    return M > 32768 || (K > 512 && (transB || K <= 640));
 }
 
 gt_status gt_gemm_reg_launch(const GemmArgs &g, int transB, hipStream_t st) {

@@ -73,3 +73,25 @@ def test_masked(n, fi, fo, pad_writable):
         assert bool((out[:, fi:] == (0 if pad_writable else 3)).all())
         got.append(out[:, :fi])
     assert torch.equal(got[1], torch.where(X[:, :fi] > 0, got[0], torch.zeros_like(got[0])))
+
+
+# the same at the lines where the row tiles come to full rounds, and where few terms keep little of A in flight
+@pytest.mark.parametrize("transB", [False, True], ids=["NN", "NT"])
+@pytest.mark.parametrize("M,N,K", [(4095, 129, 384), (4095, 256, 511), (8191, 255, 640), (98305, 129, 513), (65537, 130, 300), (32769, 300, 416), (65537, 512, 250), (65539, 385, 319), (524291, 300, 65),
+                                   (524288, 511, 128), (393217, 602, 64), (393221, 750, 100), (196611, 1001, 128), (196609, 1100, 66), (131072, 641, 250), (49153, 640, 256),
+                                   (98304, 100, 300), (262145, 70, 260), (18432, 128, 300), (18433, 70, 600), (32769, 128, 512), (8191, 200, 700), (16384, 150, 900)])
+def test_register_weights_at_lines(M, N, K, transB):
+    test_register_weights(M, N, K, transB)
+
+
+@pytest.mark.parametrize("transB", [False, True], ids=["NN", "NT"])
+@pytest.mark.parametrize("M,N,K", [(2000, 257, 70), (18432, 300, 127), (32769, 257, 70), (33001, 500, 100), (393217, 333, 75), (2001, 601, 100), (24577, 601, 100), (32771, 700, 90), (32773, 1001, 66),
+                                   (8193, 601, 129), (18433, 401, 300), (2003, 401, 200)])
+def test_contiguous_at_lines(M, N, K, transB):
+    test_contiguous(M, N, K, transB)
+
+
+@pytest.mark.parametrize("n,fi,fo", [(65539, 130, 300), (98311, 100, 304), (393217, 602, 104), (131075, 700, 200)])
+def test_masked_at_lines(n, fi, fo):
+    for pad_writable in (False, True):
+        test_masked(n, fi, fo, pad_writable)
