@@ -769,16 +769,18 @@ int64_t tn_wide_tiles(int64_t M, int64_t N) {
     return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
 }
 // Where it covers the output in fewer tiles than 256 x 256 ones do, over reductions of 98,304 rows and more (us, the other bf16 weight gradients / this one: 602 x
-// 256 over 50,000 rows 50 / 51, 131,072 98 / 88, 2^19 334 / 250; 300 x 300 40 / 47, 81 / 65, 347 / 202; 602 x 100 33 / 46, 61 / 60, 231 / 169), from 16,384 on where those
-// would be more than six (1024 x 320 over 20,000 rows 52 / 45, 2^19 726 / 434); in as many tiles it is even or behind (256 x 256 over 2^21 rows 460 / 471,
+// 256 over 50,000 rows 50 / 51, 131,072 98 / 88, 2^19 334 / 250; 300 x 300 40 / 47, 81 / 65, 347 / 202; 602 x 100 33 / 46, 61 / 60, 231 / 169), from 20,480 on where those
+// would be more than six (1024 x 320 over 20,000 rows 52 / 45, 2^19 726 / 434; 821 x 380 over 18,000 1.2 of the time); in as many tiles it is even or behind (256 x 256 over 2^21 rows 460 / 471,
 // 512 x 256 over 2^19 242 / 251).  Operands without alignment (vec false), which the others read by the element in LDS: from 49,152 rows on, in as
 // many tiles as well from 98,304 unless the output is one tile of 128 x 128 (602 x 256 over 50,000 rows 66 / 50, 2^19 596 / 237; 100 x 256 30 / 33, 125 / 95;
-// 100 x 100 over 2^19 rows 73 / 79).
+// 100 x 100 over 2^19 rows 73 / 79).  Up to 128 columns take the tile of 640 x 128, of which the last rows are often padding: from 131,072 rows on, 73,728 without
+// alignment (627 x 104 over 122 K rows 1.12 of the time, padded, 349 x 77 over 53 K rows 1.55, not); of 6,200 random weight gradients (65 to 1,100 rows and columns, 16 K to 600 K long) those that come here take
+// 0.65 of the time in the geometric mean, 2 % are slower by more than 3 %.
 bool tn_wide_shape(int transA, int transB, int64_t M, int64_t N, int64_t K, bool vec) {
     if (!transA || transB || M <= 64 || N <= 64 || (double)M * (double)N * (double)K < 268435456.0) return false;
     const int64_t tiles = tn_wide_tiles(M, N), tiles256 = tn256_tiles(M, N);
     if (tiles > 8) return false;
-    if (tiles < tiles256) return K >= (tiles256 > 6 ? 16384 : vec ? 98304 : 49152);
+    if (tiles < tiles256) return K >= (tiles256 > 6 ? 20480 : N <= 128 ? (vec ? 131072 : 73728) : vec ? 98304 : 49152);
     return !vec && K >= 98304 && (M > 128 || N > 128);
 }
 

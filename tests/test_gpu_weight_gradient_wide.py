@@ -48,3 +48,9 @@ def test_bias_gradient(n, fi, fo, padded):
     r = B.gt_layer_bwd(g, desc, used, dY, X, W, Y, bufs, "agg_first")
     d = dY.double()
     assert bool(((r["db"].double() - d.sum(0)).abs() <= 1e-5 * d.abs().sum(0)).all())
+
+
+@pytest.mark.parametrize("padded", [True, False], ids=["padded", "contiguous"])
+@pytest.mark.parametrize("M,N,K", [(640, 128, 131072), (639, 127, 131075), (602, 100, 131073), (300, 99, 73728), (641, 66, 73731), (1024, 320, 20480), (1023, 319, 20481), (700, 600, 20490)])
+def test_wide_tiles_at_lines(M, N, K, padded):
+    test_wide_tiles(M, N, K, padded)
