@@ -555,17 +555,17 @@ gt_status run_gather(const gt_graph *g, bool transposed, gt_dtype t, int64_t F, 
 
 // Whether both derivatives of the scaled aggregation come from one gather: rows of at most a wavefront's vectors.  Narrow ones without alignment
 // stay with the element-wise kernels.  Where the L2s hold the rows but not the scores, the rows are found there and the places of the products
-// are not, and two passes are ahead: rows of up to 128 bytes on skewed graphs from 4 Mi edges on, of up to 64 from 3 Mi on; on uniform graphs of
-// tables up to 16 MB from 2 Mi on (us, two passes / one: power law, 8.4 M edges, 32 bf16 columns 410 / 435, 128 columns 507 / 455; 4 M edges, 32 columns
-// 209 / 227, 2.5 M 140 / 140; uniform, 131 K rows, 8.4 M edges, 8 fp32 columns 319 / 437, 32 bf16 columns 375 / 462, 24 fp32 columns 387 / 481, 32 fp32 columns 361 / 437; 90 K rows, 2.3 M edges, 20 fp32 columns 104 / 119;
-// 262 K rows, 5 M edges, 47 bf16 columns 381 / 326; 262 K rows, 2.5 M edges, 8 columns 133 / 144, 32 bf16
-// columns 151 / 149; 500 K rows, 12 M edges 713 / 728, 774 / 735; 262 K rows, 8.4 M edges, 128 columns 772 / 567; 1 M edges, 150 fp32 columns 220 / 143; 60 K edges 14.0 / 9.0).
+// are not, and two passes are ahead: rows of up to 128 bytes, on skewed graphs from 2.25 Mi edges on, on uniform graphs of tables up to 10 MB from 1.5 Mi
+// on (us, two passes / one: power law, 8.4 M edges, 32 bf16 columns 410 / 435, 128 columns 507 / 455; 4 M edges, 32 columns
+// 209 / 227; uniform, 131 K rows, 8.4 M edges, 8 fp32 columns 319 / 437, 32 bf16 columns 375 / 462, 24 fp32 columns 387 / 481; 90 K rows, 2.3 M edges, 20 fp32 columns 104 / 119;
+// 262 K rows, 5 M edges, 47 bf16 columns 381 / 326; 262 K rows, 8.4 M edges, 128 columns 772 / 567; 1 M edges, 150 fp32 columns 220 / 143; 60 K edges 14.0 / 9.0.  One over two passes in
+// the geometric mean of 2,080 random shapes: power law, rows of 65 to 128 bytes, 1.4 to 2 Mi edges 0.94, 2 to 2.8 Mi 1.01, 2.8 to 4 Mi 1.04; uniform, 2 to 4 Mi edges, tables up to
+// 4 MB 1.07 to 1.2, 4 to 8 MB 1.03, 8 to 16 MB 0.96, larger 0.82; under 1 Mi edges 0.6 to 0.86).
 bool scale_bwd_joined(const gt_graph *g, gt_dtype t, int64_t F, const void *dY, int64_t lddy, const void *Xs, int64_t ldxs, const void *dXs, int64_t lddxs) {
     const int ve = t == GT_F32 ? 4 : 8;
     const bool vec = vec_ok(t, dY, lddy) && vec_ok(t, Xs, ldxs) && vec_ok(t, dXs, lddxs);
     const int64_t rb = F * (int64_t)gt_dtype_size(t), Mi = (int64_t)1 << 20;
-    if (agg_skewed(g->bwd.n_splits, g->bwd.n_long, g->bwd.n_items) ? rb <= 128 && g->n_edges > (rb <= 64 ? 3 : 4) * Mi
-                                                                  : rb <= 128 && g->n_edges > 2 * Mi && g->n_dst * rb <= 16 * Mi) return false;
+    if (rb <= 128 && (agg_skewed(g->bwd.n_splits, g->bwd.n_long, g->bwd.n_items) ? 4 * g->n_edges > 9 * Mi : 2 * g->n_edges > 3 * Mi && g->n_dst * rb <= 10 * Mi)) return false;
     return g->n_edges > 0 && F <= 64 * ve && (vec || F > 16);
 }
 

@@ -21,6 +21,9 @@ def _graph(kind):
         n, E = 60_000, 5_000_000
         p = 1.0 / (np.arange(n) + 30.0)
         src = rng.choice(n, E, p=p / p.sum())
+    elif kind == "many":    # uniform, more edges than the L2s hold scores of
+        n, E = 60_000, 1_700_000
+        src = rng.integers(0, n, E)
     else:
         n, E = 5003, 60_000
         src = rng.integers(0, n, E)
@@ -30,7 +33,7 @@ def _graph(kind):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("kind,F", [("hubs", F) for F in (3, 16, 17, 31, 64, 65, 101, 128, 160, 256, 257, 512)] + [("even", F) for F in (8, 23, 47, 64, 100, 140, 250, 300)] +
-                         [("large", F) for F in (8, 32, 33, 64, 100)])
+                         [("large", F) for F in (8, 32, 33, 64, 100)] + [("many", F) for F in (8, 20, 47, 64)])
 def test_derivatives(kind, F, dtype):
     from paper_2305_17469_amd import binding as B
     n, src, dst = _graph(kind)
