@@ -442,6 +442,10 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
                     if (a.coef2) c_next[k] *= a.coef2[e];
                     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
                 } else if constexpr (VWM == VWM_NONE) {
+                    // Groups of four lanes ask for the next batch's coefficients when its ids are there, which leaves the L2s to the rows in the same way (uniform
+                    // graphs, derivative of the mean, 264 shapes of one row in flight 0.905 of the time waiting for nothing 0.935; at most 1.13 and 1.36 of it).
+                    if constexpr (G == 4 && IPL > 1)
+                        if (a.coef) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
                     c_next[k] = a.coef ? a.coef[e] : 1.0f;
                 } else {
                     ei_next[k] = a.eidx ? a.eidx[e] : e;
