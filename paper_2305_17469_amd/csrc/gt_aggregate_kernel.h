@@ -398,12 +398,12 @@ __global__ void __launch_bounds__(256, (agg_waves<T, V, G, NP, U, VWM, MK>())) k
     constexpr int GB = G * IPL;
     // A coefficient that is looked up through the permutation (VWM_SCORE) waits for its place there.  EARLY: the places are requested a batch
     // earlier still, and the two factors of an entry are multiplied when they are used, so that no load waits for another between the row loads.  That is
-    // ahead in groups of four lanes, and of eight with eight rows in flight.  The others have rows in flight without it, and wait for every score
+    // ahead in groups of four lanes, and of eight and sixteen with eight rows in flight.  The others have rows in flight without it, and wait for every score
     // before the next place is asked for, which leaves the L2s to the rows.  The transposed gather alone, us, places early / waited for: power law, 262 K rows, 8.4 M edges,
-    // 4 to 16 fp32 columns 0.84, 32 fp32 columns 0.96 of the time; uniform, 500 K rows, 8 M edges, 16 fp32 columns 304 / 328, 60 K rows, 2.2 M edges 49 / 55 (with exactly 36 entries
-    // each 44 / 41); 131 K rows, 8.4 M edges, 47 bf16 columns without alignment 264 / 238; 64 bf16 columns and more, 32 fp32 columns and more: uniform 1.00 to 1.21, power law
-    // 0.99 to 1.00 of the time.
-    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = SCORE && (G == 4 || (G == 8 && U == 8 && IPL == 1));
+    // 4 to 16 fp32 columns 0.84, 32 fp32 columns 0.96, 128 bf16 columns 0.98 of the time; uniform, 500 K rows, 8 M edges, 16 fp32 columns 304 / 328, 60 K rows, 2.2 M edges 49 / 55 (with exactly 36 entries
+    // each 44 / 41); 131 K rows, 8.4 M edges, 47 bf16 columns without alignment 264 / 238; 64 bf16 columns and more, 32 fp32 columns and more, uniform: 1.00 to 1.21
+    // of the time.
+    constexpr bool SCORE = VWM == VWM_SCORE, EARLY = SCORE && (G == 4 || (G <= 16 && U == 8 && IPL == 1));
     int idx_next[IPL], ei_next[IPL];
     float c_next[IPL], f_next[IPL];
     if constexpr (EARLY) {
