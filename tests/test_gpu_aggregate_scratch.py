@@ -61,6 +61,15 @@ def test_two_streams(graph):
             assert torch.equal(Y, want[i][0]) and torch.equal(dX, want[i][1])
 
 
+def test_handle_of_the_current_stream():
+    from paper_2305_17469_amd import binding as B
+    st = torch.cuda.Stream()
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(st):
+        assert B._stream() == st.cuda_stream != torch.cuda.default_stream().cuda_stream
+    assert B._stream() == torch.cuda.current_stream().cuda_stream
+
+
 def test_captured_call_keeps_to_its_memory(graph):
     from paper_2305_17469_amd import binding as B
     X, wide = _table(28, 3), _table(47, 4)
